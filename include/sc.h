@@ -122,7 +122,8 @@ sc_status sc_get_timing(const sc_prob *p, sc_timing *out);
 typedef struct {
     int obs_per_lane;    /* 1 or 2 observation points per lane                    */
     int waves_per_block; /* 1, 2 or 4 waves of 64 lanes per workgroup             */
-    int chunk;           /* mirror nodes per split-K chunk (multiple of 64)        */
+    int chunk;           /* mirror nodes per split-K chunk (multiple of 64) where
+                            the sum is taken directly (see sc_evaluate)            */
     int blocks_per_cu;   /* persistent workgroups per compute unit (0 = max)       */
     int freq_per_lane;   /* 1, 2 or 4 frequencies per lane sharing one geometry
                             (obs_per_lane x freq_per_lane <= 4, not 2 x 4)        */
@@ -402,7 +403,21 @@ sc_status sc_set_observation(sc_prob *p, const double *xyz, int n_obs, int on_de
  * E, B: [n_k][n_obs][3] complex128 (SC_FP64) or complex64 (FP32 forms),
  * host or device per on_device; either may be NULL to keep the result only
  * on the device (for sc_to_time / sc_to_time_at / sc_get_result).  Needs mirror, frequencies,
- * incident field and observation points (SC_E_STATE).                      */
+ * incident field and observation points (SC_E_STATE).
+ * How the sum over the nodes is taken.  On the built-in paraboloid, with points
+ * from host memory, SC_FP64 and SC_FP32_SPLIT use that the kernel
+ * e^{ikR} / R, as a function of the node's direction from the focus, oscillates
+ * no faster than k r': K(o, n) = sum_m L_m(n) K(o, m) over a few interpolation
+ * nodes m (Chebyshev in the polar angle, trigonometric in phi), to the rounding
+ * of the precision, so sum_n K(o, n) c_n = sum_m K(o, m) (sum_n L_m(n) c_n) with
+ * the records c of any incident field: every node's record enters once, and the
+ * points meet the m alone (2 700 instead of 160 400 for 4 wavelengths about the
+ * focus of an f/0.67 mirror).  The library does so where |r'| <= f / 4 and it is
+ * the faster way, by a rule on the problem's sizes alone; then `chunk` and
+ * `freq_per_lane` change no bit, and the compacted tables (32 or 64 B per
+ * frequency and m) are kept with the problem until its tables change.  Elsewhere
+ * (general surfaces, device points, SC_FP32, points far from the focus, small
+ * meshes) the sum is taken node by node.                                    */
 sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B, int on_device);
 /* sc_evaluate for callers that cannot allocate (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the call allocates

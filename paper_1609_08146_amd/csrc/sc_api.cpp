@@ -103,6 +103,7 @@ extern "C" sc_status sc_ctx_destroy(sc_ctx *c)
     if (c->upload_done) (void)hipEventDestroy(c->upload_done);
     c->counter.release();
     c->jobs.release();
+    c->compact_work.release();
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
     return SC_OK;
@@ -231,6 +232,7 @@ static void invalidate_tables(sc_prob *p)
     p->fact32_built = p->fact64_built = false;
     p->fact_pending = p->cast_pending = false;   // a flag still on its way belongs to the old tables
     p->res_prec = -1;
+    p->tab_version++;
 }
 
 // Relative tolerances of the factoring test (residual of the current off its direction u, over the
@@ -797,6 +799,7 @@ static sc_status scale_tables(sc_prob *p, const std::vector<double> &fac)
     }
     p->tab32n_ok = false;
     p->res_prec = -1;
+    p->tab_version++;
     std::vector<double> P(n_k);
     HIP_TRY(hipMemcpyAsync(P.data(), p->d_power.p, sizeof(double) * n_k, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));   // fac and P are host memory, dfac is freed on return
@@ -864,12 +867,13 @@ extern "C" sc_status sc_set_observation(sc_prob *p, const double *xyz, int n_obs
     SC_TRY(p->obs64.reserve(sizeof(double) * 4 * pad, p->alloc_stream));
     SC_TRY(p->obs32.reserve(sizeof(float) * 4 * pad, p->alloc_stream));
     const double *d = xyz;
-    p->obs_r2max = -1.0;
-    double r2max = -1.0;
+    p->obs_r2max = p->obs_rho2max = -1.0;
+    double r2max = -1.0, rho2max = -1.0;
     if (!on_device) {
         for (int o = 0; o < n_obs; ++o) {
             const double *q = xyz + 3 * (size_t)o;
             r2max = std::max(r2max, q[0] * q[0] + q[1] * q[1] + q[2] * q[2]);
+            rho2max = std::max(rho2max, q[0] * q[0] + q[1] * q[1]);
         }
         double *h = nullptr;
         bool ext = false;
@@ -882,6 +886,7 @@ extern "C" sc_status sc_set_observation(sc_prob *p, const double *xyz, int n_obs
     }
     HIP_TRY(launch_obs_prep(st, d, n_obs, pad, p->obs64.as<double>(), p->obs32.as<float>()));
     p->obs_r2max = r2max;
+    p->obs_rho2max = rho2max;
     p->n_obs = n_obs;
     p->n_obs_pad = pad;
     return SC_OK;
@@ -1061,6 +1066,14 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
     return SC_OK;
 }
 
+// Nodes summed plainly in FP32 registers before each block sum is added into the chunk's running sum.
+// A plain FP32 sum of 512 terms errs by at most 511 u (3e-5) of the sum of their magnitudes and
+// typically by about sqrt(512) u (1.3e-6); the running sum over the blocks of a chunk adds at most
+// chunk / 512 - 1 further roundings.  Compacted terms are few and large, so there are few blocks for
+// the rounding to average over: blocks of 512 cost the broadband field 1.6e-6 (relative L2) where the
+// direct sum has 4.2e-7; blocks of 96 give 4.7e-7 and blocks of 32 4.2e-7, in the same time.
+constexpr int SUM_BLOCK = 512, SUM_BLOCK_COMPACT = 32;
+
 // The quadrature job of one problem (no allocation): tables `tab` of the chosen layout, split-K
 // partials in `partial` ([n_chunks][n_k][12][n_obs_pad] reals of the precision).
 static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, const void *tab, bool fact,
@@ -1097,6 +1110,7 @@ static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, co
     job.n_obs_pad = p->n_obs_pad;
     job.n_k = n_k;
     job.chunk = l.chunk;
+    job.sum_block = SUM_BLOCK;
     job.n_chunks = n_chunks;
     job.obs_blocks = p->n_obs_pad / (64 * l.obs_per_lane);
     job.tile0 = 0;
@@ -1104,7 +1118,81 @@ static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, co
     job.n_tiles = (int64_t)job.obs_blocks * n_chunks * ((n_k + l.freq_per_lane - 1) / l.freq_per_lane);
 }
 
-// Bytes of the split-K partials of an evaluation of p with launch l.
+// The compacted sum of an evaluation of p in prec (sc_compact.h), where it applies: the split forms on
+// the built-in paraboloid with points from host memory.  A function of the problem alone, so a
+// result does not depend on the launch, the batch or the calls before.
+static bool plan_compact(const sc_prob *p, sc_precision prec, CompactPlan &plan)
+{
+    if (prec == SC_FP32 || p->f <= 0.0 || p->obs_r2max < 0.0) return false;
+    CompactInput in{};
+    in.f = p->f;
+    in.r_max = p->a;
+    in.n_r = p->n_r;
+    in.n_phi = p->n_phi;
+    in.k_max = *std::max_element(p->k.begin(), p->k.end());
+    in.n_k = (int)p->k.size();
+    in.n_obs_pad = p->n_obs_pad;
+    in.obs_r2max = p->obs_r2max;
+    in.obs_rho2max = p->obs_rho2max;
+    in.fp64 = prec == SC_FP64;
+    return compact_plan(in, plan);
+}
+
+// The job of a sum over compacted nodes: fill_job's with the compacted tables, which are general
+// tables of n_c nodes, and the plan's chunk.
+static void compact_job(const CompactPlan &plan, const void *tab, const void *pos, const void *hinv, const sc_launch &l,
+                        QuadJob &job)
+{
+    job.tab = tab;
+    job.pos = pos;
+    job.hinv = hinv;
+    job.beta = job.tabp = nullptr;
+    job.factored = job.tied = 0;
+    job.n_tot = plan.n_c;
+    job.chunk = plan.chunk;
+    job.sum_block = SUM_BLOCK_COMPACT;
+    job.n_chunks = (plan.n_c + plan.chunk - 1) / plan.chunk;
+    job.n_tiles = (int64_t)job.obs_blocks * job.n_chunks * ((job.n_k + l.freq_per_lane - 1) / l.freq_per_lane);
+}
+
+// Partial rows kept at a time while compacted tables are built: more frequencies go in slabs, which
+// also keeps what one kernel writes and the next reads within the last-level cache.
+constexpr size_t COMPACT_SLAB_BYTES = 128u << 20;
+
+// The compacted tables of p in prec from its tables `tab` (layout `fact`), kept until those change.
+static sc_status ensure_compact(sc_prob *p, sc_precision prec, const CompactPlan &plan, const void *tab, bool fact)
+{
+    if (p->cplan_prec == (int)prec && p->cplan_fact == fact && p->cplan_version == p->tab_version &&
+        memcmp(&p->cplan, &plan, sizeof plan) == 0)
+        return SC_OK;
+    const int n_k = (int)p->k.size(), f64 = prec == SC_FP64;
+    const size_t rs = real_size(prec);
+    p->cplan_prec = -1;
+    SC_TRY(p->ctab.reserve(rs * 8 * (size_t)n_k * plan.n_c, p->alloc_stream));
+    SC_TRY(p->cpos.reserve(rs * 4 * (size_t)plan.n_c, p->alloc_stream));
+    SC_TRY(p->chinv.reserve(rs * (size_t)plan.n_c, p->alloc_stream));
+    const size_t nrad = (size_t)compact_radial_doubles(plan, p->n_r), nang = (size_t)compact_angular_doubles(plan, p->n_phi);
+    const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
+    const int most = (int)std::max<size_t>(1, std::min<size_t>((size_t)n_k, COMPACT_SLAB_BYTES / row_bytes));
+    const int slabs = (n_k + most - 1) / most, per = (n_k + slabs - 1) / slabs;
+    DevBuf &work = p->ctx->compact_work;   // used on the context's stream only
+    SC_TRY(work.reserve(sizeof(double) * (nrad + nang) + row_bytes * per, p->alloc_stream));
+    double *wrad = work.as<double>(), *wang = wrad + nrad, *T = wang + nang;
+    hipStream_t st = p->ctx->stream;
+    HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, p->cpos.p,
+                                    p->chinv.p));
+    const void *pos = fact ? (f64 ? p->posf64.p : p->posf.p) : nullptr;
+    for (int k0 = 0; k0 < n_k; k0 += per)
+        HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, std::min(per, n_k - k0), f64, fact ? 1 : 0, tab, pos,
+                                      wrad, wang, T, (char *)p->ctab.p + rs * 8 * (size_t)k0 * plan.n_c));
+    p->cplan = plan;
+    p->cplan_prec = (int)prec;
+    p->cplan_fact = fact;
+    p->cplan_version = p->tab_version;
+    return SC_OK;
+}
+
+// Bytes of the split-K partials of an evaluation of p with launch l, its sum taken directly.
 static size_t partial_bytes(const sc_prob *p, sc_precision prec, const sc_launch &l)
 {
     const size_t n_chunks = ((size_t)p->n_tot + l.chunk - 1) / l.chunk;
@@ -1119,10 +1207,15 @@ sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, QuadJob
     SC_TRY(select_tables(p, prec, true, &tab, &fact));
     const size_t rs = real_size(prec);
     const int n_k = (int)p->k.size();
-    SC_TRY(p->partial.reserve(partial_bytes(p, prec, l), p->alloc_stream));
+    CompactPlan plan;
+    const bool compact = plan_compact(p, prec, plan);
+    if (compact) SC_TRY(ensure_compact(p, prec, plan, tab, fact));
+    fill_job(p, prec, l, tab, fact, nullptr, job);
+    if (compact) compact_job(plan, p->ctab.p, p->cpos.p, p->chinv.p, l, job);
+    SC_TRY(p->partial.reserve(rs * 12 * (size_t)job.n_chunks * n_k * (size_t)p->n_obs_pad, p->alloc_stream));
+    job.partial = p->partial.p;
     SC_TRY(p->resE.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc_stream));
     SC_TRY(p->resB.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc_stream));
-    fill_job(p, prec, l, tab, fact, p->partial.p, job);
     return SC_OK;
 }
 
@@ -1215,7 +1308,7 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     p->res_prec = -1;
     SC_TRY(run_quad(p->ctx, jobs, prec, l, p));
     HIP_TRY(launch_reduce(p->ctx->stream, mode_of(prec), p->partial.p, job.n_chunks, job.n_k, p->n_obs,
-                          p->n_obs_pad, p->d_k.as<double>(), job.tied, p->resE.p, p->resB.p));
+                          p->n_obs_pad, p->d_k.as<double>(), job.tied, p->n_obs, 0, p->resE.p, p->resB.p));
     ev_record(p, EV_R1);
     p->ev_quad = p->ctx->profiling;
     p->res_prec = (int)prec;
@@ -1286,14 +1379,69 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     unsigned int *counter = (unsigned int *)(b + SCRATCH_COUNTERS);
     QuadJob *djob = (QuadJob *)(b + SCRATCH_JOB);
     QuadJob job{};
-    fill_job(p, prec, l, tab, fact, b + SCRATCH_PARTIAL, job);
     hipStream_t st = p->ctx->stream;
-    HIP_TRY(launch_store_job(st, job, djob));
-    HIP_TRY(launch_fill_u32(st, counter, 0u, QUAD_SEGMENTS));
-    HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
-                        quad_grid(p->ctx, prec, l, job.n_tiles), djob, 1, job.n_tiles, counter));
-    HIP_TRY(launch_reduce(st, mode_of(prec), b + SCRATCH_PARTIAL, job.n_chunks, job.n_k, p->n_obs, p->n_obs_pad,
-                          p->d_k.as<double>(), job.tied, E, B));
+    // frequencies k0 ... k0 + n - 1 and points o0 ... o0 + n_o - 1 of one job
+    auto enqueue = [&](int k0, int o0, int n_o) -> sc_status {
+        HIP_TRY(launch_store_job(st, job, djob));
+        HIP_TRY(launch_fill_u32(st, counter, 0u, QUAD_SEGMENTS));
+        HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
+                            quad_grid(p->ctx, prec, l, job.n_tiles), djob, 1, job.n_tiles, counter));
+        const size_t at = real_size(prec) * 6 * (size_t)k0 * p->n_obs;
+        HIP_TRY(launch_reduce(st, mode_of(prec), job.partial, job.n_chunks, job.n_k, n_o, job.n_obs_pad,
+                              p->d_k.as<double>() + k0, job.tied, p->n_obs, o0, (char *)E + at, (char *)B + at));
+        return SC_OK;
+    };
+    CompactPlan plan;
+    if (!plan_compact(p, prec, plan)) {
+        fill_job(p, prec, l, tab, fact, b + SCRATCH_PARTIAL, job);
+        return enqueue(0, 0, p->n_obs);
+    }
+    // The compacted sum in the scratch: weights and node records once, then slabs of frequencies (partial
+    // rows and compacted tables) and, where not even one frequency's partials fit, of points.  No bit
+    // depends on the slabs.
+    const size_t rs = real_size(prec);
+    const int n_k = (int)p->k.size(), f64 = prec == SC_FP64;
+    size_t off = SCRATCH_PARTIAL;
+    auto take = [&](size_t bytes) {
+        char *q = b + off;
+        off += (bytes + 255) & ~size_t(255);
+        return q;
+    };
+    double *wrad = (double *)take(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
+    double *wang = (double *)take(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
+    void *cpos = take(rs * 4 * (size_t)plan.n_c), *chinv = take(rs * (size_t)plan.n_c);
+    const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
+    const size_t tab_bytes = rs * 8 * (size_t)plan.n_c;
+    const size_t n_chunks = (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk);
+    const size_t part_bytes = rs * 12 * n_chunks;   // per frequency and padded point
+    const size_t left = off + 1024 < SC_NOALLOC_SCRATCH_BYTES ? SC_NOALLOC_SCRATCH_BYTES - off - 1024 : 0;
+    int per_k = (int)std::min<size_t>((size_t)n_k, left / (row_bytes + tab_bytes + part_bytes * p->n_obs_pad));
+    int per_o = p->n_obs_pad;
+    if (per_k < 1) {
+        per_k = 1;
+        const size_t rest = left > row_bytes + tab_bytes ? left - row_bytes - tab_bytes : 0;
+        per_o = (int)std::min<size_t>((size_t)p->n_obs_pad, rest / (part_bytes * OBS_PAD) * OBS_PAD);
+        if (per_o < OBS_PAD) return fail(SC_E_INVAL, "sc_evaluate_noalloc: the scratch is too small for the mirror's nodes");
+    }
+    double *T = (double *)take(row_bytes * per_k);
+    char *ctab = take(tab_bytes * per_k);
+    char *part = take(part_bytes * per_k * per_o);
+    HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, cpos, chinv));
+    const void *pos = fact ? (f64 ? p->posf64.p : p->posf.p) : nullptr;
+    for (int k0 = 0; k0 < n_k; k0 += per_k) {
+        const int nk = std::min(per_k, n_k - k0);
+        HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, nk, f64, fact ? 1 : 0, tab, pos, wrad, wang, T, ctab));
+        for (int o0 = 0; o0 < p->n_obs; o0 += per_o) {
+            fill_job(p, prec, l, tab, fact, part, job);
+            job.n_k = nk;
+            job.k = p->d_k.as<double>() + k0;
+            job.n_obs_pad = std::min(per_o, p->n_obs_pad - o0);
+            job.obs = (const char *)job.obs + rs * 4 * (size_t)o0;
+            job.obs_blocks = job.n_obs_pad / (64 * l.obs_per_lane);
+            compact_job(plan, ctab, cpos, chinv, l, job);
+            SC_TRY(enqueue(k0, o0, std::min(per_o, p->n_obs - o0)));
+        }
+    }
     return SC_OK;
 }
 
@@ -1409,7 +1557,8 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
     for (int i = 0; i < n; ++i) {
         sc_prob *p = probs[i];
         HIP_TRY(launch_reduce(c->stream, mode_of(prec), p->partial.p, jobs[i].n_chunks, jobs[i].n_k, p->n_obs,
-                              p->n_obs_pad, p->d_k.as<double>(), jobs[i].tied, p->resE.p, p->resB.p));
+                              p->n_obs_pad, p->d_k.as<double>(), jobs[i].tied, p->n_obs, 0, p->resE.p,
+                              p->resB.p));
         p->res_prec = (int)prec;
         p->last_evals = (int64_t)p->n_obs * jobs[i].n_k * p->n_surf;
         p->last_tiles = jobs[i].n_tiles;
@@ -1617,7 +1766,7 @@ static std::vector<DevBuf *> prob_buffers(sc_prob *p)
             &p->tab32n, &p->tabf,    &p->posf,      &p->betaf,   &p->tabp,     &p->tabf64, &p->posf64,
             &p->betaf64, &p->fact_flag, &p->d_power, &p->obs64,  &p->obs32,    &p->resE,   &p->resB,
             &p->partial, &p->d_t,    &p->tw,        &p->timeE,   &p->timeB,    &p->d_spec, &p->d_obs_in,
-            &p->d_modes};
+            &p->d_modes, &p->ctab,   &p->cpos,      &p->chinv};
 }
 
 void sc::prob_free_on(sc_prob *p, hipStream_t st)

@@ -1,0 +1,61 @@
+// sc_compact.h -- the compacted form of a mirror's sum, shared by the planner (host), the kernels
+// that build the compacted tables and the host runtime.  Not part of the public ABI.
+//
+// The sum over the mirror is E(o) = sum_n K(o, n) c_n: c the table records (any incident field), K
+// the kernel values e^{ik delta} / R and (ik - 1/R) e^{ik delta} R / R^2 of node n and point o.  As
+// a function of the node's direction (theta, phi) seen from the focus, K is analytic and oscillates
+// no faster than the phase k r'.(direction), so K(o, n) = sum_m L_m(n) K(o, m) over a few nodes m of
+// an interpolation rule, to rounding, and
+//   E(o) = sum_m K(o, m) c~_m,   c~_m = sum_n L_m(n) c_n:
+// the same sum over every record, with the points' part taken over far fewer nodes.  On the
+// paraboloid r = 2 f tan(theta / 2), |r_s| = f / cos^2(theta / 2), the nodes are a tensor grid in
+// (r, phi) with equispaced phi, so L is a product: Chebyshev interpolation in theta from `rows`
+// points of [0, theta_max] to the n_r + 1 radii (the rim is one of them), and on each row
+// trigonometric interpolation from cols[m] equispaced phi to the n_phi.
+#pragma once
+
+#include <stdint.h>
+
+namespace sc {
+
+constexpr int COMPACT_MAX_ROWS = 192;
+
+struct CompactPlan {
+    int rows;                               // interpolation rows in theta
+    int n_c;                                // compacted nodes in all (sum of cols)
+    int split;                              // parts the sum over the radii is cut into (partial rows)
+    int chunk;                              // compacted nodes per split-K chunk of the quadrature
+    double theta_max;                       // 2 atan(r_max / 2f)
+    uint16_t cols[COMPACT_MAX_ROWS];        // phi per row: odd, or n_phi (taken as they are)
+    int32_t off[COMPACT_MAX_ROWS + 1];      // first compacted node of each row
+    int32_t poff[COMPACT_MAX_ROWS + 1];     // the same with every row's columns rounded up to 16
+};
+
+// Working memory of the two interpolations (doubles): the radial weights [n_r + 1 rounded up to
+// 4][rows rounded up to 16], the angular weights of every row [n_phi][cols rounded up to 16], and
+// the partial rows of one frequency [split][rows][n_phi][8].  The planner keeps their sum below
+// COMPACT_WORK_MAX bytes.
+constexpr int64_t COMPACT_WORK_MAX = 47 << 20;
+inline int64_t compact_radial_doubles(const CompactPlan &p, int n_r)
+{
+    return (int64_t)((n_r + 4) / 4 * 4) * ((p.rows + 15) / 16 * 16);
+}
+inline int64_t compact_angular_doubles(const CompactPlan &p, int n_phi) { return (int64_t)p.poff[p.rows] * n_phi; }
+inline int64_t compact_rows_doubles(const CompactPlan &p, int n_phi) { return (int64_t)p.split * p.rows * n_phi * 8; }
+
+// What the plan depends on.
+struct CompactInput {
+    double f, r_max;       // paraboloid
+    int n_r, n_phi;
+    double k_max;
+    int n_k, n_obs_pad;
+    double obs_r2max;      // max |r'|^2 over the points
+    double obs_rho2max;    // max x'^2 + y'^2
+    bool fp64;
+};
+
+// Plans the compacted sum of a problem; false where it does not apply or does not pay, and the sum
+// is then taken directly.  Depends on nothing but its input (no launch shape, no history).
+bool compact_plan(const CompactInput &in, CompactPlan &plan);
+
+}  // namespace sc

@@ -114,6 +114,7 @@ struct sc_ctx {
     int n_cu = 256;
     sc::DevBuf counter;   // persistent-launch work counter
     sc::DevBuf jobs;      // QuadJob array for launches
+    sc::DevBuf compact_work;   // interpolation weights and partial rows while compacted tables are built
     std::vector<sc::QuadJob> host_jobs;
     hipEvent_t upload_done = nullptr;
     std::map<sc::TuneKey, sc_launch> tune;
@@ -162,14 +163,22 @@ struct sc_prob {
     // the factored tables built with the test when the incident field is set: FP32 split by
     // default; a caller that knows its one precision (the serving loop) picks that one's
     sc_precision eager_prec = SC_FP32_SPLIT;
+    // compacted tables of the last plan (sc_compact.h) and their node records: valid for the
+    // precision, table layout and tables (tab_version) they were built from
+    sc::DevBuf ctab, cpos, chinv;
+    sc::CompactPlan cplan{};
+    int cplan_prec = -1;
+    bool cplan_fact = false;
+    uint64_t cplan_version = 0, tab_version = 1;
     // incident power per frequency through the aperture: [n_k] then the reduction scratch
     bool has_power = false;
     sc::DevBuf d_power;
     // lower bound of |r_s| over the nodes (the paraboloid: f), -1 if unknown
     double rs_min = -1.0;
-    // observation points; obs_r2max = max |r'|^2 when they came from host memory, else -1
+    // observation points; obs_r2max = max |r'|^2 and obs_rho2max = max x'^2 + y'^2 when they came
+    // from host memory, else -1
     int n_obs = 0, n_obs_pad = 0;
-    double obs_r2max = -1.0;
+    double obs_r2max = -1.0, obs_rho2max = -1.0;
     sc::DevBuf obs64, obs32;
     // result of the last evaluate
     int res_prec = -1;

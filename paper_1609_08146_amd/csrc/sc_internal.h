@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sc_compact.h"
 #include "sc_quadjob.h"
 
 namespace sc {
@@ -76,8 +77,16 @@ hipError_t launch_energy(hipStream_t st, int is_f64, int n_t, int n_obs, const v
                          double *part, double *W);
 hipError_t launch_quad(hipStream_t st, int mode, int obs_per_lane, int freq_per_lane, int waves_per_block,
                        int grid, const QuadJob *jobs, int n_jobs, int64_t n_tiles, unsigned int *counter);
-hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_obs,
-                         int n_obs_pad, const double *k, int b_over_k, void *E, void *B);
+// E, B [n_k][n_obs][3] at the points o0 ... o0 + n_o - 1 from partials of those points (n_o_pad padded).
+hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
+                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B);
+// Compacted tables (sc_compact.h): weights and node records, then the tables of frequencies k0 ...
+// k0 + n_k - 1 (T: n_k x compact_rows_doubles) into out [n_k][n_c][8] of the precision.
+hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, double f,
+                                   const double *r, double *wrad, double *wang, int is_f64, void *pos, void *hinv);
+hipError_t launch_compact_tables(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, int k0, int n_k,
+                                 int is_f64, int fact, const void *tab, const void *pos, const double *wrad,
+                                 const double *wang, double *T, void *out);
 hipError_t launch_twiddles(hipStream_t st, int n_k, const double *k, int n_t, const double *t, double dk,
                            double *tw);
 hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw,

@@ -635,13 +635,14 @@ __global__ void k_tables_polar(int64_t n_rec, const float *__restrict__ tabf, fl
 // Split-K reduction: E[k][o][c] = sum over chunks (in FP64, fixed order); B gets the 1/(ik) factor,
 // or 1/i where the quadrature's B sums already carry 1/k (b_over_k).
 template <typename PT, typename OT>
-__global__ void k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_obs, int n_obs_pad,
-                         const double *__restrict__ kv, int b_over_k, OT *__restrict__ E, OT *__restrict__ B)
+__global__ void k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_obs_pad,
+                         const double *__restrict__ kv, int b_over_k, int n_obs, int o0, OT *__restrict__ E,
+                         OT *__restrict__ B)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_k * n_obs) return;
-    const int kk = (int)(idx / n_obs);
-    const int o = (int)(idx - (int64_t)kk * n_obs);
+    if (idx >= (int64_t)n_k * n_o) return;
+    const int kk = (int)(idx / n_o);
+    const int o = (int)(idx - (int64_t)kk * n_o);
     double acc[12];
     for (int c = 0; c < 12; ++c) acc[c] = 0.0;
     for (int ch = 0; ch < n_chunks; ++ch) {
@@ -650,7 +651,8 @@ __global__ void k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, 
         for (int c = 0; c < 12; ++c) acc[c] += (double)p[c * 64];
     }
     const double ik_inv = b_over_k ? 1.0 : 1.0 / kv[kk];   // 1/(ik) = -i/k
-    OT *e = E + idx * 6, *b = B + idx * 6;
+    const int64_t at = ((int64_t)kk * n_obs + o0 + o) * 6;
+    OT *e = E + at, *b = B + at;
     for (int c = 0; c < 3; ++c) {
         e[2 * c] = (OT)acc[2 * c];
         e[2 * c + 1] = (OT)acc[2 * c + 1];
@@ -832,16 +834,16 @@ hipError_t launch_tables_cast(hipStream_t st, int n_k, int n_tot, const double *
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_obs,
-                         int n_obs_pad, const double *k, int b_over_k, void *E, void *B)
+hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
+                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B)
 {
-    const unsigned int nb = nblocks((int64_t)n_k * n_obs, 256);
+    const unsigned int nb = nblocks((int64_t)n_k * n_o, 256);
     if (mode == MODE_FP64)
         hipLaunchKernelGGL((k_reduce<double, double>), dim3(nb), dim3(256), 0, st, (const double *)partial, n_chunks,
-                           n_k, n_obs, n_obs_pad, k, b_over_k, (double *)E, (double *)B);
+                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (double *)E, (double *)B);
     else
         hipLaunchKernelGGL((k_reduce<float, float>), dim3(nb), dim3(256), 0, st, (const float *)partial, n_chunks,
-                           n_k, n_obs, n_obs_pad, k, b_over_k, (float *)E, (float *)B);
+                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (float *)E, (float *)B);
     return hipGetLastError();
 }
 

@@ -517,13 +517,6 @@ __device__ __forceinline__ int find_job(cjob *jobs, int n_jobs, int64_t t)
     return lo;
 }
 
-// Nodes summed plainly in FP32 registers before each block sum is added into
-// the chunk's running sum.  A plain FP32 sum of 512 terms errs by at most
-// 511 u (3e-5) of the sum of their magnitudes and typically by about
-// sqrt(512) u (1.3e-6); the running sum over the blocks of a chunk adds at most
-// chunk / 512 - 1 further roundings.
-constexpr int SUM_BLOCK = 512;
-
 // One tile of the FP32 forms: nodes [n0, n1) of a chunk, 64*OPL points, FPB
 // frequencies.  FACT selects the factored layout: node records of two v4f
 // (x, y, z, |r_s|), (u, 1 / (2|r_s|)) and one v4f (s, rho_t) per table record, instead of
@@ -535,7 +528,7 @@ constexpr int SUM_BLOCK = 512;
 // SER forms delta by its series (geom_series) from h = 1 / (2|r_s|), in the
 // node record of the factored layout or the job's per-node array otherwise
 // (the job guarantees |r'| <= 4e-4 |r_s|).
-// The sums: each block of SUM_BLOCK nodes (counted from the chunk start) is
+// The sums: each block of sum_block nodes (the job's) (counted from the chunk start) is
 // summed plainly in registers, and the block sums are added in order into the
 // chunk's running sum (the first block stores, the later ones load, add and
 // store; every address belongs to one lane of one wave).  No second set of 12
@@ -584,8 +577,9 @@ __device__ __forceinline__ void tile_f32(cjob *job, int lane, int chunk, int n0,
     // the wave's running sums of E in LDS: [OPL][FPB][6][64]
     extern __shared__ float run_lds[];
     float *run = run_lds + (size_t)(threadIdx.x >> 6) * (OPL * FPB * 6 * 64) + lane;
-    for (int b0 = n0; b0 < n1; b0 += SUM_BLOCK) {
-        const int b1 = min(b0 + SUM_BLOCK, n1);
+    const int sum_block = job->sum_block;
+    for (int b0 = n0; b0 < n1; b0 += sum_block) {
+        const int b1 = min(b0 + sum_block, n1);
         float blk[OPL][FPB][12];
 #pragma unroll
         for (int s = 0; s < OPL; ++s)

@@ -23,6 +23,7 @@ struct QuadJob {
     int n_obs_pad;        // observation points, padded to the obs block
     int n_k;
     int chunk;            // nodes per split-K chunk
+    int sum_block;        // FP32 forms: nodes summed plainly before they join the chunk's running sum
     int n_chunks;
     int obs_blocks;       // n_obs_pad / (64 * obs_per_lane)
     int factored;         // split form (FP32 or FP64) with the current factored as J~ = u s (u real, per node)
