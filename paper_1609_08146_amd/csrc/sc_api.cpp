@@ -930,6 +930,19 @@ static bool uses_tied(const sc_prob *p, sc_precision prec)
 // beat two; the general tables' longer per-frequency work does not pay for the registers.
 static int auto_freq_per_lane(sc_precision prec, bool fact) { return prec != SC_FP64 && fact ? 4 : 2; }
 
+// The same for n_k frequencies: a block of frequencies past the last one repeats it, so a count that
+// does not fill the blocks takes the width with the least work, blocks x (width x per-frequency +
+// shared instructions): one frequency in a block of two cost 1.7 times the block of one.
+static int auto_freq_per_lane(sc_precision prec, bool fact, int n_k)
+{
+    int best = auto_freq_per_lane(prec, fact);
+    const int per = fact ? 37 : 57, shared = 30;
+    auto cost = [&](int f) { return (int64_t)((n_k + f - 1) / f) * (f * per + shared); };
+    for (int f = best / 2; f >= 1; f /= 2)
+        if (cost(f) < cost(best)) best = f;
+    return best;
+}
+
 static TuneKey tune_key(const sc_prob *p, sc_precision prec)
 {
     return {(int)prec, uses_tied(p, prec) ? 2 : uses_factored(p, prec) ? 1 : 0, log2_bucket(p->n_obs),
@@ -962,7 +975,8 @@ sc_launch sc::resolve_launch(const sc_prob *p, sc_precision prec)
         if (p->launch.blocks_per_cu) l.blocks_per_cu = p->launch.blocks_per_cu;
         if (p->launch.freq_per_lane) l.freq_per_lane = p->launch.freq_per_lane;
     }
-    if (l.freq_per_lane == 0) l.freq_per_lane = auto_freq_per_lane(prec, uses_factored(p, prec));
+    if (l.freq_per_lane == 0)
+        l.freq_per_lane = auto_freq_per_lane(prec, uses_factored(p, prec), std::max(1, (int)p->k.size()));
     if (l.obs_per_lane * l.freq_per_lane > 4 || (l.obs_per_lane == 2 && l.freq_per_lane == 4))
         l.freq_per_lane = 4 / (2 * l.obs_per_lane);   // 2 points per lane: at most 2 frequencies
     return l;
@@ -1074,13 +1088,27 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
 // direct sum has 4.2e-7; blocks of 96 give 4.7e-7 and blocks of 32 4.2e-7, in the same time.
 constexpr int SUM_BLOCK = 512, SUM_BLOCK_COMPACT = 32;
 
+// The chunk the direct sum really takes: the launch's, but shorter where that leaves fewer than 2048
+// tiles (two waves per SIMD), down to 64 nodes.  A wave takes its nodes one after the other, 0.11 us
+// each: 114 points at one frequency over 3 136 nodes took 256 us in 4 waves of 2 048 nodes.  A
+// function of the problem and its chunk alone (frequencies counted in the precision's usual blocks),
+// and the partials stay below 25 MB where it shortens.
+static int direct_chunk(const sc_prob *p, sc_precision prec, int chunk)
+{
+    const int f = prec == SC_FP64 ? 2 : 4;
+    const int64_t units = (int64_t)(p->n_obs_pad / 64) * (((int64_t)p->k.size() + f - 1) / f);
+    const int64_t want = ((int64_t)p->n_tot * units + 2047) / 2048;
+    return (int)std::min<int64_t>(chunk, std::max<int64_t>(64, (want + 31) / 32 * 32));
+}
+
 // The quadrature job of one problem (no allocation): tables `tab` of the chosen layout, split-K
 // partials in `partial` ([n_chunks][n_k][12][n_obs_pad] reals of the precision).
 static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, const void *tab, bool fact,
                      void *partial, QuadJob &job)
 {
     const int n_k = (int)p->k.size();
-    const int n_chunks = (p->n_tot + l.chunk - 1) / l.chunk;
+    const int chunk = direct_chunk(p, prec, l.chunk);
+    const int n_chunks = (p->n_tot + chunk - 1) / chunk;
     job.tab = tab;
     job.pos = prec == SC_FP64 ? (fact ? p->posf64.p : p->pos64.p) : (fact ? p->posf.p : p->pos32.p);
     job.factored = fact ? 1 : 0;
@@ -1109,7 +1137,7 @@ static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, co
     job.n_tot = p->n_tot;
     job.n_obs_pad = p->n_obs_pad;
     job.n_k = n_k;
-    job.chunk = l.chunk;
+    job.chunk = chunk;
     job.sum_block = SUM_BLOCK;
     job.n_chunks = n_chunks;
     job.obs_blocks = p->n_obs_pad / (64 * l.obs_per_lane);

@@ -633,31 +633,34 @@ __global__ void k_tables_polar(int64_t n_rec, const float *__restrict__ tabf, fl
 }
 
 // Split-K reduction: E[k][o][c] = sum over chunks (in FP64, fixed order); B gets the 1/(ik) factor,
-// or 1/i where the quadrature's B sums already carry 1/k (b_over_k).
+// or 1/i where the quadrature's B sums already carry 1/k (b_over_k).  Bound by the partials' read.
+// One workgroup per frequency and 64 points, one wave per real of the record: a wave's loads are
+// consecutive, and a small problem has 12 times the waves that one thread per point gave it; the
+// records are put together in LDS and written as one run.
 template <typename PT, typename OT>
-__global__ void k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_obs_pad,
-                         const double *__restrict__ kv, int b_over_k, int n_obs, int o0, OT *__restrict__ E,
-                         OT *__restrict__ B)
+__global__ void __launch_bounds__(768)
+k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_obs_pad, const double *__restrict__ kv,
+         int b_over_k, int n_obs, int o0, OT *__restrict__ E, OT *__restrict__ B)
 {
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_k * n_o) return;
-    const int kk = (int)(idx / n_o);
-    const int o = (int)(idx - (int64_t)kk * n_o);
-    double acc[12];
-    for (int c = 0; c < 12; ++c) acc[c] = 0.0;
-    for (int ch = 0; ch < n_chunks; ++ch) {
+    const int groups = (n_o + 63) / 64, c = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int half = threadIdx.x < 384 ? 0 : 1, t = threadIdx.x - 384 * half;
+    const size_t stride = (size_t)n_k * 12 * (size_t)n_obs_pad;
+    __shared__ OT rec[2][384];
+    for (int64_t b = blockIdx.x; b < (int64_t)n_k * groups; b += gridDim.x) {
+        const int kk = (int)(b / groups), g = (int)(b - (int64_t)kk * groups);
         // partials [chunk][k][point / 64][12][64]
-        const PT *p = partial + ((size_t)ch * n_k + kk) * 12 * (size_t)n_obs_pad + (size_t)(o >> 6) * 768 + (o & 63);
-        for (int c = 0; c < 12; ++c) acc[c] += (double)p[c * 64];
-    }
-    const double ik_inv = b_over_k ? 1.0 : 1.0 / kv[kk];   // 1/(ik) = -i/k
-    const int64_t at = ((int64_t)kk * n_obs + o0 + o) * 6;
-    OT *e = E + at, *b = B + at;
-    for (int c = 0; c < 3; ++c) {
-        e[2 * c] = (OT)acc[2 * c];
-        e[2 * c + 1] = (OT)acc[2 * c + 1];
-        b[2 * c] = (OT)(acc[6 + 2 * c + 1] * ik_inv);
-        b[2 * c + 1] = (OT)(-acc[6 + 2 * c] * ik_inv);
+        const PT *p = partial + (size_t)kk * 12 * (size_t)n_obs_pad + (size_t)g * 768 + c * 64 + lane;
+        double acc = 0.0;
+#pragma unroll 8
+        for (int ch = 0; ch < n_chunks; ++ch) acc += (double)p[ch * stride];
+        const double ik_inv = b_over_k ? 1.0 : 1.0 / kv[kk];   // 1/(ik) = -i/k
+        // E: re, im of x, y, z; B: times -i / k, so the real part comes from the imaginary sum
+        if (c < 6) rec[0][6 * lane + c] = (OT)acc;
+        else if (c & 1) rec[1][6 * lane + c - 7] = (OT)(acc * ik_inv);
+        else rec[1][6 * lane + c - 5] = (OT)(-acc * ik_inv);
+        __syncthreads();
+        if (64 * g + t / 6 < n_o) (half ? B : E)[((size_t)kk * n_obs + o0 + 64 * g) * 6 + t] = rec[half][t];
+        __syncthreads();
     }
 }
 
@@ -837,12 +840,13 @@ hipError_t launch_tables_cast(hipStream_t st, int n_k, int n_tot, const double *
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
                          const double *k, int b_over_k, int n_obs, int o0, void *E, void *B)
 {
-    const unsigned int nb = nblocks((int64_t)n_k * n_o, 256);
+    const int64_t all = (int64_t)n_k * ((n_o + 63) / 64);
+    const unsigned int nb = (unsigned int)(all < (1 << 20) ? all : (1 << 20));
     if (mode == MODE_FP64)
-        hipLaunchKernelGGL((k_reduce<double, double>), dim3(nb), dim3(256), 0, st, (const double *)partial, n_chunks,
+        hipLaunchKernelGGL((k_reduce<double, double>), dim3(nb), dim3(768), 0, st, (const double *)partial, n_chunks,
                            n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (double *)E, (double *)B);
     else
-        hipLaunchKernelGGL((k_reduce<float, float>), dim3(nb), dim3(256), 0, st, (const float *)partial, n_chunks,
+        hipLaunchKernelGGL((k_reduce<float, float>), dim3(nb), dim3(768), 0, st, (const float *)partial, n_chunks,
                            n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (float *)E, (float *)B);
     return hipGetLastError();
 }
