@@ -103,7 +103,6 @@ extern "C" sc_status sc_ctx_destroy(sc_ctx *c)
     if (c->upload_done) (void)hipEventDestroy(c->upload_done);
     c->counter.release();
     c->jobs.release();
-    c->compact_work.release();
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
     delete c;
     return SC_OK;
@@ -1183,36 +1182,56 @@ static void compact_job(const CompactPlan &plan, const void *tab, const void *po
     job.n_tiles = (int64_t)job.obs_blocks * job.n_chunks * ((job.n_k + l.freq_per_lane - 1) / l.freq_per_lane);
 }
 
-// Partial rows kept at a time while compacted tables are built: more frequencies go in slabs, which
-// also keeps what one kernel writes and the next reads within the last-level cache.
-constexpr size_t COMPACT_SLAB_BYTES = 128u << 20;
+// Where the compacted tables of a problem lie in its ctab buffer, and the working memory they are
+// built in: the interpolation weights and the partial rows of `per_k` frequencies at a time.
+struct CompactLayout {
+    size_t tab, pos, hinv, bytes;                // offsets in ctab, its size
+    size_t wrad, wang, rows, row_bytes, work;    // offsets in the working memory, its size
+    int per_k;
+};
+
+// Partial rows of more frequencies than fit `room` bytes go in slabs (at least one, else as many as
+// fit 32 MB, which also keeps what one kernel writes and the next reads within the last-level cache).
+static CompactLayout compact_layout(const sc_prob *p, sc_precision prec, const CompactPlan &plan, size_t room)
+{
+    const size_t rs = real_size(prec), n_k = p->k.size(), n_c = (size_t)plan.n_c;
+    auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
+    CompactLayout c;
+    c.tab = 0;
+    c.pos = up(rs * 8 * n_k * n_c);
+    c.hinv = c.pos + up(rs * 4 * n_c);
+    c.bytes = c.hinv + up(rs * n_c);
+    c.wrad = 0;
+    c.wang = up(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
+    c.rows = c.wang + up(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
+    c.row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
+    const size_t fit = std::max(room > c.rows ? room - c.rows : 0, size_t(32) << 20) / c.row_bytes;
+    const size_t most = std::max<size_t>(1, std::min(n_k, fit)), slabs = (n_k + most - 1) / most;
+    c.per_k = (int)((n_k + slabs - 1) / slabs);
+    c.work = c.rows + c.row_bytes * (size_t)c.per_k;
+    return c;
+}
 
 // The compacted tables of p in prec from its tables `tab` (layout `fact`), kept until those change.
-static sc_status ensure_compact(sc_prob *p, sc_precision prec, const CompactPlan &plan, const void *tab, bool fact)
+// They are built in the partials' buffer, which the quadrature fills afterwards.
+static sc_status ensure_compact(sc_prob *p, sc_precision prec, const CompactPlan &plan, const CompactLayout &lay,
+                                const void *tab, bool fact)
 {
     if (p->cplan_prec == (int)prec && p->cplan_fact == fact && p->cplan_version == p->tab_version &&
         memcmp(&p->cplan, &plan, sizeof plan) == 0)
         return SC_OK;
     const int n_k = (int)p->k.size(), f64 = prec == SC_FP64;
-    const size_t rs = real_size(prec);
     p->cplan_prec = -1;
-    SC_TRY(p->ctab.reserve(rs * 8 * (size_t)n_k * plan.n_c, p->alloc_stream));
-    SC_TRY(p->cpos.reserve(rs * 4 * (size_t)plan.n_c, p->alloc_stream));
-    SC_TRY(p->chinv.reserve(rs * (size_t)plan.n_c, p->alloc_stream));
-    const size_t nrad = (size_t)compact_radial_doubles(plan, p->n_r), nang = (size_t)compact_angular_doubles(plan, p->n_phi);
-    const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
-    const int most = (int)std::max<size_t>(1, std::min<size_t>((size_t)n_k, COMPACT_SLAB_BYTES / row_bytes));
-    const int slabs = (n_k + most - 1) / most, per = (n_k + slabs - 1) / slabs;
-    DevBuf &work = p->ctx->compact_work;   // used on the context's stream only
-    SC_TRY(work.reserve(sizeof(double) * (nrad + nang) + row_bytes * per, p->alloc_stream));
-    double *wrad = work.as<double>(), *wang = wrad + nrad, *T = wang + nang;
+    SC_TRY(p->ctab.reserve(lay.bytes, p->alloc_stream));
+    char *c = (char *)p->ctab.p, *w = (char *)p->partial.p;
+    double *wrad = (double *)(w + lay.wrad), *wang = (double *)(w + lay.wang), *T = (double *)(w + lay.rows);
     hipStream_t st = p->ctx->stream;
-    HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, p->cpos.p,
-                                    p->chinv.p));
+    HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, c + lay.pos,
+                                    c + lay.hinv));
     const void *pos = fact ? (f64 ? p->posf64.p : p->posf.p) : nullptr;
-    for (int k0 = 0; k0 < n_k; k0 += per)
-        HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, std::min(per, n_k - k0), f64, fact ? 1 : 0, tab, pos,
-                                      wrad, wang, T, (char *)p->ctab.p + rs * 8 * (size_t)k0 * plan.n_c));
+    for (int k0 = 0; k0 < n_k; k0 += lay.per_k)
+        HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, std::min(lay.per_k, n_k - k0), f64, fact ? 1 : 0,
+                                      tab, pos, wrad, wang, T, c + lay.tab + real_size(prec) * 8 * (size_t)k0 * plan.n_c));
     p->cplan = plan;
     p->cplan_prec = (int)prec;
     p->cplan_fact = fact;
@@ -1237,10 +1256,18 @@ sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, QuadJob
     const int n_k = (int)p->k.size();
     CompactPlan plan;
     const bool compact = plan_compact(p, prec, plan);
-    if (compact) SC_TRY(ensure_compact(p, prec, plan, tab, fact));
     fill_job(p, prec, l, tab, fact, nullptr, job);
-    if (compact) compact_job(plan, p->ctab.p, p->cpos.p, p->chinv.p, l, job);
-    SC_TRY(p->partial.reserve(rs * 12 * (size_t)job.n_chunks * n_k * (size_t)p->n_obs_pad, p->alloc_stream));
+    if (compact) compact_job(plan, nullptr, nullptr, nullptr, l, job);
+    size_t part = rs * 12 * (size_t)job.n_chunks * n_k * (size_t)p->n_obs_pad;
+    if (compact) {
+        const CompactLayout lay = compact_layout(p, prec, plan, part);
+        SC_TRY(p->partial.reserve(std::max(part, lay.work), p->alloc_stream));
+        SC_TRY(ensure_compact(p, prec, plan, lay, tab, fact));
+        const char *c = (const char *)p->ctab.p;
+        compact_job(plan, c + lay.tab, c + lay.pos, c + lay.hinv, l, job);
+    } else {
+        SC_TRY(p->partial.reserve(part, p->alloc_stream));
+    }
     job.partial = p->partial.p;
     SC_TRY(p->resE.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc_stream));
     SC_TRY(p->resB.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc_stream));
@@ -1794,7 +1821,7 @@ static std::vector<DevBuf *> prob_buffers(sc_prob *p)
             &p->tab32n, &p->tabf,    &p->posf,      &p->betaf,   &p->tabp,     &p->tabf64, &p->posf64,
             &p->betaf64, &p->fact_flag, &p->d_power, &p->obs64,  &p->obs32,    &p->resE,   &p->resB,
             &p->partial, &p->d_t,    &p->tw,        &p->timeE,   &p->timeB,    &p->d_spec, &p->d_obs_in,
-            &p->d_modes, &p->ctab,   &p->cpos,      &p->chinv};
+            &p->d_modes, &p->ctab};
 }
 
 void sc::prob_free_on(sc_prob *p, hipStream_t st)

@@ -21,15 +21,17 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double cheb_point(int j, int n) { return cospi((double)(2 * j + 1) / (double)(2 * n)); }
 
-// Blocks of 64: first one per radius (radial weights), then the angular weights (one block per (row,
-// 16 columns)), then the compacted nodes.
+// Blocks of 64: first one per radius (radial weights), then the angular weights (one block per (16
+// columns of a row, 64 phi)), then the compacted nodes.  Latency of a few sines each: 1.1e6 angular
+// weights (400 phi, 2 700 nodes) took 67 us with one block for all phi of 16 columns.
+constexpr int GEOM_PHI = 64;
 __global__ void __launch_bounds__(64)
 k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double *__restrict__ r,
                    double *__restrict__ wrad, double *__restrict__ wang, double *__restrict__ pos64,
                    double *__restrict__ hinv64, float *__restrict__ pos32, float *__restrict__ hinv32)
 {
     const int lane = threadIdx.x, rows = plan.rows, rp = (rows + 15) / 16 * 16;
-    const int n_i = (n_r + 4) / 4 * 4, n_a = plan.poff[rows] / 16;
+    const int n_i = (n_r + 4) / 4 * 4, n_g = (n_phi + GEOM_PHI - 1) / GEOM_PHI, n_a = plan.poff[rows] / 16 * n_g;
     int b = blockIdx.x;
     if (b < n_i) {
         // barycentric weights of the Chebyshev points: w_j = (-1)^j sin((2j + 1) pi / 2N)
@@ -59,12 +61,13 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     }
     b -= n_i;
     if (b < n_a) {
+        const int pt = b / n_g, j0 = (b - pt * n_g) * GEOM_PHI, j1 = min(j0 + GEOM_PHI, n_phi);
         int m = 0;
-        while (plan.poff[m + 1] <= 16 * b) ++m;
-        const int P = plan.cols[m], p0 = 16 * b - plan.poff[m], pp = (P + 15) / 16 * 16;
+        while (plan.poff[m + 1] <= 16 * pt) ++m;
+        const int P = plan.cols[m], p0 = 16 * pt - plan.poff[m], pp = (P + 15) / 16 * 16;
         double *w = wang + (size_t)plan.poff[m] * n_phi;
         const int p = p0 + (lane & 15);
-        for (int j = lane >> 4; j < n_phi; j += 4) {
+        for (int j = j0 + (lane >> 4); j < j1; j += 4) {
             double d = 0.0;
             if (p < P) {
                 // sin(P x / 2) / (P sin(x / 2)) at x = 2 pi (j / n_phi - p / P), on exact integers
@@ -171,14 +174,17 @@ k_compact_rows(int k0, int n_r, int n_phi, int rows, int split, const R *__restr
 
 constexpr int COLS_KP = 4;   // pairs of frequencies per wave
 
-// The contraction over phi: one wave per (row, 16 columns, 8 frequencies); the 16 columns of a
-// product are 2 frequencies x 8 reals, and the angular weights serve the 4 products of a wave.
+// The contraction over phi: one workgroup per (row, 16 columns, 8 frequencies), its four waves each a
+// quarter of the phi, joined in LDS in a fixed order; the 16 columns of a product are 2 frequencies x 8
+// reals, and the angular weights serve the 4 products of a wave.  Latency of the T loads is what
+// bounds it: with one wave for all phi and two steps in flight it took 135 us at 128 frequencies and
+// 130-200 us at 5 to 30, where there are few workgroups.
 template <typename OT>
-__global__ void __launch_bounds__(64)
+__global__ void __launch_bounds__(256)
 k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ wang, const double *__restrict__ T,
                OT *__restrict__ out)
 {
-    const int lane = threadIdx.x, kq = lane >> 4, col = lane & 15, c = col & 7;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kq = lane >> 4, col = lane & 15, c = col & 7;
     const int rows = plan.rows, split = plan.split;
     const int b = blockIdx.x;
     int m = 0;
@@ -194,9 +200,10 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
     d4 acc[COLS_KP];
 #pragma unroll
     for (int g = 0; g < COLS_KP; ++g) acc[g] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-    for (int j0 = 0; j0 < n_phi; j0 += 4) {
-        const int j = min(j0 + kq, n_phi - 1);
+    const int steps = (n_phi + 3) / 4, s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
+#pragma unroll 4
+    for (int js = s0; js < s1; ++js) {
+        const int j0 = 4 * js, j = min(j0 + kq, n_phi - 1);
         const double a = j0 + kq < n_phi ? w[(size_t)j * pp] : 0.0;
 #pragma unroll
         for (int g = 0; g < COLS_KP; ++g) {
@@ -205,9 +212,17 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
             acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v, acc[g], 0, 0, 0);
         }
     }
+    __shared__ d4 part[3][COLS_KP][64];
+    if (wave > 0) {
+#pragma unroll
+        for (int g = 0; g < COLS_KP; ++g) part[wave - 1][g][lane] = acc[g];
+    }
+    __syncthreads();
+    if (wave > 0) return;
 #pragma unroll
     for (int g = 0; g < COLS_KP; ++g) {
         const int k = kbase + 2 * g;
+        acc[g] = ((acc[g] + part[0][g][lane]) + part[1][g][lane]) + part[2][g][lane];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
             const int p = p0 + 4 * q + kq;
@@ -221,7 +236,8 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
 hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, double f,
                                    const double *r, double *wrad, double *wang, int is_f64, void *pos, void *hinv)
 {
-    const int blocks = (n_r + 4) / 4 * 4 + plan.poff[plan.rows] / 16 + (plan.n_c + 63) / 64;
+    const int blocks = (n_r + 4) / 4 * 4 + plan.poff[plan.rows] / 16 * ((n_phi + GEOM_PHI - 1) / GEOM_PHI) +
+                       (plan.n_c + 63) / 64;
     hipLaunchKernelGGL(k_compact_geometry, dim3(blocks), dim3(64), 0, st, plan, n_r, n_phi, f, r, wrad, wang,
                        is_f64 ? (double *)pos : nullptr, is_f64 ? (double *)hinv : nullptr,
                        is_f64 ? nullptr : (float *)pos, is_f64 ? nullptr : (float *)hinv);
@@ -244,9 +260,9 @@ hipError_t launch_compact_tables(hipStream_t st, const CompactPlan &plan, int n_
 #undef SC_COMPACT_ROWS
     const dim3 gc(plan.poff[plan.rows] / 16, (n_k + 2 * COLS_KP - 1) / (2 * COLS_KP));
     if (is_f64)
-        hipLaunchKernelGGL((k_compact_cols<double>), gc, dim3(64), 0, st, plan, n_k, n_phi, wang, T, (double *)out);
+        hipLaunchKernelGGL((k_compact_cols<double>), gc, dim3(256), 0, st, plan, n_k, n_phi, wang, T, (double *)out);
     else
-        hipLaunchKernelGGL((k_compact_cols<float>), gc, dim3(64), 0, st, plan, n_k, n_phi, wang, T, (float *)out);
+        hipLaunchKernelGGL((k_compact_cols<float>), gc, dim3(256), 0, st, plan, n_k, n_phi, wang, T, (float *)out);
     return hipGetLastError();
 }
 

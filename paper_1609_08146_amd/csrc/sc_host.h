@@ -114,7 +114,6 @@ struct sc_ctx {
     int n_cu = 256;
     sc::DevBuf counter;   // persistent-launch work counter
     sc::DevBuf jobs;      // QuadJob array for launches
-    sc::DevBuf compact_work;   // interpolation weights and partial rows while compacted tables are built
     std::vector<sc::QuadJob> host_jobs;
     hipEvent_t upload_done = nullptr;
     std::map<sc::TuneKey, sc_launch> tune;
@@ -163,9 +162,9 @@ struct sc_prob {
     // the factored tables built with the test when the incident field is set: FP32 split by
     // default; a caller that knows its one precision (the serving loop) picks that one's
     sc_precision eager_prec = SC_FP32_SPLIT;
-    // compacted tables of the last plan (sc_compact.h) and their node records: valid for the
-    // precision, table layout and tables (tab_version) they were built from
-    sc::DevBuf ctab, cpos, chinv;
+    // compacted tables of the last plan (sc_compact.h) and their node records, one after the other:
+    // valid for the precision, table layout and tables (tab_version) they were built from
+    sc::DevBuf ctab;
     sc::CompactPlan cplan{};
     int cplan_prec = -1;
     bool cplan_fact = false;
