@@ -1082,10 +1082,8 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
 // Nodes summed plainly in FP32 registers before each block sum is added into the chunk's running sum.
 // A plain FP32 sum of 512 terms errs by at most 511 u (3e-5) of the sum of their magnitudes and
 // typically by about sqrt(512) u (1.3e-6); the running sum over the blocks of a chunk adds at most
-// chunk / 512 - 1 further roundings.  Compacted terms are few and large, so there are few blocks for
-// the rounding to average over: blocks of 512 cost the broadband field 1.6e-6 (relative L2) where the
-// direct sum has 4.2e-7; blocks of 96 give 4.7e-7 and blocks of 32 4.2e-7, in the same time.
-constexpr int SUM_BLOCK = 512, SUM_BLOCK_COMPACT = 32;
+// chunk / 512 - 1 further roundings.
+constexpr int SUM_BLOCK = 512;
 
 // The chunk the direct sum really takes: the launch's, but shorter where that leaves fewer than 2048
 // tiles (two waves per SIMD), down to 64 nodes.  A wave takes its nodes one after the other, 0.11 us
@@ -1177,16 +1175,42 @@ static void compact_job(const CompactPlan &plan, const void *tab, const void *po
     job.factored = job.tied = 0;
     job.n_tot = plan.n_c;
     job.chunk = plan.chunk;
-    job.sum_block = SUM_BLOCK_COMPACT;
     job.n_chunks = (plan.n_c + plan.chunk - 1) / plan.chunk;
     job.n_tiles = (int64_t)job.obs_blocks * job.n_chunks * ((job.n_k + l.freq_per_lane - 1) / l.freq_per_lane);
 }
 
-// Where the compacted tables of a problem lie in its ctab buffer, and the working memory they are
-// built in: the interpolation weights and the partial rows of `per_k` frequencies at a time.
+// The same for the FP32 form, whose sum k_quad_mm takes: packed rows, tiles of 128 points x fpb frequencies.
+static void compact_job_mm(const CompactPlan &plan, const void *mtab, const void *mscale, const void *pos,
+                           const void *hinv, int fpb, QuadJob &job)
+{
+    sc_launch l{};
+    l.freq_per_lane = fpb;
+    compact_job(plan, nullptr, pos, hinv, l, job);
+    job.mtab = mtab;
+    job.mscale = (const float *)mscale;
+    job.mm = fpb;
+    job.far = plan.far;
+    job.scale = (float)plan.scale;
+    job.n_tiles = (int64_t)(job.n_obs_pad / 128) * job.n_chunks * ((job.n_k + fpb - 1) / fpb);
+}
+
+// Frequencies per tile of a launch of one such job: the width with the least work (54 cycles per
+// frequency and 12 shared, past the last frequency repeated).
+static int mm_freqs(int n_k)
+{
+    auto cost = [n_k](int f) { return (int64_t)((n_k + f - 1) / f) * (54 * f + 12); };
+    int best = 4;
+    for (int f : {2, 1})
+        if (cost(f) < cost(best)) best = f;
+    return best;
+}
+
+// Where the compacted tables of a problem lie in its ctab buffer (FP64: records; FP32: packed rows and
+// their scales), and the working memory they are built in: the interpolation weights and the partial
+// rows of `per_k` frequencies at a time.
 struct CompactLayout {
-    size_t tab, pos, hinv, bytes;                // offsets in ctab, its size
-    size_t wrad, wang, rows, row_bytes, work;    // offsets in the working memory, its size
+    size_t tab, scale, pos, hinv, bytes;              // offsets in ctab, its size
+    size_t wrad, wang, raw, rows, row_bytes, work;    // offsets in the working memory, its size
     int per_k;
 };
 
@@ -1197,13 +1221,17 @@ static CompactLayout compact_layout(const sc_prob *p, sc_precision prec, const C
     const size_t rs = real_size(prec), n_k = p->k.size(), n_c = (size_t)plan.n_c;
     auto up = [](size_t v) { return (v + 255) & ~size_t(255); };
     CompactLayout c;
+    const bool mm = prec == SC_FP32_SPLIT;
+    const size_t tab_bytes = up(rs * 8 * n_k * n_c);
     c.tab = 0;
-    c.pos = up(rs * 8 * n_k * n_c);
-    c.hinv = c.pos + up(rs * 4 * n_c);
-    c.bytes = c.hinv + up(rs * n_c);
+    c.scale = mm ? up(mm_table_bytes((int)n_k, (int)n_c, plan.far)) : tab_bytes;
+    c.pos = c.scale + (mm ? up(sizeof(float) * 16 * n_k) : 0);
+    c.hinv = c.pos + up(rs * 4 * (n_c + 3));
+    c.bytes = c.hinv + up(rs * (n_c + 3));
     c.wrad = 0;
     c.wang = up(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
-    c.rows = c.wang + up(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
+    c.raw = c.wang + up(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
+    c.rows = c.raw + (mm ? tab_bytes : 0);   // the FP32 records, before they are packed
     c.row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
     const size_t fit = std::max(room > c.rows ? room - c.rows : 0, size_t(32) << 20) / c.row_bytes;
     const size_t most = std::max<size_t>(1, std::min(n_k, fit)), slabs = (n_k + most - 1) / most;
@@ -1229,9 +1257,13 @@ static sc_status ensure_compact(sc_prob *p, sc_precision prec, const CompactPlan
     HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, c + lay.pos,
                                     c + lay.hinv));
     const void *pos = fact ? (f64 ? p->posf64.p : p->posf.p) : nullptr;
+    char *rec = f64 ? c + lay.tab : w + lay.raw;
     for (int k0 = 0; k0 < n_k; k0 += lay.per_k)
         HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, std::min(lay.per_k, n_k - k0), f64, fact ? 1 : 0,
-                                      tab, pos, wrad, wang, T, c + lay.tab + real_size(prec) * 8 * (size_t)k0 * plan.n_c));
+                                      tab, pos, wrad, wang, T, rec + real_size(prec) * 8 * (size_t)k0 * plan.n_c));
+    if (!f64)
+        HIP_TRY(launch_mm_tables(st, n_k, plan.n_c, plan.far, p->d_k.as<double>(), plan.scale, (const float *)rec,
+                                 (const float *)(c + lay.pos), (float *)(c + lay.scale), c + lay.tab));
     p->cplan = plan;
     p->cplan_prec = (int)prec;
     p->cplan_fact = fact;
@@ -1247,7 +1279,7 @@ static size_t partial_bytes(const sc_prob *p, sc_precision prec, const sc_launch
 }
 
 // Make sure the tables of precision `prec` exist; size the partial and result buffers.
-sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, QuadJob &job)
+sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job)
 {
     const void *tab = nullptr;
     bool fact = false;
@@ -1258,13 +1290,15 @@ sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, QuadJob
     const bool compact = plan_compact(p, prec, plan);
     fill_job(p, prec, l, tab, fact, nullptr, job);
     if (compact) compact_job(plan, nullptr, nullptr, nullptr, l, job);
+    const int fpb = mm_fpb ? mm_fpb : mm_freqs(n_k);
     size_t part = rs * 12 * (size_t)job.n_chunks * n_k * (size_t)p->n_obs_pad;
     if (compact) {
         const CompactLayout lay = compact_layout(p, prec, plan, part);
         SC_TRY(p->partial.reserve(std::max(part, lay.work), p->alloc_stream));
         SC_TRY(ensure_compact(p, prec, plan, lay, tab, fact));
         const char *c = (const char *)p->ctab.p;
-        compact_job(plan, c + lay.tab, c + lay.pos, c + lay.hinv, l, job);
+        if (prec == SC_FP32_SPLIT) compact_job_mm(plan, c + lay.tab, c + lay.scale, c + lay.pos, c + lay.hinv, fpb, job);
+        else compact_job(plan, c + lay.tab, c + lay.pos, c + lay.hinv, l, job);
     } else {
         SC_TRY(p->partial.reserve(part, p->alloc_stream));
     }
@@ -1312,30 +1346,46 @@ static int quad_grid(const sc_ctx *c, sc_precision prec, const sc_launch &l, int
     return (int)std::max<int64_t>(grid, 1);
 }
 
-// Upload jobs and run one persistent quadrature launch over all their tiles.
+// Upload jobs and run the quadrature over all their tiles: one launch of the compacted FP32 sums (job.mm)
+// and one persistent launch of the others.  A single job travels as a kernel argument.
 sc_status sc::run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec, const sc_launch &l,
                           sc_prob *timed)
 {
     hipStream_t st = c->stream;
-    int64_t n_tiles = 0;
-    for (auto &j : jobs) {
-        j.tile0 = n_tiles;
-        n_tiles += j.n_tiles;
-    }
-    if (n_tiles >= (1LL << 31) - (1LL << 24)) return fail(SC_E_UNSUPPORTED, "evaluate: too many tiles (%lld)",
-                                                           (long long)n_tiles);
+    unsigned int *counter = c->counter.as<unsigned int>();
+    std::vector<QuadJob> order;   // the mm jobs first
+    order.reserve(jobs.size());
+    int64_t tiles[2] = {0, 0};
+    int n_mm = 0;
+    for (int plain = 0; plain < 2; ++plain)
+        for (auto &j : jobs) {
+            if ((j.mm == 0) != (plain == 1)) continue;
+            j.tile0 = tiles[plain];
+            tiles[plain] += j.n_tiles;
+            n_mm += 1 - plain;
+            order.push_back(j);
+        }
+    if (tiles[0] + tiles[1] >= (1LL << 31) - (1LL << 24))
+        return fail(SC_E_UNSUPPORTED, "evaluate: too many tiles (%lld)", (long long)(tiles[0] + tiles[1]));
     SC_TRY(c->jobs.reserve(sizeof(QuadJob) * jobs.size()));
-    // the previous upload from host_jobs must have completed before it is overwritten
-    HIP_TRY(hipEventSynchronize(c->upload_done));
-    c->host_jobs = jobs;
-    HIP_TRY(hipMemcpyAsync(c->jobs.p, c->host_jobs.data(), sizeof(QuadJob) * jobs.size(), hipMemcpyHostToDevice,
-                           st));
-    HIP_TRY(hipEventRecord(c->upload_done, st));
-    HIP_TRY(launch_fill_u32(st, c->counter.as<unsigned int>(), 0u, QUAD_SEGMENTS));
-    const int grid = quad_grid(c, prec, l, n_tiles);
+    const int n_plain = (int)jobs.size() - n_mm;
+    if (jobs.size() > 1) {
+        // the previous upload from host_jobs must have completed before it is overwritten
+        HIP_TRY(hipEventSynchronize(c->upload_done));
+        c->host_jobs = order;
+        HIP_TRY(hipMemcpyAsync(c->jobs.p, c->host_jobs.data(), sizeof(QuadJob) * jobs.size(), hipMemcpyHostToDevice,
+                               st));
+        HIP_TRY(hipEventRecord(c->upload_done, st));
+        if (n_plain) HIP_TRY(launch_fill_u32(st, counter, 0u, QUAD_SEGMENTS));
+    } else if (n_plain) {
+        HIP_TRY(launch_store_job(st, order[0], c->jobs.as<QuadJob>(), counter));
+    }
     if (timed) ev_record(timed, EV_Q0);
-    HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block, grid,
-                        c->jobs.as<QuadJob>(), (int)jobs.size(), n_tiles, c->counter.as<unsigned int>()));
+    if (n_mm == 1 && n_plain == 0) HIP_TRY(launch_quad_mm_one(st, order[0].mm, order[0], tiles[0]));
+    else if (n_mm) HIP_TRY(launch_quad_mm(st, order[0].mm, c->jobs.as<QuadJob>(), n_mm, tiles[0]));
+    if (n_plain)
+        HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
+                            quad_grid(c, prec, l, tiles[1]), c->jobs.as<QuadJob>() + n_mm, n_plain, tiles[1], counter));
     if (timed) ev_record(timed, EV_Q1);
     return SC_OK;
 }
@@ -1358,7 +1408,7 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     const sc_launch l = resolve_launch(p, prec);
     SC_TRY(check_launch(l));
     QuadJob job{};
-    SC_TRY(prepare(p, prec, l, job));
+    SC_TRY(prepare(p, prec, l, 0, job));
     std::vector<QuadJob> jobs{job};
     p->res_prec = -1;
     SC_TRY(run_quad(p->ctx, jobs, prec, l, p));
@@ -1437,10 +1487,13 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     hipStream_t st = p->ctx->stream;
     // frequencies k0 ... k0 + n - 1 and points o0 ... o0 + n_o - 1 of one job
     auto enqueue = [&](int k0, int o0, int n_o) -> sc_status {
-        HIP_TRY(launch_store_job(st, job, djob));
-        HIP_TRY(launch_fill_u32(st, counter, 0u, QUAD_SEGMENTS));
-        HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
-                            quad_grid(p->ctx, prec, l, job.n_tiles), djob, 1, job.n_tiles, counter));
+        if (job.mm) {
+            HIP_TRY(launch_quad_mm_one(st, job.mm, job, job.n_tiles));
+        } else {
+            HIP_TRY(launch_store_job(st, job, djob, counter));
+            HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
+                                quad_grid(p->ctx, prec, l, job.n_tiles), djob, 1, job.n_tiles, counter));
+        }
         const size_t at = real_size(prec) * 6 * (size_t)k0 * p->n_obs;
         HIP_TRY(launch_reduce(st, mode_of(prec), job.partial, job.n_chunks, job.n_k, n_o, job.n_obs_pad,
                               p->d_k.as<double>() + k0, job.tied, p->n_obs, o0, (char *)E + at, (char *)B + at));
@@ -1464,12 +1517,14 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     };
     double *wrad = (double *)take(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
     double *wang = (double *)take(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
-    void *cpos = take(rs * 4 * (size_t)plan.n_c), *chinv = take(rs * (size_t)plan.n_c);
+    void *cpos = take(rs * 4 * (size_t)(plan.n_c + 3)), *chinv = take(rs * (size_t)(plan.n_c + 3));
     const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
-    const size_t tab_bytes = rs * 8 * (size_t)plan.n_c;
+    // compacted records, and in the FP32 form their packed rows and scales
+    const size_t rec_bytes = rs * 8 * (size_t)plan.n_c;
+    const size_t tab_bytes = rec_bytes + (f64 ? 0 : mm_table_bytes(1, plan.n_c, plan.far) + sizeof(float) * 16);
     const size_t n_chunks = (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk);
     const size_t part_bytes = rs * 12 * n_chunks;   // per frequency and padded point
-    const size_t left = off + 1024 < SC_NOALLOC_SCRATCH_BYTES ? SC_NOALLOC_SCRATCH_BYTES - off - 1024 : 0;
+    const size_t left = off + 2048 < SC_NOALLOC_SCRATCH_BYTES ? SC_NOALLOC_SCRATCH_BYTES - off - 2048 : 0;
     int per_k = (int)std::min<size_t>((size_t)n_k, left / (row_bytes + tab_bytes + part_bytes * p->n_obs_pad));
     int per_o = p->n_obs_pad;
     if (per_k < 1) {
@@ -1479,13 +1534,20 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
         if (per_o < OBS_PAD) return fail(SC_E_INVAL, "sc_evaluate_noalloc: the scratch is too small for the mirror's nodes");
     }
     double *T = (double *)take(row_bytes * per_k);
-    char *ctab = take(tab_bytes * per_k);
+    char *ctab = take(rec_bytes * per_k), *mtab = nullptr, *mscale = nullptr;
+    if (!f64) {
+        mtab = take(mm_table_bytes(per_k, plan.n_c, plan.far));
+        mscale = take(sizeof(float) * 16 * (size_t)per_k);
+    }
     char *part = take(part_bytes * per_k * per_o);
     HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, cpos, chinv));
     const void *pos = fact ? (f64 ? p->posf64.p : p->posf.p) : nullptr;
     for (int k0 = 0; k0 < n_k; k0 += per_k) {
         const int nk = std::min(per_k, n_k - k0);
         HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, nk, f64, fact ? 1 : 0, tab, pos, wrad, wang, T, ctab));
+        if (!f64)
+            HIP_TRY(launch_mm_tables(st, nk, plan.n_c, plan.far, p->d_k.as<double>() + k0, plan.scale, (const float *)ctab,
+                                     (const float *)cpos, (float *)mscale, mtab));
         for (int o0 = 0; o0 < p->n_obs; o0 += per_o) {
             fill_job(p, prec, l, tab, fact, part, job);
             job.n_k = nk;
@@ -1493,7 +1555,8 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
             job.n_obs_pad = std::min(per_o, p->n_obs_pad - o0);
             job.obs = (const char *)job.obs + rs * 4 * (size_t)o0;
             job.obs_blocks = job.n_obs_pad / (64 * l.obs_per_lane);
-            compact_job(plan, ctab, cpos, chinv, l, job);
+            if (f64) compact_job(plan, ctab, cpos, chinv, l, job);
+            else compact_job_mm(plan, mtab, mscale, cpos, chinv, mm_freqs(nk), job);
             SC_TRY(enqueue(k0, o0, std::min(per_o, p->n_obs - o0)));
         }
     }
@@ -1605,7 +1668,7 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
     }
     batch_fit_partials(probs, n, prec, ls);
     for (int i = 0; i < n; ++i) {
-        SC_TRY(prepare(probs[i], prec, ls[i], jobs[i]));
+        SC_TRY(prepare(probs[i], prec, ls[i], MM_FREQS_SHARED, jobs[i]));
         probs[i]->res_prec = -1;
     }
     SC_TRY(run_quad(c, jobs, prec, l0, probs[0]));

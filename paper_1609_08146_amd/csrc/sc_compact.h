@@ -25,6 +25,8 @@ struct CompactPlan {
     int n_c;                                // compacted nodes in all (sum of cols)
     int split;                              // parts the sum over the radii is cut into (partial rows)
     int chunk;                              // compacted nodes per split-K chunk of the quadrature
+    int far;                                // some |r'| > |r_s| / 100
+    double scale;                           // power of two near f
     double theta_max;                       // 2 atan(r_max / 2f)
     uint16_t cols[COMPACT_MAX_ROWS];        // phi per row: odd, or n_phi (taken as they are)
     int32_t off[COMPACT_MAX_ROWS + 1];      // first compacted node of each row

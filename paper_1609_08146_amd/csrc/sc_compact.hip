@@ -83,13 +83,14 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     }
     b -= n_a;
     const int q = 64 * b + lane;
-    if (q >= plan.n_c) return;
+    if (q >= (plan.n_c + 3) / 4 * 4) return;
+    const int qn = min(q, plan.n_c - 1);   // up to a multiple of 4 the last node again
     int m = 0;
-    while (plan.off[m + 1] <= q) ++m;
+    while (plan.off[m + 1] <= qn) ++m;
     const double th = 0.5 * plan.theta_max * (1.0 + cheb_point(m, rows));
     const double rr = 2.0 * f * tan(0.5 * th);
     double s, c;
-    sincospi(2.0 * (double)(q - plan.off[m]) / (double)plan.cols[m], &s, &c);
+    sincospi(2.0 * (double)(qn - plan.off[m]) / (double)plan.cols[m], &s, &c);
     const double z = rr * rr / (4.0 * f), rs = z + f;   // |r_s| = r^2 / 4f + f on the paraboloid
     const double v[4] = {rr * c, rr * s, z - f, rs};
     for (int k = 0; k < 4; ++k) {

@@ -97,12 +97,20 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     plan.n_c = (int)n_c;
     plan.theta_max = theta_max;
 
-    // The quadrature's chunk: about four rounds of tiles (64 points x 2 frequencies x chunk) over the
-    // resident waves, at least 64 nodes: the last round's empty slots stay below a quarter of the
-    // time, and the partials below 125 MB plus one chunk's.
-    const int64_t units = (int64_t)(in.n_obs_pad / 64) * ((in.n_k + 1) / 2);
-    const int64_t chunks = (20480 + units - 1) / units;
-    plan.chunk = (int)std::max<int64_t>(64, ((n_c + chunks - 1) / chunks + 31) / 32 * 32);
+    // The quadrature's chunk, at least 64 nodes.  FP64 (tiles of 64 points x 2 frequencies per wave): about
+    // four rounds of tiles over the resident waves, so that the last round's empty slots stay below a
+    // quarter of the time and the partials below 125 MB plus one chunk's.  FP32 (128 points x 4
+    // frequencies per workgroup): about four rounds of workgroups, and no more than 256 nodes, because a
+    // chunk is one FP32 sum.
+    if (in.fp64) {
+        const int64_t units = (int64_t)(in.n_obs_pad / 64) * ((in.n_k + 1) / 2), chunks = (20480 + units - 1) / units;
+        plan.chunk = (int)std::max<int64_t>(64, ((n_c + chunks - 1) / chunks + 31) / 32 * 32);
+    } else {
+        const int64_t units = (int64_t)(in.n_obs_pad / 128) * ((in.n_k + 3) / 4), chunks = (4096 + units - 1) / units;
+        plan.chunk = (int)std::min<int64_t>(256, std::max<int64_t>(64, ((n_c + chunks - 1) / chunks + 31) / 32 * 32));
+    }
+    plan.far = q > 0.01;
+    plan.scale = std::ldexp(1.0, std::ilogb(in.f));
     // The radii's sum: cut until there are about 1024 waves of it, at least 32 radii each.
     const int64_t waves = (int64_t)in.n_k * ((in.n_phi + 15) / 16) * ((rows + 15) / 16);
     plan.split = (int)std::max<int64_t>(1, std::min<int64_t>((1024 + waves - 1) / waves, (in.n_r + 1) / 32));
@@ -114,7 +122,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
         return false;
 
     // Which sum is faster, in SIMD cycles over the chip's 1024 SIMDs (measured rates: 1.5 cycles per
-    // direct FP32 evaluation on the tied tables and 4.4 in FP64, 2.9 and 5.3 on general tables; the
+    // direct FP32 evaluation on the tied tables and 4.4 in FP64, 1.2 and 5.3 per compacted one; the
     // matrix instructions of the two interpolations at 32 FP64 flops per cycle), and for small
     // problems the serial chain of a wave (0.11 us per node of a 2048-node chunk against chunk nodes
     // and three more launches).
@@ -122,7 +130,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const double direct = std::max(0.11 * (double)std::min<int64_t>(n_tot, 2048),
                                    pts * (double)n_tot * (in.fp64 ? 4.4 : 1.5) / cyc);
     const double build = (double)in.n_k * 0.5 * ((double)n_tot * ((rows + 15) / 16 * 16) + (double)n_c * in.n_phi);
-    const double compact = std::max(0.15 * std::min(plan.chunk, 512), pts * (double)n_c * (in.fp64 ? 5.3 : 2.9) / cyc) + build / cyc +
+    const double compact = std::max(0.15 * std::min(plan.chunk, 512), pts * (double)n_c * (in.fp64 ? 5.3 : 1.2) / cyc) + build / cyc +
                            25.0;
     return compact < 0.8 * direct;
 }

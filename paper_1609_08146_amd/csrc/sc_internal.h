@@ -78,6 +78,14 @@ hipError_t launch_energy(hipStream_t st, int is_f64, int n_t, int n_obs, const v
 hipError_t launch_quad(hipStream_t st, int mode, int obs_per_lane, int freq_per_lane, int waves_per_block,
                        int grid, const QuadJob *jobs, int n_jobs, int64_t n_tiles, unsigned int *counter);
 // E, B [n_k][n_obs][3] at the points o0 ... o0 + n_o - 1 from partials of those points (n_o_pad padded).
+// The compacted FP32 sums (sc_quad_mm.hip): packed rows of the compacted tables [n_k][n_c][8] for the matrix
+// instructions (mtab: mm_table_bytes, mscale: [n_k][16]), and the quadrature over the tiles of one
+// job or of several on the device, fpb (1, 2 or 4) frequencies per tile.
+inline size_t mm_table_bytes(int n_k, int n_c, int far) { return (size_t)n_k * ((n_c + 3) / 4) * 1024 * (far ? 2 : 1); }
+hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int far, const double *k, double scale, const float *ctab,
+                            const float *pos, float *mscale, void *mtab);
+hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job, int64_t n_tiles);
+hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t n_tiles);
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
                          const double *k, int b_over_k, int n_obs, int o0, void *E, void *B);
 // Compacted tables (sc_compact.h): weights and node records, then the tables of frequencies k0 ...
@@ -92,8 +100,8 @@ hipError_t launch_twiddles(hipStream_t st, int n_k, const double *k, int n_t, co
 hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw,
                        const void *F, void *Ft);
 hipError_t launch_fill_u32(hipStream_t st, unsigned int *p, unsigned int v, int n);
-// *dst = job on the device (the job travels as a kernel argument)
-hipError_t launch_store_job(hipStream_t st, const QuadJob &job, QuadJob *dst);
+// *dst = job on the device (the job travels as a kernel argument), and the launch's counters zeroed
+hipError_t launch_store_job(hipStream_t st, const QuadJob &job, QuadJob *dst, unsigned int *counter);
 
 // Occupancy helper: max resident workgroups per CU for a quadrature variant.
 int quad_max_blocks_per_cu(int mode, int obs_per_lane, int freq_per_lane, int waves_per_block);

@@ -722,9 +722,11 @@ __global__ void k_fill_u32(unsigned int *p, unsigned int v, int n)
 }
 
 // One quadrature job written to device memory from a kernel argument (no host buffer to keep alive).
-__global__ void k_store_job(QuadJob job, QuadJob *dst)
+// Its work counters are cleared in the same launch.
+__global__ void k_store_job(QuadJob job, QuadJob *dst, unsigned int *counter)
 {
-    if (threadIdx.x == 0 && blockIdx.x == 0) *dst = job;
+    if (threadIdx.x < QUAD_SEGMENTS) counter[threadIdx.x] = 0;
+    if (threadIdx.x == 0) *dst = job;
 }
 
 // ================================================================== launchers
@@ -875,9 +877,9 @@ hipError_t launch_fill_u32(hipStream_t st, unsigned int *p, unsigned int v, int 
     return hipGetLastError();
 }
 
-hipError_t launch_store_job(hipStream_t st, const QuadJob &job, QuadJob *dst)
+hipError_t launch_store_job(hipStream_t st, const QuadJob &job, QuadJob *dst, unsigned int *counter)
 {
-    hipLaunchKernelGGL(k_store_job, dim3(1), dim3(64), 0, st, job, dst);
+    hipLaunchKernelGGL(k_store_job, dim3(1), dim3(64), 0, st, job, dst, counter);
     return hipGetLastError();
 }
 

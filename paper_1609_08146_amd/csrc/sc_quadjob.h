@@ -17,6 +17,8 @@ struct QuadJob {
     const void *hinv;     // [n_tot] 1 / (2|r_s|) real (general layout, series_delta)
     const void *beta;     // [n_tot] real (factored layout with the tied charge): rho_t = -i beta s / k
     const void *tabp;     // [n_k][n_tot][2] float (FP32 split form, tied charge): (|s|, arg(s) / 2 pi)
+    const void *mtab;     // mm: packed table rows (sc_quad_mm.hip)
+    const float *mscale;  // mm: [n_k][16] column scales
     const double *k;      // [n_k]
     void *partial;        // [n_chunks][n_k][n_obs_pad / 64][12][64] real
     int n_tot;            // surface + rim nodes
@@ -31,6 +33,9 @@ struct QuadJob {
                           // per node); the B sums then carry 1/k, so the reduction drops its own 1/k
     int raw_phase;        // FP32 split form: |k delta| / 2 pi < 250 turns for every pair of the job
     int series_delta;     // split forms: |r'| <= 4e-4 |r_s| for every pair (delta and 1/|R| by series)
+    int mm;               // compacted FP32 split form: the sum is taken by k_quad_mm (tiles of 128 points)
+    int far;              // mm: some |r'| > |r_s| / 100
+    float scale;          // mm: power of two near the focal length
     int64_t tile0;        // first global tile of this job in the launch
     int64_t tile_offset;  // first job-local tile covered (a launch may cover a sub-range)
     int64_t n_tiles;      // tiles covered by this launch

@@ -304,7 +304,7 @@ static sc_status setup_finish(sc_server *s, Req *r, bool *ready)
     sc_launch l = resolve_launch(p, r->prec);
     l.obs_per_lane = server_opl(r->prec);
     l.freq_per_lane = server_fpb(r->prec);
-    SC_TRY(prepare(p, r->prec, l, r->job));
+    SC_TRY(prepare(p, r->prec, l, MM_FREQS_SHARED, r->job));
     HIP_TRY(hipEventRecord(r->ready_ev, s->prep->stream));
     // what the request holds from now on (the admission charged the set-up's peak: FP64 tables,
     // general FP32 tables and factored ones at once)
@@ -364,11 +364,20 @@ static sc_status launch_quantum(sc_server *s)
     const int fpb = server_fpb(prec);
     const double budget_evals = std::max(1.0, s->quantum_ms * s->evals_per_ms);
     const double share = budget_evals / (double)group.size();
+    // the compacted FP32 sums (job.mm) first, for a launch of their own
+    std::stable_partition(group.begin(), group.end(), [](const Req *r) { return r->job.mm != 0; });
     std::vector<QuadJob> jobs;
     std::vector<Req *> finals;
-    int64_t total = 0, evals = 0;
+    int64_t total = 0, evals = 0, mm_tiles = 0;
+    int n_mm = 0;
     for (Req *r : group) {
-        const double per_tile = 64.0 * opl * fpb * std::min<double>(r->job.chunk, r->job.n_tot);
+        if (n_mm == (int)jobs.size() && r->job.mm == 0) {   // the first of the others
+            mm_tiles = total;
+            total = 0;
+        }
+        n_mm += r->job.mm != 0;
+        const double per_tile = (r->job.mm ? 128.0 * r->job.mm : 64.0 * opl * fpb) *
+                                std::min<double>(r->job.chunk, r->job.n_tot);
         int64_t n = (int64_t)std::ceil(share / per_tile);
         n = std::max<int64_t>(1, std::min<int64_t>(n, r->job.n_tiles - r->cursor));
         QuadJob j = r->job;
@@ -380,6 +389,10 @@ static sc_status launch_quantum(sc_server *s)
         evals += (int64_t)(n * per_tile);
         r->cursor += n;
         if (r->cursor == r->job.n_tiles) finals.push_back(r);
+    }
+    if (n_mm == (int)jobs.size()) {
+        mm_tiles = total;
+        total = 0;
     }
     // a free ring slot (at most two quanta are in flight, the ring has three)
     int slot = -1;
@@ -407,15 +420,17 @@ static sc_status launch_quantum(sc_server *s)
     for (Req *r : group) HIP_TRY(hipStreamWaitEvent(st, r->ready_ev, 0));
     HIP_TRY(hipMemcpyAsync(s->jobbuf[slot].p, s->hjobs[slot], sizeof(QuadJob) * jobs.size(), hipMemcpyHostToDevice,
                            st));
-    HIP_TRY(launch_fill_u32(st, s->ctx->counter.as<unsigned int>(), 0u, QUAD_SEGMENTS));
+    if (total) HIP_TRY(launch_fill_u32(st, s->ctx->counter.as<unsigned int>(), 0u, QUAD_SEGMENTS));
     HIP_TRY(hipEventRecord(s->slot_start[slot], st));
+    if (n_mm) HIP_TRY(launch_quad_mm(st, MM_FREQS_SHARED, s->jobbuf[slot].as<QuadJob>(), n_mm, mm_tiles));
     const int mode = mode_of(prec);
     const int wpb = 4;
     const int occ = quad_max_blocks_per_cu(mode, opl, fpb, wpb);
     int64_t grid = std::min<int64_t>((int64_t)occ * s->ctx->n_cu, (total + wpb - 1) / wpb);
     grid = std::max<int64_t>(grid, 1);
-    HIP_TRY(launch_quad(st, mode, opl, fpb, wpb, (int)grid, s->jobbuf[slot].as<QuadJob>(), (int)jobs.size(),
-                        total, s->ctx->counter.as<unsigned int>()));
+    if (total)
+        HIP_TRY(launch_quad(st, mode, opl, fpb, wpb, (int)grid, s->jobbuf[slot].as<QuadJob>() + n_mm,
+                            (int)jobs.size() - n_mm, total, s->ctx->counter.as<unsigned int>()));
     HIP_TRY(hipEventRecord(s->slot_ev[slot], st));
     s->slot_busy[slot] = true;
     s->inflight.push_back({slot, evals, Clock::now()});

@@ -16,7 +16,7 @@ CLANG=/opt/rocm/llvm/bin/clang++
 mkdir -p "$OUT"
 FLAGS="--offload-arch=gfx950 -O2 -g -std=c++17 -fPIC -ffp-contract=off -Xclang -target-feature -Xclang -packed-fp32-ops -Wno-unused-result -Wno-pass-failed -I $ROOT/include"
 pids=()
-for s in sc_quad.hip sc_kernels.hip sc_compact.hip sc_diag.hip; do
+for s in sc_quad.hip sc_quad_mm.hip sc_kernels.hip sc_compact.hip sc_diag.hip; do
     $HIPCC $FLAGS -Xarch_host -fsanitize=$SAN -Xarch_host -fno-omit-frame-pointer -c "$CSRC/$s" -o "$OUT/${s%.hip}.o" &
     pids+=($!)
 done
@@ -29,5 +29,5 @@ for s in sc_gauss_host sc_compact_host; do
 done
 $CLANG -O1 -g -std=c++17 -pthread -fsanitize=$SAN -fno-omit-frame-pointer -D__HIP_PLATFORM_AMD__ -I /opt/rocm/include -I "$ROOT/include" -c "$ROOT/tests/native/abi_sanitized.cpp" -o "$OUT/abi_sanitized.o"
 for p in "${pids[@]}"; do wait "$p"; done
-$HIPCC --offload-arch=gfx950 -Xarch_host -fsanitize=$SAN -o "$OUT/abi_$SAN" "$OUT"/sc_quad.o "$OUT"/sc_kernels.o "$OUT"/sc_diag.o "$OUT"/sc_api.o "$OUT"/sc_serve.o "$OUT"/sc_compact.o "$OUT"/sc_gauss_host.o "$OUT"/sc_compact_host.o "$OUT"/abi_sanitized.o -lquadmath -lpthread
+$HIPCC --offload-arch=gfx950 -Xarch_host -fsanitize=$SAN -o "$OUT/abi_$SAN" "$OUT"/sc_quad.o "$OUT"/sc_quad_mm.o "$OUT"/sc_kernels.o "$OUT"/sc_diag.o "$OUT"/sc_api.o "$OUT"/sc_serve.o "$OUT"/sc_compact.o "$OUT"/sc_gauss_host.o "$OUT"/sc_compact_host.o "$OUT"/abi_sanitized.o -lquadmath -lpthread
 rm -f "$OUT"/*.o
