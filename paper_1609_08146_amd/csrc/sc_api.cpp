@@ -1155,6 +1155,7 @@ static bool plan_compact(const sc_prob *p, sc_precision prec, CompactPlan &plan)
     in.n_r = p->n_r;
     in.n_phi = p->n_phi;
     in.k_max = *std::max_element(p->k.begin(), p->k.end());
+    in.k_min = *std::min_element(p->k.begin(), p->k.end());
     in.n_k = (int)p->k.size();
     in.n_obs_pad = p->n_obs_pad;
     in.obs_r2max = p->obs_r2max;
@@ -1189,7 +1190,7 @@ static void compact_job_mm(const CompactPlan &plan, const void *mtab, const void
     job.mtab = mtab;
     job.mscale = (const float *)mscale;
     job.mm = fpb;
-    job.far = plan.far;
+    job.form = plan.form;
     job.scale = (float)plan.scale;
     job.n_tiles = (int64_t)(job.n_obs_pad / 128) * job.n_chunks * ((job.n_k + fpb - 1) / fpb);
 }
@@ -1224,10 +1225,10 @@ static CompactLayout compact_layout(const sc_prob *p, sc_precision prec, const C
     const bool mm = prec == SC_FP32_SPLIT;
     const size_t tab_bytes = up(rs * 8 * n_k * n_c);
     c.tab = 0;
-    c.scale = mm ? up(mm_table_bytes((int)n_k, (int)n_c, plan.far)) : tab_bytes;
+    c.scale = mm ? up(mm_table_bytes((int)n_k, (int)n_c, plan.form)) : tab_bytes;
     c.pos = c.scale + (mm ? up(sizeof(float) * 16 * n_k) : 0);
-    c.hinv = c.pos + up(rs * 4 * (n_c + 3));
-    c.bytes = c.hinv + up(rs * (n_c + 3));
+    c.hinv = c.pos + up(rs * 4 * (n_c + 7));
+    c.bytes = c.hinv + up(rs * (n_c + 7));
     c.wrad = 0;
     c.wang = up(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
     c.raw = c.wang + up(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
@@ -1262,7 +1263,7 @@ static sc_status ensure_compact(sc_prob *p, sc_precision prec, const CompactPlan
         HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, std::min(lay.per_k, n_k - k0), f64, fact ? 1 : 0,
                                       tab, pos, wrad, wang, T, rec + real_size(prec) * 8 * (size_t)k0 * plan.n_c));
     if (!f64)
-        HIP_TRY(launch_mm_tables(st, n_k, plan.n_c, plan.far, p->d_k.as<double>(), plan.scale, (const float *)rec,
+        HIP_TRY(launch_mm_tables(st, n_k, plan.n_c, plan.form, p->d_k.as<double>(), plan.scale, (const float *)rec,
                                  (const float *)(c + lay.pos), (float *)(c + lay.scale), c + lay.tab));
     p->cplan = plan;
     p->cplan_prec = (int)prec;
@@ -1517,11 +1518,11 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     };
     double *wrad = (double *)take(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
     double *wang = (double *)take(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
-    void *cpos = take(rs * 4 * (size_t)(plan.n_c + 3)), *chinv = take(rs * (size_t)(plan.n_c + 3));
+    void *cpos = take(rs * 4 * (size_t)(plan.n_c + 7)), *chinv = take(rs * (size_t)(plan.n_c + 7));
     const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
     // compacted records, and in the FP32 form their packed rows and scales
     const size_t rec_bytes = rs * 8 * (size_t)plan.n_c;
-    const size_t tab_bytes = rec_bytes + (f64 ? 0 : mm_table_bytes(1, plan.n_c, plan.far) + sizeof(float) * 16);
+    const size_t tab_bytes = rec_bytes + (f64 ? 0 : mm_table_bytes(1, plan.n_c, plan.form) + sizeof(float) * 16);
     const size_t n_chunks = (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk);
     const size_t part_bytes = rs * 12 * n_chunks;   // per frequency and padded point
     const size_t left = off + 2048 < SC_NOALLOC_SCRATCH_BYTES ? SC_NOALLOC_SCRATCH_BYTES - off - 2048 : 0;
@@ -1536,7 +1537,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     double *T = (double *)take(row_bytes * per_k);
     char *ctab = take(rec_bytes * per_k), *mtab = nullptr, *mscale = nullptr;
     if (!f64) {
-        mtab = take(mm_table_bytes(per_k, plan.n_c, plan.far));
+        mtab = take(mm_table_bytes(per_k, plan.n_c, plan.form));
         mscale = take(sizeof(float) * 16 * (size_t)per_k);
     }
     char *part = take(part_bytes * per_k * per_o);
@@ -1546,7 +1547,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
         const int nk = std::min(per_k, n_k - k0);
         HIP_TRY(launch_compact_tables(st, plan, p->n_r, p->n_phi, k0, nk, f64, fact ? 1 : 0, tab, pos, wrad, wang, T, ctab));
         if (!f64)
-            HIP_TRY(launch_mm_tables(st, nk, plan.n_c, plan.far, p->d_k.as<double>() + k0, plan.scale, (const float *)ctab,
+            HIP_TRY(launch_mm_tables(st, nk, plan.n_c, plan.form, p->d_k.as<double>() + k0, plan.scale, (const float *)ctab,
                                      (const float *)cpos, (float *)mscale, mtab));
         for (int o0 = 0; o0 < p->n_obs; o0 += per_o) {
             fill_job(p, prec, l, tab, fact, part, job);

@@ -20,12 +20,21 @@ namespace sc {
 
 constexpr int COMPACT_MAX_ROWS = 192;
 
+// How the FP32 sum forms its kernel values (sc_quad_mm.hip): G and H of every node; the same with
+// the columns that r' multiplies in two parts; or G / R alone, near the focus.
+enum CompactForm { FORM_GH = 0, FORM_GH_FAR = 1, FORM_NEAR = 2 };
+// Nodes per step and 16-byte rows per lane and step of the packed tables.
+constexpr int form_nodes(int form) { return form == FORM_NEAR ? 8 : 4; }
+constexpr int form_rows(int form) { return form == FORM_GH ? 1 : 2; }
+
+constexpr int MM_CHUNK_MAX = 256;   // nodes per chunk of the FP32 sum
+
 struct CompactPlan {
     int rows;                               // interpolation rows in theta
     int n_c;                                // compacted nodes in all (sum of cols)
     int split;                              // parts the sum over the radii is cut into (partial rows)
     int chunk;                              // compacted nodes per split-K chunk of the quadrature
-    int far;                                // some |r'| > |r_s| / 100
+    int form;                               // CompactForm of the FP32 sum
     double scale;                           // power of two near f
     double theta_max;                       // 2 atan(r_max / 2f)
     uint16_t cols[COMPACT_MAX_ROWS];        // phi per row: odd, or n_phi (taken as they are)
@@ -49,7 +58,7 @@ inline int64_t compact_rows_doubles(const CompactPlan &p, int n_phi) { return (i
 struct CompactInput {
     double f, r_max;       // paraboloid
     int n_r, n_phi;
-    double k_max;
+    double k_max, k_min;
     int n_k, n_obs_pad;
     double obs_r2max;      // max |r'|^2 over the points
     double obs_rho2max;    // max x'^2 + y'^2

@@ -83,8 +83,8 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     }
     b -= n_a;
     const int q = 64 * b + lane;
-    if (q >= (plan.n_c + 3) / 4 * 4) return;
-    const int qn = min(q, plan.n_c - 1);   // up to a multiple of 4 the last node again
+    if (q >= (plan.n_c + 7) / 8 * 8) return;
+    const int qn = min(q, plan.n_c - 1);   // up to a multiple of 8 the last node again
     int m = 0;
     while (plan.off[m + 1] <= qn) ++m;
     const double th = 0.5 * plan.theta_max * (1.0 + cheb_point(m, rows));

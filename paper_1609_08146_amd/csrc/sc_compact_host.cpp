@@ -107,9 +107,11 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
         plan.chunk = (int)std::max<int64_t>(64, ((n_c + chunks - 1) / chunks + 31) / 32 * 32);
     } else {
         const int64_t units = (int64_t)(in.n_obs_pad / 128) * ((in.n_k + 3) / 4), chunks = (4096 + units - 1) / units;
-        plan.chunk = (int)std::min<int64_t>(256, std::max<int64_t>(64, ((n_c + chunks - 1) / chunks + 31) / 32 * 32));
+        plan.chunk = (int)std::min<int64_t>(MM_CHUNK_MAX, std::max<int64_t>(64, ((n_c + chunks - 1) / chunks + 31) / 32 * 32));
     }
-    plan.far = q > 0.01;
+    // Near the focus H = (ik - 1/R) G / R is G / R times (ik - 1/|r_s|) to q / (k f) and J~ G is G / R times
+    // J~ |r_s| (1 + delta / |r_s|); the columns that r' multiplies need one part of two below q = 1/100.
+    plan.form = q <= 1e-3 && q <= 1e-9 * in.k_min * in.f ? FORM_NEAR : q <= 0.01 ? FORM_GH : FORM_GH_FAR;
     plan.scale = std::ldexp(1.0, std::ilogb(in.f));
     // The radii's sum: cut until there are about 1024 waves of it, at least 32 radii each.
     const int64_t waves = (int64_t)in.n_k * ((in.n_phi + 15) / 16) * ((rows + 15) / 16);

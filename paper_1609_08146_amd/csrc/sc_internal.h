@@ -81,8 +81,11 @@ hipError_t launch_quad(hipStream_t st, int mode, int obs_per_lane, int freq_per_
 // The compacted FP32 sums (sc_quad_mm.hip): packed rows of the compacted tables [n_k][n_c][8] for the matrix
 // instructions (mtab: mm_table_bytes, mscale: [n_k][16]), and the quadrature over the tiles of one
 // job or of several on the device, fpb (1, 2 or 4) frequencies per tile.
-inline size_t mm_table_bytes(int n_k, int n_c, int far) { return (size_t)n_k * ((n_c + 3) / 4) * 1024 * (far ? 2 : 1); }
-hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int far, const double *k, double scale, const float *ctab,
+inline size_t mm_table_bytes(int n_k, int n_c, int form)
+{
+    return (size_t)n_k * ((n_c + form_nodes(form) - 1) / form_nodes(form)) * 1024 * form_rows(form);
+}
+hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const double *k, double scale, const float *ctab,
                             const float *pos, float *mscale, void *mtab);
 hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job, int64_t n_tiles);
 hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t n_tiles);

@@ -9,16 +9,28 @@
 // phase, one sine, one cosine, 7 more instructions) and v_mfma_f32_32x32x16_f16 sums them over the
 // nodes, where the plain form spends 47 more FMAs per term on the vector ALU.
 //
+// Near the focus (|r'| <= |r_s| / 1000, and k |r_s| so large that 1/R in ik - 1/R may stand at |r_s|) one
+// complex kernel value is enough: with V = e^{ik delta} / R^2, H = (ik - 1/|r_s|) V and
+// G = R V = |r_s| V + delta V, so the columns meet V, and J~ |r_s| meets V delta / |r_s| besides.
+//
 // Precision.  Every kernel value and every table entry of E and B is the sum of two FP16 numbers,
 // hi = fp16(x) and lo = fp16(x - hi): 22 bits, and all four products of the parts are summed in FP32
 // (rows of A: hi and lo of the table; two products per step: hi and lo of the kernel values).  The
-// columns that r' multiplies (|r'| <= |r_s| / 4) are hi alone where |r'| <= |r_s| / 100, and get
-// their lo part by a third product otherwise.  Table columns are scaled by powers of two to 2^12 at
-// most, and the kernel values to about 2^6, so that no lo part falls below FP16's smallest number.
-// Against 64 bits the sums are as exact as the plain FP32 form's: broadband 4.2e-7 (plain 4.2e-7).
+// columns that r' multiplies, and the term with delta / |r_s|, are hi alone where that factor is below
+// 1/100; FORM_GH_FAR gives those columns their lo part by a third product.  Table columns are scaled by
+// powers of two to 2^12 at most, and the kernel values to about 2^6, so that no lo part falls below
+// FP16's smallest number.  Against 64 bits the sums are as exact as the plain FP32 form's (broadband
+// 4.3e-7, plain 4.2e-7).
 //
-// One step is 4 nodes: lane l holds point l % 32 and nodes 2 (l / 32), 2 (l / 32) + 1 of the step as B's
-// 8 consecutive values (Gr, Gi, Hr, Hi of each), and row l % 32 of A, 16 B loaded as they lie.
+// One step is 4 nodes (near: 8): lane l holds point l % 32 and its half's nodes as B's 8 consecutive
+// values (Gr, Gi, Hr, Hi of two nodes; near: Vr, Vi of four), and row l % 32 of A, 16 B loaded as they lie.
+//
+// Bound by the vector ALU's issue: instructions with the long encoding (cvt_pk, fma_mix) take 4.4 to 4.6
+// SIMD cycles, sine and cosine 8.4, the short ones 2.4, and the matrix instructions (37 cycles each)
+// overlap only in part: a kernel value pair and its products take 18 vector and 0.75 matrix instructions, 67 +
+// 28 cycles per 64 terms, and the launch takes 95 (broadband, 1.34e9 terms in 0.86 ms; 126 with node
+// records and rows loaded where they are used).  Two waves per SIMD with the compiler's free choice of
+// registers beat three and four (1.04 and 1.20 ms).
 #include "sc_device.h"
 #include "sc_internal.h"
 
@@ -34,7 +46,8 @@ typedef __attribute__((address_space(4))) const double cdouble;
 typedef __attribute__((address_space(4))) const float cfloat;
 
 // Kernel values are formed as G s * 2^6 and H s^2 / k * 2^6 with s a power of two near the focal length.
-constexpr float KERNEL_SCALE = 64.0f;
+// The near form's are V s^2 * 2^6 and V s^2 * 2^6 * delta / |r_s| * 2^10.
+constexpr float KERNEL_SCALE = 64.0f, NEAR_SCALE = 1024.0f;
 
 // v = hi + lo to 22 bits; m1 is -1 from memory, so that the difference is one mixed-precision FMA.
 __device__ __forceinline__ void split2(float a, float b, float m1, h2 &hi, h2 &lo)
@@ -45,83 +58,12 @@ __device__ __forceinline__ void split2(float a, float b, float m1, h2 &hi, h2 &l
     lo = __builtin_convertvector(l, h2);
 }
 
-template <int F, bool RAW, bool SER, bool FAR>
-__device__ __forceinline__ void tile_mm(cjob *job, int chunk, int pg, int kb, float m1)
+// Sums of one lane into the partials.  Rows of a lane: lanes 0-31 E hi (6), E lo (6), sum H rho~ (2),
+// (sum H J~).z (2); lanes 32-63 B hi, B lo, (sum H J~).x, .y.
+template <int F>
+__device__ __forceinline__ void store_mm(cjob *job, int chunk, int pt, int kb, const v4f o, const v16f *acc)
 {
-    const int lane = threadIdx.x & 63, half = lane >> 5;
-    const int n_k = job->n_k, n_obs_pad = job->n_obs_pad, steps = (job->n_tot + 3) / 4;
-    const int s0 = chunk * (job->chunk / 4), s1 = min(s0 + job->chunk / 4, steps);
-    const int pt = pg * 128 + (threadIdx.x >> 6) * 32 + (lane & 31);
-    const float s = job->scale;
-    float kt[F], iks[F];
-    const h8 *A[F];
-    const size_t row = (size_t)steps * 64;
-#pragma unroll
-    for (int f = 0; f < F; ++f) {
-        const int k = min(kb * F + f, n_k - 1);
-        const double kv = ((cdouble *)job->k)[k];
-        kt[f] = (float)(kv * INV_TWO_PI);
-        iks[f] = (float)(1.0 / (kv * (double)s));
-        A[f] = (const h8 *)job->mtab + (size_t)k * (FAR ? 2 : 1) * row + lane;
-    }
-    const v4f o = ((const v4f *)job->obs)[pt];
-    const v4f *pos = (const v4f *)job->pos;
-    const float *hinv = (const float *)job->hinv;
-    v16f acc[F];
-#pragma unroll
-    for (int f = 0; f < F; ++f)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[f][v] = 0.0f;
-
-    for (int st = s0; st < s1; ++st) {
-        const int n = 4 * st + 2 * half;
-        float ph[2], delta[2];   // s / R and |R| - |r_s|
-        const v2f h = *(const v2f *)(hinv + n);
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const v4f p = pos[n + q];
-            const float dot = __fmaf_rn(p.x, o.x, __fmaf_rn(p.y, o.y, p.z * o.z));
-            const float num = __fmaf_rn(-2.0f, dot, o.w);
-            if constexpr (SER) {   // series near the focus, as in the plain form
-                const float hq = q ? h.y : h.x;
-                const float d1 = num * hq, x = d1 * hq;
-                delta[q] = d1 * __fmaf_rn(x, __fmaf_rn(2.0f, x, -1.0f), 1.0f);
-                const float h2s = hq + hq, y = delta[q] * h2s;
-                ph[q] = (h2s * s) * __fmaf_rn(y, y - 1.0f, 1.0f);
-            } else {
-                const float dx = p.x - o.x, dy = p.y - o.y, dz = p.z - o.z;
-                const float R2 = __fmaf_rn(dx, dx, __fmaf_rn(dy, dy, dz * dz));
-                const float rinv = __builtin_amdgcn_rsqf(R2);
-                delta[q] = num * __builtin_amdgcn_rcpf(__fmaf_rn(R2, rinv, p.w));
-                ph[q] = rinv * s;
-            }
-        }
-#pragma unroll
-        for (int f = 0; f < F; ++f) {
-            const h8 a = A[f][(size_t)st * 64];
-            h2 hi[4], lo[4];
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const float turn = kt[f] * delta[q];
-                const float r = RAW ? turn : __builtin_amdgcn_fractf(turn);
-                const float pa = ph[q] * KERNEL_SCALE;
-                const float gr = __builtin_amdgcn_cosf(r) * pa, gi = __builtin_amdgcn_sinf(r) * pa;
-                const float b = (ph[q] * ph[q]) * iks[f];
-                // H s^2 / k = (i s / R - (s / R)^2 / (k s)) G s
-                const float hr = -__fmaf_rn(gi, ph[q], gr * b), hi_ = __fmaf_rn(gr, ph[q], -(gi * b));
-                split2(gr, gi, m1, hi[2 * q], lo[2 * q]);
-                split2(hr, hi_, m1, hi[2 * q + 1], lo[2 * q + 1]);
-            }
-            const h8 bh = {hi[0].x, hi[0].y, hi[1].x, hi[1].y, hi[2].x, hi[2].y, hi[3].x, hi[3].y};
-            const h8 bl = {lo[0].x, lo[0].y, lo[1].x, lo[1].y, lo[2].x, lo[2].y, lo[3].x, lo[3].y};
-            acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bh, acc[f], 0, 0, 0);
-            if constexpr (FAR)
-                acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(A[f][row + (size_t)st * 64], bh, acc[f], 0, 0, 0);
-            acc[f] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a, bl, acc[f], 0, 0, 0);
-        }
-    }
-    // Rows of a lane: lanes 0-31 E hi (6), E lo (6), sum H rho~ (2), (sum H J~).z (2); lanes 32-63 B hi, B lo,
-    // (sum H J~).x, .y
+    const int half = (threadIdx.x >> 5) & 1, n_k = job->n_k;
     const float ox = o.x, oy = o.y, oz = o.z;
 #pragma unroll
     for (int f = 0; f < F; ++f) {
@@ -153,11 +95,142 @@ __device__ __forceinline__ void tile_mm(cjob *job, int chunk, int pg, int kb, fl
             v[5] -= __fmaf_rn(jxi, oy, -(jyi * ox));
         }
         // partials [chunk][k][point / 64][12][64]
-        float *part = (float *)job->partial + ((size_t)chunk * n_k + k) * 12 * (size_t)n_obs_pad + (size_t)(pt >> 6) * 768 +
-                      half * 384 + (pt & 63);
+        float *part = (float *)job->partial + ((size_t)chunk * n_k + k) * 12 * (size_t)job->n_obs_pad +
+                      (size_t)(pt >> 6) * 768 + half * 384 + (pt & 63);
 #pragma unroll
         for (int c = 0; c < 6; ++c) part[c * 64] = v[c];
     }
+}
+
+// delta = |R| - |r_s| and s / R, by series near the focus as in the plain form: p = (x, y, z, h), h = 1 / 2|r_s|,
+// for the series, else (x, y, z, |r_s|).
+template <bool SER>
+__device__ __forceinline__ void geom_mm(const v4f p, const v4f o, float s, float &delta, float &ph)
+{
+    const float dot = __fmaf_rn(p.x, o.x, __fmaf_rn(p.y, o.y, p.z * o.z));
+    const float num = __fmaf_rn(-2.0f, dot, o.w);
+    if constexpr (SER) {
+        const float h = p.w;
+        const float d1 = num * h, x = d1 * h;
+        delta = d1 * __fmaf_rn(x, __fmaf_rn(2.0f, x, -1.0f), 1.0f);
+        const float h2 = h + h, y = delta * h2;
+        ph = (h2 * s) * __fmaf_rn(y, y - 1.0f, 1.0f);
+    } else {
+        const float dx = p.x - o.x, dy = p.y - o.y, dz = p.z - o.z;
+        const float R2 = __fmaf_rn(dx, dx, __fmaf_rn(dy, dy, dz * dz));
+        const float rinv = __builtin_amdgcn_rsqf(R2);
+        delta = num * __builtin_amdgcn_rcpf(__fmaf_rn(R2, rinv, p.w));
+        ph = rinv * s;
+    }
+}
+
+// Operands of one step and frequency: rows a (and b), kernel values hi, lo (and y, near).
+struct Products {
+    h8 a = {}, b = {}, hi = {}, lo = {}, y = {};
+};
+template <int FORM>
+__device__ __forceinline__ void mm_products(const Products &w, v16f &acc)
+{
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w.a, w.hi, acc, 0, 0, 0);
+    if constexpr (FORM == FORM_GH_FAR) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w.b, w.hi, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w.a, w.lo, acc, 0, 0, 0);
+    if constexpr (FORM == FORM_NEAR) acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(w.b, w.y, acc, 0, 0, 0);
+}
+
+template <int F, bool RAW, bool SER, int FORM>
+__device__ __forceinline__ void tile_mm(cjob *job, int chunk, int pg, int kb, float m1)
+{
+    constexpr int NODES = form_nodes(FORM), ROWS = form_rows(FORM), Q = NODES / 2;   // nodes per lane and step
+    const int lane = threadIdx.x & 63, half = lane >> 5;
+    const int n_k = job->n_k, steps = (job->n_tot + NODES - 1) / NODES;
+    const int s0 = chunk * (job->chunk / NODES), s1 = min(s0 + job->chunk / NODES, steps);
+    const int pt = pg * 128 + (threadIdx.x >> 6) * 32 + (lane & 31);
+    const float s = job->scale;
+    float kt[F], iks[F];
+    const h8 *A[F];
+    const size_t row = (size_t)steps * 64;
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+        const int k = min(kb * F + f, n_k - 1);
+        const double kv = ((cdouble *)job->k)[k];
+        kt[f] = (float)(kv * INV_TWO_PI);
+        iks[f] = (float)(1.0 / (kv * (double)s));
+        A[f] = (const h8 *)job->mtab + (size_t)k * ROWS * row + lane;
+    }
+    const v4f o = ((const v4f *)job->obs)[pt];
+    // the chunk's node records in LDS: every lane of a half reads the same one, which through L1 would
+    // take as many cycles as 64 different ones
+    __shared__ v4f node[MM_CHUNK_MAX];
+    __syncthreads();
+    for (int i = threadIdx.x; i < (s1 - s0) * NODES; i += 256) {
+        v4f p = ((const v4f *)job->pos)[s0 * NODES + i];
+        if constexpr (SER) p.w = ((const float *)job->hinv)[s0 * NODES + i];
+        node[i] = p;
+    }
+    __syncthreads();
+    v16f acc[F];
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[f][v] = 0.0f;
+
+    h8 a0[F], a1[F];   // this step's rows, loaded a step ahead
+#pragma unroll
+    for (int f = 0; f < F; ++f) {
+        a0[f] = A[f][(size_t)s0 * 64];
+        if constexpr (ROWS == 2) a1[f] = A[f][row + (size_t)s0 * 64];
+    }
+    Products w;   // none pending: zeros add nothing
+    for (int st = s0; st < s1; ++st) {
+        const size_t next = (size_t)min(st + 1, s1 - 1) * 64;
+        const v4f *p = node + NODES * (st - s0) + Q * half;
+        float ph[Q], delta[Q], yy[Q];
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            geom_mm<SER>(p[q], o, s, delta[q], ph[q]);
+            if constexpr (FORM == FORM_NEAR) {
+                // delta / |r_s|
+                yy[q] = delta[q] * (SER ? p[q].w * (2.0f * NEAR_SCALE) : __builtin_amdgcn_rcpf(p[q].w) * NEAR_SCALE);
+                ph[q] = (ph[q] * ph[q]) * KERNEL_SCALE;
+            }
+        }
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            const h8 a = a0[f], b = ROWS == 2 ? a1[f] : a0[f];
+            a0[f] = A[f][next];
+            if constexpr (ROWS == 2) a1[f] = A[f][row + next];
+            h2 hi[4], lo[4], yv[4];
+#pragma unroll
+            for (int q = 0; q < Q; ++q) {
+                const float turn = kt[f] * delta[q];
+                const float r = RAW ? turn : __builtin_amdgcn_fractf(turn);
+                if constexpr (FORM == FORM_NEAR) {
+                    const float vr = __builtin_amdgcn_cosf(r) * ph[q], vi = __builtin_amdgcn_sinf(r) * ph[q];
+                    split2(vr, vi, m1, hi[q], lo[q]);
+                    const v2f y = {vr * yy[q], vi * yy[q]};
+                    yv[q] = __builtin_convertvector(y, h2);
+                } else {
+                    const float pa = ph[q] * KERNEL_SCALE, nph = -ph[q];
+                    const float gr = __builtin_amdgcn_cosf(r) * pa, gi = __builtin_amdgcn_sinf(r) * pa;
+                    const float nb = (nph * ph[q]) * iks[f];
+                    // H s^2 / k = (i s / R - (s / R)^2 / (k s)) G s
+                    const float hr = __fmaf_rn(gi, nph, gr * nb), him = __fmaf_rn(gr, ph[q], gi * nb);
+                    split2(gr, gi, m1, hi[2 * q], lo[2 * q]);
+                    split2(hr, him, m1, hi[2 * q + 1], lo[2 * q + 1]);
+                }
+            }
+            // the products of the frequency before, so that they run beside this one's kernel values
+            mm_products<FORM>(w, acc[(f + F - 1) % F]);
+            w.a = a;
+            w.b = b;
+            w.hi = h8{hi[0].x, hi[0].y, hi[1].x, hi[1].y, hi[2].x, hi[2].y, hi[3].x, hi[3].y};
+            w.lo = h8{lo[0].x, lo[0].y, lo[1].x, lo[1].y, lo[2].x, lo[2].y, lo[3].x, lo[3].y};
+            if constexpr (FORM == FORM_NEAR)
+                w.y = h8{yv[0].x, yv[0].y, yv[1].x, yv[1].y, yv[2].x, yv[2].y, yv[3].x, yv[3].y};
+        }
+    }
+    mm_products<FORM>(w, acc[F - 1]);
+    store_mm<F>(job, chunk, pt, kb, o, acc);
 }
 
 // One workgroup per tile: 128 points (32 per wave) x F frequencies x one chunk of nodes, the four waves
@@ -172,15 +245,18 @@ __device__ __forceinline__ void job_tile(cjob *job, int64_t t, float m1)
     const int pg = (int)(local % pgs);
     const int64_t rest = local / pgs;
     const int chunk = (int)(rest % job->n_chunks), kb = (int)(rest / job->n_chunks);
+    // (the series of delta hold to |r'| <= 4e-4 |r_s|, so they come with the near form alone)
     const bool raw = job->raw_phase != 0, ser = job->series_delta != 0;
-    if (ser && raw) tile_mm<F, true, true, false>(job, chunk, pg, kb, m1);
-    else if (ser) tile_mm<F, false, true, false>(job, chunk, pg, kb, m1);
-    else if (!job->far) {
-        if (raw) tile_mm<F, true, false, false>(job, chunk, pg, kb, m1);
-        else tile_mm<F, false, false, false>(job, chunk, pg, kb, m1);
+    if (job->form == FORM_NEAR) {
+        if (ser && raw) tile_mm<F, true, true, FORM_NEAR>(job, chunk, pg, kb, m1);
+        else if (ser) tile_mm<F, false, true, FORM_NEAR>(job, chunk, pg, kb, m1);
+        else tile_mm<F, false, false, FORM_NEAR>(job, chunk, pg, kb, m1);
+    } else if (job->form == FORM_GH) {
+        if (raw) tile_mm<F, true, false, FORM_GH>(job, chunk, pg, kb, m1);
+        else tile_mm<F, false, false, FORM_GH>(job, chunk, pg, kb, m1);
     } else {
-        if (raw) tile_mm<F, true, false, true>(job, chunk, pg, kb, m1);
-        else tile_mm<F, false, false, true>(job, chunk, pg, kb, m1);
+        if (raw) tile_mm<F, true, false, FORM_GH_FAR>(job, chunk, pg, kb, m1);
+        else tile_mm<F, false, false, FORM_GH_FAR>(job, chunk, pg, kb, m1);
     }
 }
 
@@ -218,20 +294,32 @@ k_quad_mm(const QuadJob *__restrict__ jobs_, int n_jobs, int64_t n_tiles, float 
 
 // ------------------------------------------------------------------------------- packed tables
 
-// The ten complex columns of node q at wavenumber k, in the order of the scales: E.x, E.y, E.z as (g, h)
-// pairs (G's factor J~ / s, H's factor k / s^2 rho~ r_s), then the H columns rho~, (J~ x r_s).x, .y, .z,
-// J~.x, .y, .z times k / s^2.
-__device__ __forceinline__ void mm_columns(const float *__restrict__ rec, const v4f p, double k, double s, double *g,
-                                           double *h)
+// The ten complex columns of a node at wavenumber k, in the order of the scales: E.x, E.y, E.z, the sum
+// of rho~, (J~ x r_s).x, .y, .z, J~.x, .y, .z.  G and H forms: h the factors of H s^2 / k, and g those of
+// G s in E (J~ / s).  Near form: h the factors of V s^2 = e^{ik delta} (s / R)^2, g those of V s^2 delta / |r_s|.
+__device__ __forceinline__ void mm_columns(int form, const float *__restrict__ rec, const v4f p, double k, double s,
+                                           double *g, double *h)
 {
-    const double js = 1.0 / s, hs = k / (s * s), r[3] = {p.x, p.y, p.z};
-    double J[6], rho[2] = {hs * (double)rec[6], hs * (double)rec[7]};
-    for (int c = 0; c < 6; ++c) {
-        g[c] = js * (double)rec[c];
-        J[c] = hs * (double)rec[c];
+    const double r[3] = {p.x, p.y, p.z}, is2 = 1.0 / (s * s);
+    double J[6], rho[2];
+    if (form == FORM_NEAR) {
+        // times (ik - 1/|r_s|) / s^2
+        const double cr = -is2 / (double)p.w, ci = k * is2;
+        for (int c = 0; c < 3; ++c) {
+            J[2 * c] = cr * (double)rec[2 * c] - ci * (double)rec[2 * c + 1];
+            J[2 * c + 1] = cr * (double)rec[2 * c + 1] + ci * (double)rec[2 * c];
+        }
+        rho[0] = cr * (double)rec[6] - ci * (double)rec[7];
+        rho[1] = cr * (double)rec[7] + ci * (double)rec[6];
+    } else {
+        for (int c = 0; c < 6; ++c) J[c] = k * is2 * (double)rec[c];
+        rho[0] = k * is2 * (double)rec[6];
+        rho[1] = k * is2 * (double)rec[7];
     }
+    const double gs = form == FORM_NEAR ? is2 * (double)p.w : 1.0 / s;
+    for (int c = 0; c < 6; ++c) g[c] = gs * (double)rec[c];
     for (int z = 0; z < 2; ++z) {   // re, im
-        for (int c = 0; c < 3; ++c) h[2 * c + z] = rho[z] * r[c];
+        for (int c = 0; c < 3; ++c) h[2 * c + z] = rho[z] * r[c] + (form == FORM_NEAR ? g[2 * c + z] : 0.0);
         h[6 + z] = rho[z];
         h[8 + z] = J[2 + z] * r[2] - J[4 + z] * r[1];
         h[10 + z] = J[4 + z] * r[0] - J[z] * r[2];
@@ -243,14 +331,14 @@ __device__ __forceinline__ void mm_columns(const float *__restrict__ rec, const 
 // Powers of two that bring each column's largest entry to 2^11 ... 2^12: mscale[k][16] holds what the
 // sums are multiplied by (scale / KERNEL_SCALE).  One workgroup per frequency.
 __global__ void __launch_bounds__(1024)
-k_mm_scales(int n_c, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
+k_mm_scales(int n_c, int form, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
             const v4f *__restrict__ pos, float *__restrict__ mscale)
 {
     const int kk = blockIdx.x;
     double mx[10] = {};
     for (int q = threadIdx.x; q < n_c; q += 1024) {
         double g[6], h[20];
-        mm_columns(ctab + ((size_t)kk * n_c + q) * 8, pos[q], kv[kk], s, g, h);
+        mm_columns(form, ctab + ((size_t)kk * n_c + q) * 8, pos[q], kv[kk], s, g, h);
         for (int c = 0; c < 10; ++c) {
             double m = fmax(fabs(h[2 * c]), fabs(h[2 * c + 1]));
             if (c < 3) m = fmax(m, fmax(fabs(g[2 * c]), fabs(g[2 * c + 1])));
@@ -274,17 +362,19 @@ k_mm_scales(int n_c, const double *__restrict__ kv, double s, const float *__res
     }
 }
 
-// mtab[k][step][lane][8] halves: lane's row l % 32 of the two nodes 4 step + 2 (l / 32) + {0, 1}, for each the
-// factors of (Gr, Gi, Hr, Hi); with `far` a second such table follows each frequency's, the lo
-// parts of the columns that r' multiplies.  One wave per step.
+// mtab[k][row][step][lane][8] halves, row 0: lane's row l % 32 of the step's nodes of its half (l / 32), for each
+// node the factors of the kernel values (Gr, Gi, Hr, Hi; near Vr, Vi).  Row 1, in FORM_GH_FAR: the lo
+// parts of the columns that r' multiplies; in FORM_NEAR: the factors of V delta / |r_s| in E.  One wave per step.
+template <int FORM>
 __global__ void __launch_bounds__(256)
-k_mm_pack(int n_c, int far, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
+k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
           const v4f *__restrict__ pos, const float *__restrict__ mscale, h8 *__restrict__ mtab)
 {
-    const int steps = (n_c + 3) / 4, st = blockIdx.x * 4 + (threadIdx.x >> 6), kk = blockIdx.y;
+    constexpr int NODES = form_nodes(FORM), ROWS = form_rows(FORM), Q = NODES / 2, W = 8 / Q;   // values per node
+    const int steps = (n_c + NODES - 1) / NODES, st = blockIdx.x * 4 + (threadIdx.x >> 6), kk = blockIdx.y;
     if (st >= steps) return;
     const int lane = threadIdx.x & 63, r = lane & 31, rh = (r >> 2) & 1, v = (r & 3) + 4 * (r >> 3);
-    // row r holds value v of half rh (see tile_mm): its column, part (re, im) and whether it is the lo half
+    // row r holds value v of half rh (see store_mm): its column, part (re, im) and whether it is the lo half
     int col, part = v & 1, lo = 0;
     if (v < 12) {
         lo = v >= 6;
@@ -295,11 +385,11 @@ k_mm_pack(int n_c, int far, const double *__restrict__ kv, double s, const float
         col = v < 14 ? 7 : 8;
     }
     h8 out = {}, out2 = {};
-    for (int q = 0; q < 2; ++q) {
-        const int n = 4 * st + 2 * (lane >> 5) + q;
+    for (int q = 0; q < Q; ++q) {
+        const int n = NODES * st + Q * (lane >> 5) + q;
         if (n >= n_c) continue;   // past the last node: zero
         double g[6], h[20];
-        mm_columns(ctab + ((size_t)kk * n_c + n) * 8, pos[n], kv[kk], s, g, h);
+        mm_columns(FORM, ctab + ((size_t)kk * n_c + n) * 8, pos[n], kv[kk], s, g, h);
         const double inv = 1.0 / ((double)mscale[16 * (size_t)kk + col] * KERNEL_SCALE);   // a power of two
         double gr = 0.0, gi = 0.0, hr = 0.0, hi = 0.0;   // of this column
         for (int c = 0; c < 10; ++c)
@@ -312,27 +402,35 @@ k_mm_pack(int n_c, int far, const double *__restrict__ kv, double s, const float
                 }
             }
         // (a + ib)(Vr + iVi): re = a Vr - b Vi, im = b Vr + a Vi
-        const float w[4] = {(float)(part ? gi : gr), (float)(part ? gr : -gi), (float)(part ? hi : hr),
-                            (float)(part ? hr : -hi)};
-        for (int e = 0; e < 4; ++e) {
-            const _Float16 a = (_Float16)w[e], b = (_Float16)(w[e] - (float)a);
-            out[4 * q + e] = lo ? b : a;
-            if (v >= 12) out2[4 * q + e] = b;
+        const float wg[2] = {(float)(part ? gi : gr), (float)(part ? gr : -gi)};
+        const float wh[2] = {(float)(part ? hi : hr), (float)(part ? hr : -hi)};
+        for (int e = 0; e < W; ++e) {
+            const float w = W == 2 ? wh[e] : e < 2 ? wg[e] : wh[e - 2];
+            const _Float16 a = (_Float16)w, b = (_Float16)(w - (float)a);
+            out[W * q + e] = lo ? b : a;
+            if (FORM == FORM_GH_FAR && v >= 12) out2[W * q + e] = b;
+            if (FORM == FORM_NEAR && rh == 0 && v < 6) out2[W * q + e] = (_Float16)(wg[e] / NEAR_SCALE);
         }
     }
-    h8 *dst = mtab + ((size_t)kk * (far ? 2 : 1) * steps + st) * 64 + lane;
+    h8 *dst = mtab + ((size_t)kk * ROWS * steps + st) * 64 + lane;
     dst[0] = out;
-    if (far) dst[(size_t)steps * 64] = out2;
+    if (ROWS == 2) dst[(size_t)steps * 64] = out2;
 }
 
 // ================================================================== launchers
 
-hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int far, const double *k, double scale, const float *ctab,
+hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const double *k, double scale, const float *ctab,
                             const float *pos, float *mscale, void *mtab)
 {
-    hipLaunchKernelGGL(k_mm_scales, dim3(n_k), dim3(1024), 0, st, n_c, k, scale, ctab, (const v4f *)pos, mscale);
-    hipLaunchKernelGGL(k_mm_pack, dim3(((n_c + 3) / 4 + 3) / 4, n_k), dim3(256), 0, st, n_c, far, k, scale, ctab,
-                       (const v4f *)pos, mscale, (h8 *)mtab);
+    const int steps = (n_c + form_nodes(form) - 1) / form_nodes(form);
+    const dim3 g((steps + 3) / 4, n_k), b(256);
+    hipLaunchKernelGGL(k_mm_scales, dim3(n_k), dim3(1024), 0, st, n_c, form, k, scale, ctab, (const v4f *)pos, mscale);
+#define SC_MM_PACK(FORM)                                                                              \
+    hipLaunchKernelGGL((k_mm_pack<FORM>), g, b, 0, st, n_c, k, scale, ctab, (const v4f *)pos, mscale, (h8 *)mtab)
+    if (form == FORM_NEAR) SC_MM_PACK(FORM_NEAR);
+    else if (form == FORM_GH) SC_MM_PACK(FORM_GH);
+    else SC_MM_PACK(FORM_GH_FAR);
+#undef SC_MM_PACK
     return hipGetLastError();
 }
 

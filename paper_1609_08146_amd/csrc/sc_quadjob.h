@@ -34,7 +34,7 @@ struct QuadJob {
     int raw_phase;        // FP32 split form: |k delta| / 2 pi < 250 turns for every pair of the job
     int series_delta;     // split forms: |r'| <= 4e-4 |r_s| for every pair (delta and 1/|R| by series)
     int mm;               // compacted FP32 split form: the sum is taken by k_quad_mm (tiles of 128 points)
-    int far;              // mm: some |r'| > |r_s| / 100
+    int form;             // mm: CompactForm of the packed rows
     float scale;          // mm: power of two near the focal length
     int64_t tile0;        // first global tile of this job in the launch
     int64_t tile_offset;  // first job-local tile covered (a launch may cover a sub-range)

@@ -24,7 +24,7 @@ WRAP = r'''
 extern "C" int plan(double f, double r_max, int n_r, int n_phi, double k_max, int n_k, int n_obs_pad, double r2,
                     double rho2, int fp64, int *head, int *cols, double *theta_max)
 {
-    sc::CompactInput in{f, r_max, n_r, n_phi, k_max, n_k, n_obs_pad, r2, rho2, fp64 != 0};
+    sc::CompactInput in{f, r_max, n_r, n_phi, k_max, k_max, n_k, n_obs_pad, r2, rho2, fp64 != 0};
     sc::CompactPlan p;
     if (!sc::compact_plan(in, p)) return 0;
     head[0] = p.rows; head[1] = p.n_c; head[2] = p.split; head[3] = p.chunk;
