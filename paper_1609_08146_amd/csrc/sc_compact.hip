@@ -101,49 +101,65 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     if (hinv32) hinv32[q] = (float)(0.5 / rs);
 }
 
-// One record (J~.x, J~.y, J~.z, rho~) as 8 doubles from the tables an evaluation reads: general, or
-// factored (J~ = u s), in FP32 or FP64.
-template <typename R, bool FACT>
-__device__ __forceinline__ void load_record(const R *__restrict__ tab, const R *__restrict__ pos, int64_t rec,
-                                            int64_t node, double *v)
-{
+// One record (J~.x, J~.y, J~.z, rho~) from the tables an evaluation reads, general or factored (J~ = u s),
+// in FP32 or FP64: the loads, and the 8 doubles made of them.
+template <typename R>
+struct RawRecord {
     typedef R r4 __attribute__((ext_vector_type(4)));
+    r4 a, b;
+};
+template <typename R, bool FACT>
+__device__ __forceinline__ RawRecord<R> load_record(const R *__restrict__ tab, const R *__restrict__ pos, int64_t rec,
+                                                    int64_t node)
+{
+    typedef typename RawRecord<R>::r4 r4;
+    if constexpr (FACT) return {*(const r4 *)(tab + rec * 4), *(const r4 *)(pos + node * 8 + 4)};
+    else return {*(const r4 *)(tab + rec * 8), *(const r4 *)(tab + rec * 8 + 4)};
+}
+template <typename R, bool FACT>
+__device__ __forceinline__ void record_doubles(const RawRecord<R> &r, double *v)
+{
     if constexpr (FACT) {
-        const r4 t = *(const r4 *)(tab + rec * 4), u = *(const r4 *)(pos + node * 8 + 4);
-        v[0] = (double)u.x * (double)t.x;
-        v[1] = (double)u.x * (double)t.y;
-        v[2] = (double)u.y * (double)t.x;
-        v[3] = (double)u.y * (double)t.y;
-        v[4] = (double)u.z * (double)t.x;
-        v[5] = (double)u.z * (double)t.y;
-        v[6] = (double)t.z;
-        v[7] = (double)t.w;
+        const double x = (double)r.a.x, y = (double)r.a.y;
+        v[0] = (double)r.b.x * x;
+        v[1] = (double)r.b.x * y;
+        v[2] = (double)r.b.y * x;
+        v[3] = (double)r.b.y * y;
+        v[4] = (double)r.b.z * x;
+        v[5] = (double)r.b.z * y;
+        v[6] = (double)r.a.z;
+        v[7] = (double)r.a.w;
     } else {
-        const r4 a = *(const r4 *)(tab + rec * 8), b = *(const r4 *)(tab + rec * 8 + 4);
-        v[0] = (double)a.x;
-        v[1] = (double)a.y;
-        v[2] = (double)a.z;
-        v[3] = (double)a.w;
-        v[4] = (double)b.x;
-        v[5] = (double)b.y;
-        v[6] = (double)b.z;
-        v[7] = (double)b.w;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            v[c] = (double)r.a[c];
+            v[4 + c] = (double)r.b[c];
+        }
     }
 }
 
 // The contraction over the radii: one wave per (frequency, part of the radii, 16 phi, 16 rows), 8
-// accumulators of 16 x 16 (one per real of the record); the waves of a workgroup share the records
-// and take consecutive row tiles.
+// accumulators of 16 x 16 (one per real of the record).  Waves are numbered with the row tiles fastest,
+// so that neighbours read the same records, four to a workgroup, and load ROWS_DEPTH steps ahead.  Bound
+// by the FP64 pipe: the matrix instructions take 64 cycles each, and the conversion of a record (14
+// FP64 instructions) runs on the same pipe and is not hidden behind them: 41 rows, 128 frequencies and
+// 160 400 nodes take 0.32 ms, 50 TFLOP/s of matrix work (a large FP64 product on this card: 69).  The
+// waves-per-SIMD request keeps the accumulators in plain registers: without it the compiler moved all 64
+// through accumulation registers in every step (80 of 119 instructions), 0.41 ms.  Two or three row
+// tiles per wave, so that a record is converted once for them, took 0.40 and 0.32 ms.
+constexpr int ROWS_DEPTH = 2;
 template <typename R, bool FACT>
-__global__ void __launch_bounds__(256)
-k_compact_rows(int k0, int n_r, int n_phi, int rows, int split, const R *__restrict__ tab, const R *__restrict__ pos,
-               const double *__restrict__ wrad, double *__restrict__ T)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+k_compact_rows(int k0, int n_r, int n_phi, int rows, int split, int64_t n_waves, const R *__restrict__ tab,
+               const R *__restrict__ pos, const double *__restrict__ wrad, double *__restrict__ T)
 {
     const int lane = threadIdx.x & 63, kq = lane >> 4, col = lane & 15;
-    const int groups = (n_phi + 15) / 16, rp = (rows + 15) / 16 * 16;
-    const int m0 = 16 * (blockIdx.y * (blockDim.x >> 6) + (threadIdx.x >> 6));
-    if (m0 >= rows) return;
-    const int g = blockIdx.x % groups, ks = blockIdx.x / groups;
+    const int groups = (n_phi + 15) / 16, rp = (rows + 15) / 16 * 16, tiles = rp / 16;
+    const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (wave >= n_waves) return;
+    const int m0 = 16 * (int)(wave % tiles);
+    const int64_t rest = wave / tiles;
+    const int g = (int)(rest % groups), ks = (int)(rest / groups);
     const int part = ks % split, kk = ks / split;
     const int phi = 16 * g + col, ph = min(phi, n_phi - 1);
     const int n_i = n_r + 1, steps = (n_i + 3) / 4;
@@ -152,16 +168,32 @@ k_compact_rows(int k0, int n_r, int n_phi, int rows, int split, const R *__restr
     d4 acc[8];
 #pragma unroll
     for (int c = 0; c < 8; ++c) acc[c] = d4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll 2
-    for (int s = s0; s < s1; ++s) {
-        const int i = 4 * s + kq;
+    RawRecord<R> raw[ROWS_DEPTH];
+    double wgt[ROWS_DEPTH];
+    auto load = [&](int d, int s) {
+        const int i = 4 * min(s, s1 - 1) + kq;
         const int64_t node = (int64_t)min(i, n_r) * n_phi + ph;   // past the rim: weight 0
-        const double a = wrad[(size_t)i * rp + m0 + col];
+        wgt[d] = wrad[(size_t)i * rp + m0 + col];
+        raw[d] = load_record<R, FACT>(tab, pos, rec0 + node, node);
+    };
+    auto step = [&](int d, int s) {
         double v[8];
-        load_record<R, FACT>(tab, pos, rec0 + node, node, v);
+        record_doubles<R, FACT>(raw[d], v);
+        const double a = wgt[d];
+        load(d, s + ROWS_DEPTH);
 #pragma unroll
         for (int c = 0; c < 8; ++c) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v[c], acc[c], 0, 0, 0);
+    };
+#pragma unroll
+    for (int d = 0; d < ROWS_DEPTH; ++d) load(d, s0 + d);
+    int s = s0;
+    for (; s + ROWS_DEPTH <= s1; s += ROWS_DEPTH) {
+#pragma unroll
+        for (int d = 0; d < ROWS_DEPTH; ++d) step(d, s + d);
     }
+#pragma unroll
+    for (int d = 0; d < ROWS_DEPTH - 1; ++d)
+        if (s + d < s1) step(d, s + d);
     if (phi >= n_phi) return;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -180,8 +212,8 @@ constexpr int COLS_KP = 4;   // pairs of frequencies per wave
 // reals, and the angular weights serve the 4 products of a wave.  Latency of the T loads is what
 // bounds it: with one wave for all phi and two steps in flight it took 135 us at 128 frequencies and
 // 130-200 us at 5 to 30, where there are few workgroups.
-template <typename OT>
-__global__ void __launch_bounds__(256)
+template <typename OT, bool SPLIT>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ wang, const double *__restrict__ T,
                OT *__restrict__ out)
 {
@@ -209,7 +241,8 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
 #pragma unroll
         for (int g = 0; g < COLS_KP; ++g) {
             double v = src[g][(size_t)j * 8];
-            for (int s = 1; s < split; ++s) v += src[g][s * pstride + (size_t)j * 8];
+            if constexpr (SPLIT)
+                for (int s = 1; s < split; ++s) v += src[g][s * pstride + (size_t)j * 8];
             acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v, acc[g], 0, 0, 0);
         }
     }
@@ -249,21 +282,24 @@ hipError_t launch_compact_tables(hipStream_t st, const CompactPlan &plan, int n_
                                  int is_f64, int fact, const void *tab, const void *pos, const double *wrad,
                                  const double *wang, double *T, void *out)
 {
-    const int tiles = (plan.rows + 15) / 16, wpb = tiles < 4 ? tiles : 4;
-    const dim3 gr((unsigned)((n_phi + 15) / 16) * plan.split * n_k, (tiles + wpb - 1) / wpb), br(64 * wpb);
-#define SC_COMPACT_ROWS(R, F)                                                                                    \
-    hipLaunchKernelGGL((k_compact_rows<R, F>), gr, br, 0, st, k0, n_r, n_phi, plan.rows, plan.split, (const R *)tab, \
-                       (const R *)pos, wrad, T)
+    const int64_t n_waves = (int64_t)((plan.rows + 15) / 16) * ((n_phi + 15) / 16) * plan.split * n_k;
+    const dim3 gr((unsigned)((n_waves + 3) / 4)), br(256);
+#define SC_COMPACT_ROWS(R, F)                                                                                 \
+    hipLaunchKernelGGL((k_compact_rows<R, F>), gr, br, 0, st, k0, n_r, n_phi, plan.rows, plan.split, n_waves, \
+                       (const R *)tab, (const R *)pos, wrad, T)
     if (is_f64 && fact) SC_COMPACT_ROWS(double, true);
     else if (is_f64) SC_COMPACT_ROWS(double, false);
     else if (fact) SC_COMPACT_ROWS(float, true);
     else SC_COMPACT_ROWS(float, false);
 #undef SC_COMPACT_ROWS
     const dim3 gc(plan.poff[plan.rows] / 16, (n_k + 2 * COLS_KP - 1) / (2 * COLS_KP));
-    if (is_f64)
-        hipLaunchKernelGGL((k_compact_cols<double>), gc, dim3(256), 0, st, plan, n_k, n_phi, wang, T, (double *)out);
-    else
-        hipLaunchKernelGGL((k_compact_cols<float>), gc, dim3(256), 0, st, plan, n_k, n_phi, wang, T, (float *)out);
+#define SC_COMPACT_COLS(R, S) \
+    hipLaunchKernelGGL((k_compact_cols<R, S>), gc, dim3(256), 0, st, plan, n_k, n_phi, wang, T, (R *)out)
+    if (is_f64 && plan.split > 1) SC_COMPACT_COLS(double, true);
+    else if (is_f64) SC_COMPACT_COLS(double, false);
+    else if (plan.split > 1) SC_COMPACT_COLS(float, true);
+    else SC_COMPACT_COLS(float, false);
+#undef SC_COMPACT_COLS
     return hipGetLastError();
 }
 
