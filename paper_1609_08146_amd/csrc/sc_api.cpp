@@ -301,22 +301,10 @@ sc_status sc::resolve_factoring(sc_prob *p, bool block, bool *ready)
 // A problem's factoring state is read only after a deferred test has completed.
 static sc_status settle_factoring(sc_prob *p) { return resolve_factoring(p, true, nullptr); }
 
-// Factored tables from the FP64 tables: the test runs once per table set (one flag read back); the
-// FP32 split (need32) and FP64 (need64) tables are built when asked for and the test passed at that
-// precision's tolerance (otherwise the general tables are used).  With fact_flag_host set, the flag
-// is not waited for: the test completes in resolve_factoring.
-static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
+// The factored tables' buffers, as the kernels that write them take them, with the flag cleared.
+static sc_status factor_out(sc_prob *p, bool need32, bool need64, FactorOut &o)
 {
-    if (!p->allow_fact || !p->has_tab64) return SC_OK;
-    SC_TRY(settle_factoring(p));
-    if (p->fact_checked) {
-        need32 = need32 && p->fact_ok && !p->fact32_built;
-        need64 = need64 && p->fact64_ok && !p->fact64_built;
-        if (!need32 && !need64) return SC_OK;
-    }
-    hipStream_t st = p->ctx->stream;
-    const int n_k = (int)p->k.size();
-    const size_t nrec = (size_t)n_k * p->n_tot;
+    const size_t nrec = p->k.size() * (size_t)p->n_tot;
     if (need32) {
         SC_TRY(p->tabf.reserve(sizeof(float) * 4 * nrec, p->alloc_stream));
         SC_TRY(p->posf.reserve(sizeof(float) * 8 * (size_t)p->n_tot, p->alloc_stream));
@@ -329,19 +317,20 @@ static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
         SC_TRY(p->betaf64.reserve(sizeof(double) * (size_t)p->n_tot, p->alloc_stream));
     }
     SC_TRY(p->fact_flag.reserve(sizeof(unsigned int), p->alloc_stream));
-    HIP_TRY(launch_fill_u32(st, p->fact_flag.as<unsigned int>(), 0u, 1));
-    HIP_TRY(launch_tables_factor(st, n_k, p->n_tot, p->d_k.as<double>(), p->tab64.as<double>(),
-                                 p->pos32.as<float>(), p->pos64.as<double>(), FACTOR_TOL, FACTOR_TOL_FP64,
-                                 need32 ? p->tabf.as<float>() : nullptr, need32 ? p->posf.as<float>() : nullptr,
-                                 need32 ? p->betaf.as<float>() : nullptr, need32 ? p->tabp.as<float>() : nullptr,
-                                 need64 ? p->tabf64.as<double>() : nullptr,
-                                 need64 ? p->posf64.as<double>() : nullptr,
-                                 need64 ? p->betaf64.as<double>() : nullptr, p->fact_flag.as<unsigned int>()));
-    if (p->fact_checked) {
-        p->fact32_built = p->fact32_built || need32;
-        p->fact64_built = p->fact64_built || need64;
-        return SC_OK;
-    }
+    HIP_TRY(launch_fill_u32(p->ctx->stream, p->fact_flag.as<unsigned int>(), 0u, 1));
+    o = FactorOut{p->pos32.as<float>(), p->pos64.as<double>(), FACTOR_TOL, FACTOR_TOL_FP64,
+                  need32 ? p->tabf.as<float>() : nullptr, need32 ? p->posf.as<float>() : nullptr,
+                  need32 ? p->betaf.as<float>() : nullptr, need32 ? p->tabp.as<float>() : nullptr,
+                  need64 ? p->tabf64.as<double>() : nullptr, need64 ? p->posf64.as<double>() : nullptr,
+                  need64 ? p->betaf64.as<double>() : nullptr, p->fact_flag.as<unsigned int>()};
+    return SC_OK;
+}
+
+// The outcome of a factoring test whose kernel was just launched: one flag read back.  With
+// fact_flag_host set it is not waited for: the test completes in resolve_factoring.
+static sc_status factoring_launched(sc_prob *p, bool need32, bool need64)
+{
+    hipStream_t st = p->ctx->stream;
     if (p->fact_flag_host) {
         HIP_TRY(hipMemcpyAsync(p->fact_flag_host, p->fact_flag.p, sizeof(unsigned int), hipMemcpyDeviceToHost, st));
         if (!p->fact_ev) HIP_TRY(hipEventCreateWithFlags(&p->fact_ev, hipEventDisableTiming));
@@ -358,21 +347,51 @@ static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
     return SC_OK;
 }
 
+// Factored tables from the FP64 tables: the test runs once per table set; the FP32 split (need32) and
+// FP64 (need64) tables are built when asked for and the test passed at that precision's tolerance
+// (otherwise the general tables are used).
+static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
+{
+    if (!p->allow_fact || !p->has_tab64) return SC_OK;
+    SC_TRY(settle_factoring(p));
+    if (p->fact_checked) {
+        need32 = need32 && p->fact_ok && !p->fact32_built;
+        need64 = need64 && p->fact64_ok && !p->fact64_built;
+        if (!need32 && !need64) return SC_OK;
+    }
+    FactorOut o;
+    SC_TRY(factor_out(p, need32, need64, o));
+    HIP_TRY(launch_tables_factor(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
+                                 p->tab64.as<double>(), o));
+    if (p->fact_checked) {
+        p->fact32_built = p->fact32_built || need32;
+        p->fact64_built = p->fact64_built || need64;
+        return SC_OK;
+    }
+    return factoring_launched(p, need32, need64);
+}
+
+// The layouts built with the tables themselves: those of the expected precision.
+static bool eager32(const sc_prob *p) { return p->eager_prec == SC_FP32_SPLIT; }
+static bool eager64(const sc_prob *p) { return p->eager_prec == SC_FP64 && p->keep_fp64; }
+
 static sc_status reserve_power(sc_prob *p)
 {
-    const size_t n = p->k.size() + (size_t)power_partial_count((int)p->k.size());
+    const size_t n = p->k.size() + (size_t)power_partial_count((int)p->k.size(), p->n_tot);
     return p->d_power.reserve(sizeof(double) * n, p->alloc_stream);
 }
 
-// After tab64 was (re)built: with keep_fp64 off, cast to the FP32 split tables now and release tab64.
-static sc_status finish_tables(sc_prob *p)
+// After tab64 was (re)built (`tested`: the factoring test went with it): with keep_fp64 off, cast to the
+// FP32 split tables now and release tab64.
+static sc_status finish_tables(sc_prob *p, bool tested = false)
 {
     p->has_tab = true;
     p->has_tab64 = true;
     // the factoring test (and the factored tables of the expected precision) now, so that the table
     // layout, and with it the launch shape, is known before the first evaluation; it needs the FP64
     // tables
-    SC_TRY(ensure_factored(p, p->eager_prec == SC_FP32_SPLIT, p->eager_prec == SC_FP64 && p->keep_fp64));
+    if (tested) SC_TRY(factoring_launched(p, eager32(p), eager64(p)));
+    else SC_TRY(ensure_factored(p, eager32(p), eager64(p)));
     if (p->keep_fp64) return SC_OK;
     if (p->fact_pending) {   // the general FP32 tables only if the current does not factor
         p->cast_pending = true;
@@ -687,18 +706,23 @@ static sc_status set_incident_builtin(sc_prob *p, int beam, double w0, double po
     }
     const double *modes = beam == 3 ? p->d_modes.as<double>() : nullptr;
     ev_record(p, EV_PREP0);
-    HIP_TRY(launch_tables_gaussian(st, n_k, p->n_surf, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
-                                   p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>(), beam, w0, pol_angle,
-                                   dspec, consistent ? 1 : 0, modes, n_modes, p->tab64.as<double>()));
+    int kb = 0;   // where |Jt| ~ k |amplitude| is largest
+    for (int i = 1; spectrum && i < n_k; ++i)
+        if (p->k[i] * std::hypot(spectrum[2 * i], spectrum[2 * i + 1]) >
+            p->k[kb] * std::hypot(spectrum[2 * kb], spectrum[2 * kb + 1]))
+            kb = i;
+    if (!spectrum) kb = (int)(std::max_element(p->k.begin(), p->k.end()) - p->k.begin());
+    FactorOut out;
+    if (p->allow_fact) SC_TRY(factor_out(p, eager32(p), eager64(p), out));
     SC_TRY(reserve_power(p));
-    HIP_TRY(launch_power_gaussian(st, n_k, p->n_surf, p->d_k.as<double>(), p->pos64.as<double>(),
-                                  p->nrm.as<double>(), p->wgt.as<double>(), beam, w0, pol_angle, dspec,
-                                  consistent ? 1 : 0, modes, n_modes, p->d_power.as<double>() + n_k,
-                                  p->d_power.as<double>()));
+    HIP_TRY(launch_tables_beam(st, n_k, p->n_surf, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
+                               p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>(), beam, w0, pol_angle,
+                               dspec, consistent ? 1 : 0, modes, n_modes, p->tab64.as<double>(), kb,
+                               p->allow_fact ? &out : nullptr, p->d_power.as<double>() + n_k, p->d_power.as<double>()));
     p->has_power = true;
     ev_record(p, EV_PREP1);
     p->ev_prep = p->ctx->profiling;
-    return finish_tables(p);
+    return finish_tables(p, p->allow_fact);
 }
 
 extern "C" sc_status sc_set_incident_beam(sc_prob *p, int beam, double w0, double pol_angle, const double *spectrum,
@@ -1319,7 +1343,7 @@ size_t sc::footprint_bytes(int n_r, int n_phi, int n_k, int n_obs, int n_t, sc_p
     b += sizeof(double) * (2 * (size_t)n_r + 1 + 2 * (size_t)n_phi + 3 * (size_t)n_phi);   // 1-D rule, rim tangents
     b += n_tot * (sizeof(double) * (4 + 3 + 1 + 1) + sizeof(float) * 5);                    // node records
     b += sizeof(double) * n_k;
-    b += sizeof(double) * (size_t)n_k * (1 + (size_t)power_partial_count(1));                // incident power
+    b += sizeof(double) * (size_t)n_k * (1 + (size_t)power_partial_count(1, n_tot));         // incident power
     // FP64 tables (kept for SC_FP64; for the FP32 forms they exist only while the FP32 tables are cast)
     b += (size_t)n_k * n_tot * sizeof(double) * 8;
     if (prec != SC_FP64) b += (size_t)n_k * n_tot * sizeof(float) * 8;                      // FP32 tables

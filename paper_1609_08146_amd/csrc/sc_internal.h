@@ -29,23 +29,22 @@ hipError_t launch_tables_from_fields(hipStream_t st, int n_k, int n_surf, int n_
 // (modes: device [n_modes][SC_LG_RECORD] = p, l, ex re, ex im, ey re, ey im, the normalisation
 // C_{p,l} (including 1 / w0), unused; unused for the other beams)
 constexpr int SC_LG_RECORD = 8;
-hipError_t launch_tables_gaussian(hipStream_t st, int n_k, int n_surf, int n_tot, const double *k,
-                                  const double *pos64, const double *nrm, const double *wgt,
-                                  const double *tan, int beam, double w0, double pol, const double *spectrum,
-                                  int consistent, const double *modes, int n_modes, double *tab64);
+// With `out` the factored tables and their test in the same pass (see FactorOut); kb: the frequency where
+// |Jt| is expected largest, k |amplitude|.
+struct FactorOut;
+hipError_t launch_tables_beam(hipStream_t st, int n_k, int n_surf, int n_tot, const double *k, const double *pos64,
+                              const double *nrm, const double *wgt, const double *tan, int beam, double w0, double pol,
+                              const double *spectrum, int consistent, const double *modes, int n_modes, double *tab64,
+                              int kb, const FactorOut *out, double *part, double *P);
 // FP32 tables from the FP64 ones (tab64), or from FP32 split tables (src32, when tab64 is null)
 hipError_t launch_tables_cast(hipStream_t st, int n_k, int n_tot, const double *k, const double *pos64,
                               const double *tab64, const float *src32, float *tab32, int naive);
 // Incident power per frequency through the aperture, P[k] = 4 pi sum_surface W Re(E x B^*).(-z):
-// from field tables E, B [n_k][n_tot][3] complex, or from the built-in Gaussian beam.
-// `part` holds power_partial_count(n_k) doubles of scratch; P is [n_k] (device).
+// from field tables E, B [n_k][n_tot][3] complex (launch_tables_beam does it for its own fields).
+// `part` holds power_partial_count(n_k, n_tot) doubles of scratch; P is [n_k] (device).
 hipError_t launch_power_fields(hipStream_t st, int n_k, int n_surf, int n_tot, const double *nrm, const double *wgt,
                                const double *E, const double *B, double *part, double *P);
-hipError_t launch_power_gaussian(hipStream_t st, int n_k, int n_surf, const double *k, const double *pos64,
-                                 const double *nrm, const double *wgt, int beam, double w0, double pol,
-                                 const double *spectrum, int consistent, const double *modes, int n_modes,
-                                 double *part, double *P);
-int power_partial_count(int n_k);
+int64_t power_partial_count(int n_k, int n_tot);
 // tab[k][node] *= fac[k] (complex128 [n_k]) for the n_cplx complex numbers of each record (4 general,
 // 2 factored); exactly one of tab64, tab32 non-null
 hipError_t launch_tables_scale(hipStream_t st, int n_k, int n_tot, int n_cplx, const double *fac, double *tab64,
@@ -57,10 +56,16 @@ hipError_t launch_tables_scale(hipStream_t st, int n_k, int n_tot, int n_cplx, c
 // within tol32 (relative to its largest |Jt| over k), bit 1 for tol64; bits 2 and 3 when some
 // node's charge is not tied to its current (rho_t = -i beta s / k, beta real) within tol32, tol64
 // (relative to its largest (|rho_t|^2 + |Jt / k|^2)^1/2).
+struct FactorOut {
+    const float *pos32;
+    const double *pos64;
+    double tol32, tol64;
+    float *tabf, *posf, *betaf, *tabp;
+    double *tabf64, *posf64, *betaf64;
+    unsigned int *bad;
+};
 hipError_t launch_tables_factor(hipStream_t st, int n_k, int n_tot, const double *k, const double *tab64,
-                                const float *pos32, const double *pos64, double tol32, double tol64, float *tabf,
-                                float *posf, float *betaf, float *tabp, double *tabf64, double *posf64,
-                                double *betaf64, unsigned int *bad);
+                                const FactorOut &out);
 // tabp[r] = (|s|, arg(s) / 2 pi) from the FP32 factored records tabf[r] = (s, rho_t), r < n_rec.
 hipError_t launch_tables_polar(hipStream_t st, int64_t n_rec, const float *tabf, float *tabp);
 // Maxwell-residual diagnostics (sc_diag.hip).  Stencil results [rows][13 n_pts][3] complex (double

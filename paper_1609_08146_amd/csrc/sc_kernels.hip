@@ -3,8 +3,9 @@
 //  k_node_tables         mirror nodes, normals, weights            (Sec. III-C)
 //  k_obs_prep            observation records
 //  k_tables_from_fields  POA current / charge tables from given E_inc, B_inc
-//  k_tables_gaussian     same for the built-in collimated beams: linearly, radially or
-//                        azimuthally polarised Gaussian (Sec. III-A, IV-A)
+//  k_tables_beam         same for the built-in collimated beams: linearly, radially or azimuthally
+//                        polarised Gaussian, Laguerre-Gauss modes (Sec. III-A, IV-A); with the
+//                        factored tables in the same pass
 //  k_tables_cast         FP64 tables -> FP32 (split: as is; naive: node phase removed)
 //  k_tables_factor       FP64 tables -> factored FP32 / FP64 tables J~ = u s, when the current
 //                        of every node keeps one real direction over the frequencies, and
@@ -21,6 +22,8 @@
 // the launch shape, only on the chunking.
 #include "sc_device.h"
 #include "sc_internal.h"
+
+#include <algorithm>
 
 namespace sc {
 
@@ -221,7 +224,7 @@ __global__ void k_tables_from_fields(int n_k, int n_surf, int n_tot, const doubl
 //   with c = (2i/k)(r^2/w0^2 - 1) for the curl-consistent variants (E = (i/k) curl B,
 //   resp. B = (-i/k) curl E) and c = 0 for the literal ones (B = -z x E).  The
 //   cylindrical beams are axisymmetric, so `pol` does not enter;
-//   beam 3, a Laguerre-Gauss mode set (lg_fields), literal.
+//   beam 3, a Laguerre-Gauss mode set (lg_shape), literal.
 // Laguerre-Gauss mode set (Sec. III-A: the Laguerre-Gauss modes of the paraxial wave equation are
 // the expansion basis of the incident beams), each mode in its waist cross-section carried along -z:
 //   u_{p,l} = C_{p,l} ((X + i sgn(l) Y) sqrt(2) / w0)^|l| L_p^|l|(2 r^2 / w0^2) exp(-r^2 / w0^2),
@@ -231,8 +234,17 @@ __global__ void k_tables_from_fields(int n_k, int n_surf, int n_tot, const doubl
 // C from the host (it does not depend on the position; a device lgamma here cost the table
 // kernels 72 VGPRs and 380 bytes of scratch per lane);
 //   E = sum_m (ex_m x + ey_m y) u_m amp,   B = (-z) x E = sum_m (ey_m x - ex_m y) u_m amp.
-__device__ __forceinline__ void lg_fields(const double *__restrict__ modes, int n_modes, double X, double Y,
-                                          double w0, c64 amp, c64 *E, c64 *B)
+//
+// What does not depend on the frequency is a node's BeamShape, formed once per thread (the exponential,
+// the sine of the polarisation angle, the mode sum); beam_at adds the frequency's amplitude.
+struct BeamShape {
+    double x, y, G;   // beam 0: position in the frame of the polarisation, else (X, Y); amplitude at it
+    double cl, sl;    // beam 0: cosine and sine of the polarisation angle
+    c64 ex, ey;       // beam 3: the mode sum
+};
+
+__device__ __forceinline__ void lg_shape(const double *__restrict__ modes, int n_modes, double X, double Y,
+                                         double w0, BeamShape &b)
 {
     const double s2w = 1.4142135623730951 / w0;
     const double t = 2.0 * (X * X + Y * Y) / (w0 * w0);
@@ -260,31 +272,51 @@ __device__ __forceinline__ void lg_fields(const double *__restrict__ modes, int 
         ex = {ex.re + cx.re, ex.im + cx.im};
         ey = {ey.re + cy.re, ey.im + cy.im};
     }
-    ex = cmul(ex, amp);
-    ey = cmul(ey, amp);
-    E[0] = ex;
-    E[1] = ey;
-    E[2] = {0.0, 0.0};
-    B[0] = ey;
-    B[1] = {-ex.re, -ex.im};
-    B[2] = {0.0, 0.0};
+    b.ex = ex;
+    b.ey = ey;
 }
 
-__device__ __forceinline__ void beam_fields(int beam, double k, double X, double Y, double w0, double pol, c64 amp,
-                                            int consistent, const double *modes, int n_modes, c64 *E, c64 *B)
+__device__ __forceinline__ BeamShape beam_shape(int beam, double X, double Y, double w0, double pol,
+                                                const double *__restrict__ modes, int n_modes)
 {
+    BeamShape b = {};
     if (beam == 3) {
-        lg_fields(modes, n_modes, X, Y, w0, amp, E, B);
+        lg_shape(modes, n_modes, X, Y, w0, b);
+    } else if (beam != 0) {
+        b.x = X;
+        b.y = Y;
+        b.G = exp(-(X * X + Y * Y) / (w0 * w0)) / w0;
+    } else {
+        sincos(pol, &b.sl, &b.cl);
+        // frame where the polarisation is along x
+        b.x = b.cl * X + b.sl * Y;
+        b.y = -b.sl * X + b.cl * Y;
+        b.G = exp(-(b.x * b.x + b.y * b.y) / (w0 * w0));
+    }
+    return b;
+}
+
+__device__ __forceinline__ void beam_at(int beam, const BeamShape &b, double k, double w0, c64 amp, int consistent,
+                                        c64 *E, c64 *B)
+{
+    const c64 zero = {0.0, 0.0};
+    if (beam == 3) {
+        const c64 ex = cmul(b.ex, amp), ey = cmul(b.ey, amp);
+        E[0] = ex;
+        E[1] = ey;
+        E[2] = zero;
+        B[0] = ey;
+        B[1] = {-ex.re, -ex.im};
+        B[2] = zero;
         return;
     }
+    const double x = b.x, y = b.y;
     if (beam != 0) {
-        const double r2 = X * X + Y * Y;
-        const double G = exp(-r2 / (w0 * w0)) / w0;
-        const c64 g = {G * amp.re, G * amp.im};
+        const c64 g = {b.G * amp.re, b.G * amp.im};
+        const double r2 = x * x + y * y;
         const double c = consistent ? 2.0 / k * (r2 / (w0 * w0) - 1.0) : 0.0;   // longitudinal: i c g
         const c64 lg = {-c * g.im, c * g.re};
-        const c64 zero = {0.0, 0.0};
-        const c64 rx = {X * g.re, X * g.im}, ry = {Y * g.re, Y * g.im};
+        const c64 rx = {x * g.re, x * g.im}, ry = {y * g.re, y * g.im};
         if (beam == 1) {
             E[0] = rx;
             E[1] = ry;
@@ -302,13 +334,7 @@ __device__ __forceinline__ void beam_fields(int beam, double k, double X, double
         }
         return;
     }
-    double sl, cl;
-    sincos(pol, &sl, &cl);
-    // frame where the polarisation is along x
-    const double x = cl * X + sl * Y;
-    const double y = -sl * X + cl * Y;
-    const double G = exp(-(x * x + y * y) / (w0 * w0));
-    const c64 psi = {G * amp.re, G * amp.im};
+    const c64 psi = {b.G * amp.re, b.G * amp.im};
     c64 e[3], bb[3];
     if (consistent) {
         const double kw2 = k * w0 * w0;
@@ -319,49 +345,23 @@ __device__ __forceinline__ void beam_fields(int beam, double k, double X, double
         e[0] = {c1 * psi.re, c1 * psi.im};
         e[1] = {c2 * psi.re, c2 * psi.im};
         e[2] = {-c3 * psi.im, c3 * psi.re};
-        bb[0] = {0.0, 0.0};
+        bb[0] = zero;
         bb[1] = {-psi.re, -psi.im};
         bb[2] = {-c4 * psi.im, c4 * psi.re};
     } else {
         e[0] = psi;
-        e[1] = {0.0, 0.0};
-        e[2] = {0.0, 0.0};
-        bb[0] = {0.0, 0.0};
+        e[1] = zero;
+        e[2] = zero;
+        bb[0] = zero;
         bb[1] = {-psi.re, -psi.im};
-        bb[2] = {0.0, 0.0};
+        bb[2] = zero;
     }
-    E[0] = {cl * e[0].re - sl * e[1].re, cl * e[0].im - sl * e[1].im};
-    E[1] = {sl * e[0].re + cl * e[1].re, sl * e[0].im + cl * e[1].im};
+    E[0] = {b.cl * e[0].re - b.sl * e[1].re, b.cl * e[0].im - b.sl * e[1].im};
+    E[1] = {b.sl * e[0].re + b.cl * e[1].re, b.sl * e[0].im + b.cl * e[1].im};
     E[2] = e[2];
-    B[0] = {cl * bb[0].re - sl * bb[1].re, cl * bb[0].im - sl * bb[1].im};
-    B[1] = {sl * bb[0].re + cl * bb[1].re, sl * bb[0].im + cl * bb[1].im};
+    B[0] = {b.cl * bb[0].re - b.sl * bb[1].re, b.cl * bb[0].im - b.sl * bb[1].im};
+    B[1] = {b.sl * bb[0].re + b.cl * bb[1].re, b.sl * bb[0].im + b.cl * bb[1].im};
     B[2] = bb[2];
-}
-
-__global__ void k_tables_gaussian(int n_k, int n_surf, int n_tot, const double *__restrict__ kv,
-                                  const double *__restrict__ pos64, const double *__restrict__ nrm,
-                                  const double *__restrict__ wgt, const double *__restrict__ tan, int beam, double w0,
-                                  double pol, const double *__restrict__ spectrum, int consistent,
-                                  const double *__restrict__ modes, int n_modes, double *__restrict__ tab64)
-{
-    const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_k * n_tot) return;
-    const int kk = (int)(idx / n_tot);
-    const int q = (int)(idx - (int64_t)kk * n_tot);
-    const double k = kv[kk];
-    const double *p = pos64 + 4 * q;
-    const double X = p[0], Y = p[1], Z = p[2];
-    const c64 amp = spectrum ? c64{spectrum[2 * kk], spectrum[2 * kk + 1]} : c64{1.0, 0.0};
-    c64 E[3], B[3];
-    beam_fields(beam, k, X, Y, w0, pol, amp, consistent, modes, n_modes, E, B);
-    // propagation phase e^{-ikz} fused with the node phase e^{ik|r_s|}: e^{ik(|r_s| - z)},
-    // formed in double-double so that no ~1e6 rad phase is ever rounded to double
-    const dd rs = dd_norm3(X, Y, Z);
-    double sp, cp;
-    sincos(phase_mod_2pi(k, dd_sub_d(rs, Z)), &sp, &cp);
-    const bool rim = q >= n_surf;
-    write_record(tab64 + idx * 8, rim, k, wgt[q], nrm + 3 * q, rim ? tan + 3 * (q - n_surf) : nullptr, E, B,
-                 {cp, sp});
 }
 
 // ------------------------------------------------------------ incident power
@@ -372,9 +372,9 @@ __global__ void k_tables_gaussian(int n_k, int n_surf, int n_tot, const double *
 // aperture disk in the (x, y) plane, so P_n = 4 pi sum_q W_q Re(E x B^*) . (-z)
 // over the surface nodes; for a general surface the aperture element of a node
 // is the z component of its n dS, (n~ W).z (n~.z = 1 on the paraboloid).
-// Deterministic: block b of frequency k sums a fixed node range in a fixed
-// order; k_power_finish adds the blocks in order.
-constexpr int POWER_BLOCKS = 16;
+// Deterministic: each part (64 nodes in k_tables_beam, one of POWER_BLOCKS ranges in
+// k_power_fields) is summed in a fixed order, and so are the parts in k_power_finish.
+constexpr int POWER_BLOCKS = 64;
 
 __device__ __forceinline__ double flux_minus_z(const c64 *E, const c64 *B)
 {
@@ -416,37 +416,14 @@ __global__ void __launch_bounds__(256) k_power_fields(int n_surf, int n_tot, con
     block_sum_256(acc, part + (size_t)kk * POWER_BLOCKS + blockIdx.x);
 }
 
-__global__ void __launch_bounds__(256) k_power_gaussian(int n_surf, const double *__restrict__ kv,
-                                                        const double *__restrict__ pos64,
-                                                        const double *__restrict__ nrm,
-                                                        const double *__restrict__ wgt, int beam, double w0,
-                                                        double pol,
-                                                        const double *__restrict__ spectrum, int consistent,
-                                                        const double *__restrict__ modes, int n_modes,
-                                                        double *__restrict__ part)
+// One workgroup per frequency.
+__global__ void __launch_bounds__(256) k_power_finish(int n_part, const double *__restrict__ part, double *__restrict__ P)
 {
-    const int kk = blockIdx.y;
-    const int span = (n_surf + POWER_BLOCKS - 1) / POWER_BLOCKS;
-    const int q0 = blockIdx.x * span, q1 = min(q0 + span, n_surf);
-    const double k = kv[kk];
-    const c64 amp = spectrum ? c64{spectrum[2 * kk], spectrum[2 * kk + 1]} : c64{1.0, 0.0};
-    double acc = 0.0;
-    for (int q = q0 + (int)threadIdx.x; q < q1; q += 256) {
-        c64 E[3], B[3];
-        beam_fields(beam, k, pos64[4 * q], pos64[4 * q + 1], w0, pol, amp, consistent, modes, n_modes, E, B);
-        acc += (nrm[3 * q + 2] * wgt[q]) * flux_minus_z(E, B);
-    }
-    block_sum_256(acc, part + (size_t)kk * POWER_BLOCKS + blockIdx.x);
-}
-
-__global__ void k_power_finish(int n_k, const double *__restrict__ part, double *__restrict__ P)
-{
-    const int64_t gk = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (gk >= n_k) return;
-    const int kk = (int)gk;
     double s = 0.0;
-    for (int b = 0; b < POWER_BLOCKS; ++b) s += part[(size_t)kk * POWER_BLOCKS + b];
-    P[kk] = FOUR_PI * s;
+    for (int b = threadIdx.x; b < n_part; b += 256) s += part[(size_t)blockIdx.x * n_part + b];
+    __shared__ double sum;
+    block_sum_256(s, &sum);
+    if (threadIdx.x == 0) P[blockIdx.x] = FOUR_PI * sum;
 }
 
 // Multiply every record of frequency k by the complex factor fac[k] (spectral
@@ -524,12 +501,90 @@ __global__ void k_tables_cast(int n_k, int n_tot, const double *__restrict__ kv,
 // skips it): FP32 tabf[k][q] = (s, rho_t), posf[q] = (x, y, z, |r_s|, u_q, 1 / (2|r_s|)),
 // betaf[q] = beta_q and tabp[k][q] = (|s|, arg(s) / 2 pi), s in polar form for the tied
 // charge (the turn in (-1/2, 1/2]); FP64 tabf64, posf64 and betaf64, the same in double.
+struct FactorDir {
+    double u[3], beta;
+    bool current;   // whether the node carries any
+};
+
+// From the node's record v (|Jt|^2 = m) at wavenumber k.
+__device__ __forceinline__ FactorDir factor_dir(const double *v, double m, double k)
+{
+    FactorDir d = {{0.0, 0.0, 0.0}, 1.0, m > 0.0};
+    if (!d.current) return d;
+    const double re2 = v[0] * v[0] + v[2] * v[2] + v[4] * v[4];
+    const double im2 = v[1] * v[1] + v[3] * v[3] + v[5] * v[5];
+    const int part = re2 >= im2 ? 0 : 1;
+    const double inv = 1.0 / sqrt(part ? im2 : re2);
+    for (int c = 0; c < 3; ++c) d.u[c] = (part ? v[2 * c + 1] : v[2 * c]) * inv;
+    const double sr = d.u[0] * v[0] + d.u[1] * v[2] + d.u[2] * v[4];
+    const double si = d.u[0] * v[1] + d.u[1] * v[3] + d.u[2] * v[5];
+    const double s2 = sr * sr + si * si;
+    d.beta = s2 > 0.0 ? k * (v[6] * si - v[7] * sr) / s2 : 0.0;
+    return d;
+}
+
+// s of the record v, and the squared residuals of the current (r2) and of the tied charge (t2).
+__device__ __forceinline__ c64 factor_record(const double *v, double k, const FactorDir &d, double &r2, double &t2)
+{
+    c64 s;
+    if (d.current) s = {d.u[0] * v[0] + d.u[1] * v[2] + d.u[2] * v[4], d.u[0] * v[1] + d.u[1] * v[3] + d.u[2] * v[5]};
+    else s = {-k * v[7], k * v[6]};   // s = i k rho_t
+    r2 = 0.0;
+    for (int c = 0; c < 3; ++c) {
+        const double dr = v[2 * c] - d.u[c] * s.re, di = v[2 * c + 1] - d.u[c] * s.im;
+        r2 += dr * dr + di * di;
+    }
+    // rho_t + i beta s / k
+    const double tr = v[6] - d.beta * s.im / k, ti = v[7] + d.beta * s.re / k;
+    t2 = tr * tr + ti * ti;
+    return s;
+}
+
+__device__ __forceinline__ void factor_store(const FactorOut &o, int64_t rec, const double *v, c64 s)
+{
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    typedef float f2 __attribute__((ext_vector_type(2)));
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    if (o.tabf) {
+        *(f4 *)(o.tabf + rec * 4) = f4{(float)s.re, (float)s.im, (float)v[6], (float)v[7]};
+        *(f2 *)(o.tabp + rec * 2) =
+            f2{(float)sqrt(s.re * s.re + s.im * s.im), (float)(atan2(s.im, s.re) * INV_TWO_PI)};
+    }
+    if (o.tabf64) {
+        d2 *t = (d2 *)(o.tabf64 + rec * 4);
+        t[0] = d2{s.re, s.im};
+        t[1] = d2{v[6], v[7]};
+    }
+}
+
+__device__ __forceinline__ void factor_store_node(const FactorOut &o, int64_t q, const FactorDir &d)
+{
+    const double rs = o.pos64[q * 4 + 3], hinv = rs > 0.0 ? 0.5 / rs : 0.0;   // 1 / (2 |r_s|)
+    if (o.posf) {
+        float *pr = o.posf + q * 8;
+        for (int c = 0; c < 4; ++c) pr[c] = o.pos32[q * 4 + c];
+        for (int c = 0; c < 3; ++c) pr[4 + c] = (float)d.u[c];
+        pr[7] = (float)hinv;
+        o.betaf[q] = (float)d.beta;
+    }
+    if (o.posf64) {
+        double *pr = o.posf64 + q * 8;
+        for (int c = 0; c < 4; ++c) pr[c] = o.pos64[q * 4 + c];
+        for (int c = 0; c < 3; ++c) pr[4 + c] = d.u[c];
+        pr[7] = hinv;
+        o.betaf64[q] = d.beta;
+    }
+}
+
+__device__ __forceinline__ double current2(const double *v)
+{
+    double m = 0.0;
+    for (int c = 0; c < 6; ++c) m += v[c] * v[c];
+    return m;
+}
+
 __global__ void k_tables_factor(int n_k, int n_tot, const double *__restrict__ kv, const double *__restrict__ tab64,
-                                const float *__restrict__ pos32, const double *__restrict__ pos64, double tol32,
-                                double tol64, float *__restrict__ tabf, float *__restrict__ posf,
-                                float *__restrict__ betaf, float *__restrict__ tabp, double *__restrict__ tabf64,
-                                double *__restrict__ posf64, double *__restrict__ betaf64,
-                                unsigned int *__restrict__ bad)
+                                FactorOut o)
 {
     const int64_t gq = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gq >= n_tot) return;
@@ -537,88 +592,209 @@ __global__ void k_tables_factor(int n_k, int n_tot, const double *__restrict__ k
     int kb = 0;
     for (int kk = 0; kk < n_k; ++kk) {
         const double *v = tab64 + ((int64_t)kk * n_tot + gq) * 8;
-        double m = 0.0;
-        for (int c = 0; c < 6; ++c) m += v[c] * v[c];
+        const double m = current2(v), k = kv[kk];
         if (m > best) {
             best = m;
             kb = kk;
         }
-        const double k = kv[kk];
         bestr = fmax(bestr, v[6] * v[6] + v[7] * v[7] + m / (k * k));
     }
-    double u[3] = {0.0, 0.0, 0.0};
-    double beta = 1.0;
-    if (best > 0.0) {
-        const double *v = tab64 + ((int64_t)kb * n_tot + gq) * 8;
-        const double re2 = v[0] * v[0] + v[2] * v[2] + v[4] * v[4];
-        const double im2 = v[1] * v[1] + v[3] * v[3] + v[5] * v[5];
-        const int part = re2 >= im2 ? 0 : 1;
-        const double inv = 1.0 / sqrt(part ? im2 : re2);
-        for (int c = 0; c < 3; ++c) u[c] = v[2 * c + part] * inv;
-        const double sr = u[0] * v[0] + u[1] * v[2] + u[2] * v[4];
-        const double si = u[0] * v[1] + u[1] * v[3] + u[2] * v[5];
-        const double s2 = sr * sr + si * si;
-        beta = s2 > 0.0 ? kv[kb] * (v[6] * si - v[7] * sr) / s2 : 0.0;
-    }
-    const double lim32 = tol32 * tol32 * best, lim64 = tol64 * tol64 * best;
-    const double rlim32 = tol32 * tol32 * bestr, rlim64 = tol64 * tol64 * bestr;
+    const FactorDir dir = factor_dir(tab64 + ((int64_t)kb * n_tot + gq) * 8, best, kv[kb]);
+    const double lim32 = o.tol32 * o.tol32 * best, lim64 = o.tol64 * o.tol64 * best;
+    const double rlim32 = o.tol32 * o.tol32 * bestr, rlim64 = o.tol64 * o.tol64 * bestr;
     unsigned int flags = 0;
     for (int kk = 0; kk < n_k; ++kk) {
         const int64_t rec = (int64_t)kk * n_tot + gq;
         const double *v = tab64 + rec * 8;
-        const double k = kv[kk];
-        double sr, si;
-        if (best > 0.0) {
-            sr = u[0] * v[0] + u[1] * v[2] + u[2] * v[4];
-            si = u[0] * v[1] + u[1] * v[3] + u[2] * v[5];
-        } else {   // s = i k rho_t
-            sr = -k * v[7];
-            si = k * v[6];
-        }
-        double r2 = 0.0;
-        for (int c = 0; c < 3; ++c) {
-            const double dr = v[2 * c] - u[c] * sr, di = v[2 * c + 1] - u[c] * si;
-            r2 += dr * dr + di * di;
-        }
+        double r2, t2;
+        const c64 s = factor_record(v, kv[kk], dir, r2, t2);
         if (!(r2 <= lim32)) flags |= 1u;
         if (!(r2 <= lim64)) flags |= 2u;
-        // rho_t + i beta s / k
-        const double tr = v[6] - beta * si / k, ti = v[7] + beta * sr / k;
-        const double t2 = tr * tr + ti * ti;
         if (!(t2 <= rlim32)) flags |= 4u;
         if (!(t2 <= rlim64)) flags |= 8u;
-        if (tabf) {
-            float *t = tabf + rec * 4;
-            t[0] = (float)sr;
-            t[1] = (float)si;
-            t[2] = (float)v[6];
-            t[3] = (float)v[7];
-            tabp[rec * 2] = (float)sqrt(sr * sr + si * si);
-            tabp[rec * 2 + 1] = (float)(atan2(si, sr) * INV_TWO_PI);
+        factor_store(o, rec, v, s);
+    }
+    factor_store_node(o, gq, dir);
+    if (flags) atomicOr(o.bad, flags);
+}
+
+// Four lanes' records of 8 doubles, written so that each store instruction writes whole records: the 4 x 4
+// pieces of 16 bytes are transposed within the four lanes.
+__device__ __forceinline__ double quad_xor(double x, int ctrl_xor2)
+{
+    const long long b = __double_as_longlong(x);
+    int lo = (int)b, hi = (int)(b >> 32);
+    if (ctrl_xor2) {
+        lo = __builtin_amdgcn_mov_dpp(lo, 0x4E, 0xF, 0xF, true);   // quad_perm [2, 3, 0, 1]
+        hi = __builtin_amdgcn_mov_dpp(hi, 0x4E, 0xF, 0xF, true);
+    } else {
+        lo = __builtin_amdgcn_mov_dpp(lo, 0xB1, 0xF, 0xF, true);   // quad_perm [1, 0, 3, 2]
+        hi = __builtin_amdgcn_mov_dpp(hi, 0xB1, 0xF, 0xF, true);
+    }
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+__device__ __forceinline__ void store_records(double *base, int count, const double *rec)
+{
+    typedef double d2 __attribute__((ext_vector_type(2)));
+    const int j = threadIdx.x & 3;
+    double v[8];
+    for (int c = 0; c < 8; ++c) v[c] = rec[c];
+    const bool b0 = j & 1, b1 = j & 2;
+#pragma unroll
+    for (int p = 0; p < 8; p += 4)
+#pragma unroll
+        for (int c = p; c < p + 2; ++c) {
+            const double r = quad_xor(b0 ? v[c] : v[c + 2], 0);
+            v[c] = b0 ? r : v[c];
+            v[c + 2] = b0 ? v[c + 2] : r;
         }
-        if (tabf64) {
-            double *t = tabf64 + rec * 4;
-            t[0] = sr;
-            t[1] = si;
-            t[2] = v[6];
-            t[3] = v[7];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const double r = quad_xor(b1 ? v[c] : v[c + 4], 1);
+        v[c] = b1 ? r : v[c];
+        v[c + 4] = b1 ? v[c + 4] : r;
+    }
+    for (int i = 0; i < 4; ++i)
+        if (i < count) *(d2 *)(base + 8 * i + 2 * j) = d2{v[2 * i], v[2 * i + 1]};
+}
+
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_or_zero(double x)
+{
+    const long long b = __double_as_longlong(x);
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)b, CTRL, ROWS, 0xF, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), CTRL, ROWS, 0xF, false);
+    return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// The sum over a wave, in lane 63.
+__device__ __forceinline__ double wave_sum_63(double x)
+{
+    x += dpp_or_zero<0x111, 0xF>(x);   // row_shr 1, 2, 4, 8: lane 15 of each row of 16 holds its sum
+    x += dpp_or_zero<0x112, 0xF>(x);
+    x += dpp_or_zero<0x114, 0xF>(x);
+    x += dpp_or_zero<0x118, 0xF>(x);
+    x += dpp_or_zero<0x142, 0xA>(x);   // row_bcast 15: rows 0, 2 into rows 1, 3
+    x += dpp_or_zero<0x143, 0xC>(x);   // row_bcast 31: rows 0, 1 into rows 2, 3
+    return x;
+}
+
+// The tables of a built-in beam, and with TEST their factored form and its test in the same pass (the two
+// separate kernels wrote the FP64 tables once and read them twice: 0.51 + 0.67 ms at 128 frequencies and
+// 160 400 nodes, 3.9 GB; @BEAM@).  Workgroups of 64 nodes x blockDim.y shares of the frequencies; what
+// does not depend on the frequency is formed once per thread.  The node's direction is taken from its
+// record at the host's guess of the largest, kb = argmax k |amplitude| (exact for a beam whose shape does
+// not depend on the frequency), which is formed first; the largest |Jt| and the residuals are
+// collected on the way and compared at the end.  Where the guess proves bad (less than half of the largest
+// |Jt|), the pass is made again from the true one.
+constexpr int BEAM_PARTS = 8;
+template <int beam, bool TEST>
+__global__ void __launch_bounds__(64 * BEAM_PARTS) __attribute__((amdgpu_waves_per_eu(2)))
+k_tables_beam(int n_k, int n_surf, int n_tot, const double *__restrict__ kv, const double *__restrict__ pos64,
+              const double *__restrict__ nrm, const double *__restrict__ wgt, const double *__restrict__ tan, double w0, double pol, const double *__restrict__ spectrum, int consistent,
+              const double *__restrict__ modes, int n_modes, double *__restrict__ tab64,
+              double *__restrict__ power, int kb, FactorOut o)
+{
+    const int lane = threadIdx.x, part = __builtin_amdgcn_readfirstlane(threadIdx.y), parts = blockDim.y;
+    const int64_t gq = (int64_t)blockIdx.x * 64 + lane;
+    const bool valid = gq < n_tot;
+    const int q = valid ? (int)gq : n_tot - 1;
+    const int64_t q4 = gq & ~int64_t(3);   // the four lanes' first node, and how many of them there are
+    const int n4 = (int)max(int64_t(0), min(int64_t(4), n_tot - q4));
+    const double X = pos64[4 * (size_t)q], Y = pos64[4 * (size_t)q + 1], Z = pos64[4 * (size_t)q + 2];
+    const BeamShape shape = beam_shape(beam, X, Y, w0, pol, modes, n_modes);
+    // propagation phase e^{-ikz} fused with the node phase e^{ik|r_s|}: e^{ik(|r_s| - z)},
+    // formed in double-double so that no ~1e6 rad phase is ever rounded to double
+    const dd path = dd_sub_d(dd_norm3(X, Y, Z), Z);
+    const bool rim = q >= n_surf;
+    const double W = wgt[q];
+    const double n[3] = {nrm[3 * (size_t)q], nrm[3 * (size_t)q + 1], nrm[3 * (size_t)q + 2]};
+    double t[3] = {0.0, 0.0, 0.0};
+    if (rim)
+        for (int c = 0; c < 3; ++c) t[c] = tan[3 * (size_t)(q - n_surf) + c];
+    const double flux_w = valid && !rim ? n[2] * W : 0.0;
+    auto record = [&](int kk, double *v, bool store_power) {
+        const double k = kv[kk];
+        const c64 amp = spectrum ? c64{spectrum[2 * kk], spectrum[2 * kk + 1]} : c64{1.0, 0.0};
+        c64 E[3], B[3];
+        beam_at(beam, shape, k, w0, amp, consistent, E, B);
+        double sp, cp;
+        sincos(phase_mod_2pi(k, path), &sp, &cp);
+        write_record(v, rim, k, W, n, t, E, B, {cp, sp});
+        if (store_power) {
+            const double sum = wave_sum_63(flux_w * flux_minus_z(E, B));
+            if (lane == 63) power[(size_t)kk * gridDim.x + blockIdx.x] = sum;
+        }
+    };
+    if constexpr (!TEST) {
+        for (int kk = part; kk < n_k; kk += parts) {
+            double v[8];
+            record(kk, v, true);
+            store_records(tab64 + ((int64_t)kk * n_tot + q4) * 8, n4, v);
+        }
+        return;
+    } else {
+        __shared__ double sh_best[BEAM_PARTS][64], sh_charge[BEAM_PARTS][64], sh_r2[BEAM_PARTS][64], sh_t2[BEAM_PARTS][64];
+        __shared__ int sh_kb[BEAM_PARTS][64], sh_nan[BEAM_PARTS][64];
+        for (int pass = 0;; ++pass) {
+            double v[8];
+            record(kb, v, false);
+            const double mkb = current2(v);
+            const FactorDir dir = factor_dir(v, mkb, kv[kb]);
+            double best = 0.0, bestr = 0.0, r2max = 0.0, t2max = 0.0;
+            int kbest = 0, nan = 0;
+            for (int kk = part; kk < n_k; kk += parts) {
+                record(kk, v, true);
+                const int64_t rec = (int64_t)kk * n_tot + q;
+                store_records(tab64 + ((int64_t)kk * n_tot + q4) * 8, n4, v);
+                const double k = kv[kk], m = current2(v);
+                if (m > best) {
+                    best = m;
+                    kbest = kk;
+                }
+                bestr = fmax(bestr, v[6] * v[6] + v[7] * v[7] + m / (k * k));
+                double r2, t2;
+                const c64 s = factor_record(v, k, dir, r2, t2);
+                r2max = fmax(r2max, r2);
+                t2max = fmax(t2max, t2);
+                nan |= (r2 != r2 ? 3 : 0) | (t2 != t2 ? 12 : 0);
+                if (valid) factor_store(o, rec, v, s);
+            }
+            sh_best[part][lane] = best;
+            sh_charge[part][lane] = bestr;
+            sh_r2[part][lane] = r2max;
+            sh_t2[part][lane] = t2max;
+            sh_kb[part][lane] = kbest;
+            sh_nan[part][lane] = nan;
+            __syncthreads();
+            best = bestr = r2max = t2max = 0.0;
+            kbest = nan = 0;
+            for (int p = 0; p < parts; ++p) {
+                if (sh_best[p][lane] > best) {
+                    best = sh_best[p][lane];
+                    kbest = sh_kb[p][lane];
+                }
+                bestr = fmax(bestr, sh_charge[p][lane]);
+                r2max = fmax(r2max, sh_r2[p][lane]);
+                t2max = fmax(t2max, sh_t2[p][lane]);
+                nan |= sh_nan[p][lane];
+            }
+            const bool again = pass == 0 && mkb < 0.25 * best;
+            if (__syncthreads_or(again)) {
+                if (again) kb = kbest;
+                continue;
+            }
+            if (part == 0 && valid) {
+                unsigned int flags = (unsigned int)nan;
+                if (r2max > o.tol32 * o.tol32 * best) flags |= 1u;
+                if (r2max > o.tol64 * o.tol64 * best) flags |= 2u;
+                if (t2max > o.tol32 * o.tol32 * bestr) flags |= 4u;
+                if (t2max > o.tol64 * o.tol64 * bestr) flags |= 8u;
+                factor_store_node(o, gq, dir);
+                if (flags) atomicOr(o.bad, flags);
+            }
+            return;
         }
     }
-    if (posf) {
-        float *pr = posf + gq * 8;
-        for (int c = 0; c < 4; ++c) pr[c] = pos32[gq * 4 + c];
-        for (int c = 0; c < 3; ++c) pr[4 + c] = (float)u[c];
-        pr[7] = pos64[gq * 4 + 3] > 0.0 ? (float)(0.5 / pos64[gq * 4 + 3]) : 0.0f;   // 1 / (2 |r_s|)
-        betaf[gq] = (float)beta;
-    }
-    if (posf64) {
-        double *pr = posf64 + gq * 8;
-        for (int c = 0; c < 4; ++c) pr[c] = pos64[gq * 4 + c];
-        for (int c = 0; c < 3; ++c) pr[4 + c] = u[c];
-        pr[7] = pos64[gq * 4 + 3] > 0.0 ? 0.5 / pos64[gq * 4 + 3] : 0.0;   // 1 / (2 |r_s|)
-        betaf64[gq] = beta;
-    }
-    if (flags) atomicOr(bad, flags);
 }
 
 // The polar records of the tied charge again from the FP32 factored records, after these were
@@ -775,13 +951,31 @@ hipError_t launch_tables_from_fields(hipStream_t st, int n_k, int n_surf, int n_
     return hipGetLastError();
 }
 
-hipError_t launch_tables_gaussian(hipStream_t st, int n_k, int n_surf, int n_tot, const double *k,
-                                  const double *pos64, const double *nrm, const double *wgt, const double *tan,
-                                  int beam, double w0, double pol, const double *spectrum, int consistent,
-                                  const double *modes, int n_modes, double *tab64)
+hipError_t launch_tables_beam(hipStream_t st, int n_k, int n_surf, int n_tot, const double *k, const double *pos64,
+                              const double *nrm, const double *wgt, const double *tan, int beam, double w0, double pol,
+                              const double *spectrum, int consistent, const double *modes, int n_modes, double *tab64,
+                              int kb, const FactorOut *out, double *part, double *P)
 {
-    hipLaunchKernelGGL(k_tables_gaussian, dim3(nblocks((int64_t)n_k * n_tot, 256)), dim3(256), 0, st, n_k, n_surf,
-                       n_tot, k, pos64, nrm, wgt, tan, beam, w0, pol, spectrum, consistent, modes, n_modes, tab64);
+    // shares of the frequencies: until there are eight waves per SIMD
+    const unsigned int nb = nblocks(n_tot, 64);
+    int parts = 1;
+    while (parts < BEAM_PARTS && 2 * parts <= n_k && (int64_t)nb * parts < 8192) parts *= 2;
+#define SC_BEAM(BM, TEST)                                                                                          \
+    hipLaunchKernelGGL((k_tables_beam<BM, TEST>), dim3(nb), dim3(64, parts), 0, st, n_k, n_surf, n_tot, k, pos64, nrm, \
+                       wgt, tan, w0, pol, spectrum, consistent, modes, n_modes, tab64, part, kb,       \
+                       out ? *out : FactorOut{})
+    switch (beam + (out ? 4 : 0)) {
+    case 0: SC_BEAM(0, false); break;
+    case 1: SC_BEAM(1, false); break;
+    case 2: SC_BEAM(2, false); break;
+    case 3: SC_BEAM(3, false); break;
+    case 4: SC_BEAM(0, true); break;
+    case 5: SC_BEAM(1, true); break;
+    case 6: SC_BEAM(2, true); break;
+    default: SC_BEAM(3, true); break;
+    }
+#undef SC_BEAM
+    hipLaunchKernelGGL(k_power_finish, dim3(n_k), dim3(256), 0, st, (int)nb, part, P);
     return hipGetLastError();
 }
 
@@ -790,22 +984,11 @@ hipError_t launch_power_fields(hipStream_t st, int n_k, int n_surf, int n_tot, c
 {
     hipLaunchKernelGGL(k_power_fields, dim3(POWER_BLOCKS, n_k), dim3(256), 0, st, n_surf, n_tot, nrm, wgt, E, B,
                        part);
-    hipLaunchKernelGGL(k_power_finish, dim3(nblocks(n_k, 256)), dim3(256), 0, st, n_k, part, P);
+    hipLaunchKernelGGL(k_power_finish, dim3(n_k), dim3(256), 0, st, POWER_BLOCKS, part, P);
     return hipGetLastError();
 }
 
-hipError_t launch_power_gaussian(hipStream_t st, int n_k, int n_surf, const double *k, const double *pos64,
-                                 const double *nrm, const double *wgt, int beam, double w0, double pol,
-                                 const double *spectrum, int consistent, const double *modes, int n_modes,
-                                 double *part, double *P)
-{
-    hipLaunchKernelGGL(k_power_gaussian, dim3(POWER_BLOCKS, n_k), dim3(256), 0, st, n_surf, k, pos64, nrm, wgt, beam,
-                       w0, pol, spectrum, consistent, modes, n_modes, part);
-    hipLaunchKernelGGL(k_power_finish, dim3(nblocks(n_k, 256)), dim3(256), 0, st, n_k, part, P);
-    return hipGetLastError();
-}
-
-int power_partial_count(int n_k) { return POWER_BLOCKS * n_k; }
+int64_t power_partial_count(int n_k, int n_tot) { return (int64_t)n_k * std::max<unsigned int>(POWER_BLOCKS, nblocks(n_tot, 64)); }
 
 hipError_t launch_tables_scale(hipStream_t st, int n_k, int n_tot, int n_cplx, const double *fac, double *tab64,
                                float *tab32)
@@ -816,12 +999,9 @@ hipError_t launch_tables_scale(hipStream_t st, int n_k, int n_tot, int n_cplx, c
 }
 
 hipError_t launch_tables_factor(hipStream_t st, int n_k, int n_tot, const double *k, const double *tab64,
-                                const float *pos32, const double *pos64, double tol32, double tol64, float *tabf,
-                                float *posf, float *betaf, float *tabp, double *tabf64, double *posf64,
-                                double *betaf64, unsigned int *bad)
+                                const FactorOut &out)
 {
-    hipLaunchKernelGGL(k_tables_factor, dim3(nblocks(n_tot, 256)), dim3(256), 0, st, n_k, n_tot, k, tab64, pos32,
-                       pos64, tol32, tol64, tabf, posf, betaf, tabp, tabf64, posf64, betaf64, bad);
+    hipLaunchKernelGGL(k_tables_factor, dim3(nblocks(n_tot, 256)), dim3(256), 0, st, n_k, n_tot, k, tab64, out);
     return hipGetLastError();
 }
 
