@@ -1252,7 +1252,7 @@ static CompactLayout compact_layout(const sc_prob *p, sc_precision prec, const C
     c.scale = mm ? up(mm_table_bytes((int)n_k, (int)n_c, plan.form)) : tab_bytes;
     c.pos = c.scale + (mm ? up(sizeof(float) * 16 * n_k) : 0);
     c.hinv = c.pos + up(rs * 4 * (n_c + 7));
-    c.bytes = c.hinv + up(rs * (n_c + 7));
+    c.bytes = c.hinv + up(rs * (mm ? 4 : 1) * (n_c + 7));
     c.wrad = 0;
     c.wang = up(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
     c.raw = c.wang + up(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
@@ -1542,7 +1542,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     };
     double *wrad = (double *)take(sizeof(double) * (size_t)compact_radial_doubles(plan, p->n_r));
     double *wang = (double *)take(sizeof(double) * (size_t)compact_angular_doubles(plan, p->n_phi));
-    void *cpos = take(rs * 4 * (size_t)(plan.n_c + 7)), *chinv = take(rs * (size_t)(plan.n_c + 7));
+    void *cpos = take(rs * 4 * (size_t)(plan.n_c + 7)), *chinv = take(rs * (f64 ? 1 : 4) * (size_t)(plan.n_c + 7));
     const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
     // compacted records, and in the FP32 form their packed rows and scales
     const size_t rec_bytes = rs * 8 * (size_t)plan.n_c;

@@ -28,7 +28,7 @@ constexpr int GEOM_PHI = 64;
 __global__ void __launch_bounds__(64)
 k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double *__restrict__ r,
                    double *__restrict__ wrad, double *__restrict__ wang, double *__restrict__ pos64,
-                   double *__restrict__ hinv64, float *__restrict__ pos32, float *__restrict__ hinv32)
+                   double *__restrict__ hinv64, float *__restrict__ pos32, float *__restrict__ dir32)
 {
     const int lane = threadIdx.x, rows = plan.rows, rp = (rows + 15) / 16 * 16;
     const int n_i = (n_r + 4) / 4 * 4, n_g = (n_phi + GEOM_PHI - 1) / GEOM_PHI, n_a = plan.poff[rows] / 16 * n_g;
@@ -98,7 +98,10 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
         if (pos32) pos32[4 * (size_t)q + k] = (float)v[k];
     }
     if (hinv64) hinv64[q] = 0.5 / rs;
-    if (hinv32) hinv32[q] = (float)(0.5 / rs);
+    if (dir32) {
+        for (int k = 0; k < 3; ++k) dir32[4 * (size_t)q + k] = (float)(v[k] / rs);
+        dir32[4 * (size_t)q + 3] = (float)(0.5 / rs);
+    }
 }
 
 // One record (J~.x, J~.y, J~.z, rho~) from the tables an evaluation reads, general or factored (J~ = u s),

@@ -19,8 +19,8 @@
 // columns that r' multiplies, and the term with delta / |r_s|, are hi alone where that factor is below
 // 1/100; FORM_GH_FAR gives those columns their lo part by a third product.  Table columns are scaled by
 // powers of two to 2^12 at most, and the kernel values to about 2^6, so that no lo part falls below
-// FP16's smallest number.  Against 64 bits the sums are as exact as the plain FP32 form's (broadband
-// 4.3e-7, plain 4.2e-7).
+// FP16's smallest number.  Near the focus the error against 64 bits is about half the plain FP32
+// form's (0.1 m mirror, points within 4 wavelengths: 1.8e-7, plain 3.3e-7); elsewhere the same.
 //
 // One step is 4 nodes (near: 8): lane l holds point l % 32 and its half's nodes as B's 8 consecutive
 // values (Gr, Gi, Hr, Hi of two nodes; near: Vr, Vi of four), and row l % 32 of A, 16 B loaded as they lie.
@@ -102,20 +102,22 @@ __device__ __forceinline__ void store_mm(cjob *job, int chunk, int pt, int kb, c
     }
 }
 
-// delta = |R| - |r_s| and s / R, by series near the focus as in the plain form: p = (x, y, z, h), h = 1 / 2|r_s|,
-// for the series, else (x, y, z, |r_s|).
+// delta = |R| - |r_s| and s / R, by series near the focus as in the plain form: p = (r_s / |r_s|, h),
+// h = 1 / 2|r_s|, for the series, else (x, y, z, |r_s|).  (With the direction rounded once from FP64 the
+// phase takes two roundings less than from r_s and h, of which h's is common to a row of nodes: error
+// against 64 bits 1.8e-7 for 3.4e-7.)
 template <bool SER>
 __device__ __forceinline__ void geom_mm(const v4f p, const v4f o, float s, float &delta, float &ph)
 {
     const float dot = __fmaf_rn(p.x, o.x, __fmaf_rn(p.y, o.y, p.z * o.z));
-    const float num = __fmaf_rn(-2.0f, dot, o.w);
     if constexpr (SER) {
         const float h = p.w;
-        const float d1 = num * h, x = d1 * h;
-        delta = d1 * __fmaf_rn(x, __fmaf_rn(2.0f, x, -1.0f), 1.0f);
+        const float d1 = __fmaf_rn(o.w, h, -dot), x = d1 * h;
+        delta = __fmaf_rn(d1 * x, __fmaf_rn(2.0f, x, -1.0f), d1);
         const float h2 = h + h, y = delta * h2;
         ph = (h2 * s) * __fmaf_rn(y, y - 1.0f, 1.0f);
     } else {
+        const float num = __fmaf_rn(-2.0f, dot, o.w);
         const float dx = p.x - o.x, dy = p.y - o.y, dz = p.z - o.z;
         const float R2 = __fmaf_rn(dx, dx, __fmaf_rn(dy, dy, dz * dz));
         const float rinv = __builtin_amdgcn_rsqf(R2);
@@ -163,9 +165,7 @@ __device__ __forceinline__ void tile_mm(cjob *job, int chunk, int pg, int kb, fl
     __shared__ v4f node[MM_CHUNK_MAX];
     __syncthreads();
     for (int i = threadIdx.x; i < (s1 - s0) * NODES; i += 256) {
-        v4f p = ((const v4f *)job->pos)[s0 * NODES + i];
-        if constexpr (SER) p.w = ((const float *)job->hinv)[s0 * NODES + i];
-        node[i] = p;
+        node[i] = ((const v4f *)(SER ? job->hinv : job->pos))[s0 * NODES + i];
     }
     __syncthreads();
     v16f acc[F];
@@ -364,18 +364,54 @@ k_mm_scales(int n_c, int form, const double *__restrict__ kv, double s, const fl
 
 // mtab[k][row][step][lane][8] halves, row 0: lane's row l % 32 of the step's nodes of its half (l / 32), for each
 // node the factors of the kernel values (Gr, Gi, Hr, Hi; near Vr, Vi).  Row 1, in FORM_GH_FAR: the lo
-// parts of the columns that r' multiplies; in FORM_NEAR: the factors of V delta / |r_s| in E.  One wave per step.
+// parts of the columns that r' multiplies; in FORM_NEAR: the factors of V delta / |r_s|, those of E's G J~
+// and, in E and B, i (k - k32) |r_s| times row 0's, the first order of the phase (k - k32) delta that
+// the quadrature's FP32 wavenumber k32 leaves out.
+// One workgroup per PACK_STEPS steps, their nodes' columns formed once each and kept in LDS
+// (formed by every lane for its own row: 67 us at 128 frequencies and 4 000 nodes, now 19).
+constexpr int PACK_STEPS = 16;
 template <int FORM>
 __global__ void __launch_bounds__(256)
 k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
           const v4f *__restrict__ pos, const float *__restrict__ mscale, h8 *__restrict__ mtab)
 {
     constexpr int NODES = form_nodes(FORM), ROWS = form_rows(FORM), Q = NODES / 2, W = 8 / Q;   // values per node
-    const int steps = (n_c + NODES - 1) / NODES, st = blockIdx.x * 4 + (threadIdx.x >> 6), kk = blockIdx.y;
-    if (st >= steps) return;
+    constexpr int ALL = PACK_STEPS * NODES;
+    static_assert(ALL <= 256, "one thread per node");
+    const int steps = (n_c + NODES - 1) / NODES, st0 = blockIdx.x * PACK_STEPS, kk = blockIdx.y;
+    // per node and column: factors of H or V, then of G or V delta / |r_s|, scaled
+    __shared__ float colh[20][ALL + 1], colg[12][ALL + 1];
+    if (threadIdx.x < ALL) {
+        const int n = st0 * NODES + threadIdx.x;
+        double g[12] = {}, h[20] = {};   // past the last node: zero
+        if (n < n_c) {
+            const v4f p = pos[n];
+            const double k = kv[kk];
+            mm_columns(FORM, ctab + ((size_t)kk * n_c + n) * 8, p, k, s, g, h);
+            if (FORM == FORM_NEAR) {
+                const double turns = k * INV_TWO_PI, x = (turns - (double)(float)turns) * TWO_PI_1 * (double)p.w;
+                const double y = fabs(x) <= (double)NEAR_SCALE ? x : 0.0;   // (keeps to FP16's range)
+                for (int c = 0; c < 6; ++c) {
+                    const int hc = c < 3 ? c : c + 1;   // E, then B past the sum of rho~
+                    g[2 * c] -= y * h[2 * hc + 1];
+                    g[2 * c + 1] += y * h[2 * hc];
+                }
+            }
+        }
+        for (int c = 0; c < 10; ++c) {
+            const double inv = 1.0 / ((double)mscale[16 * (size_t)kk + c] * KERNEL_SCALE);   // a power of two
+            const int gc = c < 3 ? c : c - 1;
+            for (int z = 0; z < 2; ++z) {
+                colh[2 * c + z][threadIdx.x] = (float)(h[2 * c + z] * inv);
+                if (c != 3 && gc < 6) colg[2 * gc + z][threadIdx.x] = (float)(g[2 * gc + z] * inv);
+            }
+        }
+    }
+    __syncthreads();
     const int lane = threadIdx.x & 63, r = lane & 31, rh = (r >> 2) & 1, v = (r & 3) + 4 * (r >> 3);
     // row r holds value v of half rh (see store_mm): its column, part (re, im) and whether it is the lo half
-    int col, part = v & 1, lo = 0;
+    int col, lo = 0;
+    const int part = v & 1;
     if (v < 12) {
         lo = v >= 6;
         col = (rh ? 4 : 0) + (v % 6) / 2;
@@ -384,37 +420,31 @@ k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restr
     } else {
         col = v < 14 ? 7 : 8;
     }
-    h8 out = {}, out2 = {};
-    for (int q = 0; q < Q; ++q) {
-        const int n = NODES * st + Q * (lane >> 5) + q;
-        if (n >= n_c) continue;   // past the last node: zero
-        double g[6], h[20];
-        mm_columns(FORM, ctab + ((size_t)kk * n_c + n) * 8, pos[n], kv[kk], s, g, h);
-        const double inv = 1.0 / ((double)mscale[16 * (size_t)kk + col] * KERNEL_SCALE);   // a power of two
-        double gr = 0.0, gi = 0.0, hr = 0.0, hi = 0.0;   // of this column
-        for (int c = 0; c < 10; ++c)
-            if (c == col) {
-                hr = h[2 * c] * inv;
-                hi = h[2 * c + 1] * inv;
-                if (c < 3) {
-                    gr = g[2 * c] * inv;
-                    gi = g[2 * c + 1] * inv;
-                }
+    const int gcol = v < 12 ? 3 * rh + (v % 6) / 2 : -1;   // of E and B
+    for (int j = threadIdx.x >> 6; j < PACK_STEPS && st0 + j < steps; j += 4) {
+        h8 out = {}, out2 = {};
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            const int i = NODES * j + Q * (lane >> 5) + q;
+            const float hr = colh[2 * col][i], hi = colh[2 * col + 1][i];
+            const float gr = gcol < 0 ? 0.0f : colg[2 * max(gcol, 0)][i];
+            const float gi = gcol < 0 ? 0.0f : colg[2 * max(gcol, 0) + 1][i];
+            // (a + ib)(Vr + iVi): re = a Vr - b Vi, im = b Vr + a Vi
+            const float wg[2] = {part ? gi : gr, part ? gr : -gi};
+            const float wh[2] = {part ? hi : hr, part ? hr : -hi};
+#pragma unroll
+            for (int e = 0; e < W; ++e) {
+                const float w = W == 2 ? wh[e] : e < 2 ? wg[e] : wh[e - 2];
+                const _Float16 a = (_Float16)w, b = (_Float16)(w - (float)a);
+                out[W * q + e] = lo ? b : a;
+                if (FORM == FORM_GH_FAR && v >= 12) out2[W * q + e] = b;
+                if (FORM == FORM_NEAR && v < 6) out2[W * q + e] = (_Float16)(wg[e] / NEAR_SCALE);
             }
-        // (a + ib)(Vr + iVi): re = a Vr - b Vi, im = b Vr + a Vi
-        const float wg[2] = {(float)(part ? gi : gr), (float)(part ? gr : -gi)};
-        const float wh[2] = {(float)(part ? hi : hr), (float)(part ? hr : -hi)};
-        for (int e = 0; e < W; ++e) {
-            const float w = W == 2 ? wh[e] : e < 2 ? wg[e] : wh[e - 2];
-            const _Float16 a = (_Float16)w, b = (_Float16)(w - (float)a);
-            out[W * q + e] = lo ? b : a;
-            if (FORM == FORM_GH_FAR && v >= 12) out2[W * q + e] = b;
-            if (FORM == FORM_NEAR && rh == 0 && v < 6) out2[W * q + e] = (_Float16)(wg[e] / NEAR_SCALE);
         }
+        h8 *dst = mtab + ((size_t)kk * ROWS * steps + st0 + j) * 64 + lane;
+        dst[0] = out;
+        if (ROWS == 2) dst[(size_t)steps * 64] = out2;
     }
-    h8 *dst = mtab + ((size_t)kk * ROWS * steps + st) * 64 + lane;
-    dst[0] = out;
-    if (ROWS == 2) dst[(size_t)steps * 64] = out2;
 }
 
 // ================================================================== launchers
@@ -423,7 +453,7 @@ hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const do
                             const float *pos, float *mscale, void *mtab)
 {
     const int steps = (n_c + form_nodes(form) - 1) / form_nodes(form);
-    const dim3 g((steps + 3) / 4, n_k), b(256);
+    const dim3 g((steps + PACK_STEPS - 1) / PACK_STEPS, n_k), b(256);
     hipLaunchKernelGGL(k_mm_scales, dim3(n_k), dim3(1024), 0, st, n_c, form, k, scale, ctab, (const v4f *)pos, mscale);
 #define SC_MM_PACK(FORM)                                                                              \
     hipLaunchKernelGGL((k_mm_pack<FORM>), g, b, 0, st, n_c, k, scale, ctab, (const v4f *)pos, mscale, (h8 *)mtab)

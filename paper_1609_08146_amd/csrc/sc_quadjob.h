@@ -14,7 +14,7 @@ struct QuadJob {
     const void *tab;      // [n_k][n_tot][8] real (float or double); factored: [n_k][n_tot][4] real
     const void *pos;      // [n_tot][4] real; factored: [n_tot][8] real
     const void *obs;      // [n_obs_pad][4] real
-    const void *hinv;     // [n_tot] 1 / (2|r_s|) real (general layout, series_delta)
+    const void *hinv;     // [n_tot] 1 / (2|r_s|) real (general layout, series_delta); mm: (r_s / |r_s|, 1 / (2|r_s|))
     const void *beta;     // [n_tot] real (factored layout with the tied charge): rho_t = -i beta s / k
     const void *tabp;     // [n_k][n_tot][2] float (FP32 split form, tied charge): (|s|, arg(s) / 2 pi)
     const void *mtab;     // mm: packed table rows (sc_quad_mm.hip)
