@@ -9,9 +9,16 @@
 //   E(o) = sum_m K(o, m) c~_m,   c~_m = sum_n L_m(n) c_n:
 // the same sum over every record, with the points' part taken over far fewer nodes.  On the
 // paraboloid r = 2 f tan(theta / 2), |r_s| = f / cos^2(theta / 2), the nodes are a tensor grid in
-// (r, phi) with equispaced phi, so L is a product: Chebyshev interpolation in theta from `rows`
-// points of [0, theta_max] to the n_r + 1 radii (the rim is one of them), and on each row
-// trigonometric interpolation from cols[m] equispaced phi to the n_phi.
+// (r, phi) with equispaced phi, so L is a product: Chebyshev interpolation in theta to the n_r + 1 radii
+// (the rim is one of them), and on each row trigonometric interpolation from cols[m] equispaced phi to
+// the n_phi.  A meridian goes on through the vertex, K(-theta, phi) = K(theta, phi + pi), so theta is
+// interpolated from 2 x `rows` points of [-theta_max, theta_max], of which half are the other half turned
+// by pi.  They are Chebyshev points y of theta = theta_max asin(alpha y) / asin(alpha), and the
+// interpolation is polynomial in y: Chebyshev points of theta itself crowd at both ends, where
+// the kernel oscillates no faster than elsewhere and a row at the rim has the most columns; alpha spreads
+// them, at the price of branch points at y = +-1 / alpha.  On a mirror of theta_max 41 degrees and points
+// within 6.9 wavelengths, to 3e-10: 41 rows and 2747 nodes from points of [0, theta_max], 33 and 2631 with
+// the continuation, 27 and 2035 with alpha = 0.9 too (to 1e-15: 4219, 3795 and 3012 nodes).
 #pragma once
 
 #include <stdint.h>
@@ -30,29 +37,43 @@ constexpr int form_rows(int form) { return form == FORM_GH ? 1 : 2; }
 constexpr int MM_CHUNK_MAX = 256;   // nodes per chunk of the FP32 sum
 
 struct CompactPlan {
-    int rows;                               // interpolation rows in theta
+    int rows;                               // interpolation rows in theta > 0
+    int fold;                               // n_phi is even: phi + pi is a grid point too
     int n_c;                                // compacted nodes in all (sum of cols)
     int split;                              // parts the sum over the radii is cut into (partial rows)
     int chunk;                              // compacted nodes per split-K chunk of the quadrature
     int form;                               // CompactForm of the FP32 sum
     double scale;                           // power of two near f
     double theta_max;                       // 2 atan(r_max / 2f)
-    uint16_t cols[COMPACT_MAX_ROWS];        // phi per row: odd, or n_phi (taken as they are)
+    double alpha, beta;                     // of the rows' spread; beta = asin(alpha)
+    uint16_t cols[COMPACT_MAX_ROWS];        // phi per row: odd, or the grid's own and those + pi
     int32_t off[COMPACT_MAX_ROWS + 1];      // first compacted node of each row
     int32_t poff[COMPACT_MAX_ROWS + 1];     // the same with every row's columns rounded up to 16
 };
 
 // Working memory of the two interpolations (doubles): the radial weights [n_r + 1 rounded up to
-// 4][rows rounded up to 16], the angular weights of every row [n_phi][cols rounded up to 16], and
-// the partial rows of one frequency [split][rows][n_phi][8].  The planner keeps their sum below
+// 4][compact_radial_stride], the angular weights of every row [n_phi][cols rounded up to 16], and
+// the partial rows of one frequency [split][rows][n_phi][8]; with an odd n_phi, where theta < 0 needs
+// weights and partial rows of its own, [2 n_phi] and [2 rows].  The planner keeps their sum below
 // COMPACT_WORK_MAX bytes.
 constexpr int64_t COMPACT_WORK_MAX = 47 << 20;
+// Even and odd part of L_m in theta, each rounded up to 16 rows; with an odd n_phi L_m and L_-m, together.
+constexpr int compact_radial_stride(const CompactPlan &p)
+{
+    return p.fold ? 2 * ((p.rows + 15) / 16 * 16) : (2 * p.rows + 15) / 16 * 16;
+}
 inline int64_t compact_radial_doubles(const CompactPlan &p, int n_r)
 {
-    return (int64_t)((n_r + 4) / 4 * 4) * ((p.rows + 15) / 16 * 16);
+    return (int64_t)((n_r + 4) / 4 * 4) * compact_radial_stride(p);
 }
-inline int64_t compact_angular_doubles(const CompactPlan &p, int n_phi) { return (int64_t)p.poff[p.rows] * n_phi; }
-inline int64_t compact_rows_doubles(const CompactPlan &p, int n_phi) { return (int64_t)p.split * p.rows * n_phi * 8; }
+inline int64_t compact_angular_doubles(const CompactPlan &p, int n_phi)
+{
+    return (int64_t)p.poff[p.rows] * n_phi * (p.fold ? 1 : 2);
+}
+inline int64_t compact_rows_doubles(const CompactPlan &p, int n_phi)
+{
+    return (int64_t)p.split * p.rows * (p.fold ? 1 : 2) * n_phi * 8;
+}
 
 // What the plan depends on.
 struct CompactInput {

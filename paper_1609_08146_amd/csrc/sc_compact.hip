@@ -2,8 +2,11 @@
 // instructions: c~ = (trigonometric interpolation)^T (Chebyshev interpolation)^T c per frequency.
 //
 //  k_compact_geometry   interpolation weights and the compacted nodes' records
-//  k_compact_rows       T[m][phi] = sum_i L_m(theta_i) c[i][phi]        (contraction over the radii)
+//  k_compact_rows       T[m][phi] = sum_i L_m(theta_i) c[i][phi] + L_-m(theta_i) c[i][phi + pi]
+//                                                                       (contraction over the radii)
 //  k_compact_cols       c~[m][p]  = sum_j D_m(phi_j - psi_p) T[m][phi_j] (contraction over phi)
+// With an odd n_phi phi + pi is no grid point, and T keeps its two terms apart (rows m and rows + m), which
+// k_compact_cols joins with weights of their own.
 //
 // A record is four complex numbers (J~, rho~), 8 reals, so both steps are real matrix products with
 // the 8 reals among their columns; v_mfma_f64_16x16x4 takes A[16][4] with lane l holding row l % 16,
@@ -30,54 +33,63 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
                    double *__restrict__ wrad, double *__restrict__ wang, double *__restrict__ pos64,
                    double *__restrict__ hinv64, float *__restrict__ pos32, float *__restrict__ dir32)
 {
-    const int lane = threadIdx.x, rows = plan.rows, rp = (rows + 15) / 16 * 16;
-    const int n_i = (n_r + 4) / 4 * 4, n_g = (n_phi + GEOM_PHI - 1) / GEOM_PHI, n_a = plan.poff[rows] / 16 * n_g;
+    const int lane = threadIdx.x, rows = plan.rows, stride = compact_radial_stride(plan);
+    const int n_j = plan.fold ? n_phi : 2 * n_phi;
+    const int n_i = (n_r + 4) / 4 * 4, n_g = (n_j + GEOM_PHI - 1) / GEOM_PHI, n_a = plan.poff[rows] / 16 * n_g;
     int b = blockIdx.x;
     if (b < n_i) {
-        // barycentric weights of the Chebyshev points: w_j = (-1)^j sin((2j + 1) pi / 2N)
-        const double x = b <= n_r ? 4.0 * atan(r[b] / (2.0 * f)) / plan.theta_max - 1.0 : 0.0;
+        // barycentric weights of the 2 rows Chebyshev points: w_j = (-1)^j sin((2j + 1) pi / 4 rows), and those
+        // of -x_j are the negative ones
+        const double x = b <= n_r ? sin(plan.beta * (2.0 * atan(r[b] / (2.0 * f)) / plan.theta_max)) / plan.alpha : 0.0;
         double sum = 0.0;
         int hit = -1;
         for (int j = lane; j < rows; j += 64) {
-            const double d = x - cheb_point(j, rows);
+            const double xj = cheb_point(j, 2 * rows), d = (x - xj) * (x + xj);
             if (d == 0.0) hit = j;
-            const double w = sinpi((double)(2 * j + 1) / (double)(2 * rows));
-            sum += (d == 0.0 ? 0.0 : ((j & 1) ? -w : w) / d);
+            const double w = sinpi((double)(2 * j + 1) / (double)(4 * rows));
+            sum += (d == 0.0 ? 0.0 : ((j & 1) ? -w : w) * xj / d);
         }
         for (int o = 32; o > 0; o >>= 1) {
             sum += __shfl_xor(sum, o);
             hit = max(hit, __shfl_xor(hit, o));
         }
-        for (int j = lane; j < rp; j += 64) {
+        sum *= 2.0;
+        double *out = wrad + (size_t)b * stride;
+        for (int j = lane; j < stride; j += 64) {
+            // row, and whether this is the odd part (L_-m)
+            const int half = plan.fold ? stride / 2 : rows, odd = j >= half, m = odd ? j - half : j;
             double l = 0.0;
-            if (b <= n_r && j < rows) {
-                const double d = x - cheb_point(j, rows);
-                const double w = sinpi((double)(2 * j + 1) / (double)(2 * rows));
-                l = hit >= 0 ? (j == hit ? 1.0 : 0.0) : ((j & 1) ? -w : w) / d / sum;
+            if (b <= n_r && m < rows) {
+                const double xj = cheb_point(m, 2 * rows), d = (x - xj) * (x + xj);
+                const double w = sinpi((double)(2 * m + 1) / (double)(4 * rows)), c = ((m & 1) ? -w : w) / sum;
+                if (plan.fold) l = hit >= 0 ? (m == hit ? 0.5 : 0.0) : c * (odd ? x : xj) / d;
+                else if (hit >= 0) l = m == hit && !odd ? 1.0 : 0.0;
+                else l = odd ? -c / (x + xj) : c / (x - xj);
             }
-            wrad[(size_t)b * rp + j] = l;
+            out[j] = l;
         }
         return;
     }
     b -= n_i;
     if (b < n_a) {
-        const int pt = b / n_g, j0 = (b - pt * n_g) * GEOM_PHI, j1 = min(j0 + GEOM_PHI, n_phi);
+        const int pt = b / n_g, j0 = (b - pt * n_g) * GEOM_PHI, j1 = min(j0 + GEOM_PHI, n_j);
         int m = 0;
         while (plan.poff[m + 1] <= 16 * pt) ++m;
         const int P = plan.cols[m], p0 = 16 * pt - plan.poff[m], pp = (P + 15) / 16 * 16;
-        double *w = wang + (size_t)plan.poff[m] * n_phi;
+        double *w = wang + (size_t)plan.poff[m] * n_j;
         const int p = p0 + (lane & 15);
-        for (int j = j0 + (lane >> 4); j < j1; j += 4) {
+        for (int jj = j0 + (lane >> 4); jj < j1; jj += 4) {
             double d = 0.0;
             if (p < P) {
-                // sin(P x / 2) / (P sin(x / 2)) at x = 2 pi (j / n_phi - p / P), on exact integers
-                const int64_t a = (int64_t)j * P - (int64_t)p * n_phi;
-                if (a == 0) d = 1.0;
-                else if (P < n_phi)
-                    d = sinpi((double)(a % (2 * (int64_t)n_phi)) / (double)n_phi) /
-                        (P * sinpi((double)a / ((double)n_phi * P)));
+                // sin(P x / 2) / (P sin(x / 2)) at x = 2 pi (j / n_phi - p / P), + pi for theta < 0, on exact integers
+                const int j = jj < n_phi ? jj : jj - n_phi;
+                const int64_t np = (int64_t)n_phi * P, a = 2 * ((int64_t)j * P - (int64_t)p * n_phi) + (jj < n_phi ? 0 : np);
+                if (a % (2 * np) == 0) d = 1.0;
+                else if (P < n_j)
+                    d = sinpi((double)(a % (4 * (int64_t)n_phi)) / (double)(2 * n_phi)) /
+                        (P * sinpi((double)a / (2.0 * (double)np)));
             }
-            w[(size_t)j * pp + p] = d;
+            w[(size_t)jj * pp + p] = d;
         }
         return;
     }
@@ -87,7 +99,7 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     const int qn = min(q, plan.n_c - 1);   // up to a multiple of 8 the last node again
     int m = 0;
     while (plan.off[m + 1] <= qn) ++m;
-    const double th = 0.5 * plan.theta_max * (1.0 + cheb_point(m, rows));
+    const double th = plan.theta_max * (asin(plan.alpha * cheb_point(m, 2 * rows)) / plan.beta);
     const double rr = 2.0 * f * tan(0.5 * th);
     double s, c;
     sincospi(2.0 * (double)(qn - plan.off[m]) / (double)plan.cols[m], &s, &c);
@@ -142,50 +154,70 @@ __device__ __forceinline__ void record_doubles(const RawRecord<R> &r, double *v)
 }
 
 // The contraction over the radii: one wave per (frequency, part of the radii, 16 phi, 16 rows), 8
-// accumulators of 16 x 16 (one per real of the record).  Waves are numbered with the row tiles fastest,
-// so that neighbours read the same records, four to a workgroup, and load ROWS_DEPTH steps ahead.  Bound
-// by the FP64 pipe: the matrix instructions take 64 cycles each, and the conversion of a record (14
-// FP64 instructions) runs on the same pipe and is not hidden behind them: 41 rows, 128 frequencies and
-// 160 400 nodes take 0.32 ms, 50 TFLOP/s of matrix work (a large FP64 product on this card: 69).  The
-// waves-per-SIMD request keeps the accumulators in plain registers: without it the compiler moved all 64
-// through accumulation registers in every step (80 of 119 instructions), 0.41 ms.  Two or three row
-// tiles per wave, so that a record is converted once for them, took 0.40 and 0.32 ms.
+// accumulators of 16 x 16 (one per real of the record).  FOLD: with E and O the even and odd part of L_m
+// in theta, L_m c[phi] + L_-m c[phi + pi] = E (c[phi] + c[phi + pi]) + O (c[phi] - c[phi + pi]), and at
+// phi + pi the same with - O: two sets of accumulators over half the phi, half the products of the two
+// terms apart.  Waves are numbered with the row tiles fastest, so that neighbours read the same records,
+// four to a workgroup, and load ROWS_DEPTH steps ahead.  Bound by the FP64 pipe: the matrix
+// instructions take 64 cycles each, and the conversion of a record (14 FP64 instructions) runs on the same
+// pipe and is not hidden behind them: 29 rows, 128 frequencies and 160 400 nodes take 0.27 ms, 41 TFLOP/s
+// of matrix work (a large FP64 product on this card: 69).  The waves-per-SIMD request keeps the accumulators in plain
+// registers: without it the compiler moved them through accumulation registers in every step (80 of 119
+// instructions, 0.41 ms for 0.32 without FOLD at 41 rows).
 constexpr int ROWS_DEPTH = 2;
-template <typename R, bool FACT>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
+template <typename R, bool FACT, bool FOLD>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FOLD ? 2 : 4)))
 k_compact_rows(int k0, int n_r, int n_phi, int rows, int split, int64_t n_waves, const R *__restrict__ tab,
                const R *__restrict__ pos, const double *__restrict__ wrad, double *__restrict__ T)
 {
+    constexpr int S = FOLD ? 2 : 1;
     const int lane = threadIdx.x & 63, kq = lane >> 4, col = lane & 15;
-    const int groups = (n_phi + 15) / 16, rp = (rows + 15) / 16 * 16, tiles = rp / 16;
+    const int phis = FOLD ? n_phi / 2 : n_phi;   // of the waves; FOLD: each with phi + pi
+    const int groups = (phis + 15) / 16, rp = (rows + 15) / 16 * 16, tiles = rp / 16;
     const int64_t wave = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     if (wave >= n_waves) return;
     const int m0 = 16 * (int)(wave % tiles);
     const int64_t rest = wave / tiles;
     const int g = (int)(rest % groups), ks = (int)(rest / groups);
     const int part = ks % split, kk = ks / split;
-    const int phi = 16 * g + col, ph = min(phi, n_phi - 1);
+    const int phi = 16 * g + col, ph = min(phi, phis - 1);
     const int n_i = n_r + 1, steps = (n_i + 3) / 4;
     const int s0 = (int)((int64_t)steps * part / split), s1 = (int)((int64_t)steps * (part + 1) / split);
     const int64_t rec0 = (int64_t)(k0 + kk) * n_i * n_phi;
-    d4 acc[8];
+    d4 acc[S][8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc[c] = d4{0.0, 0.0, 0.0, 0.0};
-    RawRecord<R> raw[ROWS_DEPTH];
-    double wgt[ROWS_DEPTH];
+    for (int e = 0; e < S; ++e)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) acc[e][c] = d4{0.0, 0.0, 0.0, 0.0};
+    RawRecord<R> raw[ROWS_DEPTH][S];
+    double wgt[ROWS_DEPTH][S];
     auto load = [&](int d, int s) {
         const int i = 4 * min(s, s1 - 1) + kq;
         const int64_t node = (int64_t)min(i, n_r) * n_phi + ph;   // past the rim: weight 0
-        wgt[d] = wrad[(size_t)i * rp + m0 + col];
-        raw[d] = load_record<R, FACT>(tab, pos, rec0 + node, node);
+#pragma unroll
+        for (int e = 0; e < S; ++e) {
+            wgt[d][e] = wrad[((size_t)i * S + e) * rp + m0 + col];
+            raw[d][e] = load_record<R, FACT>(tab, pos, rec0 + node + e * phis, node + e * phis);
+        }
     };
     auto step = [&](int d, int s) {
-        double v[8];
-        record_doubles<R, FACT>(raw[d], v);
-        const double a = wgt[d];
+        double v[S][8], a[S];
+#pragma unroll
+        for (int e = 0; e < S; ++e) {
+            record_doubles<R, FACT>(raw[d][e], v[e]);
+            a[e] = wgt[d][e];
+        }
         load(d, s + ROWS_DEPTH);
 #pragma unroll
-        for (int c = 0; c < 8; ++c) acc[c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v[c], acc[c], 0, 0, 0);
+        for (int c = 0; c < 8; ++c) {
+            if constexpr (FOLD) {
+                const double sum = v[0][c] + v[1][c], dif = v[0][c] - v[1][c];
+                acc[0][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], sum, acc[0][c], 0, 0, 0);
+                acc[1][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[1], dif, acc[1][c], 0, 0, 0);
+            } else {
+                acc[0][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[0], v[0][c], acc[0][c], 0, 0, 0);
+            }
+        }
     };
 #pragma unroll
     for (int d = 0; d < ROWS_DEPTH; ++d) load(d, s0 + d);
@@ -197,14 +229,23 @@ k_compact_rows(int k0, int n_r, int n_phi, int rows, int split, int64_t n_waves,
 #pragma unroll
     for (int d = 0; d < ROWS_DEPTH - 1; ++d)
         if (s + d < s1) step(d, s + d);
-    if (phi >= n_phi) return;
+    if (phi >= phis) return;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int m = m0 + 4 * q + kq;
         if (m >= rows) continue;
         d2 *dst = (d2 *)(T + (((size_t)ks * rows + m) * n_phi + phi) * 8);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) dst[c] = d2{acc[2 * c][q], acc[2 * c + 1][q]};
+        for (int c = 0; c < 4; ++c) {
+            const d2 x = {acc[0][2 * c][q], acc[0][2 * c + 1][q]};
+            if constexpr (FOLD) {
+                const d2 y = {acc[S - 1][2 * c][q], acc[S - 1][2 * c + 1][q]};
+                dst[c] = x + y;
+                dst[c + 4 * phis] = x - y;
+            } else {
+                dst[c] = x;
+            }
+        }
     }
 }
 
@@ -215,38 +256,44 @@ constexpr int COLS_KP = 4;   // pairs of frequencies per wave
 // reals, and the angular weights serve the 4 products of a wave.  Latency of the T loads is what
 // bounds it: with one wave for all phi and two steps in flight it took 135 us at 128 frequencies and
 // 130-200 us at 5 to 30, where there are few workgroups.
-template <typename OT, bool SPLIT>
+template <typename OT, bool SPLIT, bool FOLD>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ wang, const double *__restrict__ T,
                OT *__restrict__ out)
 {
+    constexpr int S = FOLD ? 1 : 2;   // terms of T that are apart
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kq = lane >> 4, col = lane & 15, c = col & 7;
     const int rows = plan.rows, split = plan.split;
     const int b = blockIdx.x;
     int m = 0;
     while (plan.poff[m + 1] <= 16 * b) ++m;
     const int P = plan.cols[m], p0 = 16 * b - plan.poff[m], pp = (P + 15) / 16 * 16;
-    const double *w = wang + (size_t)plan.poff[m] * n_phi + p0 + col;
+    const double *w = wang + (size_t)plan.poff[m] * (S * n_phi) + p0 + col;
     const int kbase = blockIdx.y * 2 * COLS_KP + (col >> 3);
     const double *src[COLS_KP];
+    const size_t pstride = (size_t)S * rows * n_phi * 8;
 #pragma unroll
     for (int g = 0; g < COLS_KP; ++g)
-        src[g] = T + ((size_t)min(kbase + 2 * g, n_k - 1) * split * rows + m) * n_phi * 8 + c;
-    const size_t pstride = (size_t)rows * n_phi * 8;
+        src[g] = T + (size_t)min(kbase + 2 * g, n_k - 1) * split * pstride + (size_t)m * n_phi * 8 + c;
     d4 acc[COLS_KP];
 #pragma unroll
     for (int g = 0; g < COLS_KP; ++g) acc[g] = d4{0.0, 0.0, 0.0, 0.0};
     const int steps = (n_phi + 3) / 4, s0 = steps * wave / 4, s1 = steps * (wave + 1) / 4;
-#pragma unroll 4
-    for (int js = s0; js < s1; ++js) {
-        const int j0 = 4 * js, j = min(j0 + kq, n_phi - 1);
-        const double a = j0 + kq < n_phi ? w[(size_t)j * pp] : 0.0;
 #pragma unroll
-        for (int g = 0; g < COLS_KP; ++g) {
-            double v = src[g][(size_t)j * 8];
-            if constexpr (SPLIT)
-                for (int s = 1; s < split; ++s) v += src[g][s * pstride + (size_t)j * 8];
-            acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v, acc[g], 0, 0, 0);
+    for (int e = 0; e < S; ++e) {
+        const double *we = w + (size_t)e * n_phi * pp;
+        const size_t off = (size_t)e * rows * n_phi * 8;
+#pragma unroll 4
+        for (int js = s0; js < s1; ++js) {
+            const int j0 = 4 * js, j = min(j0 + kq, n_phi - 1);
+            const double a = j0 + kq < n_phi ? we[(size_t)j * pp] : 0.0;
+#pragma unroll
+            for (int g = 0; g < COLS_KP; ++g) {
+                double v = src[g][off + (size_t)j * 8];
+                if constexpr (SPLIT)
+                    for (int s = 1; s < split; ++s) v += src[g][off + s * pstride + (size_t)j * 8];
+                acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v, acc[g], 0, 0, 0);
+            }
         }
     }
     __shared__ d4 part[3][COLS_KP][64];
@@ -273,7 +320,8 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
 hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, double f,
                                    const double *r, double *wrad, double *wang, int is_f64, void *pos, void *hinv)
 {
-    const int blocks = (n_r + 4) / 4 * 4 + plan.poff[plan.rows] / 16 * ((n_phi + GEOM_PHI - 1) / GEOM_PHI) +
+    const int n_j = plan.fold ? n_phi : 2 * n_phi;
+    const int blocks = (n_r + 4) / 4 * 4 + plan.poff[plan.rows] / 16 * ((n_j + GEOM_PHI - 1) / GEOM_PHI) +
                        (plan.n_c + 63) / 64;
     hipLaunchKernelGGL(k_compact_geometry, dim3(blocks), dim3(64), 0, st, plan, n_r, n_phi, f, r, wrad, wang,
                        is_f64 ? (double *)pos : nullptr, is_f64 ? (double *)hinv : nullptr,
@@ -285,24 +333,30 @@ hipError_t launch_compact_tables(hipStream_t st, const CompactPlan &plan, int n_
                                  int is_f64, int fact, const void *tab, const void *pos, const double *wrad,
                                  const double *wang, double *T, void *out)
 {
-    const int64_t n_waves = (int64_t)((plan.rows + 15) / 16) * ((n_phi + 15) / 16) * plan.split * n_k;
+    // without the fold the rows of theta < 0 are summed as rows of their own
+    const int rows = plan.fold ? plan.rows : 2 * plan.rows, phis = plan.fold ? n_phi / 2 : n_phi;
+    const int64_t n_waves = (int64_t)((rows + 15) / 16) * ((phis + 15) / 16) * plan.split * n_k;
     const dim3 gr((unsigned)((n_waves + 3) / 4)), br(256);
-#define SC_COMPACT_ROWS(R, F)                                                                                 \
-    hipLaunchKernelGGL((k_compact_rows<R, F>), gr, br, 0, st, k0, n_r, n_phi, plan.rows, plan.split, n_waves, \
-                       (const R *)tab, (const R *)pos, wrad, T)
-    if (is_f64 && fact) SC_COMPACT_ROWS(double, true);
-    else if (is_f64) SC_COMPACT_ROWS(double, false);
-    else if (fact) SC_COMPACT_ROWS(float, true);
-    else SC_COMPACT_ROWS(float, false);
-#undef SC_COMPACT_ROWS
     const dim3 gc(plan.poff[plan.rows] / 16, (n_k + 2 * COLS_KP - 1) / (2 * COLS_KP));
-#define SC_COMPACT_COLS(R, S) \
-    hipLaunchKernelGGL((k_compact_cols<R, S>), gc, dim3(256), 0, st, plan, n_k, n_phi, wang, T, (R *)out)
-    if (is_f64 && plan.split > 1) SC_COMPACT_COLS(double, true);
-    else if (is_f64) SC_COMPACT_COLS(double, false);
-    else if (plan.split > 1) SC_COMPACT_COLS(float, true);
-    else SC_COMPACT_COLS(float, false);
+#define SC_COMPACT_ROWS(R, F, FO)                                                                              \
+    hipLaunchKernelGGL((k_compact_rows<R, F, FO>), gr, br, 0, st, k0, n_r, n_phi, rows, plan.split, n_waves,   \
+                       (const R *)tab, (const R *)pos, wrad, T)
+#define SC_COMPACT_COLS(R, S, FO) \
+    hipLaunchKernelGGL((k_compact_cols<R, S, FO>), gc, br, 0, st, plan, n_k, n_phi, wang, T, (R *)out)
+#define SC_COMPACT(R, FO)                                     \
+    do {                                                      \
+        if (fact) SC_COMPACT_ROWS(R, true, FO);               \
+        else SC_COMPACT_ROWS(R, false, FO);                   \
+        if (plan.split > 1) SC_COMPACT_COLS(R, true, FO);     \
+        else SC_COMPACT_COLS(R, false, FO);                   \
+    } while (0)
+    if (is_f64 && plan.fold) SC_COMPACT(double, true);
+    else if (is_f64) SC_COMPACT(double, false);
+    else if (plan.fold) SC_COMPACT(float, true);
+    else SC_COMPACT(float, false);
+#undef SC_COMPACT
 #undef SC_COMPACT_COLS
+#undef SC_COMPACT_ROWS
     return hipGetLastError();
 }
 

@@ -10,22 +10,48 @@ namespace sc {
 
 namespace {
 
-// Interpolation error aimed at, relative to the largest kernel value, as the bounds below state it.
-// The bounds are pessimistic: the errors met are 50 to 1000 times smaller, so 1e-8 gives about
-// 1e-10 in the FP32 form (whose own rounding is 1e-7) and 1e-14 about 1e-16 in FP64.
-constexpr double EPS_FP32 = 1e-8, EPS_FP64 = 1e-14;
+// Interpolation error aimed at, relative to the largest kernel value, as the estimates below state it.
+// Over 140 random problems the largest errors met were 0.3 of it and the median 0.02: 2e-9 in the FP32
+// form, whose own rounding is 1e-7, and 1e-16 in FP64.
+constexpr double EPS_FP32 = 1e-7, EPS_FP64 = 1e-14;
 
 constexpr int N_ETA = 80;             // widths of the strip of analyticity tried: 0.05 ... 4
 constexpr double ETA_STEP = 0.05;
+constexpr int N_ALPHA = 8, N_S = 16, N_TAU = 8;
+constexpr double ALPHAS[N_ALPHA] = {0.3, 0.7, 0.8, 0.85, 0.9, 0.93, 0.95, 0.97};
 
-struct EtaTable {
+// What the plans share: strips in phi, and the ellipses of every alpha in theta / theta_max.
+struct Tables {
     double sinh_[N_ETA], lead[N_ETA];   // sinh(eta), log(4 / (1 - e^-eta)) + eta
-    EtaTable()
+    struct Ellipse {
+        double s, lead;                 // parameter; log(4 / (1 - e^-s))
+        double re[N_TAU], im[N_TAU];    // asin(alpha cosh(s + i tau)) / beta, tau over a quarter
+    } ell[N_ALPHA][N_S];
+    double beta[N_ALPHA], node[N_ALPHA][8];   // asin(alpha); theta / theta_max of 8 rows
+    Tables()
     {
         for (int i = 0; i < N_ETA; ++i) {
             const double e = ETA_STEP * (i + 1);
             sinh_[i] = std::sinh(e);
             lead[i] = std::log(4.0 / (1.0 - std::exp(-e))) + e;
+        }
+        for (int a = 0; a < N_ALPHA; ++a) {
+            beta[a] = std::asin(ALPHAS[a]);
+            const double s_max = std::min(2.5, std::acosh(1.0 / ALPHAS[a]));
+            for (int i = 0; i < N_S; ++i) {
+                Ellipse &e = ell[a][i];
+                e.s = s_max * (i + 1) / N_S;
+                e.lead = std::log(4.0 / (1.0 - std::exp(-e.s)));
+                for (int t = 0; t < N_TAU; ++t) {
+                    const double tau = (t + 0.5) * M_PI / (2 * N_TAU);
+                    const double x = ALPHAS[a] * std::cosh(e.s) * std::cos(tau), y = ALPHAS[a] * std::sinh(e.s) * std::sin(tau);
+                    const double p = std::hypot(x + 1.0, y), m = std::hypot(x - 1.0, y);   // asin(x + iy)
+                    e.re[t] = std::asin(0.5 * (p - m)) / beta[a];
+                    e.im[t] = std::acosh(std::max(1.0, 0.5 * (p + m))) / beta[a];
+                }
+            }
+            for (int m = 0; m < 8; ++m)
+                node[a][m] = std::asin(ALPHAS[a] * std::cos((2 * m + 1) * M_PI / 32.0)) / beta[a];
         }
     }
 };
@@ -34,7 +60,7 @@ struct EtaTable {
 
 bool compact_plan(const CompactInput &in, CompactPlan &plan)
 {
-    static const EtaTable T;
+    static const Tables T;
     std::memset(&plan, 0, sizeof plan);   // plans are compared as bytes
     if (!(in.obs_r2max >= 0.0) || !(in.f > 0.0) || !(in.r_max > 0.0)) return false;
     const double rp = std::sqrt(in.obs_r2max), rho = std::sqrt(std::max(in.obs_rho2max, 0.0));
@@ -44,29 +70,11 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const double theta_max = 2.0 * std::atan(in.r_max / (2.0 * in.f));
     const double logeps = std::log(in.fp64 ? EPS_FP64 : EPS_FP32);
 
-    // Rows.  On the complex theta with |Im theta| <= h the phase k delta, delta = |r_s - r'| - |r_s|,
-    // has an imaginary part of at most k |r'| sinh(h) (1 + q cosh h) and R stays away from 0 while
-    // q cosh^2(h / 2) e^h < 1.  [0, theta_max] mapped to [-1, 1]: the ellipse with parameter
-    // s = asinh(2 h / theta_max) lies in that strip, and interpolation at N Chebyshev points errs by
-    // at most 4 M e^{-N s} / (e^s - 1), M the largest |K| on the ellipse: N >= (log M + log(4 / (e^s
-    // - 1)) - log eps) / s for the best s.
-    double n_rows = 1e300;
-    for (int i = 0; i < 60; ++i) {
-        const double h = ETA_STEP * (i + 1), ch2 = std::cosh(0.5 * h);
-        const double near = q * ch2 * ch2 * std::exp(h);
-        if (near > 0.7) break;
-        const double s = std::asinh(2.0 * h / theta_max);
-        const double logm = in.k_max * rp * T.sinh_[i] * (1.0 + q * std::cosh(h)) - 4.0 * std::log1p(-near) +
-                            4.0 * std::log(ch2) + std::log(4.0 / std::expm1(s));
-        n_rows = std::min(n_rows, (logm - logeps) / s);
-    }
-    if (!(n_rows < COMPACT_MAX_ROWS)) return false;
-    const int rows = std::max(3, (int)std::ceil(n_rows));
-    if (rows > in.n_r) return false;
-
-    // Columns of each row.  On |Im phi| <= eta the phase's imaginary part is at most
-    // k rho' sin(theta) sinh(eta); P equispaced points (P odd) alias the harmonics beyond (P - 1) / 2,
-    // which sum to at most 4 M e^{-eta (P + 1) / 2} / (1 - e^-eta).
+    // Columns of a row.  On Im phi = eta the phase's imaginary part is at most X cos(phi), X = x sinh(eta),
+    // x = k rho' sin(theta), so |K| is about e^{X cos(phi)}, whose mean is I_0(X) < e^X / (1 + X)^1/2; P
+    // equispaced points (P odd) alias the harmonics beyond (P - 1) / 2, which sum to at most
+    // 4 I_0(X) e^{-eta (P + 1) / 2} / (1 - e^-eta): (P + 1) / 2 is the least over eta of
+    // (X - log(1 + X) / 2 + amp) / eta, which has one minimum, at a smaller eta for a larger x.
     double amp[N_ETA];
     int n_eta = 0;
     for (; n_eta < N_ETA; ++n_eta) {
@@ -74,14 +82,94 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
         if (near > 0.7) break;
         amp[n_eta] = T.lead[n_eta] - 3.0 * std::log1p(-near) - logeps;
     }
+    auto columns = [&](double theta, int &at) {
+        const double x = in.k_max * rho * std::sin(theta);
+        auto half = [&](int i) {
+            const double X = x * T.sinh_[i];
+            return (X - 0.5 * std::log1p(X) + amp[i]) / (ETA_STEP * (i + 1));
+        };
+        double best = half(at);
+        while (at > 0) {
+            const double h = half(at - 1);
+            if (h > best) break;
+            best = h;
+            --at;
+        }
+        while (at + 1 < n_eta) {
+            const double h = half(at + 1);
+            if (h >= best) break;
+            best = h;
+            ++at;
+        }
+        return best;
+    };
+    const double top = std::min(theta_max, 0.5 * M_PI);
+    int eta0 = n_eta / 2, eta1 = eta0;
+    const double half0 = columns(0.0, eta0), half1 = (columns(top, eta1) - half0) / std::sin(top);
+
+    // Rows.  At theta = a + ih the phase k delta, delta = |r_s - r'| - |r_s|, has an imaginary part of at
+    // most k |rho' cos(a) + z' sin(a)| sinh(h) (1 + q cosh h), and R stays away from 0 while
+    // q cosh^2(h / 2) e^h < 1.  theta = theta_max asin(alpha y) / beta maps the ellipse of parameter s
+    // about y in [-1, 1], which ends before the branch points while alpha cosh(s) <= 1, and interpolation
+    // at N Chebyshev points y errs by at most 4 M e^{-(N - 1) s} / (e^s - 1), M the mean of |K| over the
+    // ellipse (half of it has h < 0, where |K| is below 1): N >= (log M + log(4 / (1 - e^-s)) - log eps) / s
+    // for the best s.  Half of the N points are rows; of the alphas the one with the least nodes is taken
+    // (their columns estimated as linear in sin(theta), at 8 rows).
+    const double zp = std::sqrt(std::max(rp * rp - rho * rho, 0.0));
+    auto points = [&](const Tables::Ellipse &e) {   // N of this ellipse
+        double ex[N_TAU], most = 0.0;
+        for (int t = 0; t < N_TAU; ++t) {
+            const double a = theta_max * e.re[t], h = theta_max * e.im[t], eh = std::exp(h);
+            const double sh = 0.5 * (eh - 1.0 / eh), ch = 0.5 * (eh + 1.0 / eh), ch2 = 0.5 * (ch + 1.0);   // cosh^2(h / 2)
+            const double near = q * ch2 * eh;
+            if (!(near <= 0.7)) return 1e300;
+            const double ca = std::fabs(std::cos(a)), sa = std::fabs(std::sin(a));
+            const double reach = rp * ca <= rho ? rp : rho * ca + zp * sa;   // of the points of the sphere and the cylinder
+            ex[t] = in.k_max * reach * sh * (1.0 + q * ch) + 2.0 * std::log(ch2 / ((1.0 - near) * (1.0 - near)));
+            most = std::max(most, ex[t]);
+        }
+        double mean = 0.0;
+        for (int t = 0; t < N_TAU; ++t) mean += std::exp(ex[t] - most) / (2 * N_TAU);
+        return (std::log(mean) + most + e.lead - logeps) / e.s;
+    };
+    int rows = 0;
+    double least = 1e300;
+    auto try_alpha = [&](int a) {   // whether it is the best so far
+        double n_rows = 1e300;
+        int at = N_S - 1;
+        for (int i = N_S - 1; i >= 0; i -= 3) {   // one minimum: in steps of 3, then its neighbours
+            const double n = points(T.ell[a][i]);
+            if (n > n_rows) break;
+            n_rows = n;
+            at = i;
+        }
+        for (int i = std::max(0, at - 2); i <= std::min(N_S - 1, at + 2); ++i)
+            if (i != at) n_rows = std::min(n_rows, points(T.ell[a][i]));
+        if (!(0.5 * n_rows < COMPACT_MAX_ROWS)) return false;
+        const int n = std::max(2, (int)std::ceil(0.5 * n_rows));
+        double nodes = 0.0;
+        for (int m = 0; m < 8; ++m) nodes += (half0 + half1 * std::sin(theta_max * T.node[a][m])) * n;
+        if (nodes >= least) return false;
+        least = nodes;
+        rows = n;
+        plan.alpha = ALPHAS[a];
+        plan.beta = T.beta[a];
+        return true;
+    };
+    // one minimum over the alphas too
+    try_alpha(2);
+    int a = 3;
+    for (; a < N_ALPHA && try_alpha(a); ++a) {}
+    if (a == 3)
+        for (a = 1; a >= 0 && try_alpha(a); --a) {}
+    if (rows == 0 || rows > in.n_r) return false;
+
+    const int own = in.n_phi % 2 ? 2 * in.n_phi : in.n_phi;   // the grid's phi, and those + pi
     int64_t n_c = 0, n_pad = 0;
     for (int m = 0; m < rows; ++m) {
-        const double theta = 0.5 * theta_max * (1.0 + std::cos((2 * m + 1) * M_PI / (2.0 * rows)));
-        const double x = in.k_max * rho * std::sin(theta);
-        double half = 1e300;
-        for (int i = 0; i < n_eta; ++i) half = std::min(half, (x * T.sinh_[i] + amp[i]) / (ETA_STEP * (i + 1)));
-        int p = half < 30000.0 ? 2 * std::max(1, (int)std::ceil(half)) - 1 : in.n_phi;
-        if (p >= in.n_phi) p = in.n_phi;
+        const double half = columns(theta_max / plan.beta * std::asin(plan.alpha * std::cos((2 * m + 1) * M_PI / (4.0 * rows))), eta1);
+        int p = half < 30000.0 ? 2 * std::max(1, (int)std::ceil(half)) - 1 : own;
+        if (p >= own) p = own;
         if (p > 65535) return false;
         plan.cols[m] = (uint16_t)p;
         plan.off[m] = (int32_t)n_c;
@@ -94,6 +182,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     plan.off[rows] = (int32_t)n_c;
     plan.poff[rows] = (int32_t)n_pad;
     plan.rows = rows;
+    plan.fold = in.n_phi % 2 == 0;
     plan.n_c = (int)n_c;
     plan.theta_max = theta_max;
 
@@ -114,9 +203,10 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     plan.form = q <= 1e-3 && q <= 1e-9 * in.k_min * in.f ? FORM_NEAR : q <= 0.01 ? FORM_GH : FORM_GH_FAR;
     plan.scale = std::ldexp(1.0, std::ilogb(in.f));
     // The radii's sum: cut until there are about 1024 waves of it, at least 32 radii each.
-    const int64_t waves = (int64_t)in.n_k * ((in.n_phi + 15) / 16) * ((rows + 15) / 16);
+    const int tiles = plan.fold ? (in.n_phi / 2 + 15) / 16 * ((rows + 15) / 16) : (in.n_phi + 15) / 16 * ((2 * rows + 15) / 16);
+    const int64_t waves = (int64_t)in.n_k * tiles;
     plan.split = (int)std::max<int64_t>(1, std::min<int64_t>((1024 + waves - 1) / waves, (in.n_r + 1) / 32));
-    if ((double)n_pad * in.n_phi > 4e6 || (double)rows * in.n_r > 4e6 ||
+    if ((double)n_pad * own > 4e6 || (double)rows * in.n_r > 4e6 ||
         (double)plan.split * rows * in.n_phi > 1e6)   // far outside: keep the sizes below in range
         return false;
     if (8 * (compact_radial_doubles(plan, in.n_r) + compact_angular_doubles(plan, in.n_phi) +
@@ -131,7 +221,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const double pts = (double)in.n_k * in.n_obs_pad, cyc = 1024.0 * 2.2e3;   // cycles per us
     const double direct = std::max(0.11 * (double)std::min<int64_t>(n_tot, 2048),
                                    pts * (double)n_tot * (in.fp64 ? 4.4 : 1.5) / cyc);
-    const double build = (double)in.n_k * 0.5 * ((double)n_tot * ((rows + 15) / 16 * 16) + (double)n_c * in.n_phi);
+    const double build = (double)in.n_k * 0.5 * ((in.n_r + 1.0) * 256.0 * tiles * (plan.fold ? 2 : 1) + (double)n_c * own);
     const double compact = std::max(0.15 * std::min(plan.chunk, 512), pts * (double)n_c * (in.fp64 ? 5.3 : 1.2) / cyc) + build / cyc +
                            25.0;
     return compact < 0.8 * direct;
