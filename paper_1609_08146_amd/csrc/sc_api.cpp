@@ -79,9 +79,8 @@ extern "C" sc_status sc_ctx_create(int device, void *stream, sc_ctx **out)
         }
         c->own_stream = true;
     }
-    static_assert(QUAD_SEGMENTS * sizeof(unsigned int) <= 256, "work counters must fit the counter buffer");
     sc_status st = scratch_init(device);
-    if (st == SC_OK) st = c->counter.reserve(256);
+    if (st == SC_OK) st = c->counter.reserve(sizeof(unsigned int) * QUAD_SEGMENTS * QUAD_COUNTER_STRIDE);
     if (st == SC_OK && hipEventCreateWithFlags(&c->upload_done, hipEventDisableTiming) != hipSuccess)
         st = fail(SC_E_DEVICE, "sc_ctx_create: hipEventCreate failed");
     if (st != SC_OK) {
@@ -1392,25 +1391,23 @@ sc_status sc::run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec,
         }
     if (tiles[0] + tiles[1] >= (1LL << 31) - (1LL << 24))
         return fail(SC_E_UNSUPPORTED, "evaluate: too many tiles (%lld)", (long long)(tiles[0] + tiles[1]));
-    SC_TRY(c->jobs.reserve(sizeof(QuadJob) * jobs.size()));
     const int n_plain = (int)jobs.size() - n_mm;
     if (jobs.size() > 1) {
+        SC_TRY(c->jobs.reserve(sizeof(QuadJob) * jobs.size()));
         // the previous upload from host_jobs must have completed before it is overwritten
         HIP_TRY(hipEventSynchronize(c->upload_done));
         c->host_jobs = order;
         HIP_TRY(hipMemcpyAsync(c->jobs.p, c->host_jobs.data(), sizeof(QuadJob) * jobs.size(), hipMemcpyHostToDevice,
                                st));
         HIP_TRY(hipEventRecord(c->upload_done, st));
-        if (n_plain) HIP_TRY(launch_fill_u32(st, counter, 0u, QUAD_SEGMENTS));
-    } else if (n_plain) {
-        HIP_TRY(launch_store_job(st, order[0], c->jobs.as<QuadJob>(), counter));
     }
     if (timed) ev_record(timed, EV_Q0);
     if (n_mm == 1 && n_plain == 0) HIP_TRY(launch_quad_mm_one(st, order[0].mm, order[0], tiles[0]));
     else if (n_mm) HIP_TRY(launch_quad_mm(st, order[0].mm, c->jobs.as<QuadJob>(), n_mm, tiles[0]));
     if (n_plain)
         HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
-                            quad_grid(c, prec, l, tiles[1]), c->jobs.as<QuadJob>() + n_mm, n_plain, tiles[1], counter));
+                            quad_grid(c, prec, l, tiles[1]), order.back(),
+                            jobs.size() > 1 ? c->jobs.as<QuadJob>() + n_mm : nullptr, n_plain, tiles[1], counter));
     if (timed) ev_record(timed, EV_Q1);
     return SC_OK;
 }
@@ -1450,7 +1447,7 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
 
 // ------------------------------------------------------- evaluation without allocation
 // A statically allocated device array serves sc_evaluate_noalloc as its scratch memory: the work
-// counters, the job record and the split-K partials.  The array's name is a host-side stand-in;
+// counters and the split-K partials.  The array's name is a host-side stand-in;
 // its device address (one copy per GPU) is looked up once per device with hipGetSymbolAddress
 // when a context is created there, and only that address is handed to kernels.
 static __device__ __align__(256) unsigned char scratch[SC_NOALLOC_SCRATCH_BYTES];
@@ -1458,14 +1455,12 @@ static __device__ __align__(256) unsigned char scratch[SC_NOALLOC_SCRATCH_BYTES]
 namespace {
 constexpr int MAX_DEVICES = 64;
 constexpr size_t SCRATCH_COUNTERS = 0;        // QUAD_SEGMENTS work counters
-constexpr size_t SCRATCH_JOB = 256;           // one QuadJob
 constexpr size_t SCRATCH_PARTIAL = 1024;      // split-K partials from here on
 std::mutex scratch_mu;
 void *scratch_dev[MAX_DEVICES] = {};
 }  // namespace
 
-static_assert(QUAD_SEGMENTS * sizeof(unsigned int) <= SCRATCH_JOB, "work counters overlap the job record");
-static_assert(SCRATCH_JOB + sizeof(QuadJob) <= SCRATCH_PARTIAL, "job record overlaps the partials");
+static_assert(QUAD_SEGMENTS * QUAD_COUNTER_STRIDE * sizeof(unsigned int) <= SCRATCH_PARTIAL, "work counters overlap the partials");
 
 // Called with the device current (sc_ctx_create).
 static sc_status scratch_init(int device)
@@ -1507,7 +1502,6 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
                     (size_t)SC_NOALLOC_SCRATCH_BYTES - SCRATCH_PARTIAL);
     char *b = (char *)base;
     unsigned int *counter = (unsigned int *)(b + SCRATCH_COUNTERS);
-    QuadJob *djob = (QuadJob *)(b + SCRATCH_JOB);
     QuadJob job{};
     hipStream_t st = p->ctx->stream;
     // frequencies k0 ... k0 + n - 1 and points o0 ... o0 + n_o - 1 of one job
@@ -1515,9 +1509,8 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
         if (job.mm) {
             HIP_TRY(launch_quad_mm_one(st, job.mm, job, job.n_tiles));
         } else {
-            HIP_TRY(launch_store_job(st, job, djob, counter));
             HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
-                                quad_grid(p->ctx, prec, l, job.n_tiles), djob, 1, job.n_tiles, counter));
+                                quad_grid(p->ctx, prec, l, job.n_tiles), job, nullptr, 1, job.n_tiles, counter));
         }
         const size_t at = real_size(prec) * 6 * (size_t)k0 * p->n_obs;
         HIP_TRY(launch_reduce(st, mode_of(prec), job.partial, job.n_chunks, job.n_k, n_o, job.n_obs_pad,

@@ -80,8 +80,11 @@ int diag_slots();
 int energy_partial_count(int n_t);
 hipError_t launch_energy(hipStream_t st, int is_f64, int n_t, int n_obs, const void *E, const void *B, double half_dv,
                          double *part, double *W);
+// The direct sums over all tiles of n_jobs jobs in device memory, or of the job `one` (jobs NULL, n_jobs 1);
+// counter: QUAD_SEGMENTS * QUAD_COUNTER_STRIDE words, cleared here where the launch uses them.
 hipError_t launch_quad(hipStream_t st, int mode, int obs_per_lane, int freq_per_lane, int waves_per_block,
-                       int grid, const QuadJob *jobs, int n_jobs, int64_t n_tiles, unsigned int *counter);
+                       int grid, const QuadJob &one, const QuadJob *jobs, int n_jobs, int64_t n_tiles,
+                       unsigned int *counter);
 // E, B [n_k][n_obs][3] at the points o0 ... o0 + n_o - 1 from partials of those points (n_o_pad padded).
 // The compacted FP32 sums (sc_quad_mm.hip): packed rows of the compacted tables [n_k][n_c][8] for the matrix
 // instructions (mtab: mm_table_bytes, mscale: [n_k][16]), and the quadrature over the tiles of one
@@ -108,8 +111,6 @@ hipError_t launch_twiddles(hipStream_t st, int n_k, const double *k, int n_t, co
 hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw,
                        const void *F, void *Ft);
 hipError_t launch_fill_u32(hipStream_t st, unsigned int *p, unsigned int v, int n);
-// *dst = job on the device (the job travels as a kernel argument), and the launch's counters zeroed
-hipError_t launch_store_job(hipStream_t st, const QuadJob &job, QuadJob *dst, unsigned int *counter);
 
 // Occupancy helper: max resident workgroups per CU for a quadrature variant.
 int quad_max_blocks_per_cu(int mode, int obs_per_lane, int freq_per_lane, int waves_per_block);

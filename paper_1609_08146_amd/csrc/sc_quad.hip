@@ -668,9 +668,12 @@ __device__ __forceinline__ void tile_f32(cjob *job, int lane, int chunk, int n0,
     }
 }
 
-// Persistent quadrature kernel.  Every wave repeatedly takes the next tile
-// (one node chunk, 64*OPL observation points, FPB consecutive frequencies)
-// from the device counters counter[QUAD_SEGMENTS], zeroed before the launch.
+// Persistent quadrature kernel.  Every wave takes a tile of its own (one node chunk, 64*OPL observation
+// points, FPB consecutive frequencies) and then the next from the device counters of the QUAD_SEGMENTS
+// segments, zeroed before the launch; with no more tiles than waves the counters are not touched (and
+// may be NULL).  A counter is an atomic over all XCDs, 12 ns each where they meet on a cache line:
+// taking the first tile from it, and finding each of 8 adjacent counters exhausted in turn, was 175 us
+// for 1638 tiles of 64 nodes, now 23 us.
 // Node and table data are wave-uniform (scalar loads); each lane owns OPL
 // points x FPB frequencies x 12 accumulators.  Every wave exits once all
 // segments are exhausted.
@@ -692,10 +695,10 @@ constexpr int quad_waves_per_eu()
 
 template <int MODE, int OPL, int FPB>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(quad_waves_per_eu<MODE, OPL, FPB>())))
-k_quad(const QuadJob *__restrict__ jobs_, int n_jobs, int64_t n_tiles,
-                                              unsigned int *__restrict__ counter)
+k_quad(QuadJob, const QuadJob *__restrict__ jobs_, int n_jobs, int64_t n_tiles, unsigned int *__restrict__ counter)
 {
-    cjob *jobs = (cjob *)jobs_;
+    // a single job travels as the kernel's first argument and is read where it lies
+    cjob *jobs = jobs_ ? (cjob *)jobs_ : (cjob *)__builtin_amdgcn_kernarg_segment_ptr();
     const int lane = threadIdx.x & 63;
     const double2 *ttab = nullptr;   // the FP64 form's (cos, sin) table
     if constexpr (MODE == MODE_FP64) ttab = turn_table_lds();
@@ -705,20 +708,37 @@ k_quad(const QuadJob *__restrict__ jobs_, int n_jobs, int64_t n_tiles,
     // chunk) run on one XCD and its L2 serves their table reads.  A wave that
     // drains its segment moves on to the next one; it leaves when every
     // segment it has visited (all of them, in the end) is exhausted.
+    const int wpb = (int)(blockDim.x >> 6);
     int seg = (int)(blockIdx.x % QUAD_SEGMENTS), visited = 1;
+    int own = (int)(blockIdx.x / QUAD_SEGMENTS) * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     for (;;) {
         int64_t t, s1;
         for (;;) {
-            unsigned int tt = 0;
-            if (lane == 0) tt = atomicAdd(counter + seg, 1u);
             const int64_t s0 = (int64_t)seg * n_tiles / QUAD_SEGMENTS;
             s1 = (int64_t)(seg + 1) * n_tiles / QUAD_SEGMENTS;
-            t = s0 + (int64_t)__builtin_amdgcn_readfirstlane(tt);
+            if (own >= 0) {   // the wave's own tile
+                t = s0 + own;
+                own = -1;
+                if (t < s1) break;
+            }
+            // the others, past those that the segment's waves start with
+            const int64_t c0 = s0 + ((int64_t)gridDim.x + QUAD_SEGMENTS - 1 - seg) / QUAD_SEGMENTS * wpb;
+            t = s1;
+            if (c0 < s1) {
+                unsigned int *c = counter + seg * QUAD_COUNTER_STRIDE;
+                unsigned int tt = 0;
+                // a segment not its own may be long exhausted: a load shows that without the atomic
+                if (lane == 0 && (visited == 1 || c0 + __hip_atomic_load(c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < s1))
+                    tt = atomicAdd(c, 1u) + 1u;
+                const unsigned int got = __builtin_amdgcn_readfirstlane(tt);
+                if (got) t = c0 + (int64_t)(got - 1u);
+            }
             if (t < s1 || visited == QUAD_SEGMENTS) break;
             seg = (seg + 1) % QUAD_SEGMENTS;
             ++visited;
         }
         if (t >= s1) break;
+        t = __builtin_amdgcn_readfirstlane((int)t);   // (below 2^31; keeps what follows in scalar registers)
         const int j = find_job(jobs, n_jobs, t);
         const int64_t local = t - jobs[j].tile0 + jobs[j].tile_offset;
         const int obs_blocks = jobs[j].obs_blocks, n_chunks = jobs[j].n_chunks;
@@ -839,13 +859,20 @@ int quad_max_blocks_per_cu(int mode, int opl, int fpb, int waves_per_block)
 }
 
 hipError_t launch_quad(hipStream_t st, int mode, int opl, int fpb, int waves_per_block, int grid,
-                       const QuadJob *jobs, int n_jobs, int64_t n_tiles, unsigned int *counter)
+                       const QuadJob &one, const QuadJob *jobs, int n_jobs, int64_t n_tiles, unsigned int *counter)
 {
     if (!shape_ok(opl, fpb)) return hipErrorInvalidValue;
+    for (int seg = 0; seg < QUAD_SEGMENTS; ++seg) {   // more tiles than the segment's waves start with?
+        const int64_t tiles = (seg + 1) * n_tiles / QUAD_SEGMENTS - seg * n_tiles / QUAD_SEGMENTS;
+        if (tiles <= (int64_t)((grid + QUAD_SEGMENTS - 1 - seg) / QUAD_SEGMENTS) * waves_per_block) continue;
+        const hipError_t e = launch_fill_u32(st, counter, 0u, QUAD_SEGMENTS * QUAD_COUNTER_STRIDE);
+        if (e != hipSuccess) return e;
+        break;
+    }
     dim3 g(grid), b(64 * waves_per_block);
 #define SC_QUAD_LAUNCH(M, O, F)                                                                          \
     if (mode == M && opl == O && fpb == F) {                                                            \
-        hipLaunchKernelGGL((k_quad<M, O, F>), g, b, quad_lds_bytes(M, O, F, waves_per_block), st, jobs, n_jobs, \
+        hipLaunchKernelGGL((k_quad<M, O, F>), g, b, quad_lds_bytes(M, O, F, waves_per_block), st, one, jobs, n_jobs, \
                            n_tiles, counter);                                                           \
         return hipGetLastError();                                                                       \
     }

@@ -43,7 +43,7 @@ struct QuadJob {
 
 enum QuadMode { MODE_FP64 = 0, MODE_SPLIT = 1, MODE_NAIVE = 2 };
 
-// Work counters of one quadrature launch (one per XCD-sized segment of the tile list).
-constexpr int QUAD_SEGMENTS = 8;
+// Segments of the tile list of one quadrature launch, and the spacing of their work counters (64 bytes).
+constexpr int QUAD_SEGMENTS = 8, QUAD_COUNTER_STRIDE = 16;
 
 }  // namespace sc

@@ -420,7 +420,6 @@ static sc_status launch_quantum(sc_server *s)
     for (Req *r : group) HIP_TRY(hipStreamWaitEvent(st, r->ready_ev, 0));
     HIP_TRY(hipMemcpyAsync(s->jobbuf[slot].p, s->hjobs[slot], sizeof(QuadJob) * jobs.size(), hipMemcpyHostToDevice,
                            st));
-    if (total) HIP_TRY(launch_fill_u32(st, s->ctx->counter.as<unsigned int>(), 0u, QUAD_SEGMENTS));
     HIP_TRY(hipEventRecord(s->slot_start[slot], st));
     if (n_mm) HIP_TRY(launch_quad_mm(st, MM_FREQS_SHARED, s->jobbuf[slot].as<QuadJob>(), n_mm, mm_tiles));
     const int mode = mode_of(prec);
@@ -429,7 +428,7 @@ static sc_status launch_quantum(sc_server *s)
     int64_t grid = std::min<int64_t>((int64_t)occ * s->ctx->n_cu, (total + wpb - 1) / wpb);
     grid = std::max<int64_t>(grid, 1);
     if (total)
-        HIP_TRY(launch_quad(st, mode, opl, fpb, wpb, (int)grid, s->jobbuf[slot].as<QuadJob>() + n_mm,
+        HIP_TRY(launch_quad(st, mode, opl, fpb, wpb, (int)grid, jobs.back(), s->jobbuf[slot].as<QuadJob>() + n_mm,
                             (int)jobs.size() - n_mm, total, s->ctx->counter.as<unsigned int>()));
     HIP_TRY(hipEventRecord(s->slot_ev[slot], st));
     s->slot_busy[slot] = true;
