@@ -1108,17 +1108,18 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
 // chunk / 512 - 1 further roundings.
 constexpr int SUM_BLOCK = 512;
 
-// The chunk the direct sum really takes: the launch's, but shorter where that leaves fewer than 2048
-// tiles (two waves per SIMD), down to 64 nodes.  A wave takes its nodes one after the other, 0.11 us
-// each: 114 points at one frequency over 3 136 nodes took 256 us in 4 waves of 2 048 nodes.  A
-// function of the problem and its chunk alone (frequencies counted in the precision's usual blocks),
-// and the partials stay below 25 MB where it shortens.
+// The chunk the direct sum really takes: the launch's, but shorter where that leaves fewer tiles than
+// resident waves (4 per SIMD in FP64, 5 in FP32).  A wave takes its nodes one after the other, 0.1 us each
+// on a full chip and 0.3 alone: 114 points at one frequency over 3 136 nodes took 256 us in 4 waves of
+// 2 048 nodes, and 1 500 points at 16 frequencies over 65 800 nodes 1.73 ms with two waves per SIMD, 1.33
+// with five.  A function of the problem and its chunk alone; where it would take the partials over 60 MB
+// the chunk stays (sc_evaluate_noalloc has 64 MB for them).
 static int direct_chunk(const sc_prob *p, sc_precision prec, int chunk)
 {
-    const int f = prec == SC_FP64 ? 2 : 4;
-    const int64_t units = (int64_t)(p->n_obs_pad / 64) * (((int64_t)p->k.size() + f - 1) / f);
-    const int64_t want = ((int64_t)p->n_tot * units + 2047) / 2048;
-    return (int)std::min<int64_t>(chunk, std::max<int64_t>(64, (want + 31) / 32 * 32));
+    const int64_t c = direct_chunk_nodes(p->n_tot, p->n_obs_pad, (int)p->k.size(), prec == SC_FP64);
+    if (c >= chunk) return chunk;
+    const int64_t bytes = (int64_t)real_size(prec) * 12 * ((p->n_tot + c - 1) / c) * (int64_t)p->k.size() * p->n_obs_pad;
+    return bytes > (60 << 20) ? chunk : (int)c;
 }
 
 // The quadrature job of one problem (no allocation): tables `tab` of the chosen layout, split-K

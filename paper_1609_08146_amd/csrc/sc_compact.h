@@ -75,6 +75,16 @@ inline int64_t compact_rows_doubles(const CompactPlan &p, int n_phi)
     return (int64_t)p.split * p.rows * (p.fold ? 1 : 2) * n_phi * 8;
 }
 
+// Nodes per chunk that the direct sum would take for itself: as many tiles (64 points, the usual 4
+// frequencies or 2 in FP64) as waves are resident, and at least 64 nodes.
+inline int64_t direct_chunk_nodes(int64_t n_tot, int n_obs_pad, int n_k, bool fp64)
+{
+    const int f = fp64 ? 2 : 4, waves = fp64 ? 4096 : 5120;
+    const int64_t units = (int64_t)(n_obs_pad / 64) * ((n_k + f - 1) / f);
+    const int64_t want = (n_tot * units + waves - 1) / waves;
+    return want < 64 ? 64 : (want + 31) / 32 * 32;
+}
+
 // What the plan depends on.
 struct CompactInput {
     double f, r_max;       // paraboloid

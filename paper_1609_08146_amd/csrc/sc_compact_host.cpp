@@ -67,6 +67,20 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const double q = rp / in.f;   // |r_s| >= f on the paraboloid
     // farther out the singularity R = 0 comes near the strip (and few nodes would be saved)
     if (!(q <= 0.25) || !std::isfinite(in.k_max * rp)) return false;
+    // Which sum is faster, in us of 1024 SIMDs' cycles (measured: 1.5 cycles per direct FP32 evaluation on the
+    // tied tables and 4.4 in FP64, 1.2 and 5.3 per compacted one, a quarter more for the last round of
+    // tiles; the matrix instructions of the two interpolations at 32 FP64 flops per cycle) and, for small
+    // problems, the serial chain of a wave (0.3 us per node of a direct chunk) against the launches that
+    // build the tables (55 us at 64 x 64 nodes, 115 at 256 x 256).  The tables serve every evaluation until
+    // the field changes, so they count for 0.7 of one: 64 x 64 nodes and 100 points take 49 us directly, 87
+    // compacted and 33 with the tables there; 100 x 100 and 1500 points 82, 99 and 34; 256 x 256 and
+    // 400 points at 4 frequencies 199, 184 and 39.
+    const int64_t n_tot = (int64_t)(in.n_r + 1) * in.n_phi;
+    const double pts = (double)in.n_k * in.n_obs_pad, cyc = 1024.0 * 2.2e3;   // cycles per us
+    const double launches = 40.0 + 0.14 * ((double)in.n_r + in.n_phi);
+    const double chain = 0.3 * (double)std::min<int64_t>(2048, direct_chunk_nodes(n_tot, in.n_obs_pad, in.n_k, in.fp64));
+    const double direct = std::max(chain, 1.25 * pts * (double)n_tot * (in.fp64 ? 4.4 : 1.5) / cyc);
+    if (direct < 0.7 * launches) return false;
     const double theta_max = 2.0 * std::atan(in.r_max / (2.0 * in.f));
     const double logeps = std::log(in.fp64 ? EPS_FP64 : EPS_FP32);
 
@@ -177,7 +191,6 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
         n_c += p;
         n_pad += (p + 15) / 16 * 16;
     }
-    const int64_t n_tot = (int64_t)(in.n_r + 1) * in.n_phi;
     if (n_c > 65536 || 2 * n_c > n_tot) return false;
     plan.off[rows] = (int32_t)n_c;
     plan.poff[rows] = (int32_t)n_pad;
@@ -213,18 +226,9 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
              compact_rows_doubles(plan, in.n_phi)) > COMPACT_WORK_MAX)
         return false;
 
-    // Which sum is faster, in SIMD cycles over the chip's 1024 SIMDs (measured rates: 1.5 cycles per
-    // direct FP32 evaluation on the tied tables and 4.4 in FP64, 1.2 and 5.3 per compacted one; the
-    // matrix instructions of the two interpolations at 32 FP64 flops per cycle), and for small
-    // problems the serial chain of a wave (0.11 us per node of a 2048-node chunk against chunk nodes
-    // and three more launches).
-    const double pts = (double)in.n_k * in.n_obs_pad, cyc = 1024.0 * 2.2e3;   // cycles per us
-    const double direct = std::max(0.11 * (double)std::min<int64_t>(n_tot, 2048),
-                                   pts * (double)n_tot * (in.fp64 ? 4.4 : 1.5) / cyc);
+    const double compact = std::max((in.fp64 ? 0.3 : 0.15) * plan.chunk, pts * (double)n_c * (in.fp64 ? 5.3 : 1.2) / cyc);
     const double build = (double)in.n_k * 0.5 * ((in.n_r + 1.0) * 256.0 * tiles * (plan.fold ? 2 : 1) + (double)n_c * own);
-    const double compact = std::max(0.15 * std::min(plan.chunk, 512), pts * (double)n_c * (in.fp64 ? 5.3 : 1.2) / cyc) + build / cyc +
-                           25.0;
-    return compact < 0.8 * direct;
+    return compact + 0.7 * (launches + 1.5 * build / cyc) < direct;
 }
 
 }  // namespace sc
