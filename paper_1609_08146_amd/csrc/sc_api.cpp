@@ -100,6 +100,7 @@ extern "C" sc_status sc_ctx_destroy(sc_ctx *c)
     DeviceGuard g(c->device);
     (void)hipStreamSynchronize(c->stream);
     if (c->upload_done) (void)hipEventDestroy(c->upload_done);
+    if (c->pinned) (void)hipHostFree(c->pinned);
     c->counter.release();
     c->jobs.release();
     if (c->own_stream) (void)hipStreamDestroy(c->stream);
@@ -163,7 +164,7 @@ extern "C" sc_status sc_prob_destroy(sc_prob *p)
     DeviceGuard g(p->ctx->device);
     // buffers from the stream-ordered allocator are freed behind the work queued on their stream; the
     // others need the problem's work finished first
-    if (!p->alloc_stream) (void)hipStreamSynchronize(p->ctx->stream);
+    if (!p->alloc.stream) (void)hipStreamSynchronize(p->ctx->stream);
     for (int i = 0; i < EV_N; ++i)
         if (p->ev[i]) (void)hipEventDestroy(p->ev[i]);
     if (p->stage_ev) (void)hipEventDestroy(p->stage_ev);
@@ -250,6 +251,7 @@ static void apply_factoring_flag(sc_prob *p, unsigned int bad, bool need32, bool
 {
     p->fact_checked = true;
     p->fact_ok = (bad & 1u) == 0;
+    p->fact_test_only = !p->fact_ok;
     p->fact64_ok = p->fact_ok && (bad & 2u) == 0;
     p->tie_ok = p->fact_ok && (bad & 4u) == 0;
     p->tie64_ok = p->fact64_ok && (bad & 8u) == 0;
@@ -305,17 +307,17 @@ static sc_status factor_out(sc_prob *p, bool need32, bool need64, FactorOut &o)
 {
     const size_t nrec = p->k.size() * (size_t)p->n_tot;
     if (need32) {
-        SC_TRY(p->tabf.reserve(sizeof(float) * 4 * nrec, p->alloc_stream));
-        SC_TRY(p->posf.reserve(sizeof(float) * 8 * (size_t)p->n_tot, p->alloc_stream));
-        SC_TRY(p->betaf.reserve(sizeof(float) * (size_t)p->n_tot, p->alloc_stream));
-        SC_TRY(p->tabp.reserve(sizeof(float) * 2 * nrec, p->alloc_stream));
+        SC_TRY(p->tabf.reserve(sizeof(float) * 4 * nrec, p->alloc));
+        SC_TRY(p->posf.reserve(sizeof(float) * 8 * (size_t)p->n_tot, p->alloc));
+        SC_TRY(p->betaf.reserve(sizeof(float) * (size_t)p->n_tot, p->alloc));
+        SC_TRY(p->tabp.reserve(sizeof(float) * 2 * nrec, p->alloc));
     }
     if (need64) {
-        SC_TRY(p->tabf64.reserve(sizeof(double) * 4 * nrec, p->alloc_stream));
-        SC_TRY(p->posf64.reserve(sizeof(double) * 8 * (size_t)p->n_tot, p->alloc_stream));
-        SC_TRY(p->betaf64.reserve(sizeof(double) * (size_t)p->n_tot, p->alloc_stream));
+        SC_TRY(p->tabf64.reserve(sizeof(double) * 4 * nrec, p->alloc));
+        SC_TRY(p->posf64.reserve(sizeof(double) * 8 * (size_t)p->n_tot, p->alloc));
+        SC_TRY(p->betaf64.reserve(sizeof(double) * (size_t)p->n_tot, p->alloc));
     }
-    SC_TRY(p->fact_flag.reserve(sizeof(unsigned int), p->alloc_stream));
+    SC_TRY(p->fact_flag.reserve(sizeof(unsigned int), p->alloc));
     HIP_TRY(launch_fill_u32(p->ctx->stream, p->fact_flag.as<unsigned int>(), 0u, 1));
     o = FactorOut{p->pos32.as<float>(), p->pos64.as<double>(), FACTOR_TOL, FACTOR_TOL_FP64,
                   need32 ? p->tabf.as<float>() : nullptr, need32 ? p->posf.as<float>() : nullptr,
@@ -323,6 +325,17 @@ static sc_status factor_out(sc_prob *p, bool need32, bool need64, FactorOut &o)
                   need64 ? p->tabf64.as<double>() : nullptr, need64 ? p->posf64.as<double>() : nullptr,
                   need64 ? p->betaf64.as<double>() : nullptr, p->fact_flag.as<unsigned int>()};
     return SC_OK;
+}
+
+// Pinned memory of the context for small results on their way to pageable memory (a copy straight there
+// stages by itself and waits: 60 us each for E and B of some kilobytes).
+static void *pinned_area(sc_ctx *c)
+{
+    if (!c->pinned && hipHostMalloc(&c->pinned, PINNED_BYTES, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        c->pinned = nullptr;
+    }
+    return c->pinned;
 }
 
 // The outcome of a factoring test whose kernel was just launched: one flag read back.  With
@@ -339,11 +352,22 @@ static sc_status factoring_launched(sc_prob *p, bool need32, bool need64)
         p->fact_req64 = need64;
         return SC_OK;
     }
-    unsigned int bad = 15;
-    HIP_TRY(hipMemcpyAsync(&bad, p->fact_flag.p, sizeof(bad), hipMemcpyDeviceToHost, st));
+    unsigned int pageable = 15, *bad = (unsigned int *)pinned_area(p->ctx);
+    if (!bad) bad = &pageable;
+    HIP_TRY(hipMemcpyAsync(bad, p->fact_flag.p, sizeof(*bad), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    apply_factoring_flag(p, bad, need32, need64);
+    apply_factoring_flag(p, *bad, need32, need64);
     return SC_OK;
+}
+
+// The test alone.
+static sc_status test_factoring(sc_prob *p)
+{
+    FactorOut o;
+    SC_TRY(factor_out(p, false, false, o));
+    HIP_TRY(launch_tables_factor(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
+                                 p->tab64.as<double>(), o));
+    return factoring_launched(p, false, false);
 }
 
 // Factored tables from the FP64 tables: the test runs once per table set; the FP32 split (need32) and
@@ -357,6 +381,11 @@ static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
         need32 = need32 && p->fact_ok && !p->fact32_built;
         need64 = need64 && p->fact64_ok && !p->fact64_built;
         if (!need32 && !need64) return SC_OK;
+    } else if (p->fact_test_only && !p->fact_flag_host) {
+        // (buffers taken for nothing cost 0.2 ms to take and give back)
+        SC_TRY(test_factoring(p));
+        if (!p->fact_ok) return SC_OK;
+        return ensure_factored(p, need32, need64);
     }
     FactorOut o;
     SC_TRY(factor_out(p, need32, need64, o));
@@ -370,14 +399,15 @@ static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
     return factoring_launched(p, need32, need64);
 }
 
-// The layouts built with the tables themselves: those of the expected precision.
-static bool eager32(const sc_prob *p) { return p->eager_prec == SC_FP32_SPLIT; }
-static bool eager64(const sc_prob *p) { return p->eager_prec == SC_FP64 && p->keep_fp64; }
+// The layouts built with the tables themselves: those of the expected precision, unless the last field did not
+// factor.
+static bool eager32(const sc_prob *p) { return p->eager_prec == SC_FP32_SPLIT && !p->fact_test_only; }
+static bool eager64(const sc_prob *p) { return p->eager_prec == SC_FP64 && p->keep_fp64 && !p->fact_test_only; }
 
 static sc_status reserve_power(sc_prob *p)
 {
     const size_t n = p->k.size() + (size_t)power_partial_count((int)p->k.size(), p->n_tot);
-    return p->d_power.reserve(sizeof(double) * n, p->alloc_stream);
+    return p->d_power.reserve(sizeof(double) * n, p->alloc);
 }
 
 // After tab64 was (re)built (`tested`: the factoring test went with it): with keep_fp64 off, cast to the
@@ -389,8 +419,9 @@ static sc_status finish_tables(sc_prob *p, bool tested = false)
     // the factoring test (and the factored tables of the expected precision) now, so that the table
     // layout, and with it the launch shape, is known before the first evaluation; it needs the FP64
     // tables
+    const bool e32 = p->eager_prec == SC_FP32_SPLIT, e64 = p->eager_prec == SC_FP64 && p->keep_fp64;
     if (tested) SC_TRY(factoring_launched(p, eager32(p), eager64(p)));
-    else SC_TRY(ensure_factored(p, eager32(p), eager64(p)));
+    if (!p->fact_pending) SC_TRY(ensure_factored(p, e32, e64));
     if (p->keep_fp64) return SC_OK;
     if (p->fact_pending) {   // the general FP32 tables only if the current does not factor
         p->cast_pending = true;
@@ -405,7 +436,7 @@ static sc_status drop_fp64_tables(sc_prob *p, bool cast)
 {
     if (cast) {
         const size_t nrec = p->k.size() * (size_t)p->n_tot;
-        SC_TRY(p->tab32.reserve(sizeof(float) * 8 * nrec, p->alloc_stream));
+        SC_TRY(p->tab32.reserve(sizeof(float) * 8 * nrec, p->alloc));
         HIP_TRY(launch_tables_cast(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
                                    p->pos64.as<double>(), p->tab64.as<double>(), nullptr, p->tab32.as<float>(), 0));
         p->tab32_ok = true;
@@ -490,25 +521,20 @@ extern "C" sc_status sc_set_mirror(sc_prob *p, double f, double r_max, int n_r, 
     const int n_tot = (n_r + 1) * n_phi;
     invalidate_tables(p);
     p->has_mirror = false;
-    SC_TRY(p->d_r.reserve(sizeof(double) * (n_r + 1), p->alloc_stream));
-    SC_TRY(p->d_wr.reserve(sizeof(double) * n_r, p->alloc_stream));
-    SC_TRY(p->d_c.reserve(sizeof(double) * n_phi, p->alloc_stream));
-    SC_TRY(p->d_s.reserve(sizeof(double) * n_phi, p->alloc_stream));
-    SC_TRY(p->pos64.reserve(sizeof(double) * 4 * n_tot, p->alloc_stream));
-    SC_TRY(p->pos32.reserve(sizeof(float) * 4 * n_tot, p->alloc_stream));
-    SC_TRY(p->nrm.reserve(sizeof(double) * 3 * n_tot, p->alloc_stream));
-    SC_TRY(p->wgt.reserve(sizeof(double) * n_tot, p->alloc_stream));
-    SC_TRY(p->tan.reserve(sizeof(double) * 3 * n_phi, p->alloc_stream));
-    HIP_TRY(hipMemcpyAsync(p->d_r.p, r, sizeof(double) * (n_r + 1), hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(p->d_wr.p, wr, sizeof(double) * n_r, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(p->d_c.p, c, sizeof(double) * n_phi, hipMemcpyHostToDevice, st));
-    HIP_TRY(hipMemcpyAsync(p->d_s.p, s, sizeof(double) * n_phi, hipMemcpyHostToDevice, st));
+    const size_t rule = (size_t)2 * n_r + 1 + 2 * (size_t)n_phi;
+    SC_TRY(p->d_r.reserve(sizeof(double) * rule, p->alloc));
+    SC_TRY(p->pos64.reserve(sizeof(double) * 4 * n_tot, p->alloc));
+    SC_TRY(p->pos32.reserve(sizeof(float) * 4 * n_tot, p->alloc));
+    SC_TRY(p->nrm.reserve(sizeof(double) * 3 * n_tot, p->alloc));
+    SC_TRY(p->wgt.reserve(sizeof(double) * n_tot, p->alloc));
+    SC_TRY(p->tan.reserve(sizeof(double) * 3 * n_phi, p->alloc));
+    HIP_TRY(hipMemcpyAsync(p->d_r.p, r, sizeof(double) * rule, hipMemcpyHostToDevice, st));
+    const double *dr = p->d_r.as<double>(), *dwr = dr + n_r + 1, *dc = dwr + n_r, *ds = dc + n_phi;
     if (!ext) SC_TRY(staging_mark(p));
-    HIP_TRY(launch_node_tables(st, n_r, n_phi, f, p->d_r.as<double>(), p->d_wr.as<double>(), p->d_c.as<double>(),
-                               p->d_s.as<double>(), 2.0 * M_PI / (double)n_phi, p->pos64.as<double>(),
-                               p->pos32.as<float>(), p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>()));
-    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc_stream));
-    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc_stream));
+    HIP_TRY(launch_node_tables(st, n_r, n_phi, f, dr, dwr, dc, ds, 2.0 * M_PI / (double)n_phi,
+                               p->pos64.as<double>(), p->pos32.as<float>(), p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>()));
+    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc));
+    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc));
     HIP_TRY(launch_node_half_inverse(st, n_tot, p->pos64.as<double>(), p->hinv64.as<double>(),
                                      p->hinv32.as<float>()));
     p->f = f;
@@ -546,16 +572,16 @@ extern "C" sc_status sc_set_surface(sc_prob *p, int n_surf, const double *xyz, c
     invalidate_tables(p);
     p->has_mirror = false;
     DevBuf d_xyz, d_nds, d_rx, d_rn, d_rdl;
-    SC_TRY(d_xyz.reserve(sizeof(double) * 3 * n_surf, p->alloc_stream));
-    SC_TRY(d_nds.reserve(sizeof(double) * 3 * n_surf, p->alloc_stream));
-    SC_TRY(d_rx.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc_stream));
-    SC_TRY(d_rn.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc_stream));
-    SC_TRY(d_rdl.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc_stream));
-    SC_TRY(p->pos64.reserve(sizeof(double) * 4 * n_tot, p->alloc_stream));
-    SC_TRY(p->pos32.reserve(sizeof(float) * 4 * n_tot, p->alloc_stream));
-    SC_TRY(p->nrm.reserve(sizeof(double) * 3 * n_tot, p->alloc_stream));
-    SC_TRY(p->wgt.reserve(sizeof(double) * n_tot, p->alloc_stream));
-    SC_TRY(p->tan.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc_stream));
+    SC_TRY(d_xyz.reserve(sizeof(double) * 3 * n_surf, p->alloc));
+    SC_TRY(d_nds.reserve(sizeof(double) * 3 * n_surf, p->alloc));
+    SC_TRY(d_rx.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc));
+    SC_TRY(d_rn.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc));
+    SC_TRY(d_rdl.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc));
+    SC_TRY(p->pos64.reserve(sizeof(double) * 4 * n_tot, p->alloc));
+    SC_TRY(p->pos32.reserve(sizeof(float) * 4 * n_tot, p->alloc));
+    SC_TRY(p->nrm.reserve(sizeof(double) * 3 * n_tot, p->alloc));
+    SC_TRY(p->wgt.reserve(sizeof(double) * n_tot, p->alloc));
+    SC_TRY(p->tan.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc));
     HIP_TRY(hipMemcpyAsync(d_xyz.p, xyz, sizeof(double) * 3 * n_surf, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(d_nds.p, ndS, sizeof(double) * 3 * n_surf, hipMemcpyHostToDevice, st));
     if (n_rim > 0) {
@@ -566,8 +592,8 @@ extern "C" sc_status sc_set_surface(sc_prob *p, int n_surf, const double *xyz, c
     HIP_TRY(launch_surface_records(st, n_surf, n_rim, d_xyz.as<double>(), d_nds.as<double>(), d_rx.as<double>(),
                                    d_rn.as<double>(), d_rdl.as<double>(), p->pos64.as<double>(), p->pos32.as<float>(),
                                    p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>()));
-    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc_stream));
-    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc_stream));
+    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc));
+    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc));
     HIP_TRY(launch_node_half_inverse(st, n_tot, p->pos64.as<double>(), p->hinv64.as<double>(),
                                      p->hinv32.as<float>()));
     HIP_TRY(hipStreamSynchronize(st));   // staging buffers are freed on return
@@ -626,7 +652,7 @@ extern "C" sc_status sc_set_frequencies(sc_prob *p, const double *k, int n_k)
     DeviceGuard g(p->ctx->device);
     invalidate_tables(p);
     p->k.assign(k, k + n_k);
-    SC_TRY(p->d_k.reserve(sizeof(double) * n_k, p->alloc_stream));
+    SC_TRY(p->d_k.reserve(sizeof(double) * n_k, p->alloc));
     if (p->stage_ext) {   // p->k is pageable: copy from the pinned area when there is one
         double *h = nullptr;
         bool ext = false;
@@ -655,12 +681,12 @@ extern "C" sc_status sc_set_incident(sc_prob *p, const double *E, const double *
     const int n_k = (int)p->k.size();
     const size_t nrec = (size_t)n_k * p->n_tot;
     invalidate_tables(p);
-    SC_TRY(p->tab64.reserve(sizeof(double) * 8 * nrec, p->alloc_stream));
+    SC_TRY(p->tab64.reserve(sizeof(double) * 8 * nrec, p->alloc));
     DevBuf stageE, stageB;
     const double *dE = E, *dB = B;
     if (!on_device) {
-        SC_TRY(stageE.reserve(sizeof(double) * 6 * nrec, p->alloc_stream));
-        SC_TRY(stageB.reserve(sizeof(double) * 6 * nrec, p->alloc_stream));
+        SC_TRY(stageE.reserve(sizeof(double) * 6 * nrec, p->alloc));
+        SC_TRY(stageB.reserve(sizeof(double) * 6 * nrec, p->alloc));
         HIP_TRY(hipMemcpyAsync(stageE.p, E, sizeof(double) * 6 * nrec, hipMemcpyHostToDevice, st));
         HIP_TRY(hipMemcpyAsync(stageB.p, B, sizeof(double) * 6 * nrec, hipMemcpyHostToDevice, st));
         dE = stageE.as<double>();
@@ -691,14 +717,14 @@ static sc_status set_incident_builtin(sc_prob *p, int beam, double w0, double po
     hipStream_t st = p->ctx->stream;
     const int n_k = (int)p->k.size();
     invalidate_tables(p);
-    SC_TRY(p->tab64.reserve(sizeof(double) * 8 * (size_t)n_k * p->n_tot, p->alloc_stream));
+    SC_TRY(p->tab64.reserve(sizeof(double) * 8 * (size_t)n_k * p->n_tot, p->alloc));
     const double *dspec = nullptr;
     if (spectrum) {
         double *h = nullptr;
         bool ext = false;
         SC_TRY(stage_area(p, p->h_stage_spec, 2 * (size_t)n_k, &h, &ext));
         std::copy(spectrum, spectrum + 2 * (size_t)n_k, h);
-        SC_TRY(p->d_spec.reserve(sizeof(double) * 2 * n_k, p->alloc_stream));
+        SC_TRY(p->d_spec.reserve(sizeof(double) * 2 * n_k, p->alloc));
         HIP_TRY(hipMemcpyAsync(p->d_spec.p, h, sizeof(double) * 2 * n_k, hipMemcpyHostToDevice, st));
         if (!ext) SC_TRY(staging_mark(p));
         dspec = p->d_spec.as<double>();
@@ -773,7 +799,7 @@ extern "C" sc_status sc_set_incident_lg(sc_prob *p, const sc_lg_mode *modes, int
         d[6] = std::sqrt(2.0 * std::exp(std::lgamma(modes[m].p + 1.0) - std::lgamma(modes[m].p + al + 1.0)) / M_PI) / w0;
         d[7] = 0.0;
     }
-    SC_TRY(p->d_modes.reserve(sizeof(double) * SC_LG_RECORD * (size_t)n_modes, p->alloc_stream));
+    SC_TRY(p->d_modes.reserve(sizeof(double) * SC_LG_RECORD * (size_t)n_modes, p->alloc));
     HIP_TRY(hipMemcpyAsync(p->d_modes.p, h, sizeof(double) * SC_LG_RECORD * (size_t)n_modes, hipMemcpyHostToDevice,
                            p->ctx->stream));
     if (!ext) SC_TRY(staging_mark(p));
@@ -803,7 +829,7 @@ static sc_status scale_tables(sc_prob *p, const std::vector<double> &fac)
     hipStream_t st = p->ctx->stream;
     const int n_k = (int)p->k.size();
     DevBuf dfac;
-    SC_TRY(dfac.reserve(sizeof(double) * 2 * n_k, p->alloc_stream));
+    SC_TRY(dfac.reserve(sizeof(double) * 2 * n_k, p->alloc));
     HIP_TRY(hipMemcpyAsync(dfac.p, fac.data(), sizeof(double) * 2 * n_k, hipMemcpyHostToDevice, st));
     if (p->has_tab64) {
         HIP_TRY(launch_tables_scale(st, n_k, p->n_tot, 4, dfac.as<double>(), p->tab64.as<double>(), nullptr));
@@ -886,8 +912,8 @@ extern "C" sc_status sc_set_observation(sc_prob *p, const double *xyz, int n_obs
     hipStream_t st = p->ctx->stream;
     const int pad = (int)round_up((size_t)n_obs, OBS_PAD);
     p->res_prec = -1;
-    SC_TRY(p->obs64.reserve(sizeof(double) * 4 * pad, p->alloc_stream));
-    SC_TRY(p->obs32.reserve(sizeof(float) * 4 * pad, p->alloc_stream));
+    SC_TRY(p->obs64.reserve(sizeof(double) * 4 * pad, p->alloc));
+    SC_TRY(p->obs32.reserve(sizeof(float) * 4 * pad, p->alloc));
     const double *d = xyz;
     p->obs_r2max = p->obs_rho2max = -1.0;
     double r2max = -1.0, rho2max = -1.0;
@@ -901,7 +927,7 @@ extern "C" sc_status sc_set_observation(sc_prob *p, const double *xyz, int n_obs
         bool ext = false;
         SC_TRY(stage_area(p, p->h_stage_obs, 3 * (size_t)n_obs, &h, &ext));
         std::copy(xyz, xyz + 3 * (size_t)n_obs, h);
-        SC_TRY(p->d_obs_in.reserve(sizeof(double) * 3 * n_obs, p->alloc_stream));
+        SC_TRY(p->d_obs_in.reserve(sizeof(double) * 3 * n_obs, p->alloc));
         HIP_TRY(hipMemcpyAsync(p->d_obs_in.p, h, sizeof(double) * 3 * n_obs, hipMemcpyHostToDevice, st));
         if (!ext) SC_TRY(staging_mark(p));
         d = p->d_obs_in.as<double>();
@@ -1080,7 +1106,7 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
     } else if (prec == SC_FP32_SPLIT) {
         if (!p->tab32_ok) {
             if (!build) return fail(SC_E_STATE, "%s", not_built);
-            SC_TRY(p->tab32.reserve(sizeof(float) * 8 * nrec, p->alloc_stream));
+            SC_TRY(p->tab32.reserve(sizeof(float) * 8 * nrec, p->alloc));
             HIP_TRY(launch_tables_cast(st, n_k, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
                                        p->tab64.as<double>(), nullptr, p->tab32.as<float>(), 0));
             p->tab32_ok = true;
@@ -1089,7 +1115,7 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
     } else if (prec == SC_FP32) {
         if (!p->tab32n_ok) {
             if (!build) return fail(SC_E_STATE, "%s", not_built);
-            SC_TRY(p->tab32n.reserve(sizeof(float) * 8 * nrec, p->alloc_stream));
+            SC_TRY(p->tab32n.reserve(sizeof(float) * 8 * nrec, p->alloc));
             HIP_TRY(launch_tables_cast(st, n_k, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
                                        p->has_tab64 ? p->tab64.as<double>() : nullptr, p->tab32.as<float>(),
                                        p->tab32n.as<float>(), 1));
@@ -1275,7 +1301,7 @@ static sc_status ensure_compact(sc_prob *p, sc_precision prec, const CompactPlan
         return SC_OK;
     const int n_k = (int)p->k.size(), f64 = prec == SC_FP64;
     p->cplan_prec = -1;
-    SC_TRY(p->ctab.reserve(lay.bytes, p->alloc_stream));
+    SC_TRY(p->ctab.reserve(lay.bytes, p->alloc));
     char *c = (char *)p->ctab.p, *w = (char *)p->partial.p;
     double *wrad = (double *)(w + lay.wrad), *wang = (double *)(w + lay.wang), *T = (double *)(w + lay.rows);
     hipStream_t st = p->ctx->stream;
@@ -1319,17 +1345,17 @@ sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_
     size_t part = rs * 12 * (size_t)job.n_chunks * n_k * (size_t)p->n_obs_pad;
     if (compact) {
         const CompactLayout lay = compact_layout(p, prec, plan, part);
-        SC_TRY(p->partial.reserve(std::max(part, lay.work), p->alloc_stream));
+        SC_TRY(p->partial.reserve(std::max(part, lay.work), p->alloc));
         SC_TRY(ensure_compact(p, prec, plan, lay, tab, fact));
         const char *c = (const char *)p->ctab.p;
         if (prec == SC_FP32_SPLIT) compact_job_mm(plan, c + lay.tab, c + lay.scale, c + lay.pos, c + lay.hinv, fpb, job);
         else compact_job(plan, c + lay.tab, c + lay.pos, c + lay.hinv, l, job);
     } else {
-        SC_TRY(p->partial.reserve(part, p->alloc_stream));
+        SC_TRY(p->partial.reserve(part, p->alloc));
     }
     job.partial = p->partial.p;
-    SC_TRY(p->resE.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc_stream));
-    SC_TRY(p->resB.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc_stream));
+    SC_TRY(p->resE.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc));
+    SC_TRY(p->resB.reserve(rs * 6 * (size_t)n_k * p->n_obs, p->alloc));
     return SC_OK;
 }
 
@@ -1417,9 +1443,14 @@ static sc_status copy_out(sc_prob *p, void *E, void *B, int on_device, size_t by
 {
     hipStream_t st = p->ctx->stream;
     const hipMemcpyKind kind = on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    if (E) HIP_TRY(hipMemcpyAsync(E, p->resE.p, bytes, kind, st));
-    if (B) HIP_TRY(hipMemcpyAsync(B, p->resB.p, bytes, kind, st));
-    if (!on_device && (E || B)) HIP_TRY(hipStreamSynchronize(st));
+    char *h = nullptr;
+    if (!on_device && 2 * bytes <= PINNED_BYTES) h = (char *)pinned_area(p->ctx);
+    if (E) HIP_TRY(hipMemcpyAsync(h ? h : E, p->resE.p, bytes, kind, st));
+    if (B) HIP_TRY(hipMemcpyAsync(h ? h + bytes : B, p->resB.p, bytes, kind, st));
+    if (on_device || !(E || B)) return SC_OK;
+    HIP_TRY(hipStreamSynchronize(st));
+    if (h && E) std::memcpy(E, h, bytes);
+    if (h && B) std::memcpy(B, h + bytes, bytes);
     return SC_OK;
 }
 
@@ -1718,10 +1749,10 @@ extern "C" sc_status sc_to_time_at(sc_prob *p, double dk, const double *t, int n
     const int f64 = p->res_prec == SC_FP64;
     const size_t rs = f64 ? sizeof(double) : sizeof(float);
     const int64_t n_x = (int64_t)p->n_obs * 3;
-    SC_TRY(p->d_t.reserve(sizeof(double) * n_t, p->alloc_stream));
-    SC_TRY(p->tw.reserve(sizeof(double) * 2 * (size_t)n_t * n_k, p->alloc_stream));
-    SC_TRY(p->timeE.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc_stream));
-    SC_TRY(p->timeB.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc_stream));
+    SC_TRY(p->d_t.reserve(sizeof(double) * n_t, p->alloc));
+    SC_TRY(p->tw.reserve(sizeof(double) * 2 * (size_t)n_t * n_k, p->alloc));
+    SC_TRY(p->timeE.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
+    SC_TRY(p->timeB.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
     HIP_TRY(hipMemcpyAsync(p->d_t.p, t, sizeof(double) * n_t, hipMemcpyHostToDevice, st));
     ev_record(p, EV_T0);
     HIP_TRY(launch_twiddles(st, n_k, p->d_k.as<double>(), n_t, p->d_t.as<double>(), dk, p->tw.as<double>()));
@@ -1797,9 +1828,9 @@ extern "C" sc_status sc_maxwell_residual_freq(sc_prob *p, int n_pts, double h, d
     const int n_k = (int)p->k.size();
     const size_t cells = (size_t)n_k * n_pts;
     DevBuf work, mx, out;
-    SC_TRY(work.reserve(sizeof(double) * diag_slots() * cells, p->alloc_stream));
-    SC_TRY(mx.reserve(sizeof(double) * 4 * n_k, p->alloc_stream));
-    SC_TRY(out.reserve(sizeof(double) * cells, p->alloc_stream));
+    SC_TRY(work.reserve(sizeof(double) * diag_slots() * cells, p->alloc));
+    SC_TRY(mx.reserve(sizeof(double) * 4 * n_k, p->alloc));
+    SC_TRY(out.reserve(sizeof(double) * cells, p->alloc));
     HIP_TRY(launch_maxwell_freq(st, p->res_prec == SC_FP64, n_k, n_pts, h, p->d_k.as<double>(), p->resE.p, p->resB.p,
                                 work.as<double>(), mx.as<double>(), out.as<double>()));
     HIP_TRY(hipMemcpyAsync(ef, out.p, sizeof(double) * cells, hipMemcpyDeviceToHost, st));
@@ -1816,10 +1847,10 @@ static sc_status time_fields(sc_prob *p, double dk, const std::vector<double> &t
     const size_t rs = f64 ? sizeof(double) : sizeof(float);
     const int64_t n_x = (int64_t)p->n_obs * 3;
     DevBuf dt, tw;
-    SC_TRY(dt.reserve(sizeof(double) * n_t, p->alloc_stream));
-    SC_TRY(tw.reserve(sizeof(double) * 2 * (size_t)n_t * n_k, p->alloc_stream));
-    SC_TRY(E.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc_stream));
-    SC_TRY(B.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc_stream));
+    SC_TRY(dt.reserve(sizeof(double) * n_t, p->alloc));
+    SC_TRY(tw.reserve(sizeof(double) * 2 * (size_t)n_t * n_k, p->alloc));
+    SC_TRY(E.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
+    SC_TRY(B.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
     HIP_TRY(hipMemcpyAsync(dt.p, t.data(), sizeof(double) * n_t, hipMemcpyHostToDevice, st));
     HIP_TRY(launch_twiddles(st, n_k, p->d_k.as<double>(), n_t, dt.as<double>(), dk, tw.as<double>()));
     HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, tw.as<double>(), p->resE.p, E.p));
@@ -1845,9 +1876,9 @@ extern "C" sc_status sc_maxwell_residual_time(sc_prob *p, int n_pts, double h, c
     DevBuf E, B, work, mx, out;
     SC_TRY(time_fields(p, dk, ts, E, B));
     const size_t cells = (size_t)n_t * n_pts;
-    SC_TRY(work.reserve(sizeof(double) * diag_slots() * cells, p->alloc_stream));
-    SC_TRY(mx.reserve(sizeof(double) * 4 * n_t, p->alloc_stream));
-    SC_TRY(out.reserve(sizeof(double) * cells, p->alloc_stream));
+    SC_TRY(work.reserve(sizeof(double) * diag_slots() * cells, p->alloc));
+    SC_TRY(mx.reserve(sizeof(double) * 4 * n_t, p->alloc));
+    SC_TRY(out.reserve(sizeof(double) * cells, p->alloc));
     HIP_TRY(launch_maxwell_time(st, p->res_prec == SC_FP64, n_t, n_pts, h, dt, E.p, B.p, work.as<double>(),
                                 mx.as<double>(), out.as<double>()));
     HIP_TRY(hipMemcpyAsync(et, out.p, sizeof(double) * cells, hipMemcpyDeviceToHost, st));
@@ -1867,8 +1898,8 @@ extern "C" sc_status sc_field_energy(sc_prob *p, const double *t, int n_t, doubl
     hipStream_t st = p->ctx->stream;
     DevBuf E, B, part, dW;
     SC_TRY(time_fields(p, dk, std::vector<double>(t, t + n_t), E, B));
-    SC_TRY(part.reserve(sizeof(double) * energy_partial_count(n_t), p->alloc_stream));
-    SC_TRY(dW.reserve(sizeof(double) * n_t, p->alloc_stream));
+    SC_TRY(part.reserve(sizeof(double) * energy_partial_count(n_t), p->alloc));
+    SC_TRY(dW.reserve(sizeof(double) * n_t, p->alloc));
     HIP_TRY(launch_energy(st, p->res_prec == SC_FP64, n_t, p->n_obs, E.p, B.p, 0.5 * dV, part.as<double>(),
                           dW.as<double>()));
     HIP_TRY(hipMemcpyAsync(W, dW.p, sizeof(double) * n_t, hipMemcpyDeviceToHost, st));
@@ -1898,7 +1929,7 @@ extern "C" sc_status sc_get_timing(const sc_prob *p, sc_timing *out)
 // Every device buffer a problem owns.
 static std::vector<DevBuf *> prob_buffers(sc_prob *p)
 {
-    return {&p->d_r,    &p->d_wr,    &p->d_c,       &p->d_s,     &p->pos64,    &p->pos32,  &p->hinv64,
+    return {&p->d_r,    &p->pos64,    &p->pos32,  &p->hinv64,
             &p->hinv32, &p->nrm,     &p->wgt,       &p->tan,     &p->d_k,      &p->tab64,  &p->tab32,
             &p->tab32n, &p->tabf,    &p->posf,      &p->betaf,   &p->tabp,     &p->tabf64, &p->posf64,
             &p->betaf64, &p->fact_flag, &p->d_power, &p->obs64,  &p->obs32,    &p->resE,   &p->resB,

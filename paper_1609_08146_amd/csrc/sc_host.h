@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <map>
+#include <mutex>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -35,41 +36,98 @@ sc_status fail(sc_status st, const char *fmt, ...) __attribute__((format(printf,
 // allocation of the process report SC_E_NOMEM.
 bool debug_fail_this_alloc();
 
-// A device allocation that frees itself.  With a non-null `stream` it uses the
-// stream-ordered allocator (hipMallocAsync / hipFreeAsync on that stream), so
-// that freeing never waits for unrelated work on the device.
+// Device memory that finished problems leave for the next ones (the serving loop: a request takes about 30
+// buffers, and the runtime's pool answered those of many megabytes with fresh mappings, 0.3 ms each, and
+// took 0.5 ms per request to free them).  Blocks come back when the work that used them has run, or
+// is queued on the stream that their next user's first work goes to; at most `limit` bytes wait here,
+// and the owner's destruction gives them back.
+struct BlockCache {
+    std::mutex mu;
+    std::multimap<size_t, void *> idle;
+    size_t held = 0, limit = 0;
+    hipStream_t free_stream = nullptr;
+    // an idle block of n bytes or up to a quarter more (*cap: its size), or NULL
+    void *take(size_t n, size_t *cap)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        auto it = idle.lower_bound(n);
+        if (it == idle.end() || it->first > n + n / 4 + 4096) return nullptr;
+        void *p = it->second;
+        *cap = it->first;
+        held -= it->first;
+        idle.erase(it);
+        return p;
+    }
+    bool put(void *p, size_t cap)
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        if (held + cap > limit) return false;
+        idle.emplace(cap, p);
+        held += cap;
+        return true;
+    }
+    void trim()
+    {
+        std::lock_guard<std::mutex> lk(mu);
+        for (auto &b : idle) (void)hipFreeAsync(b.second, free_stream);
+        idle.clear();
+        held = 0;
+        (void)hipStreamSynchronize(free_stream);
+    }
+};
+
+// Where buffers come from: hipMalloc, or with a stream the stream-ordered allocator (so that freeing never
+// waits for unrelated work on the device), behind a cache if there is one.
+struct Alloc {
+    hipStream_t stream = nullptr;
+    BlockCache *cache = nullptr;
+};
+
+// A device allocation that frees itself.
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
     hipStream_t stream = nullptr;
+    BlockCache *cache = nullptr;
+    size_t cap = 0;   // of a cached block: its size
     DevBuf() = default;
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf() { release(); }
     void release()
     {
-        if (p) {
+        if (p && !(cache && cache->put(p, cap))) {
             if (stream) (void)hipFreeAsync(p, stream);
             else (void)hipFree(p);
         }
         p = nullptr;
         bytes = 0;
+        cache = nullptr;
     }
     // capacity >= n bytes (contents are not preserved on growth)
-    sc_status reserve(size_t n, hipStream_t st = nullptr)
+    sc_status reserve(size_t n, const Alloc &a = {})
     {
         if (n <= bytes && p) return SC_OK;
         release();
         if (n == 0) n = 16;
         if (debug_fail_this_alloc()) return fail(SC_E_NOMEM, "injected allocation failure (%zu bytes)", n);
-        hipError_t e = st ? hipMallocAsync(&p, n, st) : hipMalloc(&p, n);
+        cap = n;
+        hipError_t e = hipSuccess;
+        if (a.cache) p = a.cache->take(n, &cap);
+        if (!p) e = a.stream ? hipMallocAsync(&p, n, a.stream) : hipMalloc(&p, n);
+        if (e != hipSuccess && a.cache) {
+            (void)hipGetLastError();
+            a.cache->trim();
+            e = hipMallocAsync(&p, n, a.stream);
+        }
         if (e != hipSuccess) {
             p = nullptr;
             (void)hipGetLastError();
             return fail(SC_E_NOMEM, "device allocation of %zu bytes failed: %s", n, hipGetErrorString(e));
         }
         bytes = n;
-        stream = st;
+        stream = a.stream;
+        cache = a.cache;
         return SC_OK;
     }
     template <typename T>
@@ -119,17 +177,18 @@ struct sc_ctx {
     std::map<sc::TuneKey, sc_launch> tune;
     std::map<int, sc_launch> batch_tune;   // batched-launch shape per precision (chunk 0: per problem)
     std::map<int, std::pair<std::vector<double>, std::vector<double>>> gauss;   // Gauss-Legendre rules by order
+    void *pinned = nullptr;   // PINNED_BYTES of pinned memory for small results on their way to pageable memory
     std::atomic<int> n_probs{0};   // live problems and servers (a context outlives them)
 };
 
 struct sc_prob {
     sc_ctx *ctx = nullptr;
-    hipStream_t alloc_stream = nullptr;   // stream-ordered allocations (serving loop)
+    sc::Alloc alloc;   // of its buffers (the serving loop: stream-ordered, cached)
     // mirror
     bool has_mirror = false;
     double f = 0, a = 0;
     int n_r = 0, n_phi = 0, n_surf = 0, n_rim = 0, n_tot = 0;
-    sc::DevBuf d_r, d_wr, d_c, d_s;          // 1-D rule (device copies)
+    sc::DevBuf d_r;                          // 1-D rule: r [n_r + 1], w_r [n_r], cos phi, sin phi [n_phi]
     sc::DevBuf pos64, pos32, nrm, wgt, tan;  // node records
     sc::DevBuf hinv64, hinv32;                 // [n_tot] 1 / (2|r_s|), FP64 and FP32
     // frequencies
@@ -153,6 +212,9 @@ struct sc_prob {
     unsigned int *fact_flag_host = nullptr;
     hipEvent_t fact_ev = nullptr;
     bool fact_pending = false, fact_req32 = false, fact_req64 = false;
+    // the last test found a field that does not factor: the next one only tests, and the factored tables are
+    // built by a second pass if it does
+    bool fact_test_only = false;
     // FP32-only storage with a test pending: the FP64 tables are dropped when the test completes,
     // after a cast to the general FP32 tables only if the current did not factor
     bool cast_pending = false;
@@ -208,6 +270,7 @@ struct sc_prob {
 
 namespace sc {
 
+constexpr size_t PINNED_BYTES = 1 << 20;
 constexpr int OBS_PAD = 128;   // observation padding (64 lanes x up to 2 points per lane)
 
 // Gauss-Legendre nodes (ascending) and weights on [-1, 1], correctly rounded (sc_gauss_host.cpp).

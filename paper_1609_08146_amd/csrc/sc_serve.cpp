@@ -168,6 +168,7 @@ struct sc_server {
     std::map<uint64_t, Req *> all;
     sc_server_stats stats{};
     static constexpr int RING = 3;
+    BlockCache blocks;   // of finished requests
     DevBuf jobbuf[RING];
     QuadJob *hjobs[RING] = {};
     size_t hjobs_cap[RING] = {};
@@ -249,7 +250,7 @@ static sc_status setup_begin(sc_server *s, Req *r)
 {
     SC_TRY(sc_prob_create(s->prep, &r->prob));
     sc_prob *p = r->prob;
-    p->alloc_stream = s->prep->stream;
+    p->alloc = {s->prep->stream, &s->blocks};
     p->keep_fp64 = r->prec == SC_FP64;   // FP32 requests keep only their FP32 tables
     p->eager_prec = r->prec;             // and the factored tables of their own precision only
     p->free_stream = s->release_stream;
@@ -276,10 +277,10 @@ static sc_status setup_begin(sc_server *s, Req *r)
                                 r->consistent));
     SC_TRY(sc_set_observation(p, r->obs.data(), r->n_obs, 0));
     if (r->n_t > 0) {
-        SC_TRY(p->d_t.reserve(sizeof(double) * r->n_t, p->alloc_stream));
-        SC_TRY(p->tw.reserve(sizeof(double) * 2 * (size_t)r->n_t * n_k, p->alloc_stream));
-        SC_TRY(p->timeE.reserve(rs * 6 * (size_t)r->n_t * r->n_obs, p->alloc_stream));
-        SC_TRY(p->timeB.reserve(rs * 6 * (size_t)r->n_t * r->n_obs, p->alloc_stream));
+        SC_TRY(p->d_t.reserve(sizeof(double) * r->n_t, p->alloc));
+        SC_TRY(p->tw.reserve(sizeof(double) * 2 * (size_t)r->n_t * n_k, p->alloc));
+        SC_TRY(p->timeE.reserve(rs * 6 * (size_t)r->n_t * r->n_obs, p->alloc));
+        SC_TRY(p->timeB.reserve(rs * 6 * (size_t)r->n_t * r->n_obs, p->alloc));
         const size_t tbytes = sizeof(double) * r->n_t;
         const void *src = r->t.data();
         if (p->stage_ext_off + tbytes <= p->stage_ext_cap) {   // the times from the pinned area
@@ -733,6 +734,12 @@ extern "C" sc_status sc_server_create(sc_ctx *ctx, size_t hbm_budget, int max_ru
             return fail(SC_E_DEVICE, "sc_server_create: hipEventCreate failed");
         }
     pool_cache_acquire(s, hbm_budget);
+    {   // idle blocks: half of what the budget leaves of the device, at most 8 GiB
+        size_t free_b = 0, total_b = 0;
+        (void)hipMemGetInfo(&free_b, &total_b);
+        s->blocks.limit = total_b > hbm_budget ? std::min<size_t>(size_t(8) << 30, (total_b - hbm_budget) / 2) : 0;
+        s->blocks.free_stream = s->release_stream;
+    }
     ctx->n_probs++;   // the context must outlive the server
     s->worker = std::thread(worker_main, s);
     s->preparer = std::thread(prep_main, s);
@@ -922,6 +929,7 @@ extern "C" sc_status sc_server_destroy(sc_server *s)
     }
     s->all.clear();
     s->pinned.clear();
+    s->blocks.trim();
     (void)hipStreamSynchronize(s->release_stream);
     (void)hipStreamDestroy(s->release_stream);
     pool_cache_release(s);

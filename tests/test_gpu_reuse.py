@@ -1,0 +1,75 @@
+"""GPU: memory kept between calls gives the same results as fresh memory.
+
+Bursts of requests of uneven size on one server, so that later bursts run in blocks that earlier ones of
+other sizes and precisions left; and a problem whose fields alternate between factoring and not, so that the
+test runs with and without its tables.  Results are sums in a fixed order, so they are compared exactly.
+"""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1609_08146_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+def test_bursts_in_used_memory(ctx):
+    import torch
+    from dataclasses import replace
+    from paper_1609_08146_amd import Context, Server
+    works = [(replace(workloads.broadband(n_k=k, n_nodes=n).subset(obs_idx=np.arange(0, 4160, s))), prec)
+             for k, n, s, prec in [(3, 60, 37, "fp32_split"), (9, 110, 11, "fp64"), (2, 150, 5, "fp32_split"),
+                                   (5, 64, 53, "fp64")]]
+    c2 = Context(0, use_torch_stream=False)
+    srv = Server(c2, hbm_budget=int(8e9), max_running=4, quantum_ms=5.0)
+    try:
+        first = None
+        for burst in range(4):
+            order = works if burst % 2 == 0 else works[::-1]
+            got = {id(w): srv.wait(t)[:2] for w, t in [(w, srv.submit(w, prec)) for w, prec in order]}
+            if first is None:
+                first = got
+            for w, _ in works:
+                for a, b in zip(first[id(w)], got[id(w)]):
+                    assert np.array_equal(a, b)
+    finally:
+        srv.close()
+        c2.close()
+    torch.cuda.synchronize()
+
+
+def test_alternating_factoring(ctx, orc):
+    from paper_1609_08146_amd import Problem
+    ks, obs = 2 * np.pi * np.array([0.9, 1.0, 1.2]), workloads.random_points(70, 1.0, seed=2)
+    m = orc.mirror(20.0, 9.0, 20, 24)
+    lin = orc.incident_tables(m, ks, orc.GAUSSIAN, 4.0, 0.2, np.array([1.0, 0.5j, -0.3]))
+    rnd = workloads.random_incident_tables(3, m.n_tot, seed=1)
+
+    def fresh(E, B):
+        p = Problem(ctx)
+        p.set_mirror(20.0, 9.0, 20, 24)
+        p.set_frequencies(ks)
+        p.set_incident(E, B)
+        p.set_observation(obs)
+        return p
+
+    p = fresh(*rnd)
+    for fields, factored in ((rnd, False), (lin, True), (lin, True), (rnd, False), (rnd, False), (lin, True)):
+        p.set_incident(*fields)
+        assert p.factored is factored and p.layout_for("fp32_split") == ("tied" if factored else "general")
+        q = fresh(*fields)
+        for prec in ("fp32_split", "fp64"):
+            for a, b in zip(p.evaluate(prec), q.evaluate(prec)):
+                assert np.array_equal(a, b)
+        q.close()
+    p.close()
