@@ -247,8 +247,10 @@ constexpr double FACTOR_TOL_FP64 = 1e-14;
 // The outcome of the factoring test (bit 0: the FP32 split tolerance failed, bit 1: the FP64
 // one; bits 2 and 3 the same for the tied charge): which factored tables exist now, and the ones
 // that will not be used are released.
-static void apply_factoring_flag(sc_prob *p, unsigned int bad, bool need32, bool need64)
+static void apply_factoring_flag(sc_prob *p, const unsigned int *words, bool need32, bool need64)
 {
+    unsigned int bad = 0;
+    for (int b = 0; b < 4; ++b) bad |= (words[b] == p->fact_epoch ? 1u : 0u) << b;
     p->fact_checked = true;
     p->fact_ok = (bad & 1u) == 0;
     p->fact_test_only = !p->fact_ok;
@@ -288,7 +290,7 @@ sc_status sc::resolve_factoring(sc_prob *p, bool block, bool *ready)
         HIP_TRY(e);
     }
     p->fact_pending = false;
-    apply_factoring_flag(p, *p->fact_flag_host, p->fact_req32, p->fact_req64);
+    apply_factoring_flag(p, p->fact_flag_host, p->fact_req32, p->fact_req64);
     if (p->cast_pending) {
         p->cast_pending = false;
         const bool cast = !(p->allow_fact && p->fact_ok);
@@ -302,7 +304,7 @@ sc_status sc::resolve_factoring(sc_prob *p, bool block, bool *ready)
 // A problem's factoring state is read only after a deferred test has completed.
 static sc_status settle_factoring(sc_prob *p) { return resolve_factoring(p, true, nullptr); }
 
-// The factored tables' buffers, as the kernels that write them take them, with the flag cleared.
+// The factored tables' buffers, as the kernels that write them take them, with a new epoch for the flags.
 static sc_status factor_out(sc_prob *p, bool need32, bool need64, FactorOut &o)
 {
     const size_t nrec = p->k.size() * (size_t)p->n_tot;
@@ -317,13 +319,16 @@ static sc_status factor_out(sc_prob *p, bool need32, bool need64, FactorOut &o)
         SC_TRY(p->posf64.reserve(sizeof(double) * 8 * (size_t)p->n_tot, p->alloc));
         SC_TRY(p->betaf64.reserve(sizeof(double) * (size_t)p->n_tot, p->alloc));
     }
-    SC_TRY(p->fact_flag.reserve(sizeof(unsigned int), p->alloc));
-    HIP_TRY(launch_fill_u32(p->ctx->stream, p->fact_flag.as<unsigned int>(), 0u, 1));
+    if (!p->fact_flag.p) {
+        SC_TRY(p->fact_flag.reserve(sizeof(unsigned int) * 4, p->alloc));
+        HIP_TRY(launch_fill_u32(p->ctx->stream, p->fact_flag.as<unsigned int>(), 0u, 4));
+    }
+    p->fact_epoch = p->fact_epoch == ~0u ? 1u : p->fact_epoch + 1u;
     o = FactorOut{p->pos32.as<float>(), p->pos64.as<double>(), FACTOR_TOL, FACTOR_TOL_FP64,
                   need32 ? p->tabf.as<float>() : nullptr, need32 ? p->posf.as<float>() : nullptr,
                   need32 ? p->betaf.as<float>() : nullptr, need32 ? p->tabp.as<float>() : nullptr,
                   need64 ? p->tabf64.as<double>() : nullptr, need64 ? p->posf64.as<double>() : nullptr,
-                  need64 ? p->betaf64.as<double>() : nullptr, p->fact_flag.as<unsigned int>()};
+                  need64 ? p->betaf64.as<double>() : nullptr, p->fact_flag.as<unsigned int>(), p->fact_epoch};
     return SC_OK;
 }
 
@@ -344,7 +349,8 @@ static sc_status factoring_launched(sc_prob *p, bool need32, bool need64)
 {
     hipStream_t st = p->ctx->stream;
     if (p->fact_flag_host) {
-        HIP_TRY(hipMemcpyAsync(p->fact_flag_host, p->fact_flag.p, sizeof(unsigned int), hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipMemcpyAsync(p->fact_flag_host, p->fact_flag.p, sizeof(unsigned int) * 4, hipMemcpyDeviceToHost,
+                               st));
         if (!p->fact_ev) HIP_TRY(hipEventCreateWithFlags(&p->fact_ev, hipEventDisableTiming));
         HIP_TRY(hipEventRecord(p->fact_ev, st));
         p->fact_pending = true;
@@ -352,11 +358,11 @@ static sc_status factoring_launched(sc_prob *p, bool need32, bool need64)
         p->fact_req64 = need64;
         return SC_OK;
     }
-    unsigned int pageable = 15, *bad = (unsigned int *)pinned_area(p->ctx);
-    if (!bad) bad = &pageable;
-    HIP_TRY(hipMemcpyAsync(bad, p->fact_flag.p, sizeof(*bad), hipMemcpyDeviceToHost, st));
+    unsigned int pageable[4], *words = (unsigned int *)pinned_area(p->ctx);
+    if (!words) words = pageable;
+    HIP_TRY(hipMemcpyAsync(words, p->fact_flag.p, sizeof(unsigned int) * 4, hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    apply_factoring_flag(p, *bad, need32, need64);
+    apply_factoring_flag(p, words, need32, need64);
     return SC_OK;
 }
 
@@ -528,15 +534,14 @@ extern "C" sc_status sc_set_mirror(sc_prob *p, double f, double r_max, int n_r, 
     SC_TRY(p->nrm.reserve(sizeof(double) * 3 * n_tot, p->alloc));
     SC_TRY(p->wgt.reserve(sizeof(double) * n_tot, p->alloc));
     SC_TRY(p->tan.reserve(sizeof(double) * 3 * n_phi, p->alloc));
+    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc));
+    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc));
     HIP_TRY(hipMemcpyAsync(p->d_r.p, r, sizeof(double) * rule, hipMemcpyHostToDevice, st));
     const double *dr = p->d_r.as<double>(), *dwr = dr + n_r + 1, *dc = dwr + n_r, *ds = dc + n_phi;
     if (!ext) SC_TRY(staging_mark(p));
     HIP_TRY(launch_node_tables(st, n_r, n_phi, f, dr, dwr, dc, ds, 2.0 * M_PI / (double)n_phi,
-                               p->pos64.as<double>(), p->pos32.as<float>(), p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>()));
-    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc));
-    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc));
-    HIP_TRY(launch_node_half_inverse(st, n_tot, p->pos64.as<double>(), p->hinv64.as<double>(),
-                                     p->hinv32.as<float>()));
+                               p->pos64.as<double>(), p->pos32.as<float>(), p->nrm.as<double>(), p->wgt.as<double>(),
+                               p->tan.as<double>(), p->hinv64.as<double>(), p->hinv32.as<float>()));
     p->f = f;
     p->a = r_max;
     p->rs_min = f;   // |r_s| = r^2 / 4f + f on the paraboloid (distance to the focus)
@@ -582,6 +587,8 @@ extern "C" sc_status sc_set_surface(sc_prob *p, int n_surf, const double *xyz, c
     SC_TRY(p->nrm.reserve(sizeof(double) * 3 * n_tot, p->alloc));
     SC_TRY(p->wgt.reserve(sizeof(double) * n_tot, p->alloc));
     SC_TRY(p->tan.reserve(sizeof(double) * 3 * std::max(n_rim, 1), p->alloc));
+    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc));
+    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc));
     HIP_TRY(hipMemcpyAsync(d_xyz.p, xyz, sizeof(double) * 3 * n_surf, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(d_nds.p, ndS, sizeof(double) * 3 * n_surf, hipMemcpyHostToDevice, st));
     if (n_rim > 0) {
@@ -591,11 +598,8 @@ extern "C" sc_status sc_set_surface(sc_prob *p, int n_surf, const double *xyz, c
     }
     HIP_TRY(launch_surface_records(st, n_surf, n_rim, d_xyz.as<double>(), d_nds.as<double>(), d_rx.as<double>(),
                                    d_rn.as<double>(), d_rdl.as<double>(), p->pos64.as<double>(), p->pos32.as<float>(),
-                                   p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>()));
-    SC_TRY(p->hinv64.reserve(sizeof(double) * n_tot, p->alloc));
-    SC_TRY(p->hinv32.reserve(sizeof(float) * n_tot, p->alloc));
-    HIP_TRY(launch_node_half_inverse(st, n_tot, p->pos64.as<double>(), p->hinv64.as<double>(),
-                                     p->hinv32.as<float>()));
+                                   p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>(),
+                                   p->hinv64.as<double>(), p->hinv32.as<float>()));
     HIP_TRY(hipStreamSynchronize(st));   // staging buffers are freed on return
     double rs2 = INFINITY;
     for (int i = 0; i < n_surf; ++i)
@@ -1393,7 +1397,8 @@ static int quad_grid(const sc_ctx *c, sc_precision prec, const sc_launch &l, int
     if (bpc <= 0 || bpc > occ) bpc = occ;
     int64_t grid = (int64_t)bpc * c->n_cu;
     const int64_t blocks_needed = (n_tiles + l.waves_per_block - 1) / l.waves_per_block;
-    if (grid > blocks_needed) grid = blocks_needed;
+    // one tile per wave: blocks for every segment of the tiles, so that none is left to the counters
+    if (grid > blocks_needed) grid = (blocks_needed + QUAD_SEGMENTS - 1) / QUAD_SEGMENTS * QUAD_SEGMENTS;
     return (int)std::max<int64_t>(grid, 1);
 }
 
@@ -1467,14 +1472,16 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     p->res_prec = -1;
     SC_TRY(run_quad(p->ctx, jobs, prec, l, p));
     HIP_TRY(launch_reduce(p->ctx->stream, mode_of(prec), p->partial.p, job.n_chunks, job.n_k, p->n_obs,
-                          p->n_obs_pad, p->d_k.as<double>(), job.tied, p->n_obs, 0, p->resE.p, p->resB.p));
+                          p->n_obs_pad, p->d_k.as<double>(), job.tied, p->n_obs, 0, p->resE.p, p->resB.p,
+                          on_device ? E : nullptr, on_device ? B : nullptr));
     ev_record(p, EV_R1);
     p->ev_quad = p->ctx->profiling;
     p->res_prec = (int)prec;
     p->last_evals = (int64_t)p->n_obs * job.n_k * p->n_surf;
     p->last_tiles = job.n_tiles;
     p->last_chunk = l.chunk;
-    return copy_out(p, E, B, on_device, real_size(prec) * 6 * (size_t)job.n_k * p->n_obs);
+    if (on_device) return SC_OK;   // the reduction wrote them
+    return copy_out(p, E, B, 0, real_size(prec) * 6 * (size_t)job.n_k * p->n_obs);
 }
 
 // ------------------------------------------------------- evaluation without allocation
@@ -1546,7 +1553,8 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
         }
         const size_t at = real_size(prec) * 6 * (size_t)k0 * p->n_obs;
         HIP_TRY(launch_reduce(st, mode_of(prec), job.partial, job.n_chunks, job.n_k, n_o, job.n_obs_pad,
-                              p->d_k.as<double>() + k0, job.tied, p->n_obs, o0, (char *)E + at, (char *)B + at));
+                              p->d_k.as<double>() + k0, job.tied, p->n_obs, o0, (char *)E + at, (char *)B + at,
+                              nullptr, nullptr));
         return SC_OK;
     };
     CompactPlan plan;
@@ -1726,7 +1734,7 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
         sc_prob *p = probs[i];
         HIP_TRY(launch_reduce(c->stream, mode_of(prec), p->partial.p, jobs[i].n_chunks, jobs[i].n_k, p->n_obs,
                               p->n_obs_pad, p->d_k.as<double>(), jobs[i].tied, p->n_obs, 0, p->resE.p,
-                              p->resB.p));
+                              p->resB.p, nullptr, nullptr));
         p->res_prec = (int)prec;
         p->last_evals = (int64_t)p->n_obs * jobs[i].n_k * p->n_surf;
         p->last_tiles = jobs[i].n_tiles;
@@ -1750,14 +1758,13 @@ extern "C" sc_status sc_to_time_at(sc_prob *p, double dk, const double *t, int n
     const size_t rs = f64 ? sizeof(double) : sizeof(float);
     const int64_t n_x = (int64_t)p->n_obs * 3;
     SC_TRY(p->d_t.reserve(sizeof(double) * n_t, p->alloc));
-    SC_TRY(p->tw.reserve(sizeof(double) * 2 * (size_t)n_t * n_k, p->alloc));
+    SC_TRY(p->tw.reserve(twiddle_bytes(n_k, n_t), p->alloc));
     SC_TRY(p->timeE.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
     SC_TRY(p->timeB.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
     HIP_TRY(hipMemcpyAsync(p->d_t.p, t, sizeof(double) * n_t, hipMemcpyHostToDevice, st));
     ev_record(p, EV_T0);
     HIP_TRY(launch_twiddles(st, n_k, p->d_k.as<double>(), n_t, p->d_t.as<double>(), dk, p->tw.as<double>()));
-    HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, p->tw.as<double>(), p->resE.p, p->timeE.p));
-    HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, p->tw.as<double>(), p->resB.p, p->timeB.p));
+    HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, p->tw.as<double>(), p->resE.p, p->resB.p, p->timeE.p, p->timeB.p));
     ev_record(p, EV_T1);
     p->ev_time = p->ctx->profiling;
     const size_t bytes = rs * 2 * (size_t)n_t * n_x;
@@ -1848,13 +1855,12 @@ static sc_status time_fields(sc_prob *p, double dk, const std::vector<double> &t
     const int64_t n_x = (int64_t)p->n_obs * 3;
     DevBuf dt, tw;
     SC_TRY(dt.reserve(sizeof(double) * n_t, p->alloc));
-    SC_TRY(tw.reserve(sizeof(double) * 2 * (size_t)n_t * n_k, p->alloc));
+    SC_TRY(tw.reserve(twiddle_bytes(n_k, n_t), p->alloc));
     SC_TRY(E.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
     SC_TRY(B.reserve(rs * 2 * (size_t)n_t * n_x, p->alloc));
     HIP_TRY(hipMemcpyAsync(dt.p, t.data(), sizeof(double) * n_t, hipMemcpyHostToDevice, st));
     HIP_TRY(launch_twiddles(st, n_k, p->d_k.as<double>(), n_t, dt.as<double>(), dk, tw.as<double>()));
-    HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, tw.as<double>(), p->resE.p, E.p));
-    HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, tw.as<double>(), p->resB.p, B.p));
+    HIP_TRY(launch_time(st, f64, n_k, n_t, n_x, tw.as<double>(), p->resE.p, p->resB.p, E.p, B.p));
     HIP_TRY(hipStreamSynchronize(st));   // t, dt and tw go out of scope
     return SC_OK;
 }

@@ -207,9 +207,10 @@ struct sc_prob {
     bool tie_ok = false, tie64_ok = false;
     bool fact32_built = false, fact64_built = false;
     sc::DevBuf tabf, posf, betaf, tabp, tabf64, posf64, betaf64, fact_flag;
-    // deferred test (set by a caller that must not wait, the serving loop): the flag goes to the
-    // pinned word fact_flag_host, fact_ev marks its arrival, and resolve_factoring completes the test
+    // deferred test (set by a caller that must not wait, the serving loop): the flags go to the
+    // four pinned words fact_flag_host, fact_ev marks its arrival, and resolve_factoring completes the test
     unsigned int *fact_flag_host = nullptr;
+    unsigned int fact_epoch = 0;   // of the last test started (sc_internal.h, FactorOut)
     hipEvent_t fact_ev = nullptr;
     bool fact_pending = false, fact_req32 = false, fact_req64 = false;
     // the last test found a field that does not factor: the next one only tests, and the factored tables are

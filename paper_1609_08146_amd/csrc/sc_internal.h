@@ -11,15 +11,16 @@
 namespace sc {
 
 // ---- launchers (all asynchronous on `stream`; return hipError_t)
+// (hinv64[q], hinv32[q] = 1 / (2 |r_s|), 0 where |r_s| = 0)
 hipError_t launch_node_tables(hipStream_t st, int n_r, int n_phi, double f, const double *r,
                               const double *wr, const double *cphi, const double *sphi, double dphi,
-                              double *pos64, float *pos32, double *nrm, double *wgt, double *tan);
+                              double *pos64, float *pos32, double *nrm, double *wgt, double *tan,
+                              double *hinv64, float *hinv32);
 // General surface: node records from surface nodes + n dS and boundary nodes + normal + dl.
 hipError_t launch_surface_records(hipStream_t st, int n_surf, int n_rim, const double *xyz, const double *ndS,
                                   const double *rim_xyz, const double *rim_n, const double *rim_dl, double *pos64,
-                                  float *pos32, double *nrm, double *wgt, double *tan);
-// hinv64[q], hinv32[q] = 1 / (2 |r_s|) from the FP64 node records (0 where |r_s| = 0).
-hipError_t launch_node_half_inverse(hipStream_t st, int n_tot, const double *pos64, double *hinv64, float *hinv32);
+                                  float *pos32, double *nrm, double *wgt, double *tan,
+                              double *hinv64, float *hinv32);
 hipError_t launch_obs_prep(hipStream_t st, const double *xyz, int n_obs, int n_obs_pad, double *obs64,
                            float *obs32);
 hipError_t launch_tables_from_fields(hipStream_t st, int n_k, int n_surf, int n_tot, const double *k,
@@ -52,7 +53,7 @@ hipError_t launch_tables_scale(hipStream_t st, int n_k, int n_tot, int n_cplx, c
 // Factored tables (Jt = u s per node): tabf [n_k][n_tot][4] = (s, rho_t), posf [n_tot][8] =
 // (x, y, z, |r_s|, u, 1 / (2|r_s|)) in FP32, tabf64 / posf64 the same in FP64 (each output may be
 // NULL);
-// *bad (zeroed by the caller) gets bit 0 when some node's current has no single real direction
+// the flags get bit 0 when some node's current has no single real direction
 // within tol32 (relative to its largest |Jt| over k), bit 1 for tol64; bits 2 and 3 when some
 // node's charge is not tied to its current (rho_t = -i beta s / k, beta real) within tol32, tol64
 // (relative to its largest (|rho_t|^2 + |Jt / k|^2)^1/2).
@@ -62,7 +63,8 @@ struct FactorOut {
     double tol32, tol64;
     float *tabf, *posf, *betaf, *tabp;
     double *tabf64, *posf64, *betaf64;
-    unsigned int *bad;
+    unsigned int *bad;     // [4]: word b is set to `epoch` for bit b
+    unsigned int epoch;
 };
 hipError_t launch_tables_factor(hipStream_t st, int n_k, int n_tot, const double *k, const double *tab64,
                                 const FactorOut &out);
@@ -97,8 +99,9 @@ hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const do
                             const float *pos, float *mscale, void *mtab);
 hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job, int64_t n_tiles);
 hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t n_tiles);
+// (and in E2, B2 where given)
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
-                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B);
+                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B, void *E2, void *B2);
 // Compacted tables (sc_compact.h): weights and node records, then the tables of frequencies k0 ...
 // k0 + n_k - 1 (T: n_k x compact_rows_doubles) into out [n_k][n_c][8] of the precision.
 hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, double f,
@@ -106,10 +109,12 @@ hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int 
 hipError_t launch_compact_tables(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, int k0, int n_k,
                                  int is_f64, int fact, const void *tab, const void *pos, const double *wrad,
                                  const double *wang, double *T, void *out);
+// Twiddles of the transform to time (twiddle_bytes), and E, B [n_k][n_x] complex -> Et, Bt [n_t][n_x].
+size_t twiddle_bytes(int n_k, int n_t);
 hipError_t launch_twiddles(hipStream_t st, int n_k, const double *k, int n_t, const double *t, double dk,
                            double *tw);
-hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw,
-                       const void *F, void *Ft);
+hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw, const void *E,
+                       const void *B, void *Et, void *Bt);
 hipError_t launch_fill_u32(hipStream_t st, unsigned int *p, unsigned int v, int n);
 
 // Occupancy helper: max resident workgroups per CU for a quadrature variant.

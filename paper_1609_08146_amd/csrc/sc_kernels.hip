@@ -29,11 +29,21 @@ namespace sc {
 
 // ======================================================================= prep
 
+// 1 / (2|r_s|) of a node in FP64 and FP32, for the series forms of delta and 1/|R| in the split quadrature (0
+// for a node at the origin, where the series is never used).
+__device__ __forceinline__ void store_half_inverse(double rs, int q, double *__restrict__ hinv64,
+                                                   float *__restrict__ hinv32)
+{
+    const double h = rs > 0.0 ? 0.5 / rs : 0.0;
+    hinv64[q] = h;
+    hinv32[q] = (float)h;
+}
+
 __global__ void k_node_tables(int n_r, int n_phi, double f, const double *__restrict__ r,
                               const double *__restrict__ wr, const double *__restrict__ cphi,
                               const double *__restrict__ sphi, double dphi, double *__restrict__ pos64,
                               float *__restrict__ pos32, double *__restrict__ nrm, double *__restrict__ wgt,
-                              double *__restrict__ tan)
+                              double *__restrict__ tan, double *__restrict__ hinv64, float *__restrict__ hinv32)
 {
     const int n_tot = (n_r + 1) * n_phi;
     const int64_t gq = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -56,6 +66,7 @@ __global__ void k_node_tables(int n_r, int n_phi, double f, const double *__rest
     pos32[4 * q + 1] = (float)y;
     pos32[4 * q + 2] = (float)z;
     pos32[4 * q + 3] = (float)rs.hi;
+    store_half_inverse(rs.hi, q, hinv64, hinv32);
     // d r_s/dr x d r_s/dphi = r (-F'(r) cos, -F'(r) sin, 1), F'(r) = r / 2f
     const double dFdr = ri / (2.0 * f);
     nrm[3 * q + 0] = -dFdr * c;
@@ -77,7 +88,8 @@ __global__ void k_surface_records(int n_surf, int n_rim, const double *__restric
                                   const double *__restrict__ ndS, const double *__restrict__ rim_xyz,
                                   const double *__restrict__ rim_n, const double *__restrict__ rim_dl,
                                   double *__restrict__ pos64, float *__restrict__ pos32, double *__restrict__ nrm,
-                                  double *__restrict__ wgt, double *__restrict__ tan)
+                                  double *__restrict__ wgt, double *__restrict__ tan, double *__restrict__ hinv64,
+                                  float *__restrict__ hinv32)
 {
     const int64_t gq = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (gq >= (int64_t)n_surf + n_rim) return;
@@ -96,24 +108,11 @@ __global__ void k_surface_records(int n_surf, int n_rim, const double *__restric
     pos32[4 * q + 1] = (float)y;
     pos32[4 * q + 2] = (float)z;
     pos32[4 * q + 3] = (float)rs.hi;
+    store_half_inverse(rs.hi, q, hinv64, hinv32);
     for (int c = 0; c < 3; ++c) nrm[3 * q + c] = nv[c];
     wgt[q] = 1.0;
     if (rim)
         for (int c = 0; c < 3; ++c) tan[3 * j + c] = rim_dl[3 * j + c];
-}
-
-// 1 / (2|r_s|) per node in FP64 and FP32, for the series forms of delta and
-// 1/|R| in the split quadrature (0 for a node at the origin, where the series
-// is never used).
-__global__ void k_node_half_inverse(int n_tot, const double *__restrict__ pos64, double *__restrict__ hinv64,
-                                    float *__restrict__ hinv32)
-{
-    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= n_tot) return;
-    const double rs = pos64[4 * q + 3];
-    const double h = rs > 0.0 ? 0.5 / rs : 0.0;
-    hinv64[q] = h;
-    hinv32[q] = (float)h;
 }
 
 __global__ void k_obs_prep(const double *__restrict__ xyz, int n_obs, int n_obs_pad, double *__restrict__ obs64,
@@ -492,7 +491,7 @@ __global__ void k_tables_cast(int n_k, int n_tot, const double *__restrict__ kv,
 // beta_q = k (Re rho_t Im s - Im rho_t Re s) / |s|^2 at kb.  A node without current
 // (the rim, whose line term is a charge only) takes u_q = 0, beta_q = 1 and
 // s = i k rho_t, which ties its charge exactly and leaves Jt = u s = 0.
-// Bit 0 of *bad is set if |Jt[k][q] - u_q s[k][q]| > tol32 max_k |Jt[k][q]| for any
+// Bit 0 of the flags is set if |Jt[k][q] - u_q s[k][q]| > tol32 max_k |Jt[k][q]| for any
 // node and k, bit 1 if it exceeds tol64; bits 2 and 3 the same for
 // |rho_t[k][q] + i beta_q s[k][q] / k| against max_k (|rho_t[k][q]|^2 + |Jt[k][q] / k|^2)^1/2,
 // the node's scale of the charge term (a charge that vanishes but for rounding, as
@@ -576,6 +575,13 @@ __device__ __forceinline__ void factor_store_node(const FactorOut &o, int64_t q,
     }
 }
 
+// The bits of `flags` in FactorOut::bad, which needs no clearing between tests: each holds the last one it was set in.
+__device__ __forceinline__ void factor_flags(const FactorOut &o, unsigned int flags)
+{
+    for (int b = 0; b < 4; ++b)
+        if (flags >> b & 1u) o.bad[b] = o.epoch;
+}
+
 __device__ __forceinline__ double current2(const double *v)
 {
     double m = 0.0;
@@ -615,7 +621,7 @@ __global__ void k_tables_factor(int n_k, int n_tot, const double *__restrict__ k
         factor_store(o, rec, v, s);
     }
     factor_store_node(o, gq, dir);
-    if (flags) atomicOr(o.bad, flags);
+    factor_flags(o, flags);
 }
 
 // Four lanes' records of 8 doubles, written so that each store instruction writes whole records: the 4 x 4
@@ -790,7 +796,7 @@ k_tables_beam(int n_k, int n_surf, int n_tot, const double *__restrict__ kv, con
                 if (t2max > o.tol32 * o.tol32 * bestr) flags |= 4u;
                 if (t2max > o.tol64 * o.tol64 * bestr) flags |= 8u;
                 factor_store_node(o, gq, dir);
-                if (flags) atomicOr(o.bad, flags);
+                factor_flags(o, flags);
             }
             return;
         }
@@ -816,7 +822,8 @@ __global__ void k_tables_polar(int64_t n_rec, const float *__restrict__ tabf, fl
 template <typename PT, typename OT>
 __global__ void __launch_bounds__(768)
 k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_obs_pad, const double *__restrict__ kv,
-         int b_over_k, int n_obs, int o0, OT *__restrict__ E, OT *__restrict__ B)
+         int b_over_k, int n_obs, int o0, OT *__restrict__ E, OT *__restrict__ B, OT *__restrict__ E2,
+         OT *__restrict__ B2)
 {
     const int groups = (n_o + 63) / 64, c = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int half = threadIdx.x < 384 ? 0 : 1, t = threadIdx.x - 384 * half;
@@ -835,22 +842,31 @@ k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_o
         else if (c & 1) rec[1][6 * lane + c - 7] = (OT)(acc * ik_inv);
         else rec[1][6 * lane + c - 5] = (OT)(-acc * ik_inv);
         __syncthreads();
-        if (64 * g + t / 6 < n_o) (half ? B : E)[((size_t)kk * n_obs + o0 + 64 * g) * 6 + t] = rec[half][t];
+        if (64 * g + t / 6 < n_o) {
+            const size_t at = ((size_t)kk * n_obs + o0 + 64 * g) * 6 + t;
+            (half ? B : E)[at] = rec[half][t];
+            if (OT *second = half ? B2 : E2) second[at] = rec[half][t];
+        }
         __syncthreads();
     }
 }
 
 // ================================================================ time transform
 
-// tw[m][n] = dk * e^{-i k_n t_m}, phase formed in double-double and reduced mod 2pi.
+constexpr int TIME_MT = 8;   // time samples per thread (register tile)
+__host__ __device__ constexpr int time_rows(int n_t) { return (n_t + TIME_MT - 1) / TIME_MT * TIME_MT; }
+
+// tw[n][m] = dk * e^{-i k_n t_m}, m up to a multiple of TIME_MT (the last again); phase formed in
+// double-double and reduced mod 2pi.
 __global__ void k_twiddles(int n_k, const double *__restrict__ kv, int n_t, const double *__restrict__ t, double dk,
                            double *__restrict__ tw)
 {
     const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (idx >= (int64_t)n_k * n_t) return;
-    const int m = (int)(idx / n_k), n = (int)(idx - (int64_t)m * n_k);
+    const int rows = time_rows(n_t);
+    if (idx >= (int64_t)n_k * rows) return;
+    const int n = (int)(idx / rows), m = min((int)(idx - (int64_t)n * rows), n_t - 1);
     double s, c;
-    sincos(phase_mod_2pi(kv[n], dd{-t[m], 0.0}), &s, &c);
+    sincos(-phase_mod_2pi(kv[n], dd{t[m], 0.0}), &s, &c);
     tw[2 * idx] = dk * c;
     tw[2 * idx + 1] = dk * s;
 }
@@ -858,37 +874,36 @@ __global__ void k_twiddles(int n_k, const double *__restrict__ kv, int n_t, cons
 // Constant-address-space view: wave-uniform loads through it become scalar loads.
 typedef __attribute__((address_space(4))) const double cdouble;
 
-constexpr int TIME_MT = 8;   // time samples per thread (register tile)
-
-// Ft[m][x] = sum_n F[n][x] tw[m][n], accumulated in FP64.  The twiddle rows
-// are wave-uniform and read through scalar loads.
+// Ft[m][x] = sum_n F[n][x] tw[n][m] for E (blockIdx.z 0) and B, accumulated in FP64.  The twiddles are
+// wave-uniform and read through scalar loads, the 8 of a frequency side by side: laid out [m][n] they were
+// 8 lines per frequency, and two launches of half the waves took 187 us at 128 frequencies, 256 times and
+// 4160 points, now 151 (3.3e9 FP64 multiply-adds, 84 us at the pipe's peak).
 template <typename T>
 __global__ void __launch_bounds__(256) k_time(int n_k, int n_t, int64_t n_x, const double *__restrict__ tw_,
-                                              const T *__restrict__ F, T *__restrict__ Ft)
+                                              const T *__restrict__ E, const T *__restrict__ B, T *__restrict__ Et,
+                                              T *__restrict__ Bt)
 {
-    cdouble *tw = (cdouble *)tw_;
-    const int m0 = blockIdx.y * TIME_MT;
-    const int mt = min(TIME_MT, n_t - m0);
+    typedef T t2 __attribute__((ext_vector_type(2)));
+    const int m0 = blockIdx.y * TIME_MT, mt = min(TIME_MT, n_t - m0), rows = time_rows(n_t);
+    cdouble *tw = (cdouble *)tw_ + 2 * m0;
+    const t2 *F = (const t2 *)(blockIdx.z ? B : E);
+    t2 *Ft = (t2 *)(blockIdx.z ? Bt : Et);
     const int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (x >= n_x) return;
     double ar[TIME_MT], ai[TIME_MT];
 #pragma unroll
     for (int mm = 0; mm < TIME_MT; ++mm) ar[mm] = ai[mm] = 0.0;
     for (int n = 0; n < n_k; ++n) {
-        const double fr = (double)F[2 * ((size_t)n * n_x + x)];
-        const double fi = (double)F[2 * ((size_t)n * n_x + x) + 1];
+        const t2 f = F[(size_t)n * n_x + x];
+        const double fr = (double)f.x, fi = (double)f.y;
 #pragma unroll
         for (int mm = 0; mm < TIME_MT; ++mm) {
-            const int m = min(m0 + mm, n_t - 1);
-            const double wr = tw[((size_t)m * n_k + n) * 2], wi = tw[((size_t)m * n_k + n) * 2 + 1];
+            const double wr = tw[2 * ((size_t)n * rows + mm)], wi = tw[2 * ((size_t)n * rows + mm) + 1];
             ar[mm] = __fma_rn(fr, wr, __fma_rn(-fi, wi, ar[mm]));
             ai[mm] = __fma_rn(fr, wi, __fma_rn(fi, wr, ai[mm]));
         }
     }
-    for (int mm = 0; mm < mt; ++mm) {
-        Ft[2 * ((size_t)(m0 + mm) * n_x + x)] = (T)ar[mm];
-        Ft[2 * ((size_t)(m0 + mm) * n_x + x) + 1] = (T)ai[mm];
-    }
+    for (int mm = 0; mm < mt; ++mm) Ft[(size_t)(m0 + mm) * n_x + x] = t2{(T)ar[mm], (T)ai[mm]};
 }
 
 __global__ void k_fill_u32(unsigned int *p, unsigned int v, int n)
@@ -903,27 +918,20 @@ static inline unsigned int nblocks(int64_t n, int bs) { return (unsigned int)((n
 
 hipError_t launch_node_tables(hipStream_t st, int n_r, int n_phi, double f, const double *r, const double *wr,
                               const double *cphi, const double *sphi, double dphi, double *pos64, float *pos32,
-                              double *nrm, double *wgt, double *tan)
+                              double *nrm, double *wgt, double *tan, double *hinv64, float *hinv32)
 {
     const int n = (n_r + 1) * n_phi;
     hipLaunchKernelGGL(k_node_tables, dim3(nblocks(n, 256)), dim3(256), 0, st, n_r, n_phi, f, r, wr, cphi, sphi,
-                       dphi, pos64, pos32, nrm, wgt, tan);
-    return hipGetLastError();
-}
-
-hipError_t launch_node_half_inverse(hipStream_t st, int n_tot, const double *pos64, double *hinv64, float *hinv32)
-{
-    hipLaunchKernelGGL(k_node_half_inverse, dim3(nblocks(n_tot, 256)), dim3(256), 0, st, n_tot, pos64, hinv64,
-                       hinv32);
+                       dphi, pos64, pos32, nrm, wgt, tan, hinv64, hinv32);
     return hipGetLastError();
 }
 
 hipError_t launch_surface_records(hipStream_t st, int n_surf, int n_rim, const double *xyz, const double *ndS,
                                   const double *rim_xyz, const double *rim_n, const double *rim_dl, double *pos64,
-                                  float *pos32, double *nrm, double *wgt, double *tan)
+                                  float *pos32, double *nrm, double *wgt, double *tan, double *hinv64, float *hinv32)
 {
     hipLaunchKernelGGL(k_surface_records, dim3(nblocks((int64_t)n_surf + n_rim, 256)), dim3(256), 0, st, n_surf,
-                       n_rim, xyz, ndS, rim_xyz, rim_n, rim_dl, pos64, pos32, nrm, wgt, tan);
+                       n_rim, xyz, ndS, rim_xyz, rim_n, rim_dl, pos64, pos32, nrm, wgt, tan, hinv64, hinv32);
     return hipGetLastError();
 }
 
@@ -1012,34 +1020,38 @@ hipError_t launch_tables_cast(hipStream_t st, int n_k, int n_tot, const double *
 }
 
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
-                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B)
+                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B, void *E2, void *B2)
 {
     const int64_t all = (int64_t)n_k * ((n_o + 63) / 64);
     const unsigned int nb = (unsigned int)(all < (1 << 20) ? all : (1 << 20));
     if (mode == MODE_FP64)
         hipLaunchKernelGGL((k_reduce<double, double>), dim3(nb), dim3(768), 0, st, (const double *)partial, n_chunks,
-                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (double *)E, (double *)B);
+                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (double *)E, (double *)B, (double *)E2, (double *)B2);
     else
         hipLaunchKernelGGL((k_reduce<float, float>), dim3(nb), dim3(768), 0, st, (const float *)partial, n_chunks,
-                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (float *)E, (float *)B);
+                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (float *)E, (float *)B, (float *)E2, (float *)B2);
     return hipGetLastError();
 }
+
+size_t twiddle_bytes(int n_k, int n_t) { return sizeof(double) * 2 * (size_t)n_k * time_rows(n_t); }
 
 hipError_t launch_twiddles(hipStream_t st, int n_k, const double *k, int n_t, const double *t, double dk, double *tw)
 {
-    hipLaunchKernelGGL(k_twiddles, dim3(nblocks((int64_t)n_k * n_t, 256)), dim3(256), 0, st, n_k, k, n_t, t, dk, tw);
+    hipLaunchKernelGGL(k_twiddles, dim3(nblocks((int64_t)n_k * time_rows(n_t), 256)), dim3(256), 0, st, n_k, k, n_t, t,
+                       dk, tw);
     return hipGetLastError();
 }
 
-hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw, const void *F,
-                       void *Ft)
+hipError_t launch_time(hipStream_t st, int is_f64, int n_k, int n_t, int64_t n_x, const double *tw, const void *E,
+                       const void *B, void *Et, void *Bt)
 {
-    dim3 g(nblocks(n_x, 256), (n_t + TIME_MT - 1) / TIME_MT);
+    dim3 g(nblocks(n_x, 256), time_rows(n_t) / TIME_MT, 2);
     if (is_f64)
-        hipLaunchKernelGGL((k_time<double>), g, dim3(256), 0, st, n_k, n_t, n_x, tw, (const double *)F,
-                           (double *)Ft);
+        hipLaunchKernelGGL((k_time<double>), g, dim3(256), 0, st, n_k, n_t, n_x, tw, (const double *)E,
+                           (const double *)B, (double *)Et, (double *)Bt);
     else
-        hipLaunchKernelGGL((k_time<float>), g, dim3(256), 0, st, n_k, n_t, n_x, tw, (const float *)F, (float *)Ft);
+        hipLaunchKernelGGL((k_time<float>), g, dim3(256), 0, st, n_k, n_t, n_x, tw, (const float *)E, (const float *)B,
+                           (float *)Et, (float *)Bt);
     return hipGetLastError();
 }
 

@@ -278,7 +278,7 @@ static sc_status setup_begin(sc_server *s, Req *r)
     SC_TRY(sc_set_observation(p, r->obs.data(), r->n_obs, 0));
     if (r->n_t > 0) {
         SC_TRY(p->d_t.reserve(sizeof(double) * r->n_t, p->alloc));
-        SC_TRY(p->tw.reserve(sizeof(double) * 2 * (size_t)r->n_t * n_k, p->alloc));
+        SC_TRY(p->tw.reserve(twiddle_bytes(n_k, r->n_t), p->alloc));
         SC_TRY(p->timeE.reserve(rs * 6 * (size_t)r->n_t * r->n_obs, p->alloc));
         SC_TRY(p->timeB.reserve(rs * 6 * (size_t)r->n_t * r->n_obs, p->alloc));
         const size_t tbytes = sizeof(double) * r->n_t;
@@ -322,13 +322,13 @@ static sc_status finish_request(sc_server *s, Req *r)
     sc_prob *p = r->prob;
     const int n_k = (int)r->k.size();
     HIP_TRY(launch_reduce(st, mode_of(r->prec), p->partial.p, r->job.n_chunks, n_k, r->n_obs, p->n_obs_pad,
-                          p->d_k.as<double>(), r->job.tied, r->n_obs, 0, p->resE.p, p->resB.p));
+                          p->d_k.as<double>(), r->job.tied, r->n_obs, 0, p->resE.p, p->resB.p, nullptr, nullptr));
     if (r->n_t > 0) {
         const int f64 = r->prec == SC_FP64;
         const int64_t n_x = (int64_t)r->n_obs * 3;
         HIP_TRY(launch_twiddles(st, n_k, p->d_k.as<double>(), r->n_t, p->d_t.as<double>(), r->dk, p->tw.as<double>()));
-        HIP_TRY(launch_time(st, f64, n_k, r->n_t, n_x, p->tw.as<double>(), p->resE.p, p->timeE.p));
-        HIP_TRY(launch_time(st, f64, n_k, r->n_t, n_x, p->tw.as<double>(), p->resB.p, p->timeB.p));
+        HIP_TRY(launch_time(st, f64, n_k, r->n_t, n_x, p->tw.as<double>(), p->resE.p, p->resB.p, p->timeE.p,
+                            p->timeB.p));
     }
     // the copies overlap the next quanta: the copy stream waits for this request's last kernel only
     hipStream_t cs = s->copy_stream;
