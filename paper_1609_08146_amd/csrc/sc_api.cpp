@@ -226,7 +226,7 @@ static void gauss_rule_cached(sc_ctx *c, int n, const std::vector<double> *out[2
 
 static void invalidate_tables(sc_prob *p)
 {
-    p->has_tab = p->tab32_ok = p->tab32n_ok = p->has_tab64 = p->has_power = false;
+    p->has_tab = p->tab32_ok = p->tab32n_ok = p->has_tab64 = p->has_power = p->tab64_unfilled = false;
     p->fact_checked = p->fact_ok = p->fact64_ok = p->tie_ok = p->tie64_ok = false;
     p->fact32_built = p->fact64_built = false;
     p->fact_pending = p->cast_pending = false;   // a flag still on its way belongs to the old tables
@@ -343,6 +343,30 @@ static void *pinned_area(sc_ctx *c)
     return c->pinned;
 }
 
+// The kernel that forms a built-in beam's tables: the FP64 ones, or with `out` the factored ones (and the FP64
+// ones into tab64 unless NULL), and the aperture power.
+static sc_status launch_beam(sc_prob *p, double *tab64, const FactorOut *out, bool power)
+{
+    const int n_k = (int)p->k.size();
+    double *P = power ? p->d_power.as<double>() : nullptr;
+    HIP_TRY(launch_tables_beam(p->ctx->stream, n_k, p->n_surf, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
+                               p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>(), p->beam.kind, p->beam.w0,
+                               p->beam.pol, p->beam.spectrum ? p->d_spec.as<double>() : nullptr, p->beam.consistent,
+                               p->beam.kind == 3 ? p->d_modes.as<double>() : nullptr, p->beam.n_modes, tab64, p->beam.kb,
+                               out, power ? P + n_k : nullptr, P));
+    return SC_OK;
+}
+
+// The FP64 tables, for what reads them.
+static sc_status ensure_tab64(sc_prob *p)
+{
+    if (!p->tab64_unfilled) return SC_OK;
+    SC_TRY(p->tab64.reserve(sizeof(double) * 8 * p->k.size() * (size_t)p->n_tot, p->alloc));
+    SC_TRY(launch_beam(p, p->tab64.as<double>(), nullptr, false));
+    p->tab64_unfilled = false;
+    return SC_OK;
+}
+
 // The outcome of a factoring test whose kernel was just launched: one flag read back.  With
 // fact_flag_host set it is not waited for: the test completes in resolve_factoring.
 static sc_status factoring_launched(sc_prob *p, bool need32, bool need64)
@@ -371,6 +395,7 @@ static sc_status test_factoring(sc_prob *p)
 {
     FactorOut o;
     SC_TRY(factor_out(p, false, false, o));
+    SC_TRY(ensure_tab64(p));
     HIP_TRY(launch_tables_factor(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
                                  p->tab64.as<double>(), o));
     return factoring_launched(p, false, false);
@@ -395,8 +420,14 @@ static sc_status ensure_factored(sc_prob *p, bool need32, bool need64)
     }
     FactorOut o;
     SC_TRY(factor_out(p, need32, need64, o));
-    HIP_TRY(launch_tables_factor(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
-                                 p->tab64.as<double>(), o));
+    if (p->tab64_unfilled) {   // (an FP64 evaluation keeps both FP64 layouts)
+        if (need64) SC_TRY(p->tab64.reserve(sizeof(double) * 8 * p->k.size() * (size_t)p->n_tot, p->alloc));
+        SC_TRY(launch_beam(p, need64 ? p->tab64.as<double>() : nullptr, &o, false));
+        if (need64) p->tab64_unfilled = false;
+    } else {
+        HIP_TRY(launch_tables_factor(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
+                                     p->tab64.as<double>(), o));
+    }
     if (p->fact_checked) {
         p->fact32_built = p->fact32_built || need32;
         p->fact64_built = p->fact64_built || need64;
@@ -428,6 +459,8 @@ static sc_status finish_tables(sc_prob *p, bool tested = false)
     const bool e32 = p->eager_prec == SC_FP32_SPLIT, e64 = p->eager_prec == SC_FP64 && p->keep_fp64;
     if (tested) SC_TRY(factoring_launched(p, eager32(p), eager64(p)));
     if (!p->fact_pending) SC_TRY(ensure_factored(p, e32, e64));
+    // what does not factor for every precision reads them
+    if (!p->fact_pending && !(p->fact_ok && p->fact64_ok)) SC_TRY(ensure_tab64(p));
     if (p->keep_fp64) return SC_OK;
     if (p->fact_pending) {   // the general FP32 tables only if the current does not factor
         p->cast_pending = true;
@@ -442,6 +475,7 @@ static sc_status drop_fp64_tables(sc_prob *p, bool cast)
 {
     if (cast) {
         const size_t nrec = p->k.size() * (size_t)p->n_tot;
+        SC_TRY(ensure_tab64(p));
         SC_TRY(p->tab32.reserve(sizeof(float) * 8 * nrec, p->alloc));
         HIP_TRY(launch_tables_cast(p->ctx->stream, (int)p->k.size(), p->n_tot, p->d_k.as<double>(),
                                    p->pos64.as<double>(), p->tab64.as<double>(), nullptr, p->tab32.as<float>(), 0));
@@ -450,7 +484,7 @@ static sc_status drop_fp64_tables(sc_prob *p, bool cast)
     // a stream-ordered free runs after the cast; a plain hipFree needs the cast to have finished
     if (!p->tab64.stream) HIP_TRY(hipStreamSynchronize(p->ctx->stream));
     p->tab64.release();
-    p->has_tab64 = false;
+    p->has_tab64 = p->tab64_unfilled = false;
     // without the FP64 tables there is no FP64 evaluation, so its factored tables go too
     p->tabf64.release();
     p->posf64.release();
@@ -472,6 +506,10 @@ extern "C" sc_status sc_set_factoring(sc_prob *p, int enable)
 {
     if (!p) return fail(SC_E_INVAL, "sc_set_factoring: prob is NULL");
     if (enable < 0 || enable > 2) return fail(SC_E_INVAL, "sc_set_factoring: enable must be 0, 1 or 2");
+    if (!enable && p->tab64_unfilled) {   // the general tables from now on
+        DeviceGuard g(p->ctx->device);
+        SC_TRY(ensure_tab64(p));
+    }
     p->allow_fact = enable != 0;
     p->allow_tie = enable == 1;
     return SC_OK;
@@ -721,8 +759,6 @@ static sc_status set_incident_builtin(sc_prob *p, int beam, double w0, double po
     hipStream_t st = p->ctx->stream;
     const int n_k = (int)p->k.size();
     invalidate_tables(p);
-    SC_TRY(p->tab64.reserve(sizeof(double) * 8 * (size_t)n_k * p->n_tot, p->alloc));
-    const double *dspec = nullptr;
     if (spectrum) {
         double *h = nullptr;
         bool ext = false;
@@ -731,9 +767,7 @@ static sc_status set_incident_builtin(sc_prob *p, int beam, double w0, double po
         SC_TRY(p->d_spec.reserve(sizeof(double) * 2 * n_k, p->alloc));
         HIP_TRY(hipMemcpyAsync(p->d_spec.p, h, sizeof(double) * 2 * n_k, hipMemcpyHostToDevice, st));
         if (!ext) SC_TRY(staging_mark(p));
-        dspec = p->d_spec.as<double>();
     }
-    const double *modes = beam == 3 ? p->d_modes.as<double>() : nullptr;
     ev_record(p, EV_PREP0);
     int kb = 0;   // where |Jt| ~ k |amplitude| is largest
     for (int i = 1; spectrum && i < n_k; ++i)
@@ -741,13 +775,16 @@ static sc_status set_incident_builtin(sc_prob *p, int beam, double w0, double po
             p->k[kb] * std::hypot(spectrum[2 * kb], spectrum[2 * kb + 1]))
             kb = i;
     if (!spectrum) kb = (int)(std::max_element(p->k.begin(), p->k.end()) - p->k.begin());
+    p->beam = {beam, consistent ? 1 : 0, n_modes, kb, w0, pol_angle, spectrum != nullptr};
     FactorOut out;
     if (p->allow_fact) SC_TRY(factor_out(p, eager32(p), eager64(p), out));
+    // The FP64 tables with it where they will be read: without factoring, or where the field does not factor
+    // (the curl-consistent linear beam and most mode sets, or if the last field did not).
+    const bool fill = !p->allow_fact || p->fact_test_only || beam == 3 || (beam == 0 && consistent);
+    if (fill) SC_TRY(p->tab64.reserve(sizeof(double) * 8 * (size_t)n_k * p->n_tot, p->alloc));
     SC_TRY(reserve_power(p));
-    HIP_TRY(launch_tables_beam(st, n_k, p->n_surf, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
-                               p->nrm.as<double>(), p->wgt.as<double>(), p->tan.as<double>(), beam, w0, pol_angle,
-                               dspec, consistent ? 1 : 0, modes, n_modes, p->tab64.as<double>(), kb,
-                               p->allow_fact ? &out : nullptr, p->d_power.as<double>() + n_k, p->d_power.as<double>()));
+    SC_TRY(launch_beam(p, fill ? p->tab64.as<double>() : nullptr, p->allow_fact ? &out : nullptr, true));
+    p->tab64_unfilled = !fill;
     p->has_power = true;
     ev_record(p, EV_PREP1);
     p->ev_prep = p->ctx->profiling;
@@ -830,6 +867,7 @@ extern "C" sc_status sc_get_incident_power(const sc_prob *p, double *P)
 static sc_status scale_tables(sc_prob *p, const std::vector<double> &fac)
 {
     SC_TRY(settle_factoring(p));
+    SC_TRY(ensure_tab64(p));
     hipStream_t st = p->ctx->stream;
     const int n_k = (int)p->k.size();
     DevBuf dfac;
@@ -1110,6 +1148,7 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
     } else if (prec == SC_FP32_SPLIT) {
         if (!p->tab32_ok) {
             if (!build) return fail(SC_E_STATE, "%s", not_built);
+            SC_TRY(ensure_tab64(p));
             SC_TRY(p->tab32.reserve(sizeof(float) * 8 * nrec, p->alloc));
             HIP_TRY(launch_tables_cast(st, n_k, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
                                        p->tab64.as<double>(), nullptr, p->tab32.as<float>(), 0));
@@ -1119,6 +1158,7 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
     } else if (prec == SC_FP32) {
         if (!p->tab32n_ok) {
             if (!build) return fail(SC_E_STATE, "%s", not_built);
+            SC_TRY(ensure_tab64(p));
             SC_TRY(p->tab32n.reserve(sizeof(float) * 8 * nrec, p->alloc));
             HIP_TRY(launch_tables_cast(st, n_k, p->n_tot, p->d_k.as<double>(), p->pos64.as<double>(),
                                        p->has_tab64 ? p->tab64.as<double>() : nullptr, p->tab32.as<float>(),
@@ -1127,6 +1167,8 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
         }
         *tab = p->tab32n.p;
     } else {
+        if (p->tab64_unfilled && !build) return fail(SC_E_STATE, "%s", not_built);
+        SC_TRY(ensure_tab64(p));
         *tab = p->tab64.p;
     }
     return SC_OK;

@@ -198,6 +198,14 @@ struct sc_prob {
     bool has_tab = false, tab32_ok = false, tab32n_ok = false;
     bool keep_fp64 = true, has_tab64 = false;
     sc::DevBuf tab64, tab32, tab32n;
+    // the FP64 tables of a built-in beam that factors are not written until something reads them: the
+    // factored ones come straight from the beam (has_tab64 holds, tab64 is unfilled; `beam` forms it)
+    bool tab64_unfilled = false;
+    struct {
+        int kind = 0, consistent = 0, n_modes = 0, kb = 0;
+        double w0 = 0.0, pol = 0.0;
+        bool spectrum = false;
+    } beam;
     // factored tables (current Jt = u s with a real direction u per node), built from tab64: the
     // test runs once per table set (fact_ok: FP32 split tolerance, fact64_ok: FP64 tolerance), the
     // FP32 (tabf, posf, betaf, and tabp: s in polar form) and FP64 (tabf64, posf64, betaf64) tables

@@ -31,7 +31,7 @@ hipError_t launch_tables_from_fields(hipStream_t st, int n_k, int n_surf, int n_
 // C_{p,l} (including 1 / w0), unused; unused for the other beams)
 constexpr int SC_LG_RECORD = 8;
 // With `out` the factored tables and their test in the same pass (see FactorOut); kb: the frequency where
-// |Jt| is expected largest, k |amplitude|.
+// |Jt| is expected largest, k |amplitude|.  With `out`, tab64 may be NULL; part and P (the power) may be.
 struct FactorOut;
 hipError_t launch_tables_beam(hipStream_t st, int n_k, int n_surf, int n_tot, const double *k, const double *pos64,
                               const double *nrm, const double *wgt, const double *tan, int beam, double w0, double pol,

@@ -691,7 +691,8 @@ __device__ __forceinline__ double wave_sum_63(double x)
 // record at the host's guess of the largest, kb = argmax k |amplitude| (exact for a beam whose shape does
 // not depend on the frequency), which is formed first; the largest |Jt| and the residuals are
 // collected on the way and compared at the end.  Where the guess proves bad (less than half of the largest
-// |Jt|), the pass is made again from the true one.
+// |Jt|), the pass is made again from the true one.  tab64 may be NULL (the FP64 tables not kept: @BEAM32@),
+// and so may part and P.
 constexpr int BEAM_PARTS = 8;
 template <int beam, bool TEST>
 __global__ void __launch_bounds__(64 * BEAM_PARTS) __attribute__((amdgpu_waves_per_eu(2)))
@@ -726,7 +727,7 @@ k_tables_beam(int n_k, int n_surf, int n_tot, const double *__restrict__ kv, con
         double sp, cp;
         sincos(phase_mod_2pi(k, path), &sp, &cp);
         write_record(v, rim, k, W, n, t, E, B, {cp, sp});
-        if (store_power) {
+        if (store_power && power) {
             const double sum = wave_sum_63(flux_w * flux_minus_z(E, B));
             if (lane == 63) power[(size_t)kk * gridDim.x + blockIdx.x] = sum;
         }
@@ -751,7 +752,7 @@ k_tables_beam(int n_k, int n_surf, int n_tot, const double *__restrict__ kv, con
             for (int kk = part; kk < n_k; kk += parts) {
                 record(kk, v, true);
                 const int64_t rec = (int64_t)kk * n_tot + q;
-                store_records(tab64 + ((int64_t)kk * n_tot + q4) * 8, n4, v);
+                if (tab64) store_records(tab64 + ((int64_t)kk * n_tot + q4) * 8, n4, v);
                 const double k = kv[kk], m = current2(v);
                 if (m > best) {
                     best = m;
@@ -975,7 +976,7 @@ hipError_t launch_tables_beam(hipStream_t st, int n_k, int n_surf, int n_tot, co
     default: SC_BEAM(3, true); break;
     }
 #undef SC_BEAM
-    hipLaunchKernelGGL(k_power_finish, dim3(n_k), dim3(256), 0, st, (int)nb, part, P);
+    if (part) hipLaunchKernelGGL(k_power_finish, dim3(n_k), dim3(256), 0, st, (int)nb, part, P);
     return hipGetLastError();
 }
 
