@@ -156,8 +156,8 @@ __device__ __forceinline__ void write_record(double *__restrict__ rec, bool rim,
         J[1] = {n[2] * B[0].re - n[0] * B[2].re, n[2] * B[0].im - n[0] * B[2].im};
         J[2] = {n[0] * B[1].re - n[1] * B[0].re, n[0] * B[1].im - n[1] * B[0].im};
         rho = {n[0] * E[0].re + n[1] * E[1].re + n[2] * E[2].re, n[0] * E[0].im + n[1] * E[1].im + n[2] * E[2].im};
-        const double cJ = 2.0 * k * W / FOUR_PI;   // Jt = i cJ J P
-        const double cR = 2.0 * W / FOUR_PI;       // rho_t = cR rho P
+        const double cR = 2.0 * W / FOUR_PI;   // rho_t = cR rho P
+        const double cJ = k * cR;              // Jt = i cJ J P
         for (int c = 0; c < 3; ++c) {
             c64 v = cmul(J[c], P);
             rec[2 * c + 0] = -cJ * v.im;
@@ -523,7 +523,9 @@ __device__ __forceinline__ FactorDir factor_dir(const double *v, double m, doubl
 }
 
 // s of the record v, and the squared residuals of the current (r2) and of the tied charge (t2).
-__device__ __forceinline__ c64 factor_record(const double *v, double k, const FactorDir &d, double &r2, double &t2)
+// (ik = 1 / k)
+__device__ __forceinline__ c64 factor_record(const double *v, double k, double ik, const FactorDir &d, double &r2,
+                                             double &t2)
 {
     c64 s;
     if (d.current) s = {d.u[0] * v[0] + d.u[1] * v[2] + d.u[2] * v[4], d.u[0] * v[1] + d.u[1] * v[3] + d.u[2] * v[5]};
@@ -534,7 +536,7 @@ __device__ __forceinline__ c64 factor_record(const double *v, double k, const Fa
         r2 += dr * dr + di * di;
     }
     // rho_t + i beta s / k
-    const double tr = v[6] - d.beta * s.im / k, ti = v[7] + d.beta * s.re / k;
+    const double bk = d.beta * ik, tr = v[6] - bk * s.im, ti = v[7] + bk * s.re;
     t2 = tr * tr + ti * ti;
     return s;
 }
@@ -598,12 +600,12 @@ __global__ void k_tables_factor(int n_k, int n_tot, const double *__restrict__ k
     int kb = 0;
     for (int kk = 0; kk < n_k; ++kk) {
         const double *v = tab64 + ((int64_t)kk * n_tot + gq) * 8;
-        const double m = current2(v), k = kv[kk];
+        const double m = current2(v), ik = 1.0 / kv[kk];
         if (m > best) {
             best = m;
             kb = kk;
         }
-        bestr = fmax(bestr, v[6] * v[6] + v[7] * v[7] + m / (k * k));
+        bestr = fmax(bestr, v[6] * v[6] + v[7] * v[7] + m * (ik * ik));
     }
     const FactorDir dir = factor_dir(tab64 + ((int64_t)kb * n_tot + gq) * 8, best, kv[kb]);
     const double lim32 = o.tol32 * o.tol32 * best, lim64 = o.tol64 * o.tol64 * best;
@@ -613,7 +615,7 @@ __global__ void k_tables_factor(int n_k, int n_tot, const double *__restrict__ k
         const int64_t rec = (int64_t)kk * n_tot + gq;
         const double *v = tab64 + rec * 8;
         double r2, t2;
-        const c64 s = factor_record(v, kv[kk], dir, r2, t2);
+        const c64 s = factor_record(v, kv[kk], 1.0 / kv[kk], dir, r2, t2);
         if (!(r2 <= lim32)) flags |= 1u;
         if (!(r2 <= lim64)) flags |= 2u;
         if (!(t2 <= rlim32)) flags |= 4u;
@@ -753,14 +755,14 @@ k_tables_beam(int n_k, int n_surf, int n_tot, const double *__restrict__ kv, con
                 record(kk, v, true);
                 const int64_t rec = (int64_t)kk * n_tot + q;
                 if (tab64) store_records(tab64 + ((int64_t)kk * n_tot + q4) * 8, n4, v);
-                const double k = kv[kk], m = current2(v);
+                const double k = kv[kk], ik = 1.0 / k, m = current2(v);
                 if (m > best) {
                     best = m;
                     kbest = kk;
                 }
-                bestr = fmax(bestr, v[6] * v[6] + v[7] * v[7] + m / (k * k));
+                bestr = fmax(bestr, v[6] * v[6] + v[7] * v[7] + m * (ik * ik));
                 double r2, t2;
-                const c64 s = factor_record(v, k, dir, r2, t2);
+                const c64 s = factor_record(v, k, ik, dir, r2, t2);
                 r2max = fmax(r2max, r2);
                 t2max = fmax(t2max, t2);
                 nan |= (r2 != r2 ? 3 : 0) | (t2 != t2 ? 12 : 0);
