@@ -1451,20 +1451,22 @@ sc_status sc::run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec,
 {
     hipStream_t st = c->stream;
     unsigned int *counter = c->counter.as<unsigned int>();
-    std::vector<QuadJob> order;   // the mm jobs first
-    order.reserve(jobs.size());
-    int64_t tiles[2] = {0, 0};
+    // the mm jobs first, those of long tiles before those of short ones
+    std::vector<QuadJob> order(jobs);
+    std::stable_sort(order.begin(), order.end(), [](const QuadJob &a, const QuadJob &b) {
+        return a.mm && b.mm ? a.chunk > b.chunk : (a.mm != 0) > (b.mm != 0);
+    });
+    int64_t tiles[2] = {0, 0};   // of each XCD by the mm launch; of the other
     int n_mm = 0;
-    for (int plain = 0; plain < 2; ++plain)
-        for (auto &j : jobs) {
-            if ((j.mm == 0) != (plain == 1)) continue;
-            j.tile0 = tiles[plain];
-            tiles[plain] += j.n_tiles;
-            n_mm += 1 - plain;
-            order.push_back(j);
-        }
-    if (tiles[0] + tiles[1] >= (1LL << 31) - (1LL << 24))
-        return fail(SC_E_UNSUPPORTED, "evaluate: too many tiles (%lld)", (long long)(tiles[0] + tiles[1]));
+    for (auto &j : order) {
+        int64_t &t = tiles[j.mm ? 0 : 1];
+        j.tile0 = t;
+        t += j.mm ? mm_tiles_per_xcd(j) : j.n_tiles;
+        n_mm += j.mm != 0;
+    }
+    if (QUAD_SEGMENTS * tiles[0] + tiles[1] >= (1LL << 31) - (1LL << 24))
+        return fail(SC_E_UNSUPPORTED, "evaluate: too many tiles (%lld)",
+                    (long long)(QUAD_SEGMENTS * tiles[0] + tiles[1]));
     const int n_plain = (int)jobs.size() - n_mm;
     if (jobs.size() > 1) {
         SC_TRY(c->jobs.reserve(sizeof(QuadJob) * jobs.size()));
@@ -1476,7 +1478,7 @@ sc_status sc::run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec,
         HIP_TRY(hipEventRecord(c->upload_done, st));
     }
     if (timed) ev_record(timed, EV_Q0);
-    if (n_mm == 1 && n_plain == 0) HIP_TRY(launch_quad_mm_one(st, order[0].mm, order[0], tiles[0]));
+    if (n_mm == 1 && n_plain == 0) HIP_TRY(launch_quad_mm_one(st, order[0].mm, order[0]));
     else if (n_mm) HIP_TRY(launch_quad_mm(st, order[0].mm, c->jobs.as<QuadJob>(), n_mm, tiles[0]));
     if (n_plain)
         HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
@@ -1588,7 +1590,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     // frequencies k0 ... k0 + n - 1 and points o0 ... o0 + n_o - 1 of one job
     auto enqueue = [&](int k0, int o0, int n_o) -> sc_status {
         if (job.mm) {
-            HIP_TRY(launch_quad_mm_one(st, job.mm, job, job.n_tiles));
+            HIP_TRY(launch_quad_mm_one(st, job.mm, job));
         } else {
             HIP_TRY(launch_quad(st, mode_of(prec), l.obs_per_lane, l.freq_per_lane, l.waves_per_block,
                                 quad_grid(p->ctx, prec, l, job.n_tiles), job, nullptr, 1, job.n_tiles, counter));

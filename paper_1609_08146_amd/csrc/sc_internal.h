@@ -97,8 +97,10 @@ inline size_t mm_table_bytes(int n_k, int n_c, int form)
 }
 hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const double *k, double scale, const float *ctab,
                             const float *pos, float *mscale, void *mtab);
-hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job, int64_t n_tiles);
-hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t n_tiles);
+// (jobs whose tile0 counts the tiles that each XCD has before them; `per`: what it has in all)
+inline int64_t mm_tiles_per_xcd(const QuadJob &j) { return (j.n_tiles + QUAD_SEGMENTS - 1) / QUAD_SEGMENTS; }
+hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job);
+hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t per);
 // (and in E2, B2 where given)
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
                          const double *k, int b_over_k, int n_obs, int o0, void *E, void *B, void *E2, void *B2);

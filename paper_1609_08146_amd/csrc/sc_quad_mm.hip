@@ -235,12 +235,16 @@ __device__ __forceinline__ void tile_mm(cjob *job, int chunk, int pg, int kb, fl
 
 // One workgroup per tile: 128 points (32 per wave) x F frequencies x one chunk of nodes, the four waves
 // reading the same table rows through L1.  Tiles run points fastest; workgroups go to the 8 XCDs in turn,
-// so each XCD takes a contiguous eighth of the tiles and its L2 serves the rows that they share.
-// (job_tile: tile t of the launch, which is one of this job's.)
+// and each XCD takes a contiguous eighth of every job's tiles, so that its L2 serves the rows that they
+// share.  (An eighth of the tiles of all jobs together, whose tiles are of 64 to 256 nodes, left XCDs idle:
+// eight problems 3.06 ms, now 2.41.)  job_tile: the XCD's i-th tile of the launch, which is one of this job's.
 template <int F>
-__device__ __forceinline__ void job_tile(cjob *job, int64_t t, float m1)
+__device__ __forceinline__ void job_tile(cjob *job, int64_t i, float m1)
 {
-    const int64_t local = t - job->tile0 + job->tile_offset;
+    const int64_t eighth = (job->n_tiles + QUAD_SEGMENTS - 1) / QUAD_SEGMENTS;
+    const int64_t t = eighth * (blockIdx.x % QUAD_SEGMENTS) + i - job->tile0;
+    if (t >= job->n_tiles) return;
+    const int64_t local = t + job->tile_offset;
     const int pgs = job->n_obs_pad / 128;
     const int pg = (int)(local % pgs);
     const int64_t rest = local / pgs;
@@ -260,16 +264,13 @@ __device__ __forceinline__ void job_tile(cjob *job, int64_t t, float m1)
     }
 }
 
-// The tiles of this workgroup: its XCD's eighth from its own place on.
-#define SC_MM_TILES(t)                                                                              \
-    const int64_t per = (n_tiles + QUAD_SEGMENTS - 1) / QUAD_SEGMENTS;                              \
-    const int64_t end = min(n_tiles, per * (int64_t)(blockIdx.x % QUAD_SEGMENTS + 1));              \
-    for (int64_t t = per * (int64_t)(blockIdx.x % QUAD_SEGMENTS) + blockIdx.x / QUAD_SEGMENTS; t < end; \
-         t += gridDim.x / QUAD_SEGMENTS)
+// The tiles of this workgroup: its XCD's `per` from its own place on.
+#define SC_MM_TILES(t) \
+    for (int64_t t = blockIdx.x / QUAD_SEGMENTS; t < per; t += gridDim.x / QUAD_SEGMENTS)
 
 // One job, which travels as the kernel's first argument and is read where it lies.
 template <int F>
-__global__ void __launch_bounds__(256) k_quad_mm_one(QuadJob, int64_t n_tiles, float m1)
+__global__ void __launch_bounds__(256) k_quad_mm_one(QuadJob, int64_t per, float m1)
 {
     cjob *job = (cjob *)__builtin_amdgcn_kernarg_segment_ptr();
     SC_MM_TILES(t) job_tile<F>(job, t, m1);
@@ -278,7 +279,7 @@ __global__ void __launch_bounds__(256) k_quad_mm_one(QuadJob, int64_t n_tiles, f
 // Tiles of several jobs.
 template <int F>
 __global__ void __launch_bounds__(256)
-k_quad_mm(const QuadJob *__restrict__ jobs_, int n_jobs, int64_t n_tiles, float m1)
+k_quad_mm(const QuadJob *__restrict__ jobs_, int n_jobs, int64_t per, float m1)
 {
     cjob *jobs = (cjob *)jobs_;
     SC_MM_TILES(t) {
@@ -464,27 +465,28 @@ hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const do
     return hipGetLastError();
 }
 
-static unsigned int mm_grid(int64_t n_tiles)
+static unsigned int mm_grid(int64_t per)
 {
-    const int64_t grid = (n_tiles + QUAD_SEGMENTS - 1) / QUAD_SEGMENTS * QUAD_SEGMENTS;
+    const int64_t grid = per * QUAD_SEGMENTS;
     return (unsigned int)(grid < (1 << 20) ? grid : (1 << 20));
 }
 
-hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job, int64_t n_tiles)
+hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job)
 {
-    const dim3 g(mm_grid(n_tiles)), b(256);
-    if (fpb == 4) hipLaunchKernelGGL((k_quad_mm_one<4>), g, b, 0, st, job, n_tiles, -1.0f);
-    else if (fpb == 2) hipLaunchKernelGGL((k_quad_mm_one<2>), g, b, 0, st, job, n_tiles, -1.0f);
-    else hipLaunchKernelGGL((k_quad_mm_one<1>), g, b, 0, st, job, n_tiles, -1.0f);
+    const int64_t per = mm_tiles_per_xcd(job);
+    const dim3 g(mm_grid(per)), b(256);
+    if (fpb == 4) hipLaunchKernelGGL((k_quad_mm_one<4>), g, b, 0, st, job, per, -1.0f);
+    else if (fpb == 2) hipLaunchKernelGGL((k_quad_mm_one<2>), g, b, 0, st, job, per, -1.0f);
+    else hipLaunchKernelGGL((k_quad_mm_one<1>), g, b, 0, st, job, per, -1.0f);
     return hipGetLastError();
 }
 
-hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t n_tiles)
+hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t per)
 {
-    const dim3 g(mm_grid(n_tiles)), b(256);
-    if (fpb == 4) hipLaunchKernelGGL((k_quad_mm<4>), g, b, 0, st, jobs, n_jobs, n_tiles, -1.0f);
-    else if (fpb == 2) hipLaunchKernelGGL((k_quad_mm<2>), g, b, 0, st, jobs, n_jobs, n_tiles, -1.0f);
-    else hipLaunchKernelGGL((k_quad_mm<1>), g, b, 0, st, jobs, n_jobs, n_tiles, -1.0f);
+    const dim3 g(mm_grid(per)), b(256);
+    if (fpb == 4) hipLaunchKernelGGL((k_quad_mm<4>), g, b, 0, st, jobs, n_jobs, per, -1.0f);
+    else if (fpb == 2) hipLaunchKernelGGL((k_quad_mm<2>), g, b, 0, st, jobs, n_jobs, per, -1.0f);
+    else hipLaunchKernelGGL((k_quad_mm<1>), g, b, 0, st, jobs, n_jobs, per, -1.0f);
     return hipGetLastError();
 }
 

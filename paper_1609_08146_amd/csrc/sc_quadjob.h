@@ -36,7 +36,7 @@ struct QuadJob {
     int mm;               // compacted FP32 split form: the sum is taken by k_quad_mm (tiles of 128 points)
     int form;             // mm: CompactForm of the packed rows
     float scale;          // mm: power of two near the focal length
-    int64_t tile0;        // first global tile of this job in the launch
+    int64_t tile0;        // first global tile of this job in the launch (mm: of each XCD's)
     int64_t tile_offset;  // first job-local tile covered (a launch may cover a sub-range)
     int64_t n_tiles;      // tiles covered by this launch
 };

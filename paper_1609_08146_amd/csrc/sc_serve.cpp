@@ -386,7 +386,7 @@ static sc_status launch_quantum(sc_server *s)
         j.tile_offset = r->cursor;
         j.n_tiles = n;
         jobs.push_back(j);
-        total += n;
+        total += j.mm ? mm_tiles_per_xcd(j) : n;
         evals += (int64_t)(n * per_tile);
         r->cursor += n;
         if (r->cursor == r->job.n_tiles) finals.push_back(r);
