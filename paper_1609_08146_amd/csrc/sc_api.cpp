@@ -1322,7 +1322,7 @@ static CompactLayout compact_layout(const sc_prob *p, sc_precision prec, const C
     const size_t tab_bytes = up(rs * 8 * n_k * n_c);
     c.tab = 0;
     c.scale = mm ? up(mm_table_bytes((int)n_k, (int)n_c, plan.form)) : tab_bytes;
-    c.pos = c.scale + (mm ? up(sizeof(float) * 16 * n_k) : 0);
+    c.pos = c.scale + (mm ? up(mm_scale_bytes((int)n_k)) : 0);
     c.hinv = c.pos + up(rs * 4 * (n_c + 7));
     c.bytes = c.hinv + up(rs * (mm ? 4 : 1) * (n_c + 7));
     c.wrad = 0;
@@ -1623,7 +1623,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     const size_t row_bytes = sizeof(double) * (size_t)compact_rows_doubles(plan, p->n_phi);
     // compacted records, and in the FP32 form their packed rows and scales
     const size_t rec_bytes = rs * 8 * (size_t)plan.n_c;
-    const size_t tab_bytes = rec_bytes + (f64 ? 0 : mm_table_bytes(1, plan.n_c, plan.form) + sizeof(float) * 16);
+    const size_t tab_bytes = rec_bytes + (f64 ? 0 : mm_table_bytes(1, plan.n_c, plan.form) + mm_scale_bytes(1));
     const size_t n_chunks = (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk);
     const size_t part_bytes = rs * 12 * n_chunks;   // per frequency and padded point
     const size_t left = off + 2048 < SC_NOALLOC_SCRATCH_BYTES ? SC_NOALLOC_SCRATCH_BYTES - off - 2048 : 0;
@@ -1639,7 +1639,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     char *ctab = take(rec_bytes * per_k), *mtab = nullptr, *mscale = nullptr;
     if (!f64) {
         mtab = take(mm_table_bytes(per_k, plan.n_c, plan.form));
-        mscale = take(sizeof(float) * 16 * (size_t)per_k);
+        mscale = take(mm_scale_bytes(per_k));
     }
     char *part = take(part_bytes * per_k * per_o);
     HIP_TRY(launch_compact_geometry(st, plan, p->n_r, p->n_phi, p->f, p->d_r.as<double>(), wrad, wang, f64, cpos, chinv));

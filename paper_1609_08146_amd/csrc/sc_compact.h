@@ -36,6 +36,8 @@ constexpr int form_rows(int form) { return form == FORM_GH ? 1 : 2; }
 
 constexpr int MM_CHUNK_MAX = 256;   // nodes per chunk of the FP32 sum
 
+constexpr int COMPACT_MAX_SPLIT = 8;
+
 struct CompactPlan {
     int rows;                               // interpolation rows in theta > 0
     int fold;                               // n_phi is even: phi + pi is a grid point too

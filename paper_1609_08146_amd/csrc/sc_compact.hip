@@ -24,6 +24,18 @@ typedef double d2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ double cheb_point(int j, int n) { return cospi((double)(2 * j + 1) / (double)(2 * n)); }
 
+// The row that x belongs to: start[m] <= x < start[m + 1].
+__device__ __forceinline__ int row_of(const int32_t *start, int rows, int x)
+{
+    int lo = 0, hi = rows - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (start[mid] <= x) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
 // Blocks of 64: first one per radius (radial weights), then the angular weights (one block per (16
 // columns of a row, 64 phi)), then the compacted nodes.  Latency of a few sines each: 1.1e6 angular
 // weights (400 phi, 2 700 nodes) took 67 us with one block for all phi of 16 columns.
@@ -73,8 +85,7 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     b -= n_i;
     if (b < n_a) {
         const int pt = b / n_g, j0 = (b - pt * n_g) * GEOM_PHI, j1 = min(j0 + GEOM_PHI, n_j);
-        int m = 0;
-        while (plan.poff[m + 1] <= 16 * pt) ++m;
+        const int m = row_of(plan.poff, rows, 16 * pt);
         const int P = plan.cols[m], p0 = 16 * pt - plan.poff[m], pp = (P + 15) / 16 * 16;
         double *w = wang + (size_t)plan.poff[m] * n_j;
         const int p = p0 + (lane & 15);
@@ -82,11 +93,12 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
             double d = 0.0;
             if (p < P) {
                 // sin(P x / 2) / (P sin(x / 2)) at x = 2 pi (j / n_phi - p / P), + pi for theta < 0, on exact integers
+                // (the plan keeps n_j P below 4e6)
                 const int j = jj < n_phi ? jj : jj - n_phi;
-                const int64_t np = (int64_t)n_phi * P, a = 2 * ((int64_t)j * P - (int64_t)p * n_phi) + (jj < n_phi ? 0 : np);
-                if (a % (2 * np) == 0) d = 1.0;
+                const int np = n_phi * P, a = 2 * (j * P - p * n_phi) + (jj < n_phi ? 0 : np);
+                if (a == 0 || a == 2 * np) d = 1.0;
                 else if (P < n_j)
-                    d = sinpi((double)(a % (4 * (int64_t)n_phi)) / (double)(2 * n_phi)) /
+                    d = sinpi((double)(a % (4 * n_phi)) / (double)(2 * n_phi)) /
                         (P * sinpi((double)a / (2.0 * (double)np)));
             }
             w[(size_t)jj * pp + p] = d;
@@ -97,8 +109,7 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     const int q = 64 * b + lane;
     if (q >= (plan.n_c + 7) / 8 * 8) return;
     const int qn = min(q, plan.n_c - 1);   // up to a multiple of 8 the last node again
-    int m = 0;
-    while (plan.off[m + 1] <= qn) ++m;
+    const int m = row_of(plan.off, rows, qn);
     const double th = plan.theta_max * (asin(plan.alpha * cheb_point(m, 2 * rows)) / plan.beta);
     const double rr = 2.0 * f * tan(0.5 * th);
     double s, c;
@@ -256,7 +267,9 @@ constexpr int COLS_KP = 4;   // pairs of frequencies per wave
 // reals, and the angular weights serve the 4 products of a wave.  Latency of the T loads is what
 // bounds it: with one wave for all phi and two steps in flight it took 135 us at 128 frequencies and
 // 130-200 us at 5 to 30, where there are few workgroups.
-template <typename OT, bool SPLIT, bool FOLD>
+// (SP: the radii's parts, rounded up to a power of two; they are loaded together and added, past the last
+// one that one again.  One after the other took 48 us for 5 parts at 12 frequencies.)
+template <typename OT, int SP, bool FOLD>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4)))
 k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ wang, const double *__restrict__ T,
                OT *__restrict__ out)
@@ -265,8 +278,7 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, kq = lane >> 4, col = lane & 15, c = col & 7;
     const int rows = plan.rows, split = plan.split;
     const int b = blockIdx.x;
-    int m = 0;
-    while (plan.poff[m + 1] <= 16 * b) ++m;
+    const int m = row_of(plan.poff, rows, 16 * b);
     const int P = plan.cols[m], p0 = 16 * b - plan.poff[m], pp = (P + 15) / 16 * 16;
     const double *w = wang + (size_t)plan.poff[m] * (S * n_phi) + p0 + col;
     const int kbase = blockIdx.y * 2 * COLS_KP + (col >> 3);
@@ -289,9 +301,12 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
             const double a = j0 + kq < n_phi ? we[(size_t)j * pp] : 0.0;
 #pragma unroll
             for (int g = 0; g < COLS_KP; ++g) {
-                double v = src[g][off + (size_t)j * 8];
-                if constexpr (SPLIT)
-                    for (int s = 1; s < split; ++s) v += src[g][off + s * pstride + (size_t)j * 8];
+                double part[SP];
+#pragma unroll
+                for (int s = 0; s < SP; ++s) part[s] = src[g][off + min(s, split - 1) * pstride + (size_t)j * 8];
+                double v = part[0];
+#pragma unroll
+                for (int s = 1; s < SP; ++s) v += s < split ? part[s] : 0.0;
                 acc[g] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, v, acc[g], 0, 0, 0);
             }
         }
@@ -347,8 +362,10 @@ hipError_t launch_compact_tables(hipStream_t st, const CompactPlan &plan, int n_
     do {                                                      \
         if (fact) SC_COMPACT_ROWS(R, true, FO);               \
         else SC_COMPACT_ROWS(R, false, FO);                   \
-        if (plan.split > 1) SC_COMPACT_COLS(R, true, FO);     \
-        else SC_COMPACT_COLS(R, false, FO);                   \
+        if (plan.split > 4) SC_COMPACT_COLS(R, 8, FO);        \
+        else if (plan.split > 2) SC_COMPACT_COLS(R, 4, FO);   \
+        else if (plan.split > 1) SC_COMPACT_COLS(R, 2, FO);   \
+        else SC_COMPACT_COLS(R, 1, FO);                       \
     } while (0)
     if (is_f64 && plan.fold) SC_COMPACT(double, true);
     else if (is_f64) SC_COMPACT(double, false);

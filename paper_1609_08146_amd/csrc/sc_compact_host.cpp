@@ -215,10 +215,11 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     // J~ |r_s| (1 + delta / |r_s|); the columns that r' multiplies need one part of two below q = 1/100.
     plan.form = q <= 1e-3 && q <= 1e-9 * in.k_min * in.f ? FORM_NEAR : q <= 0.01 ? FORM_GH : FORM_GH_FAR;
     plan.scale = std::ldexp(1.0, std::ilogb(in.f));
-    // The radii's sum: cut until there are about 1024 waves of it, at least 32 radii each.
+    // The radii's sum: cut until there are about 1024 waves of it, at least 32 radii each, at most 8 parts.
     const int tiles = plan.fold ? (in.n_phi / 2 + 15) / 16 * ((rows + 15) / 16) : (in.n_phi + 15) / 16 * ((2 * rows + 15) / 16);
     const int64_t waves = (int64_t)in.n_k * tiles;
-    plan.split = (int)std::max<int64_t>(1, std::min<int64_t>((1024 + waves - 1) / waves, (in.n_r + 1) / 32));
+    plan.split = (int)std::max<int64_t>(
+        1, std::min<int64_t>({(1024 + waves - 1) / waves, (in.n_r + 1) / 32, (int64_t)COMPACT_MAX_SPLIT}));
     if ((double)n_pad * own > 4e6 || (double)rows * in.n_r > 4e6 ||
         (double)plan.split * rows * in.n_phi > 1e6)   // far outside: keep the sizes below in range
         return false;

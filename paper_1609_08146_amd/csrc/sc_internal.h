@@ -95,6 +95,7 @@ inline size_t mm_table_bytes(int n_k, int n_c, int form)
 {
     return (size_t)n_k * ((n_c + form_nodes(form) - 1) / form_nodes(form)) * 1024 * form_rows(form);
 }
+size_t mm_scale_bytes(int n_k);   // of mscale: the scales, and the maxima they come from
 hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const double *k, double scale, const float *ctab,
                             const float *pos, float *mscale, void *mtab);
 // (jobs whose tile0 counts the tiles that each XCD has before them; `per`: what it has in all)

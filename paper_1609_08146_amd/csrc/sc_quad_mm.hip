@@ -329,15 +329,16 @@ __device__ __forceinline__ void mm_columns(int form, const float *__restrict__ r
     }
 }
 
-// Powers of two that bring each column's largest entry to 2^11 ... 2^12: mscale[k][16] holds what the
-// sums are multiplied by (scale / KERNEL_SCALE).  One workgroup per frequency.
-__global__ void __launch_bounds__(1024)
-k_mm_scales(int n_c, int form, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
-            const v4f *__restrict__ pos, float *__restrict__ mscale)
+// The largest entry of each column over a part of the nodes, SCALE_PARTS workgroups per frequency (one for
+// all nodes took 11 us, now 6): mmax[k][part][10].
+constexpr int SCALE_PARTS = 8;
+__global__ void __launch_bounds__(256)
+k_mm_max(int n_c, int form, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
+         const v4f *__restrict__ pos, double *__restrict__ mmax)
 {
     const int kk = blockIdx.x;
     double mx[10] = {};
-    for (int q = threadIdx.x; q < n_c; q += 1024) {
+    for (int q = blockIdx.y * 256 + threadIdx.x; q < n_c; q += 256 * SCALE_PARTS) {
         double g[6], h[20];
         mm_columns(form, ctab + ((size_t)kk * n_c + q) * 8, pos[q], kv[kk], s, g, h);
         for (int c = 0; c < 10; ++c) {
@@ -346,20 +347,17 @@ k_mm_scales(int n_c, int form, const double *__restrict__ kv, double s, const fl
             mx[c] = fmax(mx[c], m);
         }
     }
-    __shared__ double red[16][10];
+    __shared__ double red[4][10];
     for (int c = 0; c < 10; ++c) {
         double m = mx[c];
         for (int o = 32; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o));
         if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][c] = m;
     }
     __syncthreads();
-    if (threadIdx.x < 16) {
+    if (threadIdx.x < 10) {
         double m = 0.0;
-        if (threadIdx.x < 10)
-            for (int w = 0; w < 16; ++w) m = fmax(m, red[w][threadIdx.x]);
-        // m = f 2^e with f in [0.5, 1): times 2^(12 - e)
-        const int e = m > 0.0 && m < 1e300 ? max(-100, min(100, ilogb(m) + 1)) : 12;
-        mscale[16 * (size_t)kk + threadIdx.x] = (float)(ldexp(1.0, e - 12) / KERNEL_SCALE);
+        for (int w = 0; w < 4; ++w) m = fmax(m, red[w][threadIdx.x]);
+        mmax[((size_t)kk * SCALE_PARTS + blockIdx.y) * 10 + threadIdx.x] = m;
     }
 }
 
@@ -374,7 +372,8 @@ constexpr int PACK_STEPS = 16;
 template <int FORM>
 __global__ void __launch_bounds__(256)
 k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restrict__ ctab,
-          const v4f *__restrict__ pos, const float *__restrict__ mscale, h8 *__restrict__ mtab)
+          const v4f *__restrict__ pos, const double *__restrict__ mmax, float *__restrict__ mscale,
+          h8 *__restrict__ mtab)
 {
     constexpr int NODES = form_nodes(FORM), ROWS = form_rows(FORM), Q = NODES / 2, W = 8 / Q;   // values per node
     constexpr int ALL = PACK_STEPS * NODES;
@@ -382,6 +381,19 @@ k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restr
     const int steps = (n_c + NODES - 1) / NODES, st0 = blockIdx.x * PACK_STEPS, kk = blockIdx.y;
     // per node and column: factors of H or V, then of G or V delta / |r_s|, scaled
     __shared__ float colh[20][ALL + 1], colg[12][ALL + 1];
+    // powers of two that bring each column's largest entry to 2^11 ... 2^12; mscale[k][16] holds what the sums
+    // are multiplied by (scale / KERNEL_SCALE)
+    __shared__ double inv[10];
+    if (threadIdx.x < 16) {
+        double m = 0.0;
+        if (threadIdx.x < 10)
+            for (int w = 0; w < SCALE_PARTS; ++w) m = fmax(m, mmax[((size_t)kk * SCALE_PARTS + w) * 10 + threadIdx.x]);
+        // m = f 2^e with f in [0.5, 1): times 2^(12 - e)
+        const int e = m > 0.0 && m < 1e300 ? max(-100, min(100, ilogb(m) + 1)) : 12;
+        if (threadIdx.x < 10) inv[threadIdx.x] = ldexp(1.0, 12 - e);
+        if (blockIdx.x == 0) mscale[16 * (size_t)kk + threadIdx.x] = (float)(ldexp(1.0, e - 12) / KERNEL_SCALE);
+    }
+    __syncthreads();
     if (threadIdx.x < ALL) {
         const int n = st0 * NODES + threadIdx.x;
         double g[12] = {}, h[20] = {};   // past the last node: zero
@@ -400,11 +412,10 @@ k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restr
             }
         }
         for (int c = 0; c < 10; ++c) {
-            const double inv = 1.0 / ((double)mscale[16 * (size_t)kk + c] * KERNEL_SCALE);   // a power of two
             const int gc = c < 3 ? c : c - 1;
             for (int z = 0; z < 2; ++z) {
-                colh[2 * c + z][threadIdx.x] = (float)(h[2 * c + z] * inv);
-                if (c != 3 && gc < 6) colg[2 * gc + z][threadIdx.x] = (float)(g[2 * gc + z] * inv);
+                colh[2 * c + z][threadIdx.x] = (float)(h[2 * c + z] * inv[c]);
+                if (c != 3 && gc < 6) colg[2 * gc + z][threadIdx.x] = (float)(g[2 * gc + z] * inv[c]);
             }
         }
     }
@@ -450,14 +461,18 @@ k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restr
 
 // ================================================================== launchers
 
+size_t mm_scale_bytes(int n_k) { return (size_t)n_k * (sizeof(float) * 16 + sizeof(double) * 10 * SCALE_PARTS); }
+
 hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const double *k, double scale, const float *ctab,
                             const float *pos, float *mscale, void *mtab)
 {
     const int steps = (n_c + form_nodes(form) - 1) / form_nodes(form);
     const dim3 g((steps + PACK_STEPS - 1) / PACK_STEPS, n_k), b(256);
-    hipLaunchKernelGGL(k_mm_scales, dim3(n_k), dim3(1024), 0, st, n_c, form, k, scale, ctab, (const v4f *)pos, mscale);
+    double *mmax = (double *)((char *)mscale + mm_scale_bytes(n_k)) - (size_t)n_k * SCALE_PARTS * 10;
+    hipLaunchKernelGGL(k_mm_max, dim3(n_k, SCALE_PARTS), b, 0, st, n_c, form, k, scale, ctab, (const v4f *)pos, mmax);
 #define SC_MM_PACK(FORM)                                                                              \
-    hipLaunchKernelGGL((k_mm_pack<FORM>), g, b, 0, st, n_c, k, scale, ctab, (const v4f *)pos, mscale, (h8 *)mtab)
+    hipLaunchKernelGGL((k_mm_pack<FORM>), g, b, 0, st, n_c, k, scale, ctab, (const v4f *)pos, mmax, mscale, \
+                       (h8 *)mtab)
     if (form == FORM_NEAR) SC_MM_PACK(FORM_NEAR);
     else if (form == FORM_GH) SC_MM_PACK(FORM_GH);
     else SC_MM_PACK(FORM_GH_FAR);
