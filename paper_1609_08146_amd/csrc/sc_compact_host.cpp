@@ -70,16 +70,17 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     // Which sum is faster, in us of 1024 SIMDs' cycles (measured: 1.5 cycles per direct FP32 evaluation on the
     // tied tables and 4.4 in FP64, 1.2 and 5.3 per compacted one, a quarter more for the last round of
     // tiles; the matrix instructions of the two interpolations at 32 FP64 flops per cycle) and, for small
-    // problems, the serial chain of a wave (0.3 us per node of a direct chunk) against the launches that
-    // build the tables (55 us at 64 x 64 nodes, 115 at 256 x 256).  The tables serve every evaluation until
-    // the field changes, so they count for 0.7 of one: 64 x 64 nodes and 100 points take 49 us directly, 87
-    // compacted and 33 with the tables there; 100 x 100 and 1500 points 82, 99 and 34; 256 x 256 and
-    // 400 points at 4 frequencies 199, 184 and 39.
+    // problems, the serial chain of a wave (0.3 us per node of a direct chunk) and the reduction of the chunks,
+    // against the launches that build the tables (32 us at 64 x 64 nodes, 52 at 256 x 256).  The tables
+    // serve every evaluation until the field changes, so they count for 0.7 of one: 64 x 64 nodes and 100
+    // points take 45 us directly, 61 compacted and 29 with the tables there; 100 x 100 and 1500 points at 4
+    // frequencies 98, 79 and 38; 256 x 256 and 100 points 96, 82 and 29.
     const int64_t n_tot = (int64_t)(in.n_r + 1) * in.n_phi;
     const double pts = (double)in.n_k * in.n_obs_pad, cyc = 1024.0 * 2.2e3;   // cycles per us
-    const double launches = 40.0 + 0.14 * ((double)in.n_r + in.n_phi);
-    const double chain = 0.3 * (double)std::min<int64_t>(2048, direct_chunk_nodes(n_tot, in.n_obs_pad, in.n_k, in.fp64));
-    const double direct = std::max(chain, 1.25 * pts * (double)n_tot * (in.fp64 ? 4.4 : 1.5) / cyc);
+    const double launches = 20.0 + 0.065 * ((double)in.n_r + in.n_phi);
+    const int64_t chunk = std::min<int64_t>(2048, direct_chunk_nodes(n_tot, in.n_obs_pad, in.n_k, in.fp64));
+    const double direct = std::max(0.3 * chunk, 1.25 * pts * (double)n_tot * (in.fp64 ? 4.4 : 1.5) / cyc) + 5.0 +
+                          (in.fp64 ? 0.05 : 0.035) * (double)((n_tot + chunk - 1) / chunk);
     if (direct < 0.7 * launches) return false;
     const double theta_max = 2.0 * std::atan(in.r_max / (2.0 * in.f));
     const double logeps = std::log(in.fp64 ? EPS_FP64 : EPS_FP32);
