@@ -1,0 +1,84 @@
+"""GPU: the forms of the compacted FP32 sum, and its slabs in sc_evaluate_noalloc.
+
+Which form is taken depends on q = |r'|max / f and k f (sc_compact_host.cpp): one kernel value near the
+focus, with delta by series (q <= 4e-4) or not (q <= 1e-3), G and H beyond, with the columns that r'
+multiplies in one part (q <= 1/100) or two.  Random tables on few nodes, against the oracle.
+Tolerance: the FP32 phase k delta carries a few roundings of k |r'|, so 4 k |r'| 2^-24 besides the 2e-6 that
+the split form's compacted sum is held to elsewhere.
+"""
+import numpy as np
+import pytest
+
+import workloads
+
+pytestmark = pytest.mark.gpu
+K = 2 * np.pi
+
+
+def rel_l2(a, b):
+    return float(np.linalg.norm((np.asarray(a) - np.asarray(b)).ravel()) / np.linalg.norm(np.asarray(b).ravel()))
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1609_08146_amd import Context
+    c = Context(0)
+    yield c
+    c.close()
+
+
+# q, f (wavelengths), aperture / f, frequencies, points
+FORMS = [
+    (2e-5, 1e5, 1.5, 5, 700),     # near, series
+    (7e-4, 2e5, 0.04, 3, 700),    # near, no series
+    (5e-3, 300.0, 1.0, 4, 700),   # G and H
+    (9e-3, 150.0, 2.0, 6, 130),
+    (0.08, 20.0, 1.2, 2, 700),    # G and H, r' columns in two parts
+    (0.24, 10.0, 0.8, 1, 300),
+]
+
+
+@pytest.mark.parametrize("q,f,af,nk,n", FORMS)
+def test_forms(ctx, orc, q, f, af, nk, n):
+    from paper_1609_08146_amd import Problem
+    ks = K * np.linspace(1.0, 1.1, nk)
+    rng = np.random.default_rng(n)
+    obs = rng.normal(size=(n, 3))
+    obs *= (q * f * rng.uniform(0.05, 1.0, n) / np.linalg.norm(obs, axis=1))[:, None]
+    obs[0] = 0.0, 0.0, q * f
+    nr, nphi = 150, 220
+    m = orc.mirror(f, af * f, nr, nphi)
+    Ei, Bi = workloads.random_incident_tables(nk, m.n_tot, seed=7)
+    pick = slice(None, None, max(1, n // 40))
+    Eo, Bo = orc.reflected_field(m, ks, Ei, Bi, obs[pick])
+    p = Problem(ctx)
+    p.set_mirror(f, af * f, nr, nphi)
+    p.set_frequencies(ks)
+    p.set_incident(Ei, Bi)
+    p.set_observation(obs)
+    E, B = p.evaluate("fp32_split")
+    tol = 2e-6 + 4 * ks.max() * q * f * 2.0 ** -24
+    assert max(rel_l2(E[:, pick], Eo), rel_l2(B[:, pick], Bo)) < tol
+    E, B = p.evaluate("fp64")
+    assert max(rel_l2(E[:, pick], Eo), rel_l2(B[:, pick], Bo)) < 1e-12 + 4 * ks.max() * q * f * 2.0 ** -52
+    p.close()
+
+
+@pytest.mark.parametrize("prec,n_k", [("fp32_split", 20), ("fp64", 12)])
+def test_noalloc_in_slabs(ctx, prec, n_k):
+    """What the compacted sum needs for 4160 points does not fit the scratch at once (the direct sum's
+    partials, which the documented limit counts, do)."""
+    import torch
+    from paper_1609_08146_amd import problem_from_workload
+    p = problem_from_workload(ctx, workloads.broadband(n_k=n_k, n_nodes=140))
+    E0, B0 = p.evaluate(prec)
+    ct = torch.complex64 if prec == "fp32_split" else torch.complex128
+    out = tuple(torch.zeros(E0.shape, dtype=ct, device="cuda") for _ in range(2))
+    p.evaluate_noalloc(out, prec)
+    torch.cuda.synchronize()
+    for a, b in zip(out, (E0, B0)):
+        assert np.array_equal(a.cpu().numpy(), b)
+    p.close()
