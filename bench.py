@@ -11,9 +11,15 @@ reduction, and the transform to 256 time samples, over all 128 frequencies
 (8.5e10 integrand evaluations).  ``--shard S`` keeps every S-th frequency.
 
 Prints one JSON line.  `value` is integrand evaluations per second
-(observation points x frequencies x surface nodes) of the whole step;
-`roofline` reports the quadrature kernel against the FP32 vector ALU peak,
-with its duration measured by HIP events on the library's stream;
+(observation points x frequencies x surface nodes) of the whole step.  On this
+workload the library interpolates the kernel from far fewer nodes than the
+mirror has, so that rate, and every `..._evals_per_s` of a paraboloid with host
+points, is an effective one: evaluations that the result stands for, not kernel
+values formed.  `roofline` therefore reports the kernel that does form every one,
+the direct quadrature, which general surfaces and points in device memory take
+(here the same mirror handed over as a surface: the same tables and points),
+against the FP32 vector ALU peak, with its duration measured by HIP events on
+the library's stream;
 `cpu_baseline` is the FP64 CPU oracle timed on a bounded sample of the same
 workload.
 """
@@ -170,6 +176,39 @@ def run_step(p, w, precision):
     return p
 
 
+def direct_quad(ctx, w, precision, factoring, tie, steps=4):
+    """The direct quadrature of workload `w`, its mirror handed over as a surface: best duration of
+    `steps` evaluations after one, with the rates the kernel reaches on the table layout it reads."""
+    import torch
+    from paper_1609_08146_amd import Problem
+    m = Problem(ctx)
+    m.set_mirror(w.f, w.a, w.n_r, w.n_phi)
+    xyz, nrm, wgt = m.get_nodes()
+    ns, nr = m.num_nodes()
+    m.close()
+    rim = xyz[ns:]
+    dl = np.stack([-rim[:, 1], rim[:, 0], np.zeros(nr)], axis=1) * (2 * np.pi / nr)
+    p = Problem(ctx)
+    p.set_factoring(factoring, tie_charge=tie)
+    p.set_surface(xyz[:ns], nrm[:ns] * wgt[:ns, None], rim, nrm[ns:], dl)
+    p.set_frequencies(w.k)
+    p.set_incident_gaussian(w.w0, w.pol, w.spectrum, False)
+    p.set_observation(w.obs)
+    ms = []
+    for _ in range(steps + 1):
+        p.evaluate(precision, keep_on_device=True)
+        torch.cuda.synchronize()
+        ms.append(p.timing()["quad_ms"])
+    layout, fpl = p.layout_for(precision), p.launch(precision)["freq_per_lane"]
+    p.close()
+    fp64 = precision == "fp64"
+    quad = float(np.mean(ms[1:]))
+    fpe = flops_per_eval(layout, fpl, fp64)
+    tf = fpe * w.evals / (quad * 1e-3) / 1e12
+    return {"current": layout, "quad_ms": quad, "launches": steps, "evals_per_s": w.evals / (quad * 1e-3),
+            "flops_per_eval": fpe, "tflops": tf, "frac_peak": tf / (PEAK_FP64 if fp64 else PEAK_FP32)}
+
+
 _TIME_BUF = {}
 
 
@@ -252,11 +291,6 @@ def batch_run(n_instances: int = 256, general: bool = False, tune: bool = True, 
     layouts = [p.layout_for("fp32_split") for p in probs]
     layout_evals = {lay: sum(w.evals for w, l in zip(ws, layouts) if l == lay) for lay in FLOPS}
 
-    def partial_bytes():
-        # split-K partials: 12 reals per (chunk, frequency, padded point), at the chunk each problem used
-        return sum(4 * 12 * -(-(w.n_r + 1) * w.n_phi // p.timing()["chunk"]) * w.n_k * (-(-w.n_obs // 128) * 128)
-                   for w, p in zip(ws, probs))
-
     def timed(label, launch):
         ctx.evaluate_batch(probs, "fp32_split")          # warm-up
         torch.cuda.synchronize()
@@ -265,14 +299,9 @@ def batch_run(n_instances: int = 256, general: bool = False, tune: bool = True, 
         torch.cuda.synchronize()
         dt = time.perf_counter() - t0
         quad_ms = probs[0].timing()["quad_ms"]
-        fpl = launch["freq_per_lane"]
-        flops = sum(flops_per_eval(lay, fpl) * n for lay, n in layout_evals.items())
         return {"label": label, "value": evals / dt, "seconds": dt, "quad_ms": quad_ms,
                 "quad_evals_per_s": evals / (quad_ms * 1e-3), "launch": launch,
-                "tflops": flops / (quad_ms * 1e-3) / 1e12,
-                "frac_fp32_peak": flops / (quad_ms * 1e-3) / 1e12 / PEAK_FP32,
-                "chunks_used": sorted({p.timing()["chunk"] for p in probs}),
-                "partial_bytes": partial_bytes()}
+                "chunks_used": sorted({p.timing()["chunk"] for p in probs})}
 
     # the library's batch launch: the shape of the layout carrying most evaluations, each problem's chunk
     fact_major = 2 * (layout_evals["factored"] + layout_evals["tied"]) > evals
@@ -729,8 +758,8 @@ def main():
     ms_per_step = elapsed * 1e3 / args.steps
     value = evals * args.steps / elapsed
     quad_avg = float(np.mean(quad_ms))
-    fpe = flops_per_eval(layout, launch["freq_per_lane"], args.precision == "fp64")
-    achieved = fpe * evals / (quad_avg * 1e-3) / 1e12
+    direct = direct_quad(ctx, w, args.precision, not args.general_tables, not args.no_tie)
+    progress(f"direct quadrature {direct['quad_ms']:.1f} ms")
     peak = PEAK_FP64 if args.precision == "fp64" else PEAK_FP32
     # the counters were taken on the full FP32-split workload with the default launch
     traffic = measured_traffic() if (args.precision == "fp32_split" and args.shard == 1) else None
@@ -762,19 +791,25 @@ def main():
         },
         "roofline": {
             "bound": "alu",
-            "kernel": ("k_quad (split-form surface quadrature" + (" in FP64" if args.precision == "fp64" else "")
+            "kernel": ("k_quad, the direct sum over every node, which the timed step does not take: the same "
+                       "mirror as a general surface (split-form surface quadrature"
+                       + (" in FP64" if args.precision == "fp64" else "")
                        + {"tied": ", factored current, tied charge)", "factored": ", factored current)",
-                          "general": ")"}[layout]),
-            "achieved": achieved,
+                          "general": ")"}[direct["current"]]),
+            "achieved": direct["tflops"],
             "peak": peak,
             "unit": "TFLOP/s",
-            "frac": achieved / peak,
+            "frac": direct["frac_peak"],
             "traffic": traffic,
             "traffic_unit": "bytes per launch (rocprofv3 FETCH_SIZE + WRITE_SIZE, copy-calibrated)",
-            "flops_per_eval": fpe,
-            "quad_ms_avg": quad_avg,
-            "quad_launches": len(quad_ms),
+            "flops_per_eval": direct["flops_per_eval"],
+            "quad_ms_avg": direct["quad_ms"],
+            "quad_launches": direct["launches"],
         },
+        # the step's own quadrature, over interpolation nodes
+        "compacted": {"quad_ms_avg": quad_avg, "effective_evals_per_s": evals / (quad_avg * 1e-3),
+                      "note": "sum over interpolation nodes of the kernel: the rate counts the evaluations that the "
+                              "result stands for"},
         "phases_ms": {k: last_timing[k] for k in ("prep_ms", "quad_ms", "reduce_ms", "time_ms")},
         # one step is one complete solve of the workload (set-up to time samples on the device);
         # the latency of requests of mixed sizes under load is `python bench.py --mode serve`
@@ -798,8 +833,6 @@ def main():
         torch.cuda.synchronize()
         q64 = p.timing()["quad_ms"]
         layout64 = p.layout_for("fp64")
-        fact64 = layout64 != "general"
-        fpl64 = p.launch("fp64")["freq_per_lane"]
         # error of every output component of the chosen form against the FP64 form (itself held to the
         # oracle at 1e-12 by the tests) over the whole grid: max |F_c - F_c,64| / max |F_c,64| (the
         # paper's e_rel, Sec. IV-A) and the same maximum over the peak |F| of the field
@@ -816,86 +849,36 @@ def main():
         progress(f"FP64 form {q64:.1f} ms")
         r64 = w64.evals / (q64 * 1e-3)
         rq = evals / (quad_avg * 1e-3)
-        fpg64 = flops_per_eval("general", fpl64, True)
-        f64 = flops_per_eval(layout64, fpl64, True)
         out["forms"] = {
-            "fp64": {"quad_evals_per_s": r64, "quad_ms": q64, "n_freq": w64.n_k,
-                     "current": layout64, "flops_per_eval": f64,
-                     "tflops": f64 * r64 / 1e12, "frac_fp64_peak": f64 * r64 / 1e12 / PEAK_FP64},
-            args.precision: {"quad_evals_per_s": rq, "per_component_vs_fp64": per_comp},
+            "fp64": {"effective_evals_per_s": r64, "quad_ms": q64, "n_freq": w64.n_k, "current": layout64},
+            args.precision: {"effective_evals_per_s": rq, "per_component_vs_fp64": per_comp},
             "speedup_vs_fp64": rq / r64,
         }
-        if layout == "tied":
-            # the factored current without the tied charge (a beam with a longitudinal E, such as the
-            # curl-consistent radial one, takes this layout): its quadrature on the same workload
-            qu = []
-            p = Problem(ctx)
-            p.set_factoring(True, tie_charge=False)
-            for _ in range(4):
-                run_step(p, w, args.precision)
-                torch.cuda.synchronize()
-                qu.append(p.timing()["quad_ms"])
-            fpu = flops_per_eval("factored", p.launch(args.precision)["freq_per_lane"])
-            p.close()
-            ru = evals / (min(qu[1:]) * 1e-3)
-            out["forms"]["fp32_split_factored_untied"] = {
-                "quad_evals_per_s": ru, "quad_ms": min(qu[1:]), "flops_per_eval": fpu, "tflops": fpu * ru / 1e12,
-                "frac_fp32_peak": fpu * ru / 1e12 / PEAK_FP32}
-        if layout64 == "tied":
-            # the FP64 form on the factored current without the tied charge
-            p = Problem(ctx)
-            p.set_factoring(True, tie_charge=False)
-            p.set_mirror(w64.f, w64.a, w64.n_r, w64.n_phi)
-            p.set_frequencies(w64.k)
-            p.set_incident_gaussian(w64.w0, 0.0, w64.spectrum, False)
-            p.set_observation(w64.obs)
-            p.evaluate("fp64", keep_on_device=True)
-            torch.cuda.synchronize()
-            qu64 = p.timing()["quad_ms"]
-            fpu64 = flops_per_eval("factored", p.launch("fp64")["freq_per_lane"], True)
-            p.close()
-            ru64 = w64.evals / (qu64 * 1e-3)
-            out["forms"]["fp64_factored_untied"] = {
-                "quad_evals_per_s": ru64, "quad_ms": qu64, "flops_per_eval": fpu64, "tflops": fpu64 * ru64 / 1e12,
-                "frac_fp64_peak": fpu64 * ru64 / 1e12 / PEAK_FP64}
+        # the direct quadrature by form and layout (what a general surface or device points cost)
+        out["direct"] = {args.precision + "_" + direct["current"]: direct}
+        layouts = [("tied", True, True), ("factored", True, False), ("general", False, False)]
+        for prec in (args.precision, "fp64"):
+            for name, fact, tie in layouts:
+                if prec + "_" + name in out["direct"] or (name != "general" and layout == "general"):
+                    continue
+                d = direct_quad(ctx, w, prec, fact, tie, steps=2 if prec == "fp64" else 4)
+                out["direct"][prec + "_" + d["current"]] = d
+                progress(f"direct quadrature {prec} {d['current']} {d['quad_ms']:.1f} ms")
         if factored:
-            # the same split form on the general tables (what an arbitrary incident field costs): the
-            # whole step, timed like the headline over a few steps, and its quadrature
-            qg, sg = [], []
+            # the whole step on the general tables (what an arbitrary incident field costs)
+            sg = []
             p = Problem(ctx)
             p.set_factoring(False)
             run_step(p, w, args.precision)
-            torch.cuda.synchronize()
             for _ in range(4):
+                torch.cuda.synchronize()
                 ts = time.perf_counter()
                 run_step(p, w, args.precision)
                 torch.cuda.synchronize()
                 sg.append(time.perf_counter() - ts)
-                qg.append(p.timing()["quad_ms"])
-            fpg = flops_per_eval("general", p.launch(args.precision)["freq_per_lane"])
             p.close()
-            rg = evals / (min(qg) * 1e-3)
             out["value_general_tables"] = evals / float(np.mean(sg))
-            out["forms"]["fp32_split_general_tables"] = {
-                "step_evals_per_s": evals / float(np.mean(sg)), "ms_per_step": 1e3 * float(np.mean(sg)),
-                "quad_evals_per_s": rg, "quad_ms": min(qg), "flops_per_eval": fpg, "tflops": fpg * rg / 1e12,
-                "frac_fp32_peak": fpg * rg / 1e12 / PEAK_FP32}
-        if fact64:
-            # the FP64 form on the general tables
-            p = Problem(ctx)
-            p.set_factoring(False)
-            p.set_mirror(w64.f, w64.a, w64.n_r, w64.n_phi)
-            p.set_frequencies(w64.k)
-            p.set_incident_gaussian(w64.w0, 0.0, w64.spectrum, False)
-            p.set_observation(w64.obs)
-            p.evaluate("fp64", keep_on_device=True)
-            torch.cuda.synchronize()
-            qg64 = p.timing()["quad_ms"]
-            p.close()
-            rg64 = w64.evals / (qg64 * 1e-3)
-            out["forms"]["fp64_general_tables"] = {
-                "quad_evals_per_s": rg64, "quad_ms": qg64, "tflops": fpg64 * rg64 / 1e12,
-                "frac_fp64_peak": fpg64 * rg64 / 1e12 / PEAK_FP64}
+            out["ms_per_step_general_tables"] = 1e3 * float(np.mean(sg))
 
     ctx.close()
     if args.serve_seconds > 0 and args.shard == 1:
@@ -925,7 +908,7 @@ def main():
                                     "FP32-split, FP32-only tables",
                         "instances": b["instances"], "evals": b["evals"], "setup_s": b["setup_s"],
                         "runs": [{k: r[k] for k in ("label", "quad_evals_per_s", "quad_ms", "seconds", "launch",
-                                                      "frac_fp32_peak", "partial_bytes", "tune_seconds", "tuned_on")
+                                                      "tune_seconds", "tuned_on")
                                   if k in r} for r in b["runs"]]}
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, args.cpu_seconds)

@@ -77,7 +77,10 @@ typedef enum {
  *                the per-pair remainder k(|r_s - r'| - |r_s|) is formed without
  *                cancellation and evaluated in FP32; FP32 sums over blocks of
  *                512 nodes, added into per-chunk running sums, and the chunk
- *                sums added in FP64.  Output complex64.
+ *                sums added in FP64.  Where the sum is taken over interpolation
+ *                nodes (see sc_evaluate), kernel values and tables enter the FP16
+ *                matrix instructions as sums of two FP16 numbers (22 bits), summed
+ *                in FP32 over at most 256 nodes.  Output complex64.
  *  SC_FP32       naive FP32: per-pair phase k|r_s - r'| in FP32 (an ablation;
  *                loses accuracy once k|r_s| >> 1e3).  Output complex64.
  */
@@ -116,7 +119,8 @@ sc_status sc_get_timing(const sc_prob *p, sc_timing *out);
 /* Quadrature launch shape.  Only `chunk` changes the floating-point
  * summation order (and therefore the last bits of results); the other
  * fields change speed only.  Zero fields mean "library default": 1 point per
- * lane, 4 waves per workgroup, chunks of 2048 nodes, the resident limit of
+ * lane, 4 waves per workgroup, chunks of 2048 nodes (fewer, from 64 up, where
+ * the problem's tiles would leave compute units idle), the resident limit of
  * workgroups, and frequencies per lane by table layout (4 with the factored
  * current in the FP32 forms, else 2).                                       */
 typedef struct {
@@ -319,7 +323,8 @@ sc_status sc_scale_spectrum(sc_prob *p, const double *factor);
 sc_status sc_normalize_energy(sc_prob *p, const double *eps, double e_tot, double dk);
 
 /* Table storage.  keep_fp64 = 1 (default) keeps the FP64 tables (64 B per
- * (k, node)) so every precision can be evaluated; keep_fp64 = 0 casts them to
+ * (k, node); those of a built-in beam are filled when a call first reads them)
+ * so every precision can be evaluated; keep_fp64 = 0 casts them to
  * the FP32 split tables (32 B per record) as soon as they are built and frees
  * them, halving resident memory; SC_FP64 evaluation then fails with
  * SC_E_STATE until the incident field is set again with keep_fp64 = 1.     */
@@ -411,20 +416,21 @@ sc_status sc_set_observation(sc_prob *p, const double *xyz, int n_obs, int on_de
  * nodes m (Chebyshev in the polar angle, trigonometric in phi), to the rounding
  * of the precision, so sum_n K(o, n) c_n = sum_m K(o, m) (sum_n L_m(n) c_n) with
  * the records c of any incident field: every node's record enters once, and the
- * points meet the m alone (2 700 instead of 160 400 for 4 wavelengths about the
- * focus of an f/0.67 mirror).  The library does so where |r'| <= f / 4 and it is
+ * points meet the m alone (1 800 in SC_FP32_SPLIT and 3 200 in SC_FP64 instead of
+ * 160 400 for 4 wavelengths about the focus of an f/0.67 mirror).  The library does so where |r'| <= f / 4 and it is
  * the faster way, by a rule on the problem's sizes alone; then `chunk` and
- * `freq_per_lane` change no bit, and the compacted tables (32 or 64 B per
- * frequency and m) are kept with the problem until its tables change.  Elsewhere
+ * `freq_per_lane` change no bit, and the compacted tables (64 B per frequency and m
+ * in SC_FP64, 32 B and packed rows of 256 or 512 B in SC_FP32_SPLIT) are kept with
+ * the problem until its tables change.  Elsewhere
  * (general surfaces, device points, SC_FP32, points far from the focus, small
  * meshes) the sum is taken node by node.                                    */
 sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B, int on_device);
 /* sc_evaluate for callers that cannot allocate (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): the call allocates
- * nothing, device or host.  Its scratch memory (work counters, the job
- * record, the split-K partials) is a static device array of
- * SC_NOALLOC_SCRATCH_BYTES on each GPU, which the library holds until the
- * process ends.
+ * nothing, device or host.  Its scratch memory (work counters, the split-K
+ * partials and, of a compacted sum, its tables, which it builds on each call)
+ * is a static device array of SC_NOALLOC_SCRATCH_BYTES on each GPU, which the
+ * library holds until the process ends.
  * E, B: DEVICE arrays [n_k][n_obs][3] of complex128 (SC_FP64) or complex64
  * (the FP32 forms), written by the stream work enqueued here.  Requires the
  * problem's tables of `prec` to be built (SC_E_STATE otherwise): one

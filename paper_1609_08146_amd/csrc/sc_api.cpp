@@ -1430,6 +1430,19 @@ size_t sc::footprint_bytes(int n_r, int n_phi, int n_k, int n_obs, int n_t, sc_p
     return b;
 }
 
+size_t sc::quad_bytes(const sc_prob *p, sc_precision prec, const sc_launch &l)
+{
+    const size_t per_chunk = real_size(prec) * 12 * p->k.size() * (size_t)p->n_obs_pad;
+    CompactPlan plan;
+    if (!plan_compact(p, prec, plan)) {
+        const int chunk = direct_chunk(p, prec, l.chunk);
+        return per_chunk * (size_t)((p->n_tot + chunk - 1) / chunk);
+    }
+    const size_t part = per_chunk * (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk);
+    const CompactLayout lay = compact_layout(p, prec, plan, part);
+    return std::max(part, lay.work) + lay.bytes;
+}
+
 // Workgroups of a persistent quadrature launch: the resident limit (or the launch's blocks per CU)
 // on every CU, but no more than the tiles need (one wave per tile).
 static int quad_grid(const sc_ctx *c, sc_precision prec, const sc_launch &l, int64_t n_tiles)

@@ -171,8 +171,8 @@ __device__ __forceinline__ void record_doubles(const RawRecord<R> &r, double *v)
 // terms apart.  Waves are numbered with the row tiles fastest, so that neighbours read the same records,
 // four to a workgroup, and load ROWS_DEPTH steps ahead.  Bound by the FP64 pipe: the matrix
 // instructions take 64 cycles each, and the conversion of a record (14 FP64 instructions) runs on the same
-// pipe and is not hidden behind them: 29 rows, 128 frequencies and 160 400 nodes take 0.27 ms, 41 TFLOP/s
-// of matrix work (a large FP64 product on this card: 69).  The waves-per-SIMD request keeps the accumulators in plain
+// pipe and is not hidden behind them: 25 rows (32 with the padding), 128 frequencies and 160 400 nodes take
+// 0.26 ms, 40 TFLOP/s of matrix work (a large FP64 product on this card: 69).  The waves-per-SIMD request keeps the accumulators in plain
 // registers: without it the compiler moved them through accumulation registers in every step (80 of 119
 // instructions, 0.41 ms for 0.32 without FOLD at 41 rows).
 constexpr int ROWS_DEPTH = 2;
@@ -265,8 +265,8 @@ constexpr int COLS_KP = 4;   // pairs of frequencies per wave
 // The contraction over phi: one workgroup per (row, 16 columns, 8 frequencies), its four waves each a
 // quarter of the phi, joined in LDS in a fixed order; the 16 columns of a product are 2 frequencies x 8
 // reals, and the angular weights serve the 4 products of a wave.  Latency of the T loads is what
-// bounds it: with one wave for all phi and two steps in flight it took 135 us at 128 frequencies and
-// 130-200 us at 5 to 30, where there are few workgroups.
+// bounds it: with one wave for all phi and two steps in flight it took 135 us at 128 frequencies (41 rows,
+// not folded; now 73 us, 25 rows) and 130-200 us at 5 to 30, where there are few workgroups.
 // (SP: the radii's parts, rounded up to a power of two; they are loaded together and added, past the last
 // one that one again.  One after the other took 48 us for 5 parts at 12 frequencies.)
 template <typename OT, int SP, bool FOLD>

@@ -304,5 +304,8 @@ sc_status prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb,
 sc_status run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec, const sc_launch &l, sc_prob *timed);
 // Device bytes a problem of this shape holds after an evaluate (+ time transform with n_t samples).
 size_t footprint_bytes(int n_r, int n_phi, int n_k, int n_obs, int n_t, sc_precision prec, int chunk);
+// Device bytes of the sum of p in prec: its partials and, of a compacted sum, its tables and the memory
+// they are built in.  Reads the sizes, frequencies and extent of the points of p alone.
+size_t quad_bytes(const sc_prob *p, sc_precision prec, const sc_launch &l);
 
 }  // namespace sc

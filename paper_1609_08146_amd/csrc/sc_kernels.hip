@@ -688,12 +688,13 @@ __device__ __forceinline__ double wave_sum_63(double x)
 
 // The tables of a built-in beam, and with TEST their factored form and its test in the same pass (the two
 // separate kernels wrote the FP64 tables once and read them twice: 0.51 + 0.67 ms at 128 frequencies and
-// 160 400 nodes, 3.9 GB; now 0.41 ms, 1.8 GB, at the rate of a large copy).  Workgroups of 64 nodes x blockDim.y shares of the frequencies; what
-// does not depend on the frequency is formed once per thread.  The node's direction is taken from its
+// 160 400 nodes, 3.9 GB; now 0.41 ms with the FP64 tables, 1.8 GB, at the rate of a large copy, and 0.32
+// without them, where the FP64 pipe bounds it).  Workgroups of 64 nodes x blockDim.y shares of the
+// frequencies; what does not depend on the frequency is formed once per thread.  The node's direction is taken from its
 // record at the host's guess of the largest, kb = argmax k |amplitude| (exact for a beam whose shape does
 // not depend on the frequency), which is formed first; the largest |Jt| and the residuals are
 // collected on the way and compared at the end.  Where the guess proves bad (less than half of the largest
-// |Jt|), the pass is made again from the true one.  tab64 may be NULL (the FP64 tables not kept: @BEAM32@),
+// |Jt|), the pass is made again from the true one.  tab64 may be NULL (the FP64 tables not kept),
 // and so may part and P.
 constexpr int BEAM_PARTS = 8;
 template <int beam, bool TEST>

@@ -27,10 +27,11 @@
 //
 // Bound by the vector ALU's issue: instructions with the long encoding (cvt_pk, fma_mix) take 4.4 to 4.6
 // SIMD cycles, sine and cosine 8.4, the short ones 2.4, and the matrix instructions (37 cycles each)
-// overlap only in part: a kernel value pair and its products take 18 vector and 0.75 matrix instructions, 67 +
-// 28 cycles per 64 terms, and the launch takes 95 (broadband, 1.34e9 terms in 0.86 ms; 126 with node
-// records and rows loaded where they are used).  Two waves per SIMD with the compiler's free choice of
-// registers beat three and four (1.04 and 1.20 ms).
+// overlap only in part: near the focus a kernel value and its products take 18 vector and 0.75 matrix
+// instructions, 67 + 28 cycles per 64 terms, and the launch takes 93 (128 frequencies, 4160 points and 1799
+// nodes, 9.7e8 terms with the padding, in 0.65 ms at 2.1 GHz; 126 with node records and rows loaded where
+// they are used).  Two waves per SIMD with the compiler's free choice of registers beat three and four (at
+// 2500 nodes 0.86, 1.04 and 1.20 ms).
 #include "sc_device.h"
 #include "sc_internal.h"
 

@@ -73,3 +73,22 @@ def test_alternating_factoring(ctx, orc):
                 assert np.array_equal(a, b)
         q.close()
     p.close()
+
+
+def test_a_request_is_charged_what_it_holds():
+    # 1308 interpolation nodes in chunks of 256 take six partials of 48 B per point; the mirror's 4160 nodes
+    # in the direct sum's chunks of 2048 would take three
+    from paper_1609_08146_amd import Context, Server
+    n_pts, g = 120064, np.random.default_rng(5)
+    obs = g.uniform(-3.0, 3.0, (n_pts, 3))
+    obs[:8] = 3.0 * np.array([[x, y, z] for x in (-1, 1) for y in (-1, 1) for z in (-1, 1)])
+    w = workloads.Workload(name="points", f=100.0, a=90.0, n_r=64, n_phi=64, k=np.array([2 * np.pi]),
+                           spectrum=np.array([1.0 + 0.0j]), obs=obs, w0=50.0, t=np.zeros(1), dk=1.0, meta={})
+    c = Context(0, use_torch_stream=False)
+    srv = Server(c, hbm_budget=int(1e9), max_running=2, quantum_ms=5.0)
+    try:
+        st = srv.wait(srv.submit(w, "fp32_split"))[4]
+        assert st["device_bytes"] >= n_pts * (6 * 48 + 48)
+    finally:
+        srv.close()
+        c.close()
