@@ -51,14 +51,20 @@ struct CompactPlan {
     uint16_t cols[COMPACT_MAX_ROWS];        // phi per row: odd, or the grid's own and those + pi
     int32_t off[COMPACT_MAX_ROWS + 1];      // first compacted node of each row
     int32_t poff[COMPACT_MAX_ROWS + 1];     // the same with every row's columns rounded up to 16
+    int32_t woff[COMPACT_MAX_ROWS + 1];     // and with the columns whose weights are kept (angular_kept)
 };
 
 // Working memory of the two interpolations (doubles): the radial weights [n_r + 1 rounded up to
-// 4][compact_radial_stride], the angular weights of every row [n_phi][cols rounded up to 16], and
+// 4][compact_radial_stride], the angular weights of every row [n_phi][angular_kept], and
 // the partial rows of one frequency [split][rows][n_phi][8]; with an odd n_phi, where theta < 0 needs
 // weights and partial rows of its own, [2 n_phi] and [2 rows].  The planner keeps their sum below
-// COMPACT_WORK_MAX bytes.
-constexpr int64_t COMPACT_WORK_MAX = 47 << 20;
+// COMPACT_WORK_MAX bytes, and with a frequency's tables and its partials of OBS_PAD points below
+// COMPACT_SCRATCH bytes, what an evaluation without allocation has.
+constexpr int64_t COMPACT_WORK_MAX = 47 << 20, COMPACT_SCRATCH = 63 << 20;
+// The weights of column p > P / 2 at phi are those of column P - p at -phi, another point of the grid, so
+// half the columns are kept, rounded up to 16.  (All of them were more than the scratch holds for an odd
+// n_phi of 500 and more with 5 000 nodes, which were then summed directly.)
+constexpr int angular_kept(int cols) { return (cols / 2 + 16) / 16 * 16; }
 // Even and odd part of L_m in theta, each rounded up to 16 rows; with an odd n_phi L_m and L_-m, together.
 constexpr int compact_radial_stride(const CompactPlan &p)
 {
@@ -70,7 +76,7 @@ inline int64_t compact_radial_doubles(const CompactPlan &p, int n_r)
 }
 inline int64_t compact_angular_doubles(const CompactPlan &p, int n_phi)
 {
-    return (int64_t)p.poff[p.rows] * n_phi * (p.fold ? 1 : 2);
+    return (int64_t)p.woff[p.rows] * n_phi * (p.fold ? 1 : 2);
 }
 inline int64_t compact_rows_doubles(const CompactPlan &p, int n_phi)
 {

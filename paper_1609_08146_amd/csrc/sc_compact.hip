@@ -47,7 +47,7 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
 {
     const int lane = threadIdx.x, rows = plan.rows, stride = compact_radial_stride(plan);
     const int n_j = plan.fold ? n_phi : 2 * n_phi;
-    const int n_i = (n_r + 4) / 4 * 4, n_g = (n_j + GEOM_PHI - 1) / GEOM_PHI, n_a = plan.poff[rows] / 16 * n_g;
+    const int n_i = (n_r + 4) / 4 * 4, n_g = (n_j + GEOM_PHI - 1) / GEOM_PHI, n_a = plan.woff[rows] / 16 * n_g;
     int b = blockIdx.x;
     if (b < n_i) {
         // barycentric weights of the 2 rows Chebyshev points: w_j = (-1)^j sin((2j + 1) pi / 4 rows), and those
@@ -85,15 +85,15 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
     b -= n_i;
     if (b < n_a) {
         const int pt = b / n_g, j0 = (b - pt * n_g) * GEOM_PHI, j1 = min(j0 + GEOM_PHI, n_j);
-        const int m = row_of(plan.poff, rows, 16 * pt);
-        const int P = plan.cols[m], p0 = 16 * pt - plan.poff[m], pp = (P + 15) / 16 * 16;
-        double *w = wang + (size_t)plan.poff[m] * n_j;
+        const int m = row_of(plan.woff, rows, 16 * pt);
+        const int P = plan.cols[m], p0 = 16 * pt - plan.woff[m], pp = angular_kept(P);
+        double *w = wang + (size_t)plan.woff[m] * n_j;
         const int p = p0 + (lane & 15);
         for (int jj = j0 + (lane >> 4); jj < j1; jj += 4) {
             double d = 0.0;
             if (p < P) {
                 // sin(P x / 2) / (P sin(x / 2)) at x = 2 pi (j / n_phi - p / P), + pi for theta < 0, on exact integers
-                // (the plan keeps n_j P below 4e6)
+                // (the plan keeps n_j P below 12e6)
                 const int j = jj < n_phi ? jj : jj - n_phi;
                 const int np = n_phi * P, a = 2 * (j * P - p * n_phi) + (jj < n_phi ? 0 : np);
                 if (a == 0 || a == 2 * np) d = 1.0;
@@ -279,8 +279,11 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
     const int rows = plan.rows, split = plan.split;
     const int b = blockIdx.x;
     const int m = row_of(plan.poff, rows, 16 * b);
-    const int P = plan.cols[m], p0 = 16 * b - plan.poff[m], pp = (P + 15) / 16 * 16;
-    const double *w = wang + (size_t)plan.poff[m] * (S * n_phi) + p0 + col;
+    const int P = plan.cols[m], p0 = 16 * b - plan.poff[m], pp = angular_kept(P);
+    // a column beyond half reads its mirror image at -phi (one beyond P, never stored, the first)
+    const int p = p0 + col;
+    const bool mirror = p < P && p > P / 2;
+    const double *w = wang + (size_t)plan.woff[m] * (S * n_phi) + (p >= P ? 0 : mirror ? P - p : p);
     const int kbase = blockIdx.y * 2 * COLS_KP + (col >> 3);
     const double *src[COLS_KP];
     const size_t pstride = (size_t)S * rows * n_phi * 8;
@@ -298,7 +301,7 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
 #pragma unroll 4
         for (int js = s0; js < s1; ++js) {
             const int j0 = 4 * js, j = min(j0 + kq, n_phi - 1);
-            const double a = j0 + kq < n_phi ? we[(size_t)j * pp] : 0.0;
+            const double a = j0 + kq < n_phi ? we[(size_t)(mirror && j ? n_phi - j : j) * pp] : 0.0;
 #pragma unroll
             for (int g = 0; g < COLS_KP; ++g) {
                 double part[SP];
@@ -324,8 +327,8 @@ k_compact_cols(CompactPlan plan, int n_k, int n_phi, const double *__restrict__ 
         acc[g] = ((acc[g] + part[0][g][lane]) + part[1][g][lane]) + part[2][g][lane];
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int p = p0 + 4 * q + kq;
-            if (k < n_k && p < P) out[((size_t)k * plan.n_c + plan.off[m] + p) * 8 + c] = (OT)acc[g][q];
+            const int po = p0 + 4 * q + kq;
+            if (k < n_k && po < P) out[((size_t)k * plan.n_c + plan.off[m] + po) * 8 + c] = (OT)acc[g][q];
         }
     }
 }
@@ -336,7 +339,7 @@ hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int 
                                    const double *r, double *wrad, double *wang, int is_f64, void *pos, void *hinv)
 {
     const int n_j = plan.fold ? n_phi : 2 * n_phi;
-    const int blocks = (n_r + 4) / 4 * 4 + plan.poff[plan.rows] / 16 * ((n_j + GEOM_PHI - 1) / GEOM_PHI) +
+    const int blocks = (n_r + 4) / 4 * 4 + plan.woff[plan.rows] / 16 * ((n_j + GEOM_PHI - 1) / GEOM_PHI) +
                        (plan.n_c + 63) / 64;
     hipLaunchKernelGGL(k_compact_geometry, dim3(blocks), dim3(64), 0, st, plan, n_r, n_phi, f, r, wrad, wang,
                        is_f64 ? (double *)pos : nullptr, is_f64 ? (double *)hinv : nullptr,

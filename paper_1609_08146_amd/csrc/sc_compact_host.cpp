@@ -180,7 +180,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     if (rows == 0 || rows > in.n_r) return false;
 
     const int own = in.n_phi % 2 ? 2 * in.n_phi : in.n_phi;   // the grid's phi, and those + pi
-    int64_t n_c = 0, n_pad = 0;
+    int64_t n_c = 0, n_pad = 0, n_w = 0;
     for (int m = 0; m < rows; ++m) {
         const double half = columns(theta_max / plan.beta * std::asin(plan.alpha * std::cos((2 * m + 1) * M_PI / (4.0 * rows))), eta1);
         int p = half < 30000.0 ? 2 * std::max(1, (int)std::ceil(half)) - 1 : own;
@@ -189,12 +189,15 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
         plan.cols[m] = (uint16_t)p;
         plan.off[m] = (int32_t)n_c;
         plan.poff[m] = (int32_t)n_pad;
+        plan.woff[m] = (int32_t)n_w;
         n_c += p;
         n_pad += (p + 15) / 16 * 16;
+        n_w += angular_kept(p);
     }
     if (n_c > 65536 || 2 * n_c > n_tot) return false;
     plan.off[rows] = (int32_t)n_c;
     plan.poff[rows] = (int32_t)n_pad;
+    plan.woff[rows] = (int32_t)n_w;
     plan.rows = rows;
     plan.fold = in.n_phi % 2 == 0;
     plan.n_c = (int)n_c;
@@ -221,16 +224,24 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const int64_t waves = (int64_t)in.n_k * tiles;
     plan.split = (int)std::max<int64_t>(
         1, std::min<int64_t>({(1024 + waves - 1) / waves, (in.n_r + 1) / 32, (int64_t)COMPACT_MAX_SPLIT}));
-    if ((double)n_pad * own > 4e6 || (double)rows * in.n_r > 4e6 ||
+    if ((double)n_w * own > 6e6 || (double)rows * in.n_r > 4e6 ||
         (double)plan.split * rows * in.n_phi > 1e6)   // far outside: keep the sizes below in range
         return false;
-    if (8 * (compact_radial_doubles(plan, in.n_r) + compact_angular_doubles(plan, in.n_phi) +
-             compact_rows_doubles(plan, in.n_phi)) > COMPACT_WORK_MAX)
-        return false;
+    const int64_t fixed = 8 * (compact_radial_doubles(plan, in.n_r) + compact_angular_doubles(plan, in.n_phi));
+    const int64_t row_bytes = 8 * compact_rows_doubles(plan, in.n_phi);
+    // of a frequency: records, packed rows of the FP32 sum, and per 64 points the partials
+    const int64_t tab_bytes = in.fp64 ? 64 * n_c : 32 * n_c + (form_rows(plan.form) * 1024 / form_nodes(plan.form)) * (n_c + 7) + 4096;
+    const int64_t part_bytes = 64 * 12 * (in.fp64 ? 8 : 4) * ((n_c + plan.chunk - 1) / plan.chunk);
+    const int64_t room = COMPACT_SCRATCH - 64 * (n_c + 7) - fixed;   // (less the node records)
+    if (fixed + row_bytes > COMPACT_WORK_MAX || row_bytes + tab_bytes + 2 * part_bytes > room) return false;
+    // Weights that fill the scratch leave an evaluation without allocation slabs of a few frequencies,
+    // each with launches of its own.
+    const int64_t per_k = std::max<int64_t>(1, room / (row_bytes + tab_bytes + in.n_obs_pad / 64 * part_bytes));
+    const double slabs = fixed > 24 << 20 ? (double)((in.n_k + per_k - 1) / per_k) : 1.0;
 
     const double compact = std::max((in.fp64 ? 0.3 : 0.15) * plan.chunk, pts * (double)n_c * (in.fp64 ? 5.3 : 1.2) / cyc);
     const double build = (double)in.n_k * 0.5 * ((in.n_r + 1.0) * 256.0 * tiles * (plan.fold ? 2 : 1) + (double)n_c * own);
-    return compact + 0.7 * (launches + 1.5 * build / cyc) < direct;
+    return compact + 0.7 * (launches * slabs + 1.5 * build / cyc) < direct;
 }
 
 }  // namespace sc

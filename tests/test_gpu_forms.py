@@ -82,3 +82,36 @@ def test_noalloc_in_slabs(ctx, prec, n_k):
     for a, b in zip(out, (E0, B0)):
         assert np.array_equal(a.cpu().numpy(), b)
     p.close()
+
+
+@pytest.mark.parametrize("prec,n_phi,radius", [("fp32_split", 571, 6.5), ("fp32_split", 572, 6.5), ("fp64", 401, 4.0)])
+def test_angular_weights_that_fill_the_scratch(ctx, prec, n_phi, radius):
+    """Thousands of nodes on a mirror seen under more than a half-space, random currents (every harmonic in
+    phi): against the direct sum (points in device memory), and without allocation (bit for bit)."""
+    import torch
+    from paper_1609_08146_amd import Problem
+    n_r, ks = 300, K * np.array([1.0, 1.05, 1.1])
+    rng = np.random.default_rng(n_phi)
+    obs = rng.normal(size=(1500, 3)) * [1.0, 1.0, 0.0]
+    obs *= (radius * rng.uniform(0.0, 1.0, 1500) / np.linalg.norm(obs, axis=1))[:, None]
+    obs[0] = radius, 0.0, 0.0
+    Ei, Bi = workloads.random_incident_tables(3, (n_r + 1) * n_phi, seed=3)
+    p = Problem(ctx)
+    p.set_mirror(1e3, 2.9e3, n_r, n_phi)
+    p.set_frequencies(ks)
+    p.set_incident(Ei, Bi)
+    p.set_observation(obs)
+    p.set_launch(chunk=16384)
+    E, B = p.evaluate(prec)
+    ct = torch.complex64 if prec == "fp32_split" else torch.complex128
+    out = tuple(torch.zeros(E.shape, dtype=ct, device="cuda") for _ in range(2))
+    p.evaluate_noalloc(out, prec)
+    torch.cuda.synchronize()
+    for a, b in zip(out, (E, B)):
+        assert np.array_equal(a.cpu().numpy(), b)
+    p.set_observation(torch.tensor(obs, device="cuda"))
+    Ed, Bd = p.evaluate("fp64")
+    kr = ks.max() * radius
+    tol = 2e-6 + 4 * kr * 2.0 ** -24 if prec == "fp32_split" else 1e-12 + 4 * kr * 2.0 ** -52
+    assert max(rel_l2(E, Ed), rel_l2(B, Bd)) < tol
+    p.close()
