@@ -369,7 +369,7 @@ static sc_status launch_quantum(sc_server *s)
     std::stable_partition(group.begin(), group.end(), [](const Req *r) { return r->job.mm != 0; });
     std::vector<QuadJob> jobs;
     std::vector<Req *> finals;
-    int64_t total = 0, evals = 0, mm_tiles = 0;
+    int64_t total = 0, evals = 0, stood_for = 0, mm_tiles = 0;   // kernel values formed, and evaluations they stand for
     int n_mm = 0;
     for (Req *r : group) {
         if (n_mm == (int)jobs.size() && r->job.mm == 0) {   // the first of the others
@@ -388,6 +388,7 @@ static sc_status launch_quantum(sc_server *s)
         jobs.push_back(j);
         total += j.mm ? mm_tiles_per_xcd(j) : n;
         evals += (int64_t)(n * per_tile);
+        stood_for += (int64_t)(n * per_tile * ((double)r->prob->n_tot / r->job.n_tot));
         r->cursor += n;
         if (r->cursor == r->job.n_tiles) finals.push_back(r);
     }
@@ -435,7 +436,7 @@ static sc_status launch_quantum(sc_server *s)
     s->slot_busy[slot] = true;
     s->inflight.push_back({slot, evals, Clock::now()});
     s->stats.launches++;
-    s->stats.evals_launched += evals;
+    s->stats.evals_launched += stood_for;
     for (Req *r : finals) {
         sc_status fs = finish_request(s, r);
         if (fs != SC_OK) return fs;
