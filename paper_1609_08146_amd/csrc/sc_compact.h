@@ -60,7 +60,7 @@ struct CompactPlan {
 // weights and partial rows of its own, [2 n_phi] and [2 rows].  The planner keeps their sum below
 // COMPACT_WORK_MAX bytes, and with a frequency's tables and its partials of OBS_PAD points below
 // COMPACT_SCRATCH bytes, what an evaluation without allocation has.
-constexpr int64_t COMPACT_WORK_MAX = 47 << 20, COMPACT_SCRATCH = 63 << 20;
+constexpr int64_t COMPACT_WORK_MAX = 56 << 20, COMPACT_SCRATCH = 63 << 20;
 // The weights of column p > P / 2 at phi are those of column P - p at -phi, another point of the grid, so
 // half the columns are kept, rounded up to 16.  (All of them were more than the scratch holds for an odd
 // n_phi of 500 and more with 5 000 nodes, which were then summed directly.)

@@ -93,7 +93,7 @@ k_compact_geometry(CompactPlan plan, int n_r, int n_phi, double f, const double 
             double d = 0.0;
             if (p < P) {
                 // sin(P x / 2) / (P sin(x / 2)) at x = 2 pi (j / n_phi - p / P), + pi for theta < 0, on exact integers
-                // (the plan keeps n_j P below 12e6)
+                // (the plan keeps n_j P below 16e6)
                 const int j = jj < n_phi ? jj : jj - n_phi;
                 const int np = n_phi * P, a = 2 * (j * P - p * n_phi) + (jj < n_phi ? 0 : np);
                 if (a == 0 || a == 2 * np) d = 1.0;

@@ -224,7 +224,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const int64_t waves = (int64_t)in.n_k * tiles;
     plan.split = (int)std::max<int64_t>(
         1, std::min<int64_t>({(1024 + waves - 1) / waves, (in.n_r + 1) / 32, (int64_t)COMPACT_MAX_SPLIT}));
-    if ((double)n_w * own > 6e6 || (double)rows * in.n_r > 4e6 ||
+    if ((double)n_w * own > 8e6 || (double)rows * in.n_r > 4e6 ||
         (double)plan.split * rows * in.n_phi > 1e6)   // far outside: keep the sizes below in range
         return false;
     const int64_t fixed = 8 * (compact_radial_doubles(plan, in.n_r) + compact_angular_doubles(plan, in.n_phi));

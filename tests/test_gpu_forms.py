@@ -84,7 +84,8 @@ def test_noalloc_in_slabs(ctx, prec, n_k):
     p.close()
 
 
-@pytest.mark.parametrize("prec,n_phi,radius", [("fp32_split", 571, 6.5), ("fp32_split", 572, 6.5), ("fp64", 401, 4.0)])
+@pytest.mark.parametrize("prec,n_phi,radius", [("fp32_split", 571, 6.5), ("fp32_split", 572, 6.5), ("fp64", 401, 4.0),
+                                                ("fp64", 573, 5.5)])
 def test_angular_weights_that_fill_the_scratch(ctx, prec, n_phi, radius):
     """Thousands of nodes on a mirror seen under more than a half-space, random currents (every harmonic in
     phi): against the direct sum (points in device memory), and without allocation (bit for bit)."""
