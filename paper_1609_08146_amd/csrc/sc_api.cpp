@@ -1376,7 +1376,7 @@ static size_t partial_bytes(const sc_prob *p, sc_precision prec, const sc_launch
 }
 
 // Make sure the tables of precision `prec` exist; size the partial and result buffers.
-sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job)
+sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job, bool own_partials)
 {
     const void *tab = nullptr;
     bool fact = false;
@@ -1389,6 +1389,7 @@ sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_
     if (compact) compact_job(plan, nullptr, nullptr, nullptr, l, job);
     const int fpb = mm_fpb ? mm_fpb : mm_freqs(n_k);
     size_t part = rs * 12 * (size_t)job.n_chunks * n_k * (size_t)p->n_obs_pad;
+    if (compact && !own_partials) part = 0;
     if (compact) {
         const CompactLayout lay = compact_layout(p, prec, plan, part);
         SC_TRY(p->partial.reserve(std::max(part, lay.work), p->alloc));
@@ -1712,11 +1713,16 @@ static sc_launch batch_launch(const sc_ctx *c, sc_prob *const *probs, int n, sc_
 // the chunks chosen so far exceed that, the problems that fix no chunk of their own take the
 // smallest power-of-two chunk from 2048 up (never below their own) that fits; the result of each
 // problem is then its result alone at that chunk.  Deterministic in the batch's sizes.
-static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, std::vector<sc_launch> &ls)
+static double batch_partial_cap(sc_prob *const *probs, int n, sc_precision prec)
 {
     double table_ref = 0.0;
     for (int i = 0; i < n; ++i) table_ref += 16.0 * (double)probs[i]->k.size() * (double)probs[i]->n_tot;
-    const double cap = std::max(2.0 * table_ref * (prec == SC_FP64 ? 2.0 : 1.0), 8.0 * 1073741824.0);
+    return std::max(2.0 * table_ref * (prec == SC_FP64 ? 2.0 : 1.0), 8.0 * 1073741824.0);
+}
+
+static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, std::vector<sc_launch> &ls)
+{
+    const double cap = batch_partial_cap(probs, n, prec);
     auto total = [&](int floor_chunk) {
         double b = 0.0;
         for (int i = 0; i < n; ++i) {
@@ -1747,6 +1753,14 @@ extern "C" sc_status sc_set_batch_launch(sc_ctx *c, sc_precision prec, const sc_
     SC_TRY(check_launch(full));
     c->batch_tune[(int)prec] = *l;
     return SC_OK;
+}
+
+// Bytes of the partials of p's compacted sum; 0 where the sum is taken directly.
+static size_t compact_partial_bytes(const sc_prob *p, sc_precision prec)
+{
+    CompactPlan plan;
+    if (!plan_compact(p, prec, plan)) return 0;
+    return real_size(prec) * 12 * (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk) * p->k.size() * (size_t)p->n_obs_pad;
 }
 
 extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, sc_precision prec)
@@ -1782,20 +1796,58 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
         SC_TRY(check_launch(ls[i]));
     }
     batch_fit_partials(probs, n, prec, ls);
+    // Compacted sums have chunks of at most 256 nodes whatever the launch, so beyond the cap the problems
+    // go in groups whose partials share one buffer, that of the first of them, one group after the other
+    // (256 problems of the sweep: 88 GB of partials for a cap of 69).
+    const size_t cap = (size_t)batch_partial_cap(probs, n, prec);
+    std::vector<size_t> part(n), at(n, 0);
+    std::vector<int> group(n, 0);
+    size_t total = 0, used = 0, most = 0;
+    int holder = -1, groups = 1;
     for (int i = 0; i < n; ++i) {
-        SC_TRY(prepare(probs[i], prec, ls[i], MM_FREQS_SHARED, jobs[i]));
+        part[i] = (compact_partial_bytes(probs[i], prec) + 255) & ~size_t(255);
+        total += part[i];
+    }
+    if (total > cap) {
+        for (int i = 0; i < n; ++i) {
+            if (part[i] == 0) continue;
+            if (holder < 0) holder = i;
+            if (used && used + part[i] > cap) {
+                ++groups;
+                used = 0;
+            }
+            group[i] = groups - 1;
+            at[i] = used;
+            used += part[i];
+            most = std::max(most, used);
+        }
+        SC_TRY(probs[holder]->partial.reserve(most, probs[holder]->alloc));
+    }
+    for (int i = 0; i < n; ++i) {
+        SC_TRY(prepare(probs[i], prec, ls[i], MM_FREQS_SHARED, jobs[i], holder < 0));
         probs[i]->res_prec = -1;
     }
-    SC_TRY(run_quad(c, jobs, prec, l0, probs[0]));
-    for (int i = 0; i < n; ++i) {
-        sc_prob *p = probs[i];
-        HIP_TRY(launch_reduce(c->stream, mode_of(prec), p->partial.p, jobs[i].n_chunks, jobs[i].n_k, p->n_obs,
-                              p->n_obs_pad, p->d_k.as<double>(), jobs[i].tied, p->n_obs, 0, p->resE.p,
-                              p->resB.p, nullptr, nullptr));
-        p->res_prec = (int)prec;
-        p->last_evals = (int64_t)p->n_obs * jobs[i].n_k * p->n_surf;
-        p->last_tiles = jobs[i].n_tiles;
-        p->last_chunk = ls[i].chunk;
+    if (holder >= 0)
+        for (int i = 0; i < n; ++i)
+            if (part[i]) jobs[i].partial = (char *)probs[holder]->partial.p + at[i];
+    if (groups > 1) ev_record(probs[0], EV_Q0);
+    for (int gr = 0; gr < groups; ++gr) {
+        std::vector<QuadJob> now;
+        for (int i = 0; i < n; ++i)
+            if (group[i] == gr) now.push_back(jobs[i]);
+        SC_TRY(run_quad(c, now, prec, l0, groups > 1 ? nullptr : probs[0]));
+        if (groups > 1 && gr == groups - 1) ev_record(probs[0], EV_Q1);
+        for (int i = 0; i < n; ++i) {
+            if (group[i] != gr) continue;
+            sc_prob *p = probs[i];
+            HIP_TRY(launch_reduce(c->stream, mode_of(prec), jobs[i].partial, jobs[i].n_chunks, jobs[i].n_k, p->n_obs,
+                                  p->n_obs_pad, p->d_k.as<double>(), jobs[i].tied, p->n_obs, 0, p->resE.p,
+                                  p->resB.p, nullptr, nullptr));
+            p->res_prec = (int)prec;
+            p->last_evals = (int64_t)p->n_obs * jobs[i].n_k * p->n_surf;
+            p->last_tiles = jobs[i].n_tiles;
+            p->last_chunk = ls[i].chunk;
+        }
     }
     ev_record(probs[0], EV_R1);
     probs[0]->ev_quad = c->profiling;

@@ -299,7 +299,8 @@ void prob_free_on(sc_prob *p, hipStream_t st);
 // Tables of the precision, partial and result buffers; fills `job` (tile0 = 0, offset 0, all tiles).
 // mm_fpb: frequencies per tile of the compacted FP32 sum (0: the problem's best, for a launch of its own).
 constexpr int MM_FREQS_SHARED = 4;
-sc_status prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job);
+// own_partials = false: of a compacted sum none are sized, and the caller sets job.partial.
+sc_status prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job, bool own_partials = true);
 // Upload `jobs` (tile0 assigned here) and run one persistent quadrature launch on ctx's stream.
 sc_status run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec, const sc_launch &l, sc_prob *timed);
 // Device bytes a problem of this shape holds after an evaluate (+ time transform with n_t samples).

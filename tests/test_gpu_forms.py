@@ -116,3 +116,30 @@ def test_angular_weights_that_fill_the_scratch(ctx, prec, n_phi, radius):
     tol = 2e-6 + 4 * kr * 2.0 ** -24 if prec == "fp32_split" else 1e-12 + 4 * kr * 2.0 ** -52
     assert max(rel_l2(E, Ed), rel_l2(B, Bd)) < tol
     p.close()
+
+
+def test_batch_partials_in_groups(ctx):
+    """Three problems of 3.4 GB of partials each (7 chunks of 256 nodes and less) beside a surface-summed one, for
+    the documented 8 GiB: the results are those of each alone, bit for bit."""
+    import torch
+    from paper_1609_08146_amd import Problem
+    probs, alone = [], []
+    for i, n_obs in enumerate((100, 60000, 61000, 62000)):
+        p = Problem(ctx)
+        p.set_mirror(1e5, 7.5e4, 100, 100)
+        p.set_frequencies(K * np.linspace(0.9, 1.1, 160))
+        p.set_incident_gaussian(5e4, 0.3 * i)
+        g = np.random.default_rng(i)
+        obs = g.uniform(-4.0, 4.0, (n_obs, 3)) * [1.0, 1.0, 0.25]
+        obs[:4] = [[4.0, 4.0, 1.0], [-4.0, 4.0, 1.0], [4.0, -4.0, -1.0], [-4.0, -4.0, 1.0]]
+        p.set_observation(torch.tensor(obs, device="cuda") if i == 0 else obs)
+        probs.append(p)
+    ctx.evaluate_batch(probs, "fp32_split")
+    held = probs[1].device_bytes()
+    got = [p.result() for p in probs]
+    for i, (p, (E, B)) in enumerate(zip(probs, got)):
+        Ea, Ba = p.evaluate("fp32_split")
+        assert np.array_equal(E, Ea) and np.array_equal(B, Ba), i
+    assert held < 10.5e9 and probs[2].device_bytes() > 3e9
+    for p in probs:
+        p.close()
