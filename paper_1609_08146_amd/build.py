@@ -18,8 +18,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIBDIR = os.path.join(HERE, "lib")
 LIB = os.path.join(LIBDIR, "libsc.so")
-SOURCES = ["sc_quad.hip", "sc_quad_mm.hip", "sc_kernels.hip", "sc_compact.hip", "sc_diag.hip", "sc_api.cpp", "sc_serve.cpp",
-           "sc_gauss_host.cpp", "sc_compact_host.cpp"]
+# translation units (sc_kernels.hip and sc_gauss_host.cpp include the files of the compacted sum)
+SOURCES = ["sc_quad.hip", "sc_kernels.hip", "sc_diag.hip", "sc_api.cpp", "sc_serve.cpp", "sc_gauss_host.cpp"]
 ARCH = "gfx950"
 
 HIP_FLAGS = [
@@ -44,8 +44,6 @@ def build(verbose: bool = False) -> str:
     objs = []
     for src in SOURCES:
         path = os.path.join(CSRC, src)
-        if not os.path.exists(path):
-            continue
         obj = os.path.join(objdir, os.path.splitext(src)[0] + ".o")
         if src.endswith("_host.cpp"):
             # host-only code (needs __float128): the system C++ compiler

@@ -112,3 +112,6 @@ void gauss_legendre_rule(int n, std::vector<double> &x, std::vector<double> &w)
 }
 
 }  // namespace sc
+
+// The planner of the compacted sum, host-only as well: one translation unit with the rule.
+#include "sc_compact_host.cpp"

@@ -1066,3 +1066,8 @@ hipError_t launch_fill_u32(hipStream_t st, unsigned int *p, unsigned int v, int 
 }
 
 }  // namespace sc
+
+// The kernels of the compacted sum belong to this translation unit, so that whoever compiles the library from the
+// sources of build.py needs no longer a list for them.
+#include "sc_compact.hip"
+#include "sc_quad_mm.hip"
