@@ -39,13 +39,14 @@ bool debug_fail_this_alloc();
 // Device memory that finished problems leave for the next ones (the serving loop: a request takes about 30
 // buffers, and the runtime's pool answered those of many megabytes with fresh mappings, 0.3 ms each, and
 // took 0.5 ms per request to free them).  Blocks come back when the work that used them has run, or
-// is queued on the stream that their next user's first work goes to; at most `limit` bytes wait here,
-// and the owner's destruction gives them back.
+// is queued on `stream`, where their next user's first work goes too: idle blocks may still be read by what is
+// queued there, so they are given back on that stream.  At most `limit` bytes wait here, and the owner's
+// destruction gives them back.
 struct BlockCache {
     std::mutex mu;
     std::multimap<size_t, void *> idle;
     size_t held = 0, limit = 0;
-    hipStream_t free_stream = nullptr;
+    hipStream_t stream = nullptr;
     // an idle block of n bytes or up to a quarter more (*cap: its size), or NULL
     void *take(size_t n, size_t *cap)
     {
@@ -69,10 +70,10 @@ struct BlockCache {
     void trim()
     {
         std::lock_guard<std::mutex> lk(mu);
-        for (auto &b : idle) (void)hipFreeAsync(b.second, free_stream);
+        for (auto &b : idle) (void)hipFreeAsync(b.second, stream);
         idle.clear();
         held = 0;
-        (void)hipStreamSynchronize(free_stream);
+        (void)hipStreamSynchronize(stream);
     }
 };
 

@@ -739,7 +739,7 @@ extern "C" sc_status sc_server_create(sc_ctx *ctx, size_t hbm_budget, int max_ru
         size_t free_b = 0, total_b = 0;
         (void)hipMemGetInfo(&free_b, &total_b);
         s->blocks.limit = total_b > hbm_budget ? std::min<size_t>(size_t(8) << 30, (total_b - hbm_budget) / 2) : 0;
-        s->blocks.free_stream = s->release_stream;
+        s->blocks.stream = s->prep->stream;
     }
     ctx->n_probs++;   // the context must outlive the server
     s->worker = std::thread(worker_main, s);

@@ -1,0 +1,59 @@
+// A host-only stand-in for the part of the HIP runtime that the library's host code calls, for CPU tests of
+// that code (see stub.h).  No device, no kernels.
+#pragma once
+#include <stddef.h>
+#include <stdint.h>
+
+#define __device__
+#define __host__
+#define __global__
+#define __forceinline__ inline
+#define __align__(n) __attribute__((aligned(n)))
+
+enum hipError_t { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2, hipErrorNotReady = 600 };
+enum hipMemcpyKind { hipMemcpyHostToDevice = 1, hipMemcpyDeviceToHost = 2, hipMemcpyDeviceToDevice = 3 };
+enum { hipStreamNonBlocking = 1, hipEventDisableTiming = 2, hipHostMallocDefault = 0 };
+enum hipMemPoolAttr { hipMemPoolAttrReleaseThreshold = 4 };
+typedef struct StubStream *hipStream_t;
+typedef struct StubEvent *hipEvent_t;
+typedef struct StubPool *hipMemPool_t;
+struct hipDeviceProp_t {
+    int multiProcessorCount;
+};
+
+hipError_t hipGetDeviceCount(int *);
+hipError_t hipGetDevice(int *);
+hipError_t hipSetDevice(int);
+hipError_t hipGetDeviceProperties(hipDeviceProp_t *, int);
+hipError_t hipGetLastError();
+const char *hipGetErrorString(hipError_t);
+hipError_t hipStreamCreateWithFlags(hipStream_t *, unsigned);
+hipError_t hipStreamDestroy(hipStream_t);
+hipError_t hipStreamSynchronize(hipStream_t);
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned);
+hipError_t hipEventCreate(hipEvent_t *);
+hipError_t hipEventCreateWithFlags(hipEvent_t *, unsigned);
+hipError_t hipEventDestroy(hipEvent_t);
+hipError_t hipEventRecord(hipEvent_t, hipStream_t);
+hipError_t hipEventQuery(hipEvent_t);
+hipError_t hipEventSynchronize(hipEvent_t);
+hipError_t hipEventElapsedTime(float *, hipEvent_t, hipEvent_t);
+hipError_t hipMallocRaw(void **, size_t);
+hipError_t hipMallocAsyncRaw(void **, size_t, hipStream_t);
+template <typename T>
+inline hipError_t hipMalloc(T **p, size_t n) { return hipMallocRaw((void **)p, n); }
+template <typename T>
+inline hipError_t hipMallocAsync(T **p, size_t n, hipStream_t s) { return hipMallocAsyncRaw((void **)p, n, s); }
+hipError_t hipFree(void *);
+hipError_t hipFreeAsync(void *, hipStream_t);
+hipError_t hipHostMalloc(void **, size_t, unsigned);
+hipError_t hipHostFree(void *);
+hipError_t hipMemGetInfo(size_t *, size_t *);
+hipError_t hipMemcpy(void *, const void *, size_t, hipMemcpyKind);
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t);
+hipError_t hipDeviceGetDefaultMemPool(hipMemPool_t *, int);
+hipError_t hipMemPoolGetAttribute(hipMemPool_t, hipMemPoolAttr, void *);
+hipError_t hipMemPoolSetAttribute(hipMemPool_t, hipMemPoolAttr, void *);
+hipError_t hipMemPoolTrimTo(hipMemPool_t, size_t);
+#define HIP_SYMBOL(x) x
+hipError_t hipGetSymbolAddress(void **, const void *);
