@@ -126,7 +126,7 @@ struct DevBuf {
             (void)hipGetLastError();
             return fail(SC_E_NOMEM, "device allocation of %zu bytes failed: %s", n, hipGetErrorString(e));
         }
-        bytes = n;
+        bytes = cap;   // what is held (and charged), not what was asked for
         stream = a.stream;
         cache = a.cache;
         return SC_OK;

@@ -13,6 +13,7 @@
 #include <string>
 #include <vector>
 
+#include "sc_host.h"
 #include "stub.h"
 
 static int failures = 0;
@@ -95,10 +96,28 @@ static void idle_blocks()
     EXPECT(stub::live_bytes() == 0, "%zu bytes not freed", stub::live_bytes());
 }
 
+// A block from the cache counts with its own size, which may be a quarter more than was asked for.
+static void block_sizes()
+{
+    sc::BlockCache cache;
+    cache.limit = 64 << 20;
+    {
+        sc::DevBuf a, b;
+        EXPECT(a.reserve(10 << 20, {nullptr, &cache}) == SC_OK, "reserve");
+        void *block = a.p;
+        a.release();
+        EXPECT(b.reserve(9 << 20, {nullptr, &cache}) == SC_OK && b.p == block, "the idle block was not taken");
+        EXPECT(b.bytes == 10 << 20, "%zu bytes counted of %d held", b.bytes, 10 << 20);
+    }
+    cache.trim();
+    EXPECT(stub::live_bytes() == 0, "%zu bytes not freed", stub::live_bytes());
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, std::function<void()>> checks = {
         {"idle_blocks", idle_blocks},
+        {"block_sizes", block_sizes},
     };
     if (argc == 2 && checks.count(argv[1])) {
         checks.at(argv[1])();
