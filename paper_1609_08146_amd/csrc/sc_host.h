@@ -7,6 +7,7 @@
 #include <atomic>
 #include <map>
 #include <mutex>
+#include <new>
 #include <string>
 #include <tuple>
 #include <vector>
@@ -43,9 +44,14 @@ bool debug_fail_this_alloc();
 // queued there, so they are given back on that stream.  At most `limit` bytes wait here, and the owner's
 // destruction gives them back.
 struct BlockCache {
+    struct Block {
+        void *p;
+        uint64_t put;   // number of the put() that brought it
+    };
     std::mutex mu;
-    std::multimap<size_t, void *> idle;
+    std::multimap<size_t, Block> idle;   // by size
     size_t held = 0, limit = 0;
+    uint64_t puts = 0;
     hipStream_t stream = nullptr;
     // an idle block of n bytes or up to a quarter more (*cap: its size), or NULL
     void *take(size_t n, size_t *cap)
@@ -53,24 +59,38 @@ struct BlockCache {
         std::lock_guard<std::mutex> lk(mu);
         auto it = idle.lower_bound(n);
         if (it == idle.end() || it->first > n + n / 4 + 4096) return nullptr;
-        void *p = it->second;
+        void *p = it->second.p;
         *cap = it->first;
         held -= it->first;
         idle.erase(it);
         return p;
     }
-    bool put(void *p, size_t cap)
+    // Keeps a block; those that have waited longest make room for it.  False where it is larger than the limit (or
+    // the host is out of memory).
+    bool put(void *p, size_t cap) noexcept
     {
         std::lock_guard<std::mutex> lk(mu);
-        if (held + cap > limit) return false;
-        idle.emplace(cap, p);
+        if (cap > limit) return false;
+        while (held + cap > limit) {
+            auto old = idle.begin();
+            for (auto it = idle.begin(); it != idle.end(); ++it)
+                if (it->second.put < old->second.put) old = it;
+            (void)hipFreeAsync(old->second.p, stream);
+            held -= old->first;
+            idle.erase(old);
+        }
+        try {
+            idle.emplace(cap, Block{p, ++puts});
+        } catch (const std::bad_alloc &) {
+            return false;
+        }
         held += cap;
         return true;
     }
     void trim()
     {
         std::lock_guard<std::mutex> lk(mu);
-        for (auto &b : idle) (void)hipFreeAsync(b.second, stream);
+        for (auto &b : idle) (void)hipFreeAsync(b.second.p, stream);
         idle.clear();
         held = 0;
         (void)hipStreamSynchronize(stream);

@@ -113,11 +113,35 @@ static void block_sizes()
     EXPECT(stub::live_bytes() == 0, "%zu bytes not freed", stub::live_bytes());
 }
 
+// Blocks of sizes that nobody asks for again do not fill the cache for good.
+static void block_turnover()
+{
+    sc::BlockCache cache;
+    cache.limit = 16 << 20;
+    {
+        sc::DevBuf all[8];
+        for (auto &a : all) EXPECT(a.reserve(2 << 20, {nullptr, &cache}) == SC_OK, "reserve");
+    }
+    EXPECT(cache.held == cache.limit, "%zu bytes wait", cache.held);
+    for (size_t n : {size_t(9) << 20, size_t(13) << 20}) {
+        sc::DevBuf a, b;
+        EXPECT(a.reserve(n, {nullptr, &cache}) == SC_OK, "reserve");
+        void *block = a.p;
+        a.release();
+        EXPECT(cache.held <= cache.limit, "%zu bytes wait", cache.held);
+        EXPECT(b.reserve(n, {nullptr, &cache}) == SC_OK && b.p == block, "a block of %zu bytes was not kept", n);
+    }
+    cache.trim();
+    EXPECT(stub::live_bytes() == 0, "%zu bytes not freed", stub::live_bytes());
+    no_violations("turnover");
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, std::function<void()>> checks = {
         {"idle_blocks", idle_blocks},
         {"block_sizes", block_sizes},
+        {"block_turnover", block_turnover},
     };
     if (argc == 2 && checks.count(argv[1])) {
         checks.at(argv[1])();
