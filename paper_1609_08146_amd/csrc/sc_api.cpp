@@ -482,7 +482,8 @@ static sc_status drop_fp64_tables(sc_prob *p, bool cast)
         p->tab32_ok = true;
     }
     // a stream-ordered free runs after the cast; a plain hipFree needs the cast to have finished
-    if (!p->tab64.stream) HIP_TRY(hipStreamSynchronize(p->ctx->stream));
+    // (and tables that were never filled are no one's input)
+    if (p->tab64.p && !p->tab64.stream) HIP_TRY(hipStreamSynchronize(p->ctx->stream));
     p->tab64.release();
     p->has_tab64 = p->tab64_unfilled = false;
     // without the FP64 tables there is no FP64 evaluation, so its factored tables go too

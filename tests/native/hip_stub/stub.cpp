@@ -35,6 +35,7 @@ std::vector<Launch> launches;
 long long fail_alloc_at = 0, fail_allocs = 0;
 bool fields_factor = false;
 double sim = 0.0;
+long long waits = 0;
 }  // namespace stub
 using namespace stub;
 
@@ -131,6 +132,16 @@ hipError_t give(void *p, StubStream *s)
     allocs.erase(it);
     return hipSuccess;
 }
+// The host waits for what `before` holds.
+void host_waits(const Clock &before)
+{
+    for (auto &x : before)
+        if (host[x.first] < x.second) {
+            ++waits;
+            break;
+        }
+    merge(host, before);
+}
 void wait_until(Time::time_point t)
 {
     if (sim > 0.0) std::this_thread::sleep_until(t);
@@ -168,7 +179,7 @@ hipError_t hipStreamSynchronize(hipStream_t st)
     }
     wait_until(t);
     LOCK;
-    merge(host, real(st)->before);
+    host_waits(real(st)->before);
     return hipSuccess;
 }
 hipError_t hipStreamWaitEvent(hipStream_t st, hipEvent_t e, unsigned)
@@ -204,7 +215,7 @@ hipError_t hipEventSynchronize(hipEvent_t e)
     }
     wait_until(t);
     LOCK;
-    merge(host, e->before);
+    host_waits(e->before);
     return hipSuccess;
 }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b)

@@ -25,6 +25,8 @@ extern long long fail_allocs;                 // ... and this many after it
 extern bool fields_factor;                    // outcome of the factoring test of fields from the caller
 extern double sim;                            // > 0: device work takes time (a model of it), times this
 
+extern long long waits;                       // waits of the host for work that it did not know to be done
+
 size_t live_bytes();    // device memory not freed
 size_t peak_bytes();
 long long allocations();

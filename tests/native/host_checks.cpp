@@ -137,12 +137,34 @@ static void block_turnover()
     no_violations("turnover");
 }
 
+// Serving a request whose current factors, no thread waits for the device.
+static void no_waits()
+{
+    for (sc_precision prec : {SC_FP32_SPLIT, SC_FP64}) {
+        sc_ctx *ctx = nullptr;
+        sc_server *s = nullptr;
+        OK(sc_ctx_create(0, nullptr, &ctx));
+        OK(sc_server_create(ctx, size_t(20) << 30, 4, 20.0, &s));
+        Request r(60, 64, 3, 900, 0);
+        r.q.prec = prec;
+        uint64_t ticket = 0;
+        const long long before = stub::waits;
+        OK(sc_server_submit(s, &r.q, &ticket));
+        OK(sc_server_wait(s, ticket, 10000.0, nullptr, nullptr, nullptr, nullptr, nullptr));
+        EXPECT(stub::waits == before, "%lld waits", stub::waits - before);
+        OK(sc_server_destroy(s));
+        OK(sc_ctx_destroy(ctx));
+    }
+    no_violations("served requests");
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, std::function<void()>> checks = {
         {"idle_blocks", idle_blocks},
         {"block_sizes", block_sizes},
         {"block_turnover", block_turnover},
+        {"no_waits", no_waits},
     };
     if (argc == 2 && checks.count(argv[1])) {
         checks.at(argv[1])();
