@@ -1211,18 +1211,16 @@ static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, co
     job.tabp = job.tied && prec != SC_FP64 ? p->tabp.p : nullptr;
     // |delta| = ||R| - |r_s|| <= |r'|, so the split phase k delta stays below k_max |r'|_max; the
     // hardware sin / cos take up to 256 turns directly (kept below 250 for the FP32 rounding of k delta;
-    // the tied charge adds the phase of s, at most half a turn)
-    {
-        const double kmax = *std::max_element(p->k.begin(), p->k.end());
-        const double tmax = p->obs_r2max >= 0.0 ? kmax / (2.0 * M_PI) * std::sqrt(p->obs_r2max) : 1e300;
-        job.raw_phase = prec == SC_FP32_SPLIT && tmax < 250.0 ? 1 : 0;
-    }
+    // the tied charge adds the phase of s, at most half a turn), the FP64 form's table 2^42
+    const double kmax = *std::max_element(p->k.begin(), p->k.end());
+    const double tmax = p->obs_r2max >= 0.0 ? kmax / (2.0 * M_PI) * std::sqrt(p->obs_r2max) : 1e300;
+    job.raw_phase = (prec == SC_FP32_SPLIT && tmax < 250.0) || (prec == SC_FP64 && tmax < 0x1p40) ? 1 : 0;
     // delta = (|r'|^2 - 2 r_s.r') / (|R| + |r_s|) by its series in x = delta_1 / (2|r_s|), where
     // |x| <= |r'| / (2|r_s|) <= 2e-4 keeps the truncation (5 x^3, relative) far below FP32 rounding
     // (1 / (2|r_s|) rides in the factored node records, or in hinv32); per job, like the phase path
     job.hinv = prec == SC_FP64 ? p->hinv64.p : p->hinv32.p;
     job.series_delta = (prec == SC_FP32_SPLIT || prec == SC_FP64) && p->rs_min > 0.0 && p->obs_r2max >= 0.0 &&
-                               std::sqrt(p->obs_r2max) <= 4e-4 * p->rs_min
+                               std::sqrt(p->obs_r2max) <= 4e-4 * p->rs_min && tmax < 0x1p40
                            ? 1
                            : 0;
     job.obs = prec == SC_FP64 ? p->obs64.p : p->obs32.p;

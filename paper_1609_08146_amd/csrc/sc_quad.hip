@@ -267,13 +267,17 @@ __device__ __forceinline__ const double2 *turn_table_lds()
     return tab;
 }
 
-// sin and cos of 2 pi t in FP64, |t| < 2^42.  Adding 1.5 2^52 to 256 t rounds it to the integer j, whose last
+// sin and cos of 2 pi t in FP64; without FAR for |t| < 2^42, with it for any t, which is first reduced to its
+// fractional turn (exactly, so that both give the same bits where both hold).  Adding 1.5 2^52 to 256 t rounds it to the integer j, whose last
 // eight bits lie last in the sum; z = t - j / 256 is exact (|z| <= 1/512 turn), and the angle sum combines
 // the tabulated (cos, sin) of 2 pi j / 256 with sin x = x - x^3/6 + x^5/120 and cos x = 1 - x^2/2 + x^4/24 -
 // x^6/720 at x = 2 pi z, written in z (the first omitted terms are below 1e-17 and 2e-20).  15 instructions
-// of the FP64 rate; with the fractional turn and x formed first it was 20 of the 83 of a general evaluation.
+// of the FP64 rate (FAR 17); with the fractional turn and x formed first it was 20 of the 83 of a general
+// evaluation.
+template <bool FAR>
 __device__ __forceinline__ void sincos_turns_f64(double t, const double2 *tab, double &s, double &c)
 {
+    if constexpr (FAR) t -= rint(t);
     constexpr double P = TWO_PI_1, P2 = P * P, ROUND = 6755399441055744.0;   // 1.5 2^52
     const double a = __fma_rn(t, (double)TURN_STEPS, ROUND);
     const double z = __fma_rn(-1.0 / TURN_STEPS, a - ROUND, t);
@@ -338,11 +342,12 @@ __device__ __forceinline__ GeomD geom_f64(const double *p, const double4 o)
     return g;
 }
 
+template <bool FAR>
 __device__ __forceinline__ void freq_f64(const GeomD &g, const double *t, double k, double kt, const double2 *ttab,
                                          double *acc)
 {
     double s, c;
-    sincos_turns_f64(kt * g.delta, ttab, s, c);
+    sincos_turns_f64<FAR>(kt * g.delta, ttab, s, c);
     const double dx = g.dx, dy = g.dy, dz = g.dz, rinv = g.rinv;
     const double gr = c * rinv, gi = s * rinv;
     const double a = -(rinv * rinv), b = k * rinv;
@@ -376,12 +381,13 @@ __device__ __forceinline__ void freq_f64(const GeomD &g, const double *t, double
 // Factored current in FP64, one frequency: the algebra of freq_factored
 // (A = s Z, C = rho_t Z, m = ik - 1/R; E += v A + (C m) e, B += (A m) w) with
 // t = (s, rho_t) as (re, im) pairs.
+template <bool FAR>
 __device__ __forceinline__ void freq_f64_factored(double rinv, double delta, const double *v, const double *e,
                                                   const double *w, const double *t, double k, double kt,
                                                   const double2 *ttab, double *acc)
 {
     double sn, c;
-    sincos_turns_f64(kt * delta, ttab, sn, c);
+    sincos_turns_f64<FAR>(kt * delta, ttab, sn, c);
     const double ar = __fma_rn(t[0], c, -(t[1] * sn)), ai = __fma_rn(t[0], sn, t[1] * c);
     const double cr = __fma_rn(t[2], c, -(t[3] * sn)), ci = __fma_rn(t[2], sn, t[3] * c);
     const double amr = __fma_rn(-rinv, ar, -(k * ai)), ami = __fma_rn(-rinv, ai, k * ar);
@@ -397,12 +403,13 @@ __device__ __forceinline__ void freq_f64_factored(double rinv, double delta, con
 
 // The tied charge in FP64, one frequency: the algebra of freq_tied (M = A m / k = A (i - q),
 // q = 1 / (k R); E += v A + e (-i M) with e = beta R / R^2, B += M w).
+template <bool FAR>
 __device__ __forceinline__ void freq_f64_tied(double rinv, double delta, const double *v, const double *e,
                                               const double *w, const double *t, double kinv, double kt,
                                               const double2 *ttab, double *acc)
 {
     double sn, c;
-    sincos_turns_f64(kt * delta, ttab, sn, c);
+    sincos_turns_f64<FAR>(kt * delta, ttab, sn, c);
     const double ar = __fma_rn(t[0], c, -(t[1] * sn)), ai = __fma_rn(t[0], sn, t[1] * c);
     const double q = rinv * kinv;
     const double mr = __fma_rn(-q, ar, -ai), mi = __fma_rn(-q, ai, ar);
@@ -420,8 +427,9 @@ __device__ __forceinline__ void freq_f64_tied(double rinv, double delta, const d
 // records (Jt.x, Jt.y, Jt.z, rho_t) as (re, im) pairs, 4 and 8 doubles;
 // factored (FACT): node records (x, y, z, |r_s|, u, 1 / (2|r_s|)) and table
 // records (s, rho_t), 8 and 4 doubles; with the tied charge (TIE) only s of a
-// table record is read, and beta from the job's per-node array.  Plain FP64 sums.
-template <int OPL, int FPB, bool FACT, bool SER = false, bool TIE = false>
+// table record is read, and beta from the job's per-node array; FAR as in
+// sincos_turns_f64.  Plain FP64 sums.
+template <int OPL, int FPB, bool FACT, bool SER = false, bool TIE = false, bool FAR = false>
 __device__ __forceinline__ void tile_f64(cjob *job, int lane, int chunk, int n0, int n1, int obase, const int *kidx,
                                          const double *k64, int n_valid, const double2 *ttab)
 {
@@ -480,15 +488,15 @@ __device__ __forceinline__ void tile_f64(cjob *job, int lane, int chunk, int n0,
                     const double eb[3] = {e[0] * bn, e[1] * bn, e[2] * bn};
 #pragma unroll
                     for (int f = 0; f < FPB; ++f)
-                        freq_f64_tied(g.rinv, g.delta, v, eb, w, tn[f], kinv64[f], kt64[f], ttab, acc[s][f]);
+                        freq_f64_tied<FAR>(g.rinv, g.delta, v, eb, w, tn[f], kinv64[f], kt64[f], ttab, acc[s][f]);
                 } else {
 #pragma unroll
                     for (int f = 0; f < FPB; ++f)
-                        freq_f64_factored(g.rinv, g.delta, v, e, w, tn[f], k64[f], kt64[f], ttab, acc[s][f]);
+                        freq_f64_factored<FAR>(g.rinv, g.delta, v, e, w, tn[f], k64[f], kt64[f], ttab, acc[s][f]);
                 }
             } else {
 #pragma unroll
-                for (int f = 0; f < FPB; ++f) freq_f64(g, tn[f], k64[f], kt64[f], ttab, acc[s][f]);
+                for (int f = 0; f < FPB; ++f) freq_f64<FAR>(g, tn[f], k64[f], kt64[f], ttab, acc[s][f]);
             }
         }
     }
@@ -761,19 +769,19 @@ k_quad(QuadJob, const QuadJob *__restrict__ jobs_, int n_jobs, int64_t n_tiles, 
         const int n_valid = min(FPB, n_k - kb * FPB);
 
         if constexpr (MODE == MODE_FP64) {
-            const bool ser = jobs[j].series_delta != 0;
-            if (jobs[j].tied && ser)
-                tile_f64<OPL, FPB, true, true, true>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab);
-            else if (jobs[j].tied)
-                tile_f64<OPL, FPB, true, false, true>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab);
-            else if (jobs[j].factored && ser)
-                tile_f64<OPL, FPB, true, true>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab);
-            else if (jobs[j].factored)
-                tile_f64<OPL, FPB, true, false>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab);
-            else if (ser)
-                tile_f64<OPL, FPB, false, true>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab);
-            else
-                tile_f64<OPL, FPB, false, false>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab);
+            // the phase's range per job as well; the series come with the short one
+            const bool ser = jobs[j].series_delta != 0, raw = jobs[j].raw_phase != 0;
+#define SC_TILE_F64(...) tile_f64<OPL, FPB, __VA_ARGS__>(jobs + j, lane, chunk, n0, n1, obase, kidx, k64, n_valid, ttab)
+            if (jobs[j].tied && ser) SC_TILE_F64(true, true, true);
+            else if (jobs[j].tied && raw) SC_TILE_F64(true, false, true);
+            else if (jobs[j].tied) SC_TILE_F64(true, false, true, true);
+            else if (jobs[j].factored && ser) SC_TILE_F64(true, true);
+            else if (jobs[j].factored && raw) SC_TILE_F64(true, false);
+            else if (jobs[j].factored) SC_TILE_F64(true, false, false, true);
+            else if (ser) SC_TILE_F64(false, true);
+            else if (raw) SC_TILE_F64(false, false);
+            else SC_TILE_F64(false, false, false, true);
+#undef SC_TILE_F64
         } else if constexpr (MODE == MODE_SPLIT) {
             // per job (not per tile), so the bits of a point do not depend on the launch shape
             const bool raw = jobs[j].raw_phase != 0;

@@ -31,7 +31,7 @@ struct QuadJob {
     int factored;         // split form (FP32 or FP64) with the current factored as J~ = u s (u real, per node)
     int tied;             // factored, and the charge tied to the current: rho_t = -i beta s / k (beta real,
                           // per node); the B sums then carry 1/k, so the reduction drops its own 1/k
-    int raw_phase;        // FP32 split form: |k delta| / 2 pi < 250 turns for every pair of the job
+    int raw_phase;        // for every pair of the job |k delta| / 2 pi < 250 turns (FP32 split form), < 2^40 (FP64)
     int series_delta;     // split forms: |r'| <= 4e-4 |r_s| for every pair (delta and 1/|R| by series)
     int mm;               // compacted FP32 split form: the sum is taken by k_quad_mm (tiles of 128 points)
     int form;             // mm: CompactForm of the packed rows
