@@ -67,6 +67,12 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     const double q = rp / in.f;   // |r_s| >= f on the paraboloid
     // farther out the singularity R = 0 comes near the strip (and few nodes would be saved)
     if (!(q <= 0.25) || !std::isfinite(in.k_max * rp)) return false;
+    // Very deep mirrors: |r_s| at the rim is many f, where the kernel is that much smaller than at the vertex while
+    // its nodes stand for larger areas, so an error relative to the largest kernel value is not small there, and the
+    // FP32 form's second FP16 parts reach their smallest number.  With the rim lit alone the FP32 error was 1.0 times
+    // the direct sum's at a rim of 8 f (aperture radius 5.3 f), 1.1 to 1.3 times at 17 f, twice at 37 f and 150 times
+    // at 401 f; in FP64 the difference to the direct sum grew from 4e-15 at 8 f to 6e-15 and 4e-14.
+    if (in.r_max * in.r_max > 28.0 * in.f * in.f) return false;   // |r_s| = f + r^2 / 4f
     // Which sum is faster, in us of 1024 SIMDs' cycles (measured: 1.5 cycles per direct FP32 evaluation on the
     // tied tables and 4.4 in FP64, 1.2 and 5.3 per compacted one, a quarter more for the last round of
     // tiles; the matrix instructions of the two interpolations at 32 FP64 flops per cycle) and, for small
