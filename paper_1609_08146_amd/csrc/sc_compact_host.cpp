@@ -73,6 +73,8 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     // the direct sum's at a rim of 8 f (aperture radius 5.3 f), 1.1 to 1.3 times at 17 f, twice at 37 f and 150 times
     // at 401 f; in FP64 the difference to the direct sum grew from 4e-15 at 8 f to 6e-15 and 4e-14.
     if (in.r_max * in.r_max > 28.0 * in.f * in.f) return false;   // |r_s| = f + r^2 / 4f
+    // Wavelengths beyond the mirror's size: 1 / kR in the FP32 form's H leaves the range of FP16.
+    if (!in.fp64 && !(in.k_min * in.f >= 1.0 / 32.0)) return false;
     // Which sum is faster, in us of 1024 SIMDs' cycles (measured: 1.5 cycles per direct FP32 evaluation on the
     // tied tables and 4.4 in FP64, 1.2 and 5.3 per compacted one, a quarter more for the last round of
     // tiles; the matrix instructions of the two interpolations at 32 FP64 flops per cycle) and, for small

@@ -80,3 +80,11 @@ def test_deep_mirrors(planner, af, f, rp):
         if p:
             tol = 4e-14 + 3e-16 * rim * max(10.0, k * rp) if fp64 else 1e-7
             assert local_error(p, f, k, rp, 0.7 * rp) < tol
+
+
+def test_long_waves(planner):
+    """A frequency whose wave is longer than 64 pi f: the FP32 form is left to the direct sum, FP64 is not."""
+    args = dict(f=10.0, a=15.0, n_r=200, n_phi=240, k_max=2 * math.pi, n_k=2, pad=512, rp=1.0, rho=0.7)
+    for k_min, taken in ((1.0, True), (0.0032, True), (0.0031, False), (1e-6, False)):
+        assert (planner(k_min=k_min, fp64=False, **args) is not None) == taken
+        assert planner(k_min=k_min, fp64=True, **args) is not None
