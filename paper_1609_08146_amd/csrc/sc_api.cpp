@@ -1529,7 +1529,7 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     p->res_prec = -1;
     SC_TRY(run_quad(p->ctx, jobs, prec, l, p));
     HIP_TRY(launch_reduce(p->ctx->stream, mode_of(prec), p->partial.p, job.n_chunks, job.n_k, p->n_obs,
-                          p->n_obs_pad, p->d_k.as<double>(), job.tied, p->n_obs, 0, p->resE.p, p->resB.p,
+                          p->n_obs_pad, p->d_k.as<double>(), b_scale(job), p->n_obs, 0, p->resE.p, p->resB.p,
                           on_device ? E : nullptr, on_device ? B : nullptr));
     ev_record(p, EV_R1);
     p->ev_quad = p->ctx->profiling;
@@ -1610,7 +1610,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
         }
         const size_t at = real_size(prec) * 6 * (size_t)k0 * p->n_obs;
         HIP_TRY(launch_reduce(st, mode_of(prec), job.partial, job.n_chunks, job.n_k, n_o, job.n_obs_pad,
-                              p->d_k.as<double>() + k0, job.tied, p->n_obs, o0, (char *)E + at, (char *)B + at,
+                              p->d_k.as<double>() + k0, b_scale(job), p->n_obs, o0, (char *)E + at, (char *)B + at,
                               nullptr, nullptr));
         return SC_OK;
     };
@@ -1840,7 +1840,7 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
             if (group[i] != gr) continue;
             sc_prob *p = probs[i];
             HIP_TRY(launch_reduce(c->stream, mode_of(prec), jobs[i].partial, jobs[i].n_chunks, jobs[i].n_k, p->n_obs,
-                                  p->n_obs_pad, p->d_k.as<double>(), jobs[i].tied, p->n_obs, 0, p->resE.p,
+                                  p->n_obs_pad, p->d_k.as<double>(), b_scale(jobs[i]), p->n_obs, 0, p->resE.p,
                                   p->resB.p, nullptr, nullptr));
             p->res_prec = (int)prec;
             p->last_evals = (int64_t)p->n_obs * jobs[i].n_k * p->n_surf;

@@ -104,7 +104,7 @@ hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job);
 hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t per);
 // (and in E2, B2 where given)
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
-                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B, void *E2, void *B2);
+                         const double *k, int b_scale, int n_obs, int o0, void *E, void *B, void *E2, void *B2);
 // Compacted tables (sc_compact.h): weights and node records, then the tables of frequencies k0 ...
 // k0 + n_k - 1 (T: n_k x compact_rows_doubles) into out [n_k][n_c][8] of the precision.
 hipError_t launch_compact_geometry(hipStream_t st, const CompactPlan &plan, int n_r, int n_phi, double f,

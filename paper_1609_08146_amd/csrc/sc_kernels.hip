@@ -819,14 +819,14 @@ __global__ void k_tables_polar(int64_t n_rec, const float *__restrict__ tabf, fl
 }
 
 // Split-K reduction: E[k][o][c] = sum over chunks (in FP64, fixed order); B gets the 1/(ik) factor,
-// or 1/i where the quadrature's B sums already carry 1/k (b_over_k).  Bound by the partials' read.
+// less the part of 1/k that the quadrature's B sums carry already (b_scale).  Bound by the partials' read.
 // One workgroup per frequency and 64 points, one wave per real of the record: a wave's loads are
 // consecutive, and a small problem has 12 times the waves that one thread per point gave it; the
 // records are put together in LDS and written as one run.
 template <typename PT, typename OT>
 __global__ void __launch_bounds__(768)
 k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_obs_pad, const double *__restrict__ kv,
-         int b_over_k, int n_obs, int o0, OT *__restrict__ E, OT *__restrict__ B, OT *__restrict__ E2,
+         int b_scale, int n_obs, int o0, OT *__restrict__ E, OT *__restrict__ B, OT *__restrict__ E2,
          OT *__restrict__ B2)
 {
     const int groups = (n_o + 63) / 64, c = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -840,7 +840,8 @@ k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_o
         double acc = 0.0;
 #pragma unroll 8
         for (int ch = 0; ch < n_chunks; ++ch) acc += (double)p[ch * stride];
-        const double ik_inv = b_over_k ? 1.0 : 1.0 / kv[kk];   // 1/(ik) = -i/k
+        const double k = kv[kk];   // 1/(ik) = -i/k
+        const double ik_inv = b_scale == B_OVER_K ? 1.0 : (b_scale == B_OVER_K_POW2 ? ldexp(1.0, ilogb(k)) : 1.0) / k;
         // E: re, im of x, y, z; B: times -i / k, so the real part comes from the imaginary sum
         if (c < 6) rec[0][6 * lane + c] = (OT)acc;
         else if (c & 1) rec[1][6 * lane + c - 7] = (OT)(acc * ik_inv);
@@ -1024,16 +1025,16 @@ hipError_t launch_tables_cast(hipStream_t st, int n_k, int n_tot, const double *
 }
 
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
-                         const double *k, int b_over_k, int n_obs, int o0, void *E, void *B, void *E2, void *B2)
+                         const double *k, int b_scale, int n_obs, int o0, void *E, void *B, void *E2, void *B2)
 {
     const int64_t all = (int64_t)n_k * ((n_o + 63) / 64);
     const unsigned int nb = (unsigned int)(all < (1 << 20) ? all : (1 << 20));
     if (mode == MODE_FP64)
         hipLaunchKernelGGL((k_reduce<double, double>), dim3(nb), dim3(768), 0, st, (const double *)partial, n_chunks,
-                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (double *)E, (double *)B, (double *)E2, (double *)B2);
+                           n_k, n_o, n_o_pad, k, b_scale, n_obs, o0, (double *)E, (double *)B, (double *)E2, (double *)B2);
     else
         hipLaunchKernelGGL((k_reduce<float, float>), dim3(nb), dim3(768), 0, st, (const float *)partial, n_chunks,
-                           n_k, n_o, n_o_pad, k, b_over_k, n_obs, o0, (float *)E, (float *)B, (float *)E2, (float *)B2);
+                           n_k, n_o, n_o_pad, k, b_scale, n_obs, o0, (float *)E, (float *)B, (float *)E2, (float *)B2);
     return hipGetLastError();
 }
 

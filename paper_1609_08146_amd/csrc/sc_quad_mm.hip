@@ -383,16 +383,18 @@ k_mm_pack(int n_c, const double *__restrict__ kv, double s, const float *__restr
     // per node and column: factors of H or V, then of G or V delta / |r_s|, scaled
     __shared__ float colh[20][ALL + 1], colg[12][ALL + 1];
     // powers of two that bring each column's largest entry to 2^11 ... 2^12; mscale[k][16] holds what the sums
-    // are multiplied by (scale / KERNEL_SCALE)
+    // are multiplied by (scale / KERNEL_SCALE, and for B over the power of two at or below k: the sums of B' = ik B
+    // would leave FP32's range 2^23 earlier than B in metres), over the whole range of FP32
     __shared__ double inv[10];
     if (threadIdx.x < 16) {
         double m = 0.0;
         if (threadIdx.x < 10)
             for (int w = 0; w < SCALE_PARTS; ++w) m = fmax(m, mmax[((size_t)kk * SCALE_PARTS + w) * 10 + threadIdx.x]);
         // m = f 2^e with f in [0.5, 1): times 2^(12 - e)
-        const int e = m > 0.0 && m < 1e300 ? max(-100, min(100, ilogb(m) + 1)) : 12;
+        const int kb = threadIdx.x >= 4 ? ilogb(kv[kk]) : 0;
+        const int e = m > 0.0 && m < 1e300 ? max(kb - 131, min(kb + 145, ilogb(m) + 1)) : 12;
         if (threadIdx.x < 10) inv[threadIdx.x] = ldexp(1.0, 12 - e);
-        if (blockIdx.x == 0) mscale[16 * (size_t)kk + threadIdx.x] = (float)(ldexp(1.0, e - 12) / KERNEL_SCALE);
+        if (blockIdx.x == 0) mscale[16 * (size_t)kk + threadIdx.x] = (float)(ldexp(1.0, e - 12 - kb) / KERNEL_SCALE);
     }
     __syncthreads();
     if (threadIdx.x < ALL) {

@@ -43,6 +43,10 @@ struct QuadJob {
 
 enum QuadMode { MODE_FP64 = 0, MODE_SPLIT = 1, MODE_NAIVE = 2 };
 
+// What the B sums of a job carry besides i (see k_reduce): nothing of 1/k, all of it, or its power of two.
+enum BScale { B_PLAIN = 0, B_OVER_K = 1, B_OVER_K_POW2 = 2 };
+inline int b_scale(const QuadJob &j) { return j.mm ? B_OVER_K_POW2 : j.tied ? B_OVER_K : B_PLAIN; }
+
 // Segments of the tile list of one quadrature launch, and the spacing of their work counters (64 bytes).
 constexpr int QUAD_SEGMENTS = 8, QUAD_COUNTER_STRIDE = 16;
 
