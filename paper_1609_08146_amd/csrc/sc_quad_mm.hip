@@ -17,7 +17,7 @@
 // hi = fp16(x) and lo = fp16(x - hi): 22 bits, and all four products of the parts are summed in FP32
 // (rows of A: hi and lo of the table; two products per step: hi and lo of the kernel values).  The
 // columns that r' multiplies, and the term with delta / |r_s|, are hi alone where that factor is below
-// 1/100; FORM_GH_FAR gives those columns their lo part by a third product.  Table columns are scaled by
+// 1/1000; FORM_GH_FAR gives those columns their lo part by a third product.  Table columns are scaled by
 // powers of two to 2^12 at most, and the kernel values to about 2^6, so that no lo part falls below
 // FP16's smallest number.  Near the focus the error against 64 bits is about half the plain FP32
 // form's (0.1 m mirror, points within 4 wavelengths: 1.8e-7, plain 3.3e-7); elsewhere the same.
