@@ -112,17 +112,21 @@ typedef struct {
     double time_ms;      /* the semi-discrete time transform                      */
     int64_t evals;       /* obs x freq x surface nodes of the last evaluate       */
     int64_t tiles;       /* quadrature tiles of the last evaluate                 */
-    int32_t chunk;       /* node chunk of the last evaluate (fixes its bits)      */
+    int32_t chunk;       /* node chunk of the last evaluate: of a sum taken
+                            directly the one it used (it fixes the bits); of a
+                            compacted one, whose bits it does not change, the
+                            launch's                                              */
 } sc_timing;
 sc_status sc_get_timing(const sc_prob *p, sc_timing *out);
 
 /* Quadrature launch shape.  Only `chunk` changes the floating-point
  * summation order (and therefore the last bits of results); the other
  * fields change speed only.  Zero fields mean "library default": 1 point per
- * lane, 4 waves per workgroup, chunks of 2048 nodes (fewer, from 64 up, where
- * the problem's tiles would leave compute units idle), the resident limit of
- * workgroups, and frequencies per lane by table layout (4 with the factored
- * current in the FP32 forms, else 2).                                       */
+ * lane, 4 waves per workgroup, chunks of 2048 nodes (fewer, a multiple of 32
+ * from 64 up, where the problem's tiles would leave compute units idle; a chunk
+ * that is set is used as it is), the resident limit of workgroups, and
+ * frequencies per lane by table layout (4 with the factored current in the FP32
+ * forms, else 2; fewer where n_k does not fill them).                       */
 typedef struct {
     int obs_per_lane;    /* 1 or 2 observation points per lane                    */
     int waves_per_block; /* 1, 2 or 4 waves of 64 lanes per workgroup             */

@@ -1054,15 +1054,18 @@ sc_status sc::check_launch(const sc_launch &l)
     return SC_OK;
 }
 
-sc_launch sc::resolve_launch(const sc_prob *p, sc_precision prec)
+Launch sc::resolve_launch(const sc_prob *p, sc_precision prec)
 {
-    sc_launch l = default_launch(prec);
+    Launch l{default_launch(prec), true};
     auto it = p->ctx->tune.find(tune_key(p, prec));
-    if (it != p->ctx->tune.end()) l = it->second;
+    if (it != p->ctx->tune.end()) l = {it->second, false};
     if (p->has_launch) {
         if (p->launch.obs_per_lane) l.obs_per_lane = p->launch.obs_per_lane;
         if (p->launch.waves_per_block) l.waves_per_block = p->launch.waves_per_block;
-        if (p->launch.chunk) l.chunk = p->launch.chunk;
+        if (p->launch.chunk) {
+            l.chunk = p->launch.chunk;
+            l.own_chunk = false;
+        }
         if (p->launch.blocks_per_cu) l.blocks_per_cu = p->launch.blocks_per_cu;
         if (p->launch.freq_per_lane) l.freq_per_lane = p->launch.freq_per_lane;
     }
@@ -1181,27 +1184,28 @@ static sc_status select_tables(sc_prob *p, sc_precision prec, bool build, const 
 // chunk / 512 - 1 further roundings.
 constexpr int SUM_BLOCK = 512;
 
-// The chunk the direct sum really takes: the launch's, but shorter where that leaves fewer tiles than
-// resident waves (4 per SIMD in FP64, 5 in FP32).  A wave takes its nodes one after the other, 0.1 us each
+// The chunk the direct sum really takes: a given one as it is, and the library's own shorter where it leaves fewer
+// tiles than resident waves (4 per SIMD in FP64, 5 in FP32).  A wave takes its nodes one after the other, 0.1 us each
 // on a full chip and 0.3 alone: 114 points at one frequency over 3 136 nodes took 256 us in 4 waves of
 // 2 048 nodes, and 1 500 points at 16 frequencies over 65 800 nodes 1.73 ms with two waves per SIMD, 1.33
-// with five.  A function of the problem and its chunk alone; where it would take the partials over 60 MB
+// with five.  A function of the problem alone; where it would take the partials over 60 MB
 // the chunk stays (sc_evaluate_noalloc has 64 MB for them).
-static int direct_chunk(const sc_prob *p, sc_precision prec, int chunk)
+static int direct_chunk(const sc_prob *p, sc_precision prec, const Launch &l)
 {
+    if (!l.own_chunk) return l.chunk;
     const int64_t c = direct_chunk_nodes(p->n_tot, p->n_obs_pad, (int)p->k.size(), prec == SC_FP64);
-    if (c >= chunk) return chunk;
+    if (c >= l.chunk) return l.chunk;
     const int64_t bytes = (int64_t)real_size(prec) * 12 * ((p->n_tot + c - 1) / c) * (int64_t)p->k.size() * p->n_obs_pad;
-    return bytes > (60 << 20) ? chunk : (int)c;
+    return bytes > (60 << 20) ? l.chunk : (int)c;
 }
 
 // The quadrature job of one problem (no allocation): tables `tab` of the chosen layout, split-K
 // partials in `partial` ([n_chunks][n_k][12][n_obs_pad] reals of the precision).
-static void fill_job(const sc_prob *p, sc_precision prec, const sc_launch &l, const void *tab, bool fact,
+static void fill_job(const sc_prob *p, sc_precision prec, const Launch &l, const void *tab, bool fact,
                      void *partial, QuadJob &job)
 {
     const int n_k = (int)p->k.size();
-    const int chunk = direct_chunk(p, prec, l.chunk);
+    const int chunk = direct_chunk(p, prec, l);
     const int n_chunks = (p->n_tot + chunk - 1) / chunk;
     job.tab = tab;
     job.pos = prec == SC_FP64 ? (fact ? p->posf64.p : p->pos64.p) : (fact ? p->posf.p : p->pos32.p);
@@ -1374,8 +1378,14 @@ static size_t partial_bytes(const sc_prob *p, sc_precision prec, const sc_launch
     return real_size(prec) * 12 * n_chunks * p->k.size() * (size_t)p->n_obs_pad;
 }
 
+// The chunk that sc_get_timing reports.
+static int used_chunk(const sc_prob *p, const Launch &l, const QuadJob &job)
+{
+    return job.n_tot == p->n_tot ? job.chunk : l.chunk;   // (a compacted sum has at most half the nodes)
+}
+
 // Make sure the tables of precision `prec` exist; size the partial and result buffers.
-sc_status sc::prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job, bool own_partials)
+sc_status sc::prepare(sc_prob *p, sc_precision prec, const Launch &l, int mm_fpb, QuadJob &job, bool own_partials)
 {
     const void *tab = nullptr;
     bool fact = false;
@@ -1430,12 +1440,12 @@ size_t sc::footprint_bytes(int n_r, int n_phi, int n_k, int n_obs, int n_t, sc_p
     return b;
 }
 
-size_t sc::quad_bytes(const sc_prob *p, sc_precision prec, const sc_launch &l)
+size_t sc::quad_bytes(const sc_prob *p, sc_precision prec, const Launch &l)
 {
     const size_t per_chunk = real_size(prec) * 12 * p->k.size() * (size_t)p->n_obs_pad;
     CompactPlan plan;
     if (!plan_compact(p, prec, plan)) {
-        const int chunk = direct_chunk(p, prec, l.chunk);
+        const int chunk = direct_chunk(p, prec, l);
         return per_chunk * (size_t)((p->n_tot + chunk - 1) / chunk);
     }
     const size_t part = per_chunk * (size_t)((plan.n_c + plan.chunk - 1) / plan.chunk);
@@ -1521,7 +1531,7 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     if (!p) return fail(SC_E_INVAL, "sc_evaluate: prob is NULL");
     DeviceGuard g(p->ctx->device);
     SC_TRY(settle_factoring(p));
-    const sc_launch l = resolve_launch(p, prec);
+    const Launch l = resolve_launch(p, prec);
     SC_TRY(check_launch(l));
     QuadJob job{};
     SC_TRY(prepare(p, prec, l, 0, job));
@@ -1536,7 +1546,7 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     p->res_prec = (int)prec;
     p->last_evals = (int64_t)p->n_obs * job.n_k * p->n_surf;
     p->last_tiles = job.n_tiles;
-    p->last_chunk = l.chunk;
+    p->last_chunk = used_chunk(p, l, job);
     if (on_device) return SC_OK;   // the reduction wrote them
     return copy_out(p, E, B, 0, real_size(prec) * 6 * (size_t)job.n_k * p->n_obs);
 }
@@ -1584,7 +1594,7 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
     if (!base) return fail(SC_E_STATE, "sc_evaluate_noalloc: no scratch memory on device %d", dev);
     DeviceGuard g(dev);
     SC_TRY(settle_factoring(p));   // only a problem of the serving loop can have a test pending
-    const sc_launch l = resolve_launch(p, prec);
+    const Launch l = resolve_launch(p, prec);
     SC_TRY(check_launch(l));
     const void *tab = nullptr;
     bool fact = false;
@@ -1719,7 +1729,7 @@ static double batch_partial_cap(sc_prob *const *probs, int n, sc_precision prec)
     return std::max(2.0 * table_ref * (prec == SC_FP64 ? 2.0 : 1.0), 8.0 * 1073741824.0);
 }
 
-static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, std::vector<sc_launch> &ls)
+static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, std::vector<Launch> &ls)
 {
     const double cap = batch_partial_cap(probs, n, prec);
     auto total = [&](int floor_chunk) {
@@ -1731,11 +1741,14 @@ static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, 
         }
         return b;
     };
-    if (total(0) <= cap) return;
-    int floor_chunk = 2048;
-    while (floor_chunk < (1 << 20) && total(floor_chunk) > cap) floor_chunk *= 2;
-    for (int i = 0; i < n; ++i)
-        if (!(probs[i]->has_launch && probs[i]->launch.chunk)) ls[i].chunk = std::max(ls[i].chunk, floor_chunk);
+    if (total(0) > cap) {
+        int floor_chunk = 2048;
+        while (floor_chunk < (1 << 20) && total(floor_chunk) > cap) floor_chunk *= 2;
+        for (int i = 0; i < n; ++i)
+            if (!(probs[i]->has_launch && probs[i]->launch.chunk))
+                ls[i].chunk = std::max(ls[i].chunk, floor_chunk);
+        for (Launch &l : ls) l.own_chunk = false;
+    }
 }
 
 extern "C" sc_status sc_set_batch_launch(sc_ctx *c, sc_precision prec, const sc_launch *l)
@@ -1784,27 +1797,30 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
         SC_TRY(check_launch(shape));
     }
     std::vector<QuadJob> jobs(n);
-    std::vector<sc_launch> ls(n);
+    std::vector<Launch> ls(n);
     for (int i = 0; i < n; ++i) {
         // one kernel shape per launch; the chunk stays per problem (it alone fixes the summation
         // order), unless the context's tuned batch launch sets one for problems that fix none
         ls[i] = resolve_launch(probs[i], prec);
         ls[i].obs_per_lane = l0.obs_per_lane;
         ls[i].freq_per_lane = l0.freq_per_lane;
-        if (l0.chunk && !(probs[i]->has_launch && probs[i]->launch.chunk)) ls[i].chunk = l0.chunk;
+        if (l0.chunk && !(probs[i]->has_launch && probs[i]->launch.chunk)) {
+            ls[i].chunk = l0.chunk;
+            ls[i].own_chunk = false;
+        }
         SC_TRY(check_launch(ls[i]));
     }
+    std::vector<size_t> part(n), at(n, 0);
+    for (int i = 0; i < n; ++i) part[i] = (compact_partial_bytes(probs[i], prec) + 255) & ~size_t(255);
     batch_fit_partials(probs, n, prec, ls);
     // Compacted sums have chunks of at most 256 nodes whatever the launch, so beyond the cap the problems
     // go in groups whose partials share one buffer, that of the first of them, one group after the other
     // (256 problems of the sweep: 88 GB of partials for a cap of 69).
     const size_t cap = (size_t)batch_partial_cap(probs, n, prec);
-    std::vector<size_t> part(n), at(n, 0);
     std::vector<int> group(n, 0);
     size_t total = 0, used = 0, most = 0;
     int holder = -1, groups = 1;
     for (int i = 0; i < n; ++i) {
-        part[i] = (compact_partial_bytes(probs[i], prec) + 255) & ~size_t(255);
         total += part[i];
     }
     if (total > cap) {
@@ -1845,7 +1861,7 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
             p->res_prec = (int)prec;
             p->last_evals = (int64_t)p->n_obs * jobs[i].n_k * p->n_surf;
             p->last_tiles = jobs[i].n_tiles;
-            p->last_chunk = ls[i].chunk;
+            p->last_chunk = used_chunk(p, ls[i], jobs[i]);
         }
     }
     ev_record(probs[0], EV_R1);

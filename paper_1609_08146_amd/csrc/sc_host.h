@@ -181,6 +181,14 @@ struct TuneKey {
     }
 };
 
+// A launch shape, and whether its chunk is the library's own, which the direct sum may shorten (direct_chunk); one that
+// a caller, a tuned entry, a batch launch or the cap on a batch's partials has set is used as given.
+struct Launch : sc_launch {
+    bool own_chunk = true;
+    Launch() : sc_launch{} {}
+    Launch(const sc_launch &l, bool own) : sc_launch(l), own_chunk(own) {}
+};
+
 enum { EV_PREP0, EV_PREP1, EV_Q0, EV_Q1, EV_R1, EV_T0, EV_T1, EV_N };
 
 }  // namespace sc
@@ -295,7 +303,7 @@ struct sc_prob {
     hipEvent_t ev[sc::EV_N] = {};
     bool ev_prep = false, ev_quad = false, ev_time = false;
     int64_t last_evals = 0, last_tiles = 0;
-    int last_chunk = 0;   // node chunk of the last evaluation
+    int last_chunk = 0;   // node chunk of the last evaluation (of a compacted sum: the launch's)
 };
 
 namespace sc {
@@ -307,7 +315,7 @@ constexpr int OBS_PAD = 128;   // observation padding (64 lanes x up to 2 points
 void gauss_legendre_rule(int n, std::vector<double> &x, std::vector<double> &w);
 
 // Launch shape for a problem and precision (override > tuned > default).
-sc_launch resolve_launch(const sc_prob *p, sc_precision prec);
+Launch resolve_launch(const sc_prob *p, sc_precision prec);
 sc_status check_launch(const sc_launch &l);
 int mode_of(sc_precision prec);
 size_t real_size(sc_precision prec);
@@ -321,13 +329,13 @@ void prob_free_on(sc_prob *p, hipStream_t st);
 // mm_fpb: frequencies per tile of the compacted FP32 sum (0: the problem's best, for a launch of its own).
 constexpr int MM_FREQS_SHARED = 4;
 // own_partials = false: of a compacted sum none are sized, and the caller sets job.partial.
-sc_status prepare(sc_prob *p, sc_precision prec, const sc_launch &l, int mm_fpb, QuadJob &job, bool own_partials = true);
+sc_status prepare(sc_prob *p, sc_precision prec, const Launch &l, int mm_fpb, QuadJob &job, bool own_partials = true);
 // Upload `jobs` (tile0 assigned here) and run one persistent quadrature launch on ctx's stream.
 sc_status run_quad(sc_ctx *c, std::vector<QuadJob> &jobs, sc_precision prec, const sc_launch &l, sc_prob *timed);
 // Device bytes a problem of this shape holds after an evaluate (+ time transform with n_t samples).
 size_t footprint_bytes(int n_r, int n_phi, int n_k, int n_obs, int n_t, sc_precision prec, int chunk);
 // Device bytes of the sum of p in prec: its partials and, of a compacted sum, its tables and the memory
 // they are built in.  Reads the sizes, frequencies and extent of the points of p alone.
-size_t quad_bytes(const sc_prob *p, sc_precision prec, const sc_launch &l);
+size_t quad_bytes(const sc_prob *p, sc_precision prec, const Launch &l);
 
 }  // namespace sc

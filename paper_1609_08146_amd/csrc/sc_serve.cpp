@@ -302,7 +302,7 @@ static sc_status setup_finish(sc_server *s, Req *r, bool *ready)
     sc_prob *p = r->prob;
     SC_TRY(resolve_factoring(p, false, ready));
     if (!*ready) return SC_OK;
-    sc_launch l = resolve_launch(p, r->prec);
+    Launch l = resolve_launch(p, r->prec);
     l.obs_per_lane = server_opl(r->prec);
     l.freq_per_lane = server_fpb(r->prec);
     SC_TRY(prepare(p, r->prec, l, MM_FREQS_SHARED, r->job));
@@ -800,7 +800,7 @@ extern "C" sc_status sc_server_submit(sc_server *s, const sc_request *q, uint64_
         probe.n_obs = q->n_obs;
         probe.k = r->k;
         probe.n_tot = (q->n_r + 1) * q->n_phi;
-        const sc_launch l = resolve_launch(&probe, q->prec);
+        const Launch l = resolve_launch(&probe, q->prec);
         r->bytes = footprint_bytes(q->n_r, q->n_phi, q->n_k, q->n_obs, q->n_t, q->prec, l.chunk);
         // the footprint counts the partials of the direct sum at the launch's chunk; what the sum takes
         // beyond them is charged too, though no request is too large for the budget because of it

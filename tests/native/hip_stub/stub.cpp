@@ -53,6 +53,7 @@ struct Use {
 };
 struct Alloc_ {
     size_t bytes;
+    bool partials = false;
     std::map<StubStream *, Use> uses;
 };
 std::map<char *, Alloc_> allocs;
@@ -109,7 +110,7 @@ hipError_t take(void **p, size_t n)
     n = (n + 4095) / 4096 * 4096;
     void *q = mmap(nullptr, n, PROT_READ | PROT_WRITE, MAP_PRIVATE | MAP_ANONYMOUS | MAP_NORESERVE, -1, 0);
     if (q == MAP_FAILED) return hipErrorOutOfMemory;
-    allocs[(char *)q] = {n, {}};
+    allocs[(char *)q].bytes = n;
     live += n;
     peak = std::max(peak, live);
     *p = q;
@@ -153,6 +154,14 @@ namespace stub {
 size_t live_bytes() { LOCK; return live; }
 size_t peak_bytes() { LOCK; return peak; }
 long long allocations() { LOCK; return n_alloc; }
+std::vector<PartialUse> partials()
+{
+    LOCK;
+    std::vector<PartialUse> v;
+    for (auto &a : allocs)
+        if (a.second.partials) v.push_back({a.first, a.second.bytes});
+    return v;
+}
 void clear()
 {
     LOCK;
@@ -351,6 +360,10 @@ static void quad(hipStream_t st, const QuadJob *jobs, const QuadJob &one, int n_
              i ? 0.0 : 12.0 + values / 1.2e6);
     }
     LOCK;
+    for (int i = 0; i < n_jobs; ++i) {
+        auto it = allocs.upper_bound((char *)js[i].partial);
+        if (it != allocs.begin()) std::prev(it)->second.partials = true;
+    }
     launches.push_back({js[0].mm ? "matrix" : "direct", js[0].chunk, js[0].n_tot, js[0].n_chunks, js[0].mm, js[0].form,
                         n_jobs, (long long)js[0].n_tiles});
 }

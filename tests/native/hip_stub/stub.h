@@ -27,6 +27,12 @@ extern double sim;                            // > 0: device work takes time (a 
 
 extern long long waits;                       // waits of the host for work that it did not know to be done
 
+struct PartialUse {
+    const void *block;
+    size_t bytes;
+};
+std::vector<PartialUse> partials();           // the live allocations that quadratures have written partials to
+
 size_t live_bytes();    // device memory not freed
 size_t peak_bytes();
 long long allocations();

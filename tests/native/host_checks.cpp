@@ -13,6 +13,8 @@
 #include <string>
 #include <vector>
 
+#include <hip/hip_runtime.h>
+
 #include "sc_host.h"
 #include "stub.h"
 
@@ -158,6 +160,116 @@ static void no_waits()
     no_violations("served requests");
 }
 
+// ------------------------------------------------------------------------------ single problems
+
+struct Problem {
+    sc_prob *p = nullptr;
+    void *points = nullptr;
+    // `direct`: the points in device memory, so that the sum is taken node by node
+    Problem(sc_ctx *ctx, int n_r, int n_phi, int n_k, int n_obs, bool direct, double k0 = 2.0 * M_PI)
+    {
+        std::vector<double> k, obs;
+        for (int i = 0; i < n_k; ++i) k.push_back(k0 * (1.0 + 0.01 * i));
+        for (int i = 0; i < 3 * n_obs; ++i) obs.push_back(std::sin(1.0 + 3.0 * i));
+        OK(sc_prob_create(ctx, &p));
+        OK(sc_set_mirror(p, 20.0, 30.0, n_r, n_phi));
+        OK(sc_set_frequencies(p, k.data(), n_k));
+        OK(sc_set_incident_gaussian(p, 15.0, 0.0, nullptr, 0));
+        if (direct) {
+            (void)hipMalloc(&points, sizeof(double) * obs.size());
+            memcpy(points, obs.data(), sizeof(double) * obs.size());
+        }
+        OK(sc_set_observation(p, direct ? (double *)points : obs.data(), n_obs, direct));
+    }
+    ~Problem()
+    {
+        OK(sc_prob_destroy(p));
+        if (points) (void)hipFree(points);
+    }
+    void launch(int chunk) const
+    {
+        sc_launch l{};
+        l.chunk = chunk;
+        OK(sc_set_launch(p, &l));
+    }
+    int reported() const
+    {
+        sc_timing t{};
+        OK(sc_get_timing(p, &t));
+        return t.chunk;
+    }
+};
+
+// A chunk that the caller, a tuned entry or a batch launch sets is the one the direct sum takes, and sc_get_timing
+// tells the one it took.
+static void chunks()
+{
+    sc_ctx *ctx = nullptr;
+    OK(sc_ctx_create(0, nullptr, &ctx));
+    for (sc_precision prec : {SC_FP32_SPLIT, SC_FP64, SC_FP32}) {
+        Problem a(ctx, 80, 64, 3, 200, true);
+        auto evaluate = [&](int want) {
+            stub::clear();
+            OK(sc_evaluate(a.p, prec, nullptr, nullptr, 0));
+            const stub::Launch &l = stub::launches.back();
+            EXPECT(!l.mm && (want == 0 ? l.chunk < 2048 : l.chunk == want), "took %d for %d", l.chunk, want);
+            EXPECT(a.reported() == l.chunk, "reported %d, took %d", a.reported(), l.chunk);
+        };
+        evaluate(0);
+        for (int chunk : {64, 256, 2048, 4096}) {
+            a.launch(chunk);
+            evaluate(chunk);
+        }
+        OK(sc_set_launch(a.p, nullptr));
+        sc_launch shape{1, 4, 1024, 0, 1};
+        OK(sc_set_batch_launch(ctx, prec, &shape));
+        sc_prob *one[1] = {a.p};
+        stub::clear();
+        OK(sc_evaluate_batch(ctx, one, 1, prec));
+        EXPECT(stub::launches.back().chunk == 1024 && a.reported() == 1024, "%d", stub::launches.back().chunk);
+        OK(sc_set_batch_launch(ctx, prec, nullptr));
+        // a tuned entry, written as sc_autotune_save does (layouts 0 ... 2, so that one of them is this problem's)
+        FILE *f = fopen("tune.txt", "w");
+        for (int layout = 0; layout < 3; ++layout) fprintf(f, "%d %d 7 1 12 1 4 512 0 1\n", (int)prec, layout);
+        fclose(f);
+        OK(sc_autotune_load(ctx, "tune.txt"));
+        evaluate(512);
+    }
+    OK(sc_ctx_destroy(ctx));
+}
+
+// The partials of a batch stay within 8 GiB (the documented cap for few nodes), whether the chunk is raised to
+// that end or only not shortened, and with compacted sums beside them.
+static void batch_cap()
+{
+    const double cap = 8.0 * 1073741824.0;
+    for (bool mixed : {false, true}) {
+        sc_ctx *ctx = nullptr;
+        OK(sc_ctx_create(0, nullptr, &ctx));
+        {
+            std::vector<Problem *> ps;
+            std::vector<sc_prob *> h;
+            // 12 x 4 B x 64 frequencies x 768 points x 25 chunks of 384 nodes: 59 MB each; 15 MB at 2048 nodes
+            for (int i = 0; i < 190; ++i) ps.push_back(new Problem(ctx, 95, 100, 64, 700, !mixed || i % 2));
+            for (Problem *p : ps) h.push_back(p->p);
+            OK(sc_evaluate_batch(ctx, h.data(), (int)h.size(), SC_FP32_SPLIT));
+            double held = 0.0;
+            for (const stub::PartialUse &u : stub::partials()) held += (double)u.bytes;
+            EXPECT(held < cap, "%.1f GB of partials", held * 1e-9);
+            for (Problem *p : ps) delete p;
+        }
+        // and where the chunk had to be raised, it stays raised: 12 x 4 B x 256 x 16384 points x 51 chunks = 10.3 GB
+        {
+            Problem big(ctx, 320, 320, 256, 16384, true);
+            sc_prob *one[1] = {big.p};
+            stub::clear();
+            OK(sc_evaluate_batch(ctx, one, 1, SC_FP32_SPLIT));
+            EXPECT(stub::launches.back().chunk == 4096 && big.reported() == 4096, "%d", stub::launches.back().chunk);
+        }
+        OK(sc_ctx_destroy(ctx));
+    }
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, std::function<void()>> checks = {
@@ -165,6 +277,8 @@ int main(int argc, char **argv)
         {"block_sizes", block_sizes},
         {"block_turnover", block_turnover},
         {"no_waits", no_waits},
+        {"chunks", chunks},
+        {"batch_cap", batch_cap},
     };
     if (argc == 2 && checks.count(argv[1])) {
         checks.at(argv[1])();
