@@ -510,9 +510,10 @@ sc_status sc_field_energy(sc_prob *p, const double *t, int n_t, double dk, doubl
  * problem) are kept within max(2 x 16 B x sum of frequencies x nodes, 8 GiB),
  * doubled for SC_FP64: if the chunks so far exceed that, the problems that fix
  * no chunk with sc_set_launch take the smallest power-of-two chunk from 2048
- * up that fits (sc_get_timing reports each problem's chunk), and the problems
- * whose sum is compacted (sc_evaluate) go in several launches, one after the
- * other, that share one buffer of partials.  Each problem's
+ * up that fits (sc_get_timing reports each problem's chunk); if only the shorter
+ * chunks that the library takes for small problems exceed it, they are 2048; and
+ * the problems whose sum is compacted (sc_evaluate) go in several launches, one
+ * after the other, that share one buffer of partials.  Each problem's
  * result is bitwise identical to what sc_evaluate gives it alone with the
  * same chunk.                                                               */
 sc_status sc_evaluate_batch(sc_ctx *ctx, sc_prob *const *probs, int n, sc_precision prec);

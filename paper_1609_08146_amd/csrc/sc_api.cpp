@@ -1721,7 +1721,8 @@ static sc_launch batch_launch(const sc_ctx *c, sc_prob *const *probs, int n, sc_
 // so many problems with many points at a small chunk would hold several times their tables.  If
 // the chunks chosen so far exceed that, the problems that fix no chunk of their own take the
 // smallest power-of-two chunk from 2048 up (never below their own) that fits; the result of each
-// problem is then its result alone at that chunk.  Deterministic in the batch's sizes.
+// problem is then its result alone at that chunk.  If only the library's shorter chunks exceed it, they are
+// not shortened.  Deterministic in the batch's sizes.
 static double batch_partial_cap(sc_prob *const *probs, int n, sc_precision prec)
 {
     double table_ref = 0.0;
@@ -1729,7 +1730,9 @@ static double batch_partial_cap(sc_prob *const *probs, int n, sc_precision prec)
     return std::max(2.0 * table_ref * (prec == SC_FP64 ? 2.0 : 1.0), 8.0 * 1073741824.0);
 }
 
-static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, std::vector<Launch> &ls)
+// `compact`: per problem the bytes of a compacted sum's partials, 0 where the sum is taken directly.
+static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, const std::vector<size_t> &compact,
+                               std::vector<Launch> &ls)
 {
     const double cap = batch_partial_cap(probs, n, prec);
     auto total = [&](int floor_chunk) {
@@ -1748,7 +1751,17 @@ static void batch_fit_partials(sc_prob *const *probs, int n, sc_precision prec, 
             if (!(probs[i]->has_launch && probs[i]->launch.chunk))
                 ls[i].chunk = std::max(ls[i].chunk, floor_chunk);
         for (Launch &l : ls) l.own_chunk = false;
+        return;
     }
+    double held = 0.0;
+    for (int i = 0; i < n; ++i) {
+        if (compact[i]) continue;   // (go in groups that keep to what the others leave)
+        sc_launch l = ls[i];
+        l.chunk = direct_chunk(probs[i], prec, ls[i]);
+        held += (double)partial_bytes(probs[i], prec, l);
+    }
+    if (held > cap)
+        for (Launch &l : ls) l.own_chunk = false;
 }
 
 extern "C" sc_status sc_set_batch_launch(sc_ctx *c, sc_precision prec, const sc_launch *l)
@@ -1812,16 +1825,20 @@ extern "C" sc_status sc_evaluate_batch(sc_ctx *c, sc_prob *const *probs, int n, 
     }
     std::vector<size_t> part(n), at(n, 0);
     for (int i = 0; i < n; ++i) part[i] = (compact_partial_bytes(probs[i], prec) + 255) & ~size_t(255);
-    batch_fit_partials(probs, n, prec, ls);
+    batch_fit_partials(probs, n, prec, part, ls);
     // Compacted sums have chunks of at most 256 nodes whatever the launch, so beyond the cap the problems
     // go in groups whose partials share one buffer, that of the first of them, one group after the other
     // (256 problems of the sweep: 88 GB of partials for a cap of 69).
-    const size_t cap = (size_t)batch_partial_cap(probs, n, prec);
+    size_t cap = (size_t)batch_partial_cap(probs, n, prec);
     std::vector<int> group(n, 0);
     size_t total = 0, used = 0, most = 0;
     int holder = -1, groups = 1;
     for (int i = 0; i < n; ++i) {
         total += part[i];
+        if (part[i]) continue;
+        sc_launch l = ls[i];
+        l.chunk = direct_chunk(probs[i], prec, ls[i]);
+        cap -= std::min(cap, partial_bytes(probs[i], prec, l));   // the directly summed problems' own
     }
     if (total > cap) {
         for (int i = 0; i < n; ++i) {
