@@ -145,11 +145,15 @@ sc_status sc_set_launch(sc_prob *p, const sc_launch *launch);
 sc_status sc_get_launch(const sc_prob *p, sc_precision prec, sc_launch *out);
 /* Time candidate launches on problem `p` (quadrature plus reduction, best of
  * two runs each) and store the fastest in the context's cache, keyed by
- * (precision, table layout, size buckets of n_obs, n_k and nodes): first the
+ * (precision, table layout or compacted sum, size buckets of n_obs, n_k and
+ * nodes): first the
  * kernel shape and waves per workgroup at the library's chunk, then the chunk
  * (512 ... 16384 nodes) and workgroups per CU.  A tuned chunk sets the
  * summation order, so every problem of the bucket then gets that chunk's bits
- * (alone and in batches alike).  `budget_ms` bounds the time spent (0 = 20 s);
+ * (alone and in batches alike); for a problem so small that the library's own
+ * chunk is below 512 nodes, the library's launch can be the faster one.  Of a
+ * compacted sum (sc_evaluate) only what can differ is tried: shapes in SC_FP64,
+ * nothing in SC_FP32_SPLIT.  `budget_ms` bounds the time spent (0 = 20 s);
  * *best (may be NULL) receives the winner.                                  */
 sc_status sc_autotune(sc_prob *p, sc_precision prec, double budget_ms, sc_launch *best);
 /* The launch of sc_evaluate_batch in precision `prec`: the kernel shape,

@@ -1034,10 +1034,14 @@ static int auto_freq_per_lane(sc_precision prec, bool fact, int n_k)
     return best;
 }
 
+static bool plan_compact(const sc_prob *p, sc_precision prec, CompactPlan &plan);
+
+// A compacted sum reads neither layout in its quadrature and takes other shapes than a direct one of its sizes.
 static TuneKey tune_key(const sc_prob *p, sc_precision prec)
 {
-    return {(int)prec, uses_tied(p, prec) ? 2 : uses_factored(p, prec) ? 1 : 0, log2_bucket(p->n_obs),
-            log2_bucket((int64_t)p->k.size()), log2_bucket(p->n_tot)};
+    CompactPlan plan;
+    const int layout = plan_compact(p, prec, plan) ? 3 : uses_tied(p, prec) ? 2 : uses_factored(p, prec) ? 1 : 0;
+    return {(int)prec, layout, log2_bucket(p->n_obs), log2_bucket((int64_t)p->k.size()), log2_bucket(p->n_tot)};
 }
 
 sc_status sc::check_launch(const sc_launch &l)
@@ -1057,8 +1061,10 @@ sc_status sc::check_launch(const sc_launch &l)
 Launch sc::resolve_launch(const sc_prob *p, sc_precision prec)
 {
     Launch l{default_launch(prec), true};
-    auto it = p->ctx->tune.find(tune_key(p, prec));
-    if (it != p->ctx->tune.end()) l = {it->second, false};
+    if (!p->ctx->tune.empty()) {
+        auto it = p->ctx->tune.find(tune_key(p, prec));
+        if (it != p->ctx->tune.end()) l = {it->second, false};
+    }
     if (p->has_launch) {
         if (p->launch.obs_per_lane) l.obs_per_lane = p->launch.obs_per_lane;
         if (p->launch.waves_per_block) l.waves_per_block = p->launch.waves_per_block;
@@ -1247,7 +1253,7 @@ static void fill_job(const sc_prob *p, sc_precision prec, const Launch &l, const
 // result does not depend on the launch, the batch or the calls before.
 static bool plan_compact(const sc_prob *p, sc_precision prec, CompactPlan &plan)
 {
-    if (prec == SC_FP32 || p->f <= 0.0 || p->obs_r2max < 0.0) return false;
+    if (prec == SC_FP32 || p->f <= 0.0 || p->obs_r2max < 0.0 || p->k.empty()) return false;
     CompactInput in{};
     in.f = p->f;
     in.r_max = p->a;
@@ -2160,10 +2166,16 @@ extern "C" sc_status sc_autotune(sc_prob *p, sc_precision prec, double budget_ms
     };
     // stage 1: kernel shape and waves per workgroup at the library's chunk; stage 2: the chunk (it
     // sets the split-K partials' size and the summation order) and workgroups per CU for that shape
+    // (a compacted sum has no chunk, and in the FP32 form no shape that a launch could choose: the library's is the
+    // result, instead of the noise of equal launches)
     const sc_launch lib = resolve_launch(p, prec);
+    CompactPlan plan;
+    const bool compact = plan_compact(p, prec, plan), fixed = compact && prec == SC_FP32_SPLIT;
     std::vector<sc_launch> cands;
+    if (fixed) cands.push_back(lib);
     for (auto &sh : TUNE_SHAPES)
         for (int wpb : {4, 2, 1}) {
+            if (fixed) continue;
             sc_launch l = lib;
             l.obs_per_lane = sh[0];
             l.freq_per_lane = sh[1];
@@ -2176,10 +2188,10 @@ extern "C" sc_status sc_autotune(sc_prob *p, sc_precision prec, double budget_ms
     int bi = -1;
     sc_status st = tune_loop(cands, 0.6 * budget_ms, t_start, run, &bi, &best_ms);
     sc_launch best_l = bi >= 0 ? cands[bi] : lib;
-    if (st == SC_OK && bi >= 0) {
+    if (st == SC_OK && bi >= 0 && !fixed) {
         std::vector<sc_launch> c2;
         for (int chunk = 512; chunk <= 16384; chunk *= 2) {
-            if (chunk > 2 * p->n_tot && chunk != best_l.chunk) continue;
+            if ((compact || chunk > 2 * p->n_tot) && chunk != best_l.chunk) continue;
             for (int bpc : {0, 2, 1}) {
                 if (chunk == best_l.chunk && bpc == 0) continue;   // timed in stage 1
                 sc_launch l = best_l;
@@ -2223,9 +2235,18 @@ extern "C" sc_status sc_autotune_batch(sc_ctx *c, sc_prob *const *probs, int n, 
     };
     c->batch_tune.erase((int)prec);
     const sc_launch lib = batch_launch(c, probs, n, prec);
+    // (as in sc_autotune, where every sum of the batch is compacted)
+    bool compact = true;
+    for (int i = 0; i < n && compact; ++i) {
+        CompactPlan plan;
+        compact = probs[i] && plan_compact(probs[i], prec, plan);
+    }
+    const bool fixed = compact && prec == SC_FP32_SPLIT;
     std::vector<sc_launch> cands;
+    if (fixed) cands.push_back(lib);
     for (auto &sh : TUNE_SHAPES)
         for (int wpb : {4, 2}) {
+            if (fixed) continue;
             sc_launch l = lib;
             l.obs_per_lane = sh[0];
             l.freq_per_lane = sh[1];
@@ -2237,12 +2258,12 @@ extern "C" sc_status sc_autotune_batch(sc_ctx *c, sc_prob *const *probs, int n, 
     int bi = -1;
     sc_status st = tune_loop(cands, 0.6 * budget_ms, t_start, run, &bi, &best_ms);
     sc_launch best_l = bi >= 0 ? cands[bi] : lib;
-    if (st == SC_OK && bi >= 0) {
+    if (st == SC_OK && bi >= 0 && !fixed) {
         // one chunk for the whole batch (0: each problem's own), and workgroups per CU
         std::vector<sc_launch> c2;
         for (int chunk : {0, 1024, 2048, 4096, 8192, 16384})
             for (int bpc : {0, 2}) {
-                if (chunk == best_l.chunk && bpc == best_l.blocks_per_cu) continue;
+                if ((compact && chunk) || (chunk == best_l.chunk && bpc == best_l.blocks_per_cu)) continue;
                 sc_launch l = best_l;
                 l.chunk = chunk;
                 l.blocks_per_cu = bpc;

@@ -171,7 +171,7 @@ struct DeviceGuard {
     }
 };
 
-// Autotuner cache key: precision, table layout (2 factored current with the tied charge, 1 factored
+// Autotuner cache key: precision, table layout (3 compacted sum, 2 factored current with the tied charge, 1 factored
 // current, 0 general tables) and the log2 size buckets of points, frequencies and nodes.
 struct TuneKey {
     int prec, fact, b_obs, b_k, b_nodes;

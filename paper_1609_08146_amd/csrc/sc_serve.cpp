@@ -800,10 +800,6 @@ extern "C" sc_status sc_server_submit(sc_server *s, const sc_request *q, uint64_
         probe.n_obs = q->n_obs;
         probe.k = r->k;
         probe.n_tot = (q->n_r + 1) * q->n_phi;
-        const Launch l = resolve_launch(&probe, q->prec);
-        r->bytes = footprint_bytes(q->n_r, q->n_phi, q->n_k, q->n_obs, q->n_t, q->prec, l.chunk);
-        // the footprint counts the partials of the direct sum at the launch's chunk; what the sum takes
-        // beyond them is charged too, though no request is too large for the budget because of it
         probe.f = q->f;
         probe.a = q->r_max;
         probe.n_r = q->n_r;
@@ -814,6 +810,10 @@ extern "C" sc_status sc_server_submit(sc_server *s, const sc_request *q, uint64_
             probe.obs_rho2max = std::max(probe.obs_rho2max, x[0] * x[0] + x[1] * x[1]);
             probe.obs_r2max = std::max(probe.obs_r2max, x[0] * x[0] + x[1] * x[1] + x[2] * x[2]);
         }
+        const Launch l = resolve_launch(&probe, q->prec);
+        r->bytes = footprint_bytes(q->n_r, q->n_phi, q->n_k, q->n_obs, q->n_t, q->prec, l.chunk);
+        // the footprint counts the partials of the direct sum at the launch's chunk; what the sum takes
+        // beyond them is charged too, though no request is too large for the budget because of it
         const size_t direct = real_size(q->prec) * 12 * (size_t)((probe.n_tot + l.chunk - 1) / l.chunk) * q->n_k *
                               (size_t)probe.n_obs_pad;
         const size_t more = quad_bytes(&probe, q->prec, l);

@@ -34,6 +34,7 @@ std::vector<std::string> violations;
 std::vector<Launch> launches;
 long long fail_alloc_at = 0, fail_allocs = 0;
 bool fields_factor = false;
+float (*elapsed)() = nullptr;
 double sim = 0.0;
 long long waits = 0;
 }  // namespace stub
@@ -229,7 +230,7 @@ hipError_t hipEventSynchronize(hipEvent_t e)
 }
 hipError_t hipEventElapsedTime(float *ms, hipEvent_t a, hipEvent_t b)
 {
-    *ms = std::chrono::duration<float, std::milli>(b->at - a->at).count();
+    *ms = elapsed ? elapsed() : std::chrono::duration<float, std::milli>(b->at - a->at).count();
     return hipSuccess;
 }
 hipError_t hipMallocRaw(void **p, size_t n) { return take(p, n); }

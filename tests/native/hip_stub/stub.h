@@ -23,6 +23,7 @@ extern std::vector<Launch> launches;          // quadratures since the start (or
 extern long long fail_alloc_at;               // the n-th device allocation from now on fails (0: none) ...
 extern long long fail_allocs;                 // ... and this many after it
 extern bool fields_factor;                    // outcome of the factoring test of fields from the caller
+extern float (*elapsed)();                    // what hipEventElapsedTime gives, if set (ms)
 extern double sim;                            // > 0: device work takes time (a model of it), times this
 
 extern long long waits;                       // waits of the host for work that it did not know to be done

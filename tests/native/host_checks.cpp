@@ -270,6 +270,48 @@ static void batch_cap()
     }
 }
 
+// Each candidate seems faster than the one before: tuning a compacted sum times nothing that cannot differ, and
+// what it keeps is not taken by direct sums of the same sizes.
+static void tuner()
+{
+    static float ms;
+    ms = 1000.0f;
+    stub::elapsed = [] { return ms -= 1.0f; };
+    for (sc_precision prec : {SC_FP32_SPLIT, SC_FP64}) {
+        sc_ctx *ctx = nullptr;
+        OK(sc_ctx_create(0, nullptr, &ctx));
+        {
+            Problem a(ctx, 200, 200, 4, 2000, false), b(ctx, 200, 200, 4, 2000, true);
+            sc_launch before{}, after{}, best{};
+            OK(sc_get_launch(b.p, prec, &before));
+            stub::clear();
+            OK(sc_autotune(a.p, prec, 1e6, &best));
+            EXPECT(stub::launches[0].n_tot < 20000, "not compacted");
+            const size_t n = stub::launches.size();
+            EXPECT(n <= (prec == SC_FP64 ? 40 : 2), "%zu evaluations", n);
+            EXPECT(best.chunk == before.chunk, "a chunk of %d for a sum without one", best.chunk);
+            if (prec == SC_FP32_SPLIT) EXPECT(best.obs_per_lane == before.obs_per_lane, "%d", best.obs_per_lane);
+            OK(sc_get_launch(b.p, prec, &after));
+            EXPECT(memcmp(&before, &after, sizeof before) == 0, "the direct sum's launch changed");
+            OK(sc_get_launch(a.p, prec, &after));
+            EXPECT(memcmp(&best, &after, sizeof best) == 0, "the tuned launch is not taken");
+            OK(sc_autotune_save(ctx, "tune.txt"));
+            OK(sc_autotune_load(ctx, "tune.txt"));
+            sc_prob *ps[1] = {a.p};
+            stub::clear();
+            OK(sc_autotune_batch(ctx, ps, 1, prec, 1e6, &best));
+            EXPECT(stub::launches.size() <= (prec == SC_FP64 ? 24u : 2u) && best.chunk == 0, "%zu evaluations, chunk %d",
+                   stub::launches.size(), best.chunk);
+            // a direct sum is tuned as ever: the last candidate, one workgroup per CU and the largest chunk tried
+            OK(sc_set_batch_launch(ctx, prec, nullptr));
+            OK(sc_autotune(b.p, prec, 1e6, &best));
+            EXPECT(best.chunk == 16384 && best.blocks_per_cu == 1, "%d %d", best.chunk, best.blocks_per_cu);
+        }
+        OK(sc_ctx_destroy(ctx));
+    }
+    stub::elapsed = nullptr;
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, std::function<void()>> checks = {
@@ -279,6 +321,7 @@ int main(int argc, char **argv)
         {"no_waits", no_waits},
         {"chunks", chunks},
         {"batch_cap", batch_cap},
+        {"tuner", tuner},
     };
     if (argc == 2 && checks.count(argv[1])) {
         checks.at(argv[1])();

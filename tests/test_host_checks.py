@@ -23,7 +23,8 @@ def host_checks(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("name", ["idle_blocks", "block_sizes", "block_turnover", "no_waits", "chunks", "batch_cap"])
+@pytest.mark.parametrize("name", ["idle_blocks", "block_sizes", "block_turnover", "no_waits", "chunks", "batch_cap",
+                                  "tuner"])
 def test_host_code(host_checks, name, tmp_path):
     r = subprocess.run([host_checks, name], capture_output=True, text=True, timeout=300, cwd=tmp_path)
     assert r.returncode == 0, r.stdout + r.stderr
