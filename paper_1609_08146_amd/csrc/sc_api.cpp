@@ -1544,17 +1544,21 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     std::vector<QuadJob> jobs{job};
     p->res_prec = -1;
     SC_TRY(run_quad(p->ctx, jobs, prec, l, p));
+    // E and B in device memory are written by the reduction, unless they overlap: then one after the other
+    const size_t bytes = real_size(prec) * 6 * (size_t)job.n_k * p->n_obs;
+    const uintptr_t e = (uintptr_t)E, b = (uintptr_t)B;
+    const bool direct = on_device && !(E && B && e < b + bytes && b < e + bytes);
     HIP_TRY(launch_reduce(p->ctx->stream, mode_of(prec), p->partial.p, job.n_chunks, job.n_k, p->n_obs,
                           p->n_obs_pad, p->d_k.as<double>(), b_scale(job), p->n_obs, 0, p->resE.p, p->resB.p,
-                          on_device ? E : nullptr, on_device ? B : nullptr));
+                          direct ? E : nullptr, direct ? B : nullptr));
     ev_record(p, EV_R1);
     p->ev_quad = p->ctx->profiling;
     p->res_prec = (int)prec;
     p->last_evals = (int64_t)p->n_obs * job.n_k * p->n_surf;
     p->last_tiles = job.n_tiles;
     p->last_chunk = used_chunk(p, l, job);
-    if (on_device) return SC_OK;   // the reduction wrote them
-    return copy_out(p, E, B, 0, real_size(prec) * 6 * (size_t)job.n_k * p->n_obs);
+    if (direct) return SC_OK;   // the reduction wrote them
+    return copy_out(p, E, B, on_device, bytes);
 }
 
 // ------------------------------------------------------- evaluation without allocation
@@ -1626,8 +1630,8 @@ extern "C" sc_status sc_evaluate_noalloc(sc_prob *p, sc_precision prec, void *E,
         }
         const size_t at = real_size(prec) * 6 * (size_t)k0 * p->n_obs;
         HIP_TRY(launch_reduce(st, mode_of(prec), job.partial, job.n_chunks, job.n_k, n_o, job.n_obs_pad,
-                              p->d_k.as<double>() + k0, b_scale(job), p->n_obs, o0, (char *)E + at, (char *)B + at,
-                              nullptr, nullptr));
+                              p->d_k.as<double>() + k0, b_scale(job), p->n_obs, o0,
+                              E == B ? nullptr : (char *)E + at, (char *)B + at, nullptr, nullptr));
         return SC_OK;
     };
     CompactPlan plan;

@@ -102,7 +102,7 @@ hipError_t launch_mm_tables(hipStream_t st, int n_k, int n_c, int form, const do
 inline int64_t mm_tiles_per_xcd(const QuadJob &j) { return (j.n_tiles + QUAD_SEGMENTS - 1) / QUAD_SEGMENTS; }
 hipError_t launch_quad_mm_one(hipStream_t st, int fpb, const QuadJob &job);
 hipError_t launch_quad_mm(hipStream_t st, int fpb, const QuadJob *jobs, int n_jobs, int64_t per);
-// (and in E2, B2 where given)
+// (E or B may be NULL; and in E2, B2 where given)
 hipError_t launch_reduce(hipStream_t st, int mode, const void *partial, int n_chunks, int n_k, int n_o, int n_o_pad,
                          const double *k, int b_scale, int n_obs, int o0, void *E, void *B, void *E2, void *B2);
 // Compacted tables (sc_compact.h): weights and node records, then the tables of frequencies k0 ...

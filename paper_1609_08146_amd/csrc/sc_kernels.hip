@@ -849,7 +849,7 @@ k_reduce(const PT *__restrict__ partial, int n_chunks, int n_k, int n_o, int n_o
         __syncthreads();
         if (64 * g + t / 6 < n_o) {
             const size_t at = ((size_t)kk * n_obs + o0 + 64 * g) * 6 + t;
-            (half ? B : E)[at] = rec[half][t];
+            if (OT *first = half ? B : E) first[at] = rec[half][t];
             if (OT *second = half ? B2 : E2) second[at] = rec[half][t];
         }
         __syncthreads();
