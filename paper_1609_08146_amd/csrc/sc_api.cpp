@@ -1532,6 +1532,17 @@ static sc_status copy_out(sc_prob *p, void *E, void *B, int on_device, size_t by
     return SC_OK;
 }
 
+// Whether x lies in the memory of the context's device.
+static bool on_this_device(const sc_ctx *c, const void *x)
+{
+    hipPointerAttribute_t a{};
+    if (hipPointerGetAttributes(&a, x) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return a.type == hipMemoryTypeDevice && a.device == c->device;
+}
+
 extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B, int on_device)
 {
     if (!p) return fail(SC_E_INVAL, "sc_evaluate: prob is NULL");
@@ -1544,10 +1555,12 @@ extern "C" sc_status sc_evaluate(sc_prob *p, sc_precision prec, void *E, void *B
     std::vector<QuadJob> jobs{job};
     p->res_prec = -1;
     SC_TRY(run_quad(p->ctx, jobs, prec, l, p));
-    // E and B in device memory are written by the reduction, unless they overlap: then one after the other
+    // E and B in this device's memory are written by the reduction, unless they overlap: then, and where a kernel
+    // here may not write (another device's memory), they are copied, one after the other
     const size_t bytes = real_size(prec) * 6 * (size_t)job.n_k * p->n_obs;
     const uintptr_t e = (uintptr_t)E, b = (uintptr_t)B;
-    const bool direct = on_device && !(E && B && e < b + bytes && b < e + bytes);
+    const bool direct = on_device && !(E && B && e < b + bytes && b < e + bytes) && (!E || on_this_device(p->ctx, E)) &&
+                        (!B || on_this_device(p->ctx, B));
     HIP_TRY(launch_reduce(p->ctx->stream, mode_of(prec), p->partial.p, job.n_chunks, job.n_k, p->n_obs,
                           p->n_obs_pad, p->d_k.as<double>(), b_scale(job), p->n_obs, 0, p->resE.p, p->resB.p,
                           direct ? E : nullptr, direct ? B : nullptr));

@@ -21,6 +21,13 @@ struct hipDeviceProp_t {
     int multiProcessorCount;
 };
 
+enum hipMemoryType { hipMemoryTypeHost = 1, hipMemoryTypeDevice = 2 };
+struct hipPointerAttribute_t {
+    hipMemoryType type;
+    int device;
+};
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *, const void *);
+
 hipError_t hipGetDeviceCount(int *);
 hipError_t hipGetDevice(int *);
 hipError_t hipSetDevice(int);

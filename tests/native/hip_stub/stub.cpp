@@ -37,6 +37,7 @@ bool fields_factor = false;
 float (*elapsed)() = nullptr;
 double sim = 0.0;
 long long waits = 0;
+const void *elsewhere = nullptr;
 }  // namespace stub
 using namespace stub;
 
@@ -90,6 +91,7 @@ void work(hipStream_t st, const char *what, std::initializer_list<const void *> 
         if (it == allocs.begin()) continue;
         --it;
         if ((char *)p >= it->first + it->second.bytes) continue;
+        if (it->first == elsewhere && strcmp(what, "copy") != 0) violations.push_back(std::string(what) + " on another device's memory");
         check(s, it->second, what);
         it->second.uses[s] = {s->seq, what};
     }
@@ -172,6 +174,15 @@ void clear()
 }
 }  // namespace stub
 
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
+{
+    LOCK;
+    auto it = allocs.upper_bound((char *)p);
+    if (it == allocs.begin() || (char *)p >= std::prev(it)->first + std::prev(it)->second.bytes) return hipErrorInvalidValue;
+    a->type = hipMemoryTypeDevice;
+    a->device = std::prev(it)->first == elsewhere ? 1 : 0;
+    return hipSuccess;
+}
 hipError_t hipGetDeviceCount(int *n) { *n = 1; return hipSuccess; }
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }

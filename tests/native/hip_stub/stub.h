@@ -26,6 +26,7 @@ extern bool fields_factor;                    // outcome of the factoring test o
 extern float (*elapsed)();                    // what hipEventElapsedTime gives, if set (ms)
 extern double sim;                            // > 0: device work takes time (a model of it), times this
 
+extern const void *elsewhere;                 // an allocation of another device; work here that touches it is a violation
 extern long long waits;                       // waits of the host for work that it did not know to be done
 
 struct PartialUse {

@@ -312,6 +312,29 @@ static void tuner()
     stub::elapsed = nullptr;
 }
 
+// Results for another device's memory are copied there: no kernel of this one writes to it.
+static void other_device()
+{
+    sc_ctx *ctx = nullptr;
+    OK(sc_ctx_create(0, nullptr, &ctx));
+    {
+        Problem a(ctx, 80, 64, 3, 200, false);
+        void *E = nullptr, *B = nullptr;
+        const size_t n = sizeof(float) * 6 * 3 * 200;
+        (void)hipMalloc(&E, n);
+        (void)hipMalloc(&B, n);
+        for (const void *x : {(const void *)nullptr, (const void *)E, (const void *)B}) {
+            stub::elsewhere = x;
+            OK(sc_evaluate(a.p, SC_FP32_SPLIT, E, B, 1));
+        }
+        OK(sc_ctx_synchronize(ctx));
+        (void)hipFree(E);
+        (void)hipFree(B);
+    }
+    OK(sc_ctx_destroy(ctx));
+    no_violations("results elsewhere");
+}
+
 int main(int argc, char **argv)
 {
     const std::map<std::string, std::function<void()>> checks = {
@@ -322,6 +345,7 @@ int main(int argc, char **argv)
         {"chunks", chunks},
         {"batch_cap", batch_cap},
         {"tuner", tuner},
+        {"other_device", other_device},
     };
     if (argc == 2 && checks.count(argv[1])) {
         checks.at(argv[1])();

@@ -24,7 +24,7 @@ def host_checks(tmp_path_factory):
 
 
 @pytest.mark.parametrize("name", ["idle_blocks", "block_sizes", "block_turnover", "no_waits", "chunks", "batch_cap",
-                                  "tuner"])
+                                  "tuner", "other_device"])
 def test_host_code(host_checks, name, tmp_path):
     r = subprocess.run([host_checks, name], capture_output=True, text=True, timeout=300, cwd=tmp_path)
     assert r.returncode == 0, r.stdout + r.stderr
