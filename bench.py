@@ -340,6 +340,23 @@ def bench_serve(args):
     print(json.dumps(serve_run(args.rate, args.duration, args.budget_gb, args.quantum_ms)), flush=True)
 
 
+def run_mode(mode, limit_s, *options):
+    """Another mode of this program in a process of its own, ended after limit_s seconds: its JSON line, or a
+    dictionary that says why there is none, so that the step's figures are printed whatever becomes of it."""
+    import subprocess
+    cmd = [sys.executable, os.path.abspath(__file__), "--mode", mode, *map(str, options)]
+    try:
+        res = subprocess.run(cmd, stdout=subprocess.PIPE, text=True, timeout=limit_s)
+    except subprocess.TimeoutExpired:
+        progress(f"{mode}: ended after {limit_s:.0f} s without a result")
+        return {"error": f"no result after {limit_s:.0f} s"}
+    lines = res.stdout.strip().splitlines()
+    if res.returncode != 0 or not lines:
+        progress(f"{mode}: exit status {res.returncode}")
+        return {"error": f"exit status {res.returncode}"}
+    return json.loads(lines[-1])
+
+
 def serve_run(rate: float, duration: float, budget_gb: float = 200.0, quantum_ms: float = 20.0) -> dict:
     """Poisson stream of sweep-like requests through the serving loop; p50/p99 latency and throughput.
 
@@ -363,10 +380,16 @@ def serve_run(rate: float, duration: float, budget_gb: float = 200.0, quantum_ms
     start = time.perf_counter()
 
     def submitter():
+        said = 0.0
         for i, ta in enumerate(times):
             now = time.perf_counter() - start
             if ta > now:
                 time.sleep(ta - now)
+            if now > said + 10.0:
+                said = now
+                st = srv.stats()
+                progress(f"serving at {rate:g}/s: {now:.0f} s, {i} submitted, {int(st['admitted'])} admitted, "
+                         f"{int(st['completed'])} completed")
             w = draw(i)
             try:
                 tk = srv.submit(w, "fp32_split", t=w.t, dk=w.dk)
@@ -890,26 +913,29 @@ def main():
         for rate, secs in ((args.serve_rate_low, args.serve_seconds_low), (args.serve_rate, args.serve_seconds)):
             if secs <= 0:
                 continue
-            sv = serve_run(rate, secs)
-            progress(f"serving at {rate:g}/s: p50 {sv['p50_ms']:.0f} ms, p99 {sv['p99_ms']:.0f} ms")
+            sv = run_mode("serve", 1.25 * secs + 45.0, "--rate", rate, "--duration", secs)
             row = {k: sv[k] for k in ("rate_hz", "duration_s", "arrivals", "completed", "cancelled", "rejected",
                                       "p50_ms", "p99_ms", "evals_per_s", "device_busy_frac",
-                                      "quanta_evals_per_device_s", "prep_ms_per_request")}
+                                      "quanta_evals_per_device_s", "prep_ms_per_request", "error") if k in sv}
+            row.setdefault("rate_hz", rate)
             row["workload"] = ("seeded Poisson stream of sweep-like requests (mean 3.6e10 evaluations), FP32-split "
                                "with time transform, 200 GB admission budget")
             out["serving"].append(row)
+            if "error" not in sv:
+                progress(f"serving at {rate:g}/s: p50 {sv['p50_ms']:.0f} ms, p99 {sv['p99_ms']:.0f} ms")
 
     if not args.no_batch and args.shard == 1:
         # the 256-instance sweep in one persistent launch, library and tuned batch launch
-        b = batch_run(256, tune=True, tune_budget_ms=20000.0)
-        progress(f"batch of {b['instances']} instances done")
+        b = run_mode("batch", 120.0, "--instances", 256)
         out["batch"] = {"workload": "seeded sweep of 256 uneven instances (f 2-20 cm, 1-256 frequencies, "
                                     "100^2-600^2 nodes, 16^2-128^2 + 16-128 axial points) in one persistent launch, "
                                     "FP32-split, FP32-only tables",
-                        "instances": b["instances"], "evals": b["evals"], "setup_s": b["setup_s"],
+                        **{k: b[k] for k in ("instances", "evals", "setup_s", "error") if k in b},
                         "runs": [{k: r[k] for k in ("label", "quad_evals_per_s", "quad_ms", "seconds", "launch",
                                                       "tune_seconds", "tuned_on")
-                                  if k in r} for r in b["runs"]]}
+                                  if k in r} for r in b.get("runs", [])]}
+        if "error" not in b:
+            progress(f"batch of {b['instances']} instances done")
     if not args.no_cpu_baseline:
         out["cpu_baseline"] = cpu_baseline(w, args.cpu_seconds)
 
