@@ -441,8 +441,11 @@ def serve_run(rate: float, duration: float, budget_gb: float = 200.0, quantum_ms
     th_c.join()
     elapsed = time.perf_counter() - start
     s = srv.stats()
+    progress(f"serving at {rate:g}/s: {elapsed:.0f} s, {int(s['completed'])} completed, {int(s['cancelled'])} cancelled, "
+             f"{s['host_in_use'] / 1e9:.1f} GB of results uncollected")
     srv.close()
     ctx.close()
+    progress(f"serving at {rate:g}/s: closed after {time.perf_counter() - start - elapsed:.1f} s")
     lat = np.array(lat) if lat else np.array([np.nan])
     return {
         "metric": "serving: p50/p99 request latency and integrand evals/s",
