@@ -67,3 +67,30 @@ def test_branches(orc, planner, name, prec):  # noqa: F811
     assert max(rel_l2(E[:, pick], Eo), rel_l2(B[:, pick], Bo)) < TOL[prec][0] + 4 * ks.max() * r * TOL[prec][1]
     p.close()
     ctx.close()
+
+
+@pytest.mark.parametrize("nphi", [2, 3, 4, 5])
+def test_few_phi(orc, planner, nphi):  # noqa: F811
+    """A handful of phi (their own columns in every row), 3 000 radii; and every point at the focus itself."""
+    from paper_1609_08146_amd import Context, Problem
+    f, a, nr, n = 30.0, 40.0, 3000, 6000
+    ks = K * np.array([0.9, 1.0, 1.1])
+    m = orc.mirror(f, a, nr, nphi)
+    Ei, Bi = workloads.random_incident_tables(3, m.n_tot, seed=nphi)
+    ctx = Context(0)
+    p = Problem(ctx)
+    p.set_mirror(f, a, nr, nphi)
+    p.set_frequencies(ks)
+    p.set_incident(Ei, Bi)
+    for size in (1.0, 0.0):
+        obs = np.random.default_rng(nphi).uniform(-1.0, 1.0, (n, 3)) * size
+        r, rho = np.linalg.norm(obs, axis=1).max(), np.linalg.norm(obs[:, :2], axis=1).max()
+        Eo, Bo = orc.reflected_field(m, ks, Ei, Bi, obs[::240])
+        p.set_observation(obs)
+        for prec in ("fp64", "fp32_split")[: 1 if nphi < 4 else 2]:      # (FP32: the direct sum is the faster one)
+            plan = planner(f, a, nr, nphi, ks.min(), ks.max(), 3, -(-n // 128) * 128, r, rho, prec == "fp64")
+            assert max(plan["cols"]) == (nphi if nphi % 2 == 0 else 2 * nphi)
+            E, B = p.evaluate(prec)
+            assert max(rel_l2(E[:, ::240], Eo), rel_l2(B[:, ::240], Bo)) < TOL[prec][0] + 4 * ks.max() * r * TOL[prec][1]
+    p.close()
+    ctx.close()
