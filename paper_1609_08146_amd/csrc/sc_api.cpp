@@ -1254,7 +1254,8 @@ static void fill_job(const sc_prob *p, sc_precision prec, const Launch &l, const
 static bool plan_compact(const sc_prob *p, sc_precision prec, CompactPlan &plan)
 {
     if (prec == SC_FP32 || p->f <= 0.0 || p->obs_r2max < 0.0 || p->k.empty()) return false;
-    CompactInput in{};
+    CompactInput in;
+    memset(&in, 0, sizeof in);   // compared as bytes
     in.f = p->f;
     in.r_max = p->a;
     in.n_r = p->n_r;
@@ -1266,7 +1267,14 @@ static bool plan_compact(const sc_prob *p, sc_precision prec, CompactPlan &plan)
     in.obs_r2max = p->obs_r2max;
     in.obs_rho2max = p->obs_rho2max;
     in.fp64 = prec == SC_FP64;
-    return compact_plan(in, plan);
+    auto &known = p->planned;
+    if (!known.known || memcmp(&known.in, &in, sizeof in) != 0) {
+        known.compact = compact_plan(in, known.plan);
+        memcpy(&known.in, &in, sizeof in);
+        known.known = true;
+    }
+    plan = known.plan;
+    return known.compact;
 }
 
 // The job of a sum over compacted nodes: fill_job's with the compacted tables, which are general

@@ -262,6 +262,12 @@ struct sc_prob {
     // the factored tables built with the test when the incident field is set: FP32 split by
     // default; a caller that knows its one precision (the serving loop) picks that one's
     sc_precision eager_prec = SC_FP32_SPLIT;
+    // the last plan asked for and what it depends on (compact_plan takes 10 us and is a function of its input alone)
+    mutable struct {
+        bool known = false, compact = false;
+        sc::CompactInput in;
+        sc::CompactPlan plan;
+    } planned;
     // compacted tables of the last plan (sc_compact.h) and their node records, one after the other:
     // valid for the precision, table layout and tables (tab_version) they were built from
     sc::DevBuf ctab;
