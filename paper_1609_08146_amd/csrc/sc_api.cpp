@@ -2189,7 +2189,7 @@ extern "C" sc_status sc_autotune(sc_prob *p, sc_precision prec, double budget_ms
         *ms = timed_ms(p);
         return SC_OK;
     };
-    // stage 1: kernel shape and waves per workgroup at the library's chunk; stage 2: the chunk (it
+    // stage 1: kernel shape and waves per workgroup at 2048 nodes (or the chunk in use); stage 2: the chunk (it
     // sets the split-K partials' size and the summation order) and workgroups per CU for that shape
     // (a compacted sum has no chunk, and in the FP32 form no shape that a launch could choose: the library's is the
     // result, instead of the noise of equal launches)

@@ -17,8 +17,8 @@
 // interpolation is polynomial in y: Chebyshev points of theta itself crowd at both ends, where
 // the kernel oscillates no faster than elsewhere and a row at the rim has the most columns; alpha spreads
 // them, at the price of branch points at y = +-1 / alpha.  On a mirror of theta_max 41 degrees and points
-// within 6.9 wavelengths, to 3e-10: 41 rows and 2747 nodes from points of [0, theta_max], 33 and 2631 with
-// the continuation, 27 and 2035 with alpha = 0.9 too (to 1e-15: 4219, 3795 and 3012 nodes).
+// within 5.7 wavelengths of 800 nm +-16 %, for the FP32 form: 25 rows and 1799 nodes, 2066 with alpha near 0; in
+// FP64 34 rows and 3168 nodes, 3422.
 #pragma once
 
 #include <stdint.h>

@@ -80,9 +80,10 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
     // tiles; the matrix instructions of the two interpolations at 32 FP64 flops per cycle) and, for small
     // problems, the serial chain of a wave (0.3 us per node of a direct chunk) and the reduction of the chunks,
     // against the launches that build the tables (32 us at 64 x 64 nodes, 52 at 256 x 256).  The tables
-    // serve every evaluation until the field changes, so they count for 0.7 of one: 64 x 64 nodes and 100
-    // points take 45 us directly, 61 compacted and 29 with the tables there; 100 x 100 and 1500 points at 4
-    // frequencies 98, 79 and 38; 256 x 256 and 100 points 96, 82 and 29.
+    // serve every evaluation until the field changes, so they count for 0.7 of one.  That is where a first pass
+    // breaks even: 36 random problems that are compacted at 0.7 and would not be at 1 took, over the direct sum's
+    // time, 1.00 with a new built-in beam (0.77 to 1.21), 0.87 with a new field of the caller's (slower in 6), 0.79
+    // without allocation, where the tables are built on each call (slower in 2), and 0.21 with the tables there.
     const int64_t n_tot = (int64_t)(in.n_r + 1) * in.n_phi;
     const double pts = (double)in.n_k * in.n_obs_pad, cyc = 1024.0 * 2.2e3;   // cycles per us
     const double launches = 20.0 + 0.065 * ((double)in.n_r + in.n_phi);
@@ -213,7 +214,7 @@ bool compact_plan(const CompactInput &in, CompactPlan &plan)
 
     // The quadrature's chunk, at least 64 nodes.  FP64 (tiles of 64 points x 2 frequencies per wave): about
     // four rounds of tiles over the resident waves, so that the last round's empty slots stay below a
-    // quarter of the time and the partials below 125 MB plus one chunk's.  FP32 (128 points x 4
+    // quarter of the time and the partials below 252 MB (20480 tiles of 64 x 2 x 12 x 8 bytes) plus one chunk's.  FP32 (128 points x 4
     // frequencies per workgroup): about four rounds of workgroups, and no more than 256 nodes, because a
     // chunk is one FP32 sum.
     if (in.fp64) {
